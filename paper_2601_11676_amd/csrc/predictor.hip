@@ -6,11 +6,14 @@
 // partial per lane of a wave64, eight consecutive elements = one 16-byte bf16
 // load), each partial is a fused-multiply-add chain in increasing i starting at
 // +0, and the 64 partials are combined by a butterfly at distances 32..1.
-// The work is plain float ALU on purpose: a matrix-core instruction would not
-// expose its internal summation order.
+// A matrix instruction that reduces several elements at once would not expose its
+// internal summation order; one that takes a single element per instruction has none
+// (hidden_mfma_kernel below), and a few tokens stay on the plain float ALUs.
 #include "kernels.hpp"
 
 namespace halo {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 template <typename XT, typename WT, bool RELU>
 __global__ __launch_bounds__(256) void dot_rows_kernel(const XT *__restrict__ X,
@@ -25,106 +28,163 @@ __global__ __launch_bounds__(256) void dot_rows_kernel(const XT *__restrict__ X,
     if (lane == 0) out[idx] = RELU ? (p > 0.0f ? p : 0.0f) : p;
 }
 
-// First layer for many tokens, bf16, d = NCH*512: a wave keeps JB rows of At in registers
-// (as floats) and sweeps a range of tokens, so At is read once per 32 tokens instead of once
-// per token.  Same arithmetic per (token, row) as dot_order64: lane l owns the 8-element
-// pieces l, l+64, ... in increasing order, one fused-multiply-add chain from +0, butterfly.
-constexpr int kPredTokens = 32;     // tokens per workgroup (64: 44 us, 32: 29 us, 16: 32 us at 512 tokens, 7B shape)
+// The first layer for many tokens, bf16, on the matrix cores in the fixed order.
+//
+// v_mfma_f32_16x16x1_4b_f32 multiplies four independent blocks of 16 x 16 results by ONE element of the
+// reduction dimension: every result is c = fma(a, b, c), rounded once (checked bit by bit against fmaf over
+// ordinary values, denormals, overflow and infinities), so the order of a chain is the order in which the
+// instructions are issued, which is exactly what the fixed order asks for.  Block b of a wave's instruction
+// holds partial sums l + 16 b: lane (b, i) supplies element e of piece 64 k + l + 16 b of row i, e = 0..7 are
+// eight instructions, and k walks the row.  A wave owns 16 / WAVES consecutive values of l, so a
+// workgroup holds all 64 partial sums of its (16 JT rows of At) x (16 TT tokens); distances 32 and 16 are
+// then additions between a lane's own blocks, 8 .. 1 go through LDS once at the end.
+// Nothing is spent on lane-crossing sums per result (half of the instructions of a wave-per-row form), and
+// the instruction runs at 130 TFLOP/s here against 51 for dependent vector multiply-adds.  Measured, first
+// layer alone: 512 tokens, d = 4096, rank 256: 18 us (59 TFLOP/s; vector form 32 us); 128 tokens, d = 5120: 11.7 us
+// (26); 1000 tokens, d = 8192, rank 512: 96 us (87 TFLOP/s; 370).  What is left above the instruction's rate
+// is the barrier and the first LDS read of every 512-element step.
+// Rows go through LDS a step at a time (coalesced 1 KiB per wave instruction; a row is padded by 16 bytes so
+// that 16 rows' pieces fall into different banks), double-buffered; the step after next travels in
+// registers.  Two waves per SIMD (four with one tile), so that one wave's LDS reads hide behind another's
+// matrix instructions: with one wave and one buffer 24, 15.6 and 130 us.
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+constexpr int kHidRow = 512 + 8;            // padded LDS row, elements
 
-template <int NCH, int JB, int TB>
-__global__ __launch_bounds__(256) void hidden_rows_kernel(const bf16_t *__restrict__ X,
-                                                          const bf16_t *__restrict__ At,
-                                                          float *__restrict__ h, int T, int r)
+template <int TT, int JT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4))) void hidden_mfma_kernel(
+    const bf16_t *__restrict__ X, const bf16_t *__restrict__ At, float *__restrict__ h, int T, int d, int r,
+    int n_tt, int n_jt)
 {
-    constexpr int d = NCH * 512;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j0 = (blockIdx.x * 4 + wave) * JB;
-    if (j0 >= r) return;
-    float wr[JB][NCH][8];
+    constexpr int kTiles = TT * JT, kRows = 16 * (TT + JT), kPer = kRows / WAVES, kL = 16 / WAVES;
+    constexpr size_t kStage = (size_t)2 * kRows * kHidRow * sizeof(bf16_t), kSums = (size_t)16 * kTiles * 64 * 16;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kStage > kSums ? kStage : kSums];
+    bf16_t *rows = reinterpret_cast<bf16_t *>(lds);              // two of: TT * 16 token rows, then JT * 16 rows of At
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    // a die (workgroups are dealt round-robin to eight) takes consecutive items, the rows of At fastest: its
+    // token rows stay in its L2
+    const int n_items = n_tt * n_jt, per_die = (n_items + 7) >> 3;
+    const int slot = blockIdx.x >> 3, item = (blockIdx.x & 7) * per_die + slot;
+    if (slot >= per_die || item >= n_items) return;
+    const int t0 = (item / n_jt) * 16 * TT, j0 = (item % n_jt) * 16 * JT;
+    const int nk = (d + 511) / 512;
+    // this wave stages rows wave, wave + WAVES, ...; rows past the end repeat the last one (never stored)
+    const bf16_t *src[kPer];
 #pragma unroll
-    for (int b = 0; b < JB; ++b) {
-        const int j = j0 + b < r ? j0 + b : r - 1;
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) load8(At + (size_t)j * d + (k * kWave + lane) * 8, wr[b][k]);
+    for (int n = 0; n < kPer; ++n) {
+        const int row = wave + WAVES * n;
+        src[n] = row < 16 * TT ? X + (size_t)min(t0 + row, T - 1) * d : At + (size_t)min(j0 + row - 16 * TT, r - 1) * d;
     }
-    const int t0 = blockIdx.y * kPredTokens, t1 = min(T, t0 + kPredTokens);
-    // TB tokens per iteration; the next iteration's x pieces are requested before the current
-    // ones are used, so the sweep is not one memory round trip per token
-    auto fetch = [&](u32x4 (&xv)[TB][NCH], int t) {
+    u32x4 v[kPer];
+    auto fetch = [&](int k) {
+        const int e = k * 512 + lane * 8;
+        const bool ok = e < d;                                   // (d is a multiple of 8)
 #pragma unroll
-        for (int c = 0; c < TB; ++c) {
-            const int tc = t + c < t1 ? t + c : t1 - 1;          // past the end: a duplicate, not stored
-#pragma unroll
-            for (int k = 0; k < NCH; ++k)
-                xv[c][k] = *reinterpret_cast<const u32x4 *>(X + (size_t)tc * d + (k * kWave + lane) * 8);
+        for (int n = 0; n < kPer; ++n) {
+            v[n] = *reinterpret_cast<const u32x4 *>(src[n] + (ok ? e : 0));
+            if (!ok) v[n] = u32x4{0u, 0u, 0u, 0u};               // 0 * 0 leaves a chain as it is
         }
     };
-    auto finish = [&](const u32x4 (&xv)[TB][NCH], int t) {
-        float p[TB][JB];
+    static_assert(kPer <= 8, "a row per element of the last piece");
+    auto park = [&](int k, int n) {
+        *reinterpret_cast<u32x4 *>(rows + ((k & 1) * kRows + wave + WAVES * n) * kHidRow + lane * 8) = v[n];
+    };
+    f32x16_t acc[kL][kTiles];
 #pragma unroll
-        for (int c = 0; c < TB; ++c)
+    for (int l = 0; l < kL; ++l)
 #pragma unroll
-            for (int b = 0; b < JB; ++b) p[c][b] = 0.0f;
+        for (int n = 0; n < kTiles; ++n)
 #pragma unroll
-        for (int k = 0; k < NCH; ++k) {
+            for (int e = 0; e < 16; ++e) acc[l][n][e] = 0.0f;
+    const int i = lane & 15, b = lane >> 4;
+    fetch(0);
 #pragma unroll
-            for (int c = 0; c < TB; ++c) {
-                float xf[8];
-                unpack8(xv[c][k], xf);
+    for (int n = 0; n < kPer; ++n) park(0, n);
+    fetch(nk > 1 ? 1 : 0);
+    for (int k = 0; k < nk; ++k) {
+        __syncthreads();                                         // step k is in LDS, step k - 1 is used up
+        const bf16_t *piece = rows + (k & 1) * kRows * kHidRow + i * kHidRow + (kL * wave + 16 * b) * 8;
+        u32x4 raw[TT + JT];
 #pragma unroll
-                for (int b = 0; b < JB; ++b)
+        for (int n = 0; n < TT + JT; ++n) raw[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) p[c][b] = __builtin_fmaf(xf[e], wr[b][k][e], p[c][b]);
+        for (int l = 0; l < kL; ++l) {
+            float f[TT + JT][8];
+#pragma unroll
+            for (int n = 0; n < TT + JT; ++n) unpack8(raw[n], f[n]);
+            if (l + 1 < kL) {
+#pragma unroll
+                for (int n = 0; n < TT + JT; ++n)
+                    raw[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow + (l + 1) * 8);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+#pragma unroll
+                for (int n = 0; n < kTiles; ++n)
+                    acc[l][n] = __builtin_amdgcn_mfma_f32_16x16x1f32(f[TT + n % JT][e], f[n / JT][e], acc[l][n], 0, 0, 0);
+                // the next step's rows go to the other buffer one by one between the matrix instructions
+                if (l == kL - 1 && e < kPer) park(k + 1, e);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-#define HALO_STEP(OFF)                                               \
-    _Pragma("unroll") for (int c = 0; c < TB; ++c)                   \
-        _Pragma("unroll") for (int b = 0; b < JB; ++b) p[c][b] = xor_add<OFF>(p[c][b]);
-        HALO_STEP(32) HALO_STEP(16) HALO_STEP(8) HALO_STEP(4) HALO_STEP(2) HALO_STEP(1)
-#undef HALO_STEP
-        if (lane == 0) {
+        fetch(k + 2 < nk ? k + 2 : nk - 1);
+    }
+    __syncthreads();
+    // distances 32 and 16: blocks (0, 2) and (1, 3); result element 4 b + m of a lane is block b, row 4 (lane / 16) + m,
+    // token lane % 16
+    f32x4_t *sums = reinterpret_cast<f32x4_t *>(lds);            // [l][tile][lane]
 #pragma unroll
-            for (int c = 0; c < TB; ++c)
+    for (int l = 0; l < kL; ++l)
 #pragma unroll
-                for (int b = 0; b < JB; ++b)
-                    if (t + c < t1 && j0 + b < r)
-                        h[(size_t)(t + c) * r + j0 + b] = p[c][b] > 0.0f ? p[c][b] : 0.0f;
+        for (int n = 0; n < kTiles; ++n) {
+            f32x4_t s;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) s[m] = (acc[l][n][m] + acc[l][n][8 + m]) + (acc[l][n][4 + m] + acc[l][n][12 + m]);
+            sums[((kL * wave + l) * kTiles + n) * 64 + lane] = s;
         }
-    };
-    u32x4 xa[TB][NCH], xb[TB][NCH];
-    fetch(xa, t0);
-    int t = t0;
-    for (; t + 2 * TB < t1; t += 2 * TB) {      // two iterations per trip: the buffers swap by name
-        fetch(xb, t + TB);
-        finish(xa, t);
-        fetch(xa, t + 2 * TB);
-        finish(xb, t + TB);
-    }
-    if (t + TB < t1) {
-        fetch(xb, t + TB);
-        finish(xa, t);
-        finish(xb, t + TB);
-    } else {
-        finish(xa, t);
+    __syncthreads();
+    // distances 8, 4, 2, 1
+    for (int n = wave; n < kTiles; n += WAVES) {
+        f32x4_t p[16];
+#pragma unroll
+        for (int l = 0; l < 16; ++l) p[l] = sums[(l * kTiles + n) * 64 + lane];
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+            for (int l = 0; l < 8; ++l)
+                if (l < off)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) p[l][m] = p[l][m] + p[l + off][m];
+        const int t = t0 + (n / JT) * 16 + i, j = j0 + (n % JT) * 16 + 4 * b;
+        if (t < T) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (j + m < r) h[(size_t)t * r + j + m] = p[0][m] > 0.0f ? p[0][m] : 0.0f;
+        }
     }
 }
 
-template <int NCH, int JB, int TB>
-static void launch_hidden_rows(const bf16_t *x, int T, int r, const bf16_t *At, float *h, hipStream_t s)
+template <int TT, int JT, int WAVES>
+static void launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
-    hidden_rows_kernel<NCH, JB, TB><<<dim3((r + 4 * JB - 1) / (4 * JB), (T + kPredTokens - 1) / kPredTokens),
-                                     dim3(256), 0, s>>>(x, At, h, T, r);
+    const int n_tt = (T + 16 * TT - 1) / (16 * TT), n_jt = (r + 16 * JT - 1) / (16 * JT);
+    hidden_mfma_kernel<TT, JT, WAVES><<<dim3((n_tt * n_jt + 7) / 8 * 8), dim3(WAVES * 64), 0, s>>>(x, At, h, T, d, r, n_tt, n_jt);
 }
 
+// The largest tile that still gives every compute unit a workgroup: the bytes staged per result fall with the
+// tile (2 x 2: 64 rows per 1024 results, 1 x 1: 32 per 256), but a unit without a workgroup does nothing.  Fewer
+// than 16 tokens do not fill a tile and stay with a wave per result (2..8 tokens: 7-13 us).
 static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
     if (T < 16) return false;
-    switch (d) {
-    case 4096: launch_hidden_rows<8, 2, 1>(x, T, r, At, h, s); return true;
-    case 5120: launch_hidden_rows<10, 2, 1>(x, T, r, At, h, s); return true;
-    case 8192: launch_hidden_rows<16, 1, 1>(x, T, r, At, h, s); return true;
-    default: return false;
-    }
+    const int n_tt = (T + 31) / 32;
+    if (n_tt * ((r + 31) / 32) >= 256)
+        launch_hidden_mfma<2, 2, 8>(x, T, d, r, At, h, s);
+    else if (n_tt * ((r + 15) / 16) >= 256)
+        launch_hidden_mfma<2, 1, 8>(x, T, d, r, At, h, s);
+    else
+        launch_hidden_mfma<1, 1, 16>(x, T, d, r, At, h, s);
+    return true;
 }
 static bool hidden_rows_tiled(const float *, int, int, int, const float *, float *, hipStream_t) { return false; }
 

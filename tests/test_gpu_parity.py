@@ -549,3 +549,28 @@ def test_stack_glue_and_ceiling_aids():
     assert 500.0 < tf < 2600.0, tf
     assert not sink.any()
     _say(f"read stream {gbps:.0f} GB/s, bf16 matrix instructions {tf:.0f} TFLOP/s")
+
+
+@pytest.mark.parametrize("T,d,r,G", [
+    (16, 520, 40, 9),          # one 16 x 16 tile per workgroup, a ragged last step of the row, rows past the end
+    (33, 4096, 256, 86),       # a token tile with one token in it
+    (300, 2048, 264, 70),
+    (512, 1032, 256, 8),       # two token tiles x one row tile per workgroup
+    (530, 640, 512, 33),       # two x two, both ragged
+])
+def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
+    # bit for bit, with denormal, huge and zero elements among ordinary ones
+    w = dataclasses.replace(hs.LLAMA7B_DECODE, name="case", d=d, ffn=G * 128, rank=r, T=T, seed=61)
+    _say(f"predictor of many tokens T={T} d={d} r={r} G={G}")
+    s = hz.shape_of(w)
+    At, Bt = hs.predictor_weights(w, 0, hz.DEV)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    x[0, :8] = torch.tensor([1e-40, -1e-39, 0.0, -0.0, 3e38, -3e38, 1e-38, 1e30], dtype=torch.bfloat16)
+    x[T - 1] *= 1e-38
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    sc = torch.empty((T, G), dtype=torch.float32, device=hz.DEV)
+    H.halo_predict_scores(s, x, At, Bt, sc, ws)
+    c = ref.predict_scores(hz.to_np32(x), hz.to_np32(At), hz.to_np32(Bt))
+    g = sc.cpu().numpy()
+    same = (g.view(np.uint32) == c.view(np.uint32)) | (np.isnan(g) & np.isnan(c))
+    assert same.all()

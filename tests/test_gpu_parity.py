@@ -574,3 +574,24 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     g = sc.cpu().numpy()
     same = (g.view(np.uint32) == c.view(np.uint32)) | (np.isnan(g) & np.isnan(c))
     assert same.all()
+
+
+@pytest.mark.parametrize("T,d,G,gs", [
+    (1, 8, 1, 16),             # the smallest: half a piece of the row, one tile of one group
+    (1, 1000, 24, 128),        # a last tile of eight outputs
+    (17, 264, 5, 48),          # two token tiles, a half piece at the end of the row
+    (33, 512, 9, 128),         # four token tiles, one of them empty
+    (70, 136, 300, 32),        # two ranges of tokens, more groups than a wave's ballot
+])
+def test_float32_tiles(T, d, G, gs):
+    w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * gs, group_size=gs, rank=64, T=T, seed=71)
+    _say(f"float32 tiles T={T} d={d} G={G} gs={gs}")
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    for K in (max(1, G // 3), G):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        drop = hs.drop_outcomes(w, T=T)
+        drop[0] = 1                                            # a token with no survivor
+        g = hz.gpu_forward(w, L, x, K, pd, drop)
+        c = hz.oracle_forward(w, L, x, K, pd, drop)
+        hz.assert_parity(g, c, TOL["f32"], f"f32 K={K}")

@@ -173,12 +173,13 @@ int halo_build_group_mask(const float *scores, int32_t T, int32_t G, int32_t k_k
  * Accumulation is float32; the tuned bf16 paths round the activation SiLU(gate)*up to bf16 before
  * the down projection.
  * Which kernels run (results are the same to the stated tolerance either way; throughput is not):
- *   bf16, group size 128, n_groups <= 256, one token, d = 5120 or a multiple of 1024 in [2048, 8192]:
- *       the streaming one-token kernels;
+ *   bf16, group size 128, n_groups <= 256, one token, d <= 8192: the streaming one-token kernels (d other
+ *       than 5120 and the multiples of 1024 from 2048: the activation stays in float32);
  *   bf16, group size 128, 2..16 tokens, d a multiple of 128: the few-token kernels (2..4 tokens with
  *       d in {4096, 5120, 8192} and n_groups <= 256 on the float ALUs, otherwise matrix cores);
  *   bf16, group size 128, more than 16 tokens, d a multiple of 128: the many-token matrix-core kernels;
- *   anything else (float32, other group sizes or row lengths): plain wave-per-row kernels, several
+ *   float32, group size a multiple of 16: float32 matrix-core kernels;
+ *   anything else (other group sizes, longer rows, more groups): plain wave-per-row kernels, several
  *       times slower per byte.
  */
 int halo_group_sparse_ffn(const halo_shape *shape, const void *x, int32_t T, const void *Wg,
@@ -234,8 +235,7 @@ int halo_ffn_forward_static(const halo_shape *shape, const void *x, const void *
  *   - predictor + group mask of the next block from x_pred_next with that block's
  *     predictor weights -> mask_next (and the optional outputs, same meaning as in
  *     halo_build_group_mask; NULL = not produced).
- * For one token (bf16, group size 128, n_groups <= 256, d = 5120 or a multiple of 1024 from 2048 to
- * 8192) and for 2..16 tokens (bf16, d a multiple of 128, group size 128, n_groups <= 256) the
+ * For one token (bf16, group size 128, n_groups <= 256, d <= 8192) and for 2..16 tokens (bf16, d a multiple of 128, group size 128, n_groups <= 256) the
  * prediction occupies spare
  * workgroups of the FFN's own two launches (first predictor layer beside gate/up, second
  * layer + ranking + mask beside the down projection), so it costs no launch and little or no
@@ -323,7 +323,7 @@ int halo_ffn_forward_ahead_q4(const halo_shape *shape, const void *x, int32_t T,
  * outputs have the meaning they have in halo_ffn_forward.
  * halo_mha_forward_ahead is the overlapped form (same contract as halo_ffn_forward_ahead):
  * attention of the current block with mask_cur, and beside it predictor + head mask of the next
- * block from x_pred_next; for d in {4096, 5120, 8192} the prediction rides in spare workgroups of
+ * block from x_pred_next; for d <= 8192 the prediction rides in spare workgroups of
  * the q/k/v launch and of the output-projection launch, otherwise it is enqueued afterwards.
  * Errors: as halo_group_sparse_ffn, plus HALO_ERR_ARG for pos outside [0, max_len) or
  * max_len > 131072.

@@ -12,8 +12,8 @@
 //             surviving groups, so no partial sums ever leave the workgroup.
 // Groups that no token keeps are never addressed.
 //
-// This file holds the one-token hot path and a generic path (any T, d, group size, f32 or
-// bf16) that favours simplicity; a few tokens in bf16 go to the matrix-core path instead.
+// This file holds the one-token path (bf16) and a generic path (any T, d, group size, f32 or
+// bf16) that favours simplicity; more tokens in bf16 and float32 go to matrix-core paths instead.
 #include "kernels.hpp"
 #include "mask_device.hpp"
 #include "mask_words.hpp"
@@ -139,25 +139,28 @@ __global__ __launch_bounds__(256) void down_generic(
 }
 
 // ---------------------------------------------------------------------------
-// one token, bf16, d = NCH*512, group size 128, G <= 256: the decode hot path
+// one token, bf16, rows of up to NCH*512 elements, group size 128, G <= 256: the decode hot path
 // ---------------------------------------------------------------------------
 // x stays packed (two bf16 per register); products go through the packed dot instruction
-template <int NCH>
-__device__ __forceinline__ float gate_up_dot(const RowPair<NCH> &r, const u32x4 (&xr)[NCH])
+template <int NCH, bool TAIL>
+__device__ __forceinline__ void gate_up_dot(const RowPair<NCH> &r, const u32x4 (&xr)[NCH], const RowLanes<NCH, TAIL> &rl,
+                                            float &gate, float &up)
 {
     float ag = 0.0f, au = 0.0f;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        ag = dot2_bf16(r.g[k].x, xr[k].x, ag);
-        au = dot2_bf16(r.u[k].x, xr[k].x, au);
-        ag = dot2_bf16(r.g[k].y, xr[k].y, ag);
-        au = dot2_bf16(r.u[k].y, xr[k].y, au);
-        ag = dot2_bf16(r.g[k].z, xr[k].z, ag);
-        au = dot2_bf16(r.u[k].z, xr[k].z, au);
-        ag = dot2_bf16(r.g[k].w, xr[k].w, ag);
-        au = dot2_bf16(r.u[k].w, xr[k].w, au);
+        const u32x4 g = rl.keep(r.g[k], k), u = rl.keep(r.u[k], k);
+        ag = dot2_bf16(g.x, xr[k].x, ag);
+        au = dot2_bf16(u.x, xr[k].x, au);
+        ag = dot2_bf16(g.y, xr[k].y, ag);
+        au = dot2_bf16(u.y, xr[k].y, au);
+        ag = dot2_bf16(g.z, xr[k].z, ag);
+        au = dot2_bf16(u.z, xr[k].z, au);
+        ag = dot2_bf16(g.w, xr[k].w, ag);
+        au = dot2_bf16(u.w, xr[k].w, au);
     }
-    return silu_mul(wave_sum_fast(ag), wave_sum_fast(au));
+    gate = wave_sum_fast(ag);
+    up = wave_sum_fast(au);
 }
 
 // One wave per neuron at a time; each wave owns a contiguous run of the surviving neurons
@@ -165,14 +168,16 @@ __device__ __forceinline__ float gate_up_dot(const RowPair<NCH> &r, const u32x4 
 // it reduces the current one.  The steady-state loop has no branch between a load batch
 // and the reduction that precedes it, so the wait counters can leave that batch in flight.
 // vblock / nblocks: this workgroup's index among the workgroups doing this job.
-template <int NCH>
+// TAIL: rows of any length (RowLanes), with the activation kept in float32 (AT) as the plain path keeps it.
+template <int NCH, bool TAIL, typename AT>
 __device__ __forceinline__ void gate_up_t1_body(
-    const bf16_t *__restrict__ x, int G, int gs, const bf16_t *__restrict__ Wg,
-    const bf16_t *__restrict__ Wu, const uint8_t *__restrict__ mask, bf16_t *__restrict__ act,
+    const bf16_t *__restrict__ x, int d, int G, const bf16_t *__restrict__ Wg,
+    const bf16_t *__restrict__ Wu, const uint8_t *__restrict__ mask, AT *__restrict__ act,
     int vblock, int nblocks)
 {
     constexpr int kGs = 128;                                       // the group size of this path
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const RowLanes<NCH, TAIL> rl(d, lane);
     const MaskWords mw = load_mask_words(mask, G, lane);
     const int total = mw.count * kGs;
     const int nw = nblocks * 4, w = vblock * 4 + wave;
@@ -188,49 +193,41 @@ __device__ __forceinline__ void gate_up_t1_body(
         return (size_t)(u == u_first ? g_first : g_last) * kGs + (n - u * kGs);
     };
     RowPair<NCH> A, B;
-    load_rows<NCH>(A, Wg, Wu, row_of(n0), lane);
+    load_rows<NCH, TAIL>(A, Wg, Wu, row_of(n0), lane, rl);
     u32x4 xr[NCH];
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) xr[k] = *reinterpret_cast<const u32x4 *>(x + (k * kWave + lane) * 8);
+    for (int k = 0; k < NCH; ++k) xr[k] = rl.keep(reinterpret_cast<const u32x4 *>(x)[rl.piece(k, lane)], k);
+    auto finish = [&](const RowPair<NCH> &r, int n) {
+        float gate, up;
+        gate_up_dot<NCH, TAIL>(r, xr, rl, gate, up);
+        if (lane == 0) store_out(act + n, silu_mul(gate, up));
+    };
     int n = n0;
     while (n + 2 < n1) {
-        load_rows<NCH>(B, Wg, Wu, row_of(n + 1), lane);
+        load_rows<NCH, TAIL>(B, Wg, Wu, row_of(n + 1), lane, rl);
         __builtin_amdgcn_sched_barrier(0);      // the requests go out before anything waits for the rows in flight
-        const float va = gate_up_dot<NCH>(A, xr);
-        if (lane == 0) act[n] = f32_to_bf16(va);
-        load_rows<NCH>(A, Wg, Wu, row_of(n + 2), lane);
+        finish(A, n);
+        load_rows<NCH, TAIL>(A, Wg, Wu, row_of(n + 2), lane, rl);
         __builtin_amdgcn_sched_barrier(0);
-        const float vb = gate_up_dot<NCH>(B, xr);
-        if (lane == 0) act[n + 1] = f32_to_bf16(vb);
+        finish(B, n + 1);
         n += 2;
     }
     if (n + 1 < n1) {
-        load_rows<NCH>(B, Wg, Wu, row_of(n + 1), lane);
-        const float va = gate_up_dot<NCH>(A, xr);
-        if (lane == 0) act[n] = f32_to_bf16(va);
-        const float vb = gate_up_dot<NCH>(B, xr);
-        if (lane == 0) act[n + 1] = f32_to_bf16(vb);
+        load_rows<NCH, TAIL>(B, Wg, Wu, row_of(n + 1), lane, rl);
+        finish(A, n);
+        finish(B, n + 1);
     } else {
-        const float va = gate_up_dot<NCH>(A, xr);
-        if (lane == 0) act[n] = f32_to_bf16(va);
+        finish(A, n);
     }
 }
 
-template <int NCH>
-__global__ __launch_bounds__(256) void gate_up_t1(
-    const bf16_t *__restrict__ x, int G, int gs, const bf16_t *__restrict__ Wg,
-    const bf16_t *__restrict__ Wu, const uint8_t *__restrict__ mask, bf16_t *__restrict__ act)
-{
-    gate_up_t1_body<NCH>(x, G, gs, Wg, Wu, mask, act, blockIdx.x, gridDim.x);
-}
-
-// The same, with the first predictor layer of the NEXT block riding along (paper Sec. III-B.3,
-// Pred beside Load/Comp, one layer ahead): the first n_pred workgroups each take four rows
-// of At and produce h_next = ReLU(x_next A); the others do this block's gate/up work.
-template <int NCH>
+// With the first predictor layer of the NEXT block riding along (paper Sec. III-B.3, Pred beside Load/Comp, one
+// layer ahead): the first n_pred workgroups each take four rows of At and produce h_next = ReLU(x_next A); the
+// others do this block's gate/up work.  (n_pred == 0: nothing rides along.)
+template <int NCH, bool TAIL, typename AT>
 __global__ __launch_bounds__(256) void gate_up_pred_t1(
-    const bf16_t *__restrict__ x, int G, int gs, const bf16_t *__restrict__ Wg,
-    const bf16_t *__restrict__ Wu, const uint8_t *__restrict__ mask, bf16_t *__restrict__ act,
+    const bf16_t *__restrict__ x, int d, int G, const bf16_t *__restrict__ Wg,
+    const bf16_t *__restrict__ Wu, const uint8_t *__restrict__ mask, AT *__restrict__ act,
     const bf16_t *__restrict__ x_next, const bf16_t *__restrict__ At_next, int r,
     float *__restrict__ h_next, int n_pred)
 {
@@ -238,12 +235,13 @@ __global__ __launch_bounds__(256) void gate_up_pred_t1(
         const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
         const int j = blockIdx.x * 4 + wave;
         if (j < r) {
-            const float p = dot_order64_fixed<NCH * 512>(x_next, At_next + (size_t)j * (NCH * 512), lane);
+            const RowLanes<NCH, TAIL> rl(d, lane);
+            const float p = dot_order64_row<NCH, TAIL>(x_next, At_next + rl.row(j), rl, lane);
             if (lane == 0) h_next[j] = p > 0.0f ? p : 0.0f;
         }
         return;
     }
-    gate_up_t1_body<NCH>(x, G, gs, Wg, Wu, mask, act, blockIdx.x - n_pred, gridDim.x - n_pred);
+    gate_up_t1_body<NCH, TAIL, AT>(x, d, G, Wg, Wu, mask, act, blockIdx.x - n_pred, gridDim.x - n_pred);
 }
 
 // Down projection for one token.  16 lanes share an output row (16 bytes each = the 128
@@ -253,19 +251,51 @@ __global__ __launch_bounds__(256) void gate_up_pred_t1(
 // Each lane accumulates over its groups, the 16 lanes of a row are summed once at the end
 // and the two halves meet in LDS, so y is written directly: no partial sums in memory, no
 // second pass.  The activation arrives in bf16 and meets the weights in the packed dot.
-constexpr int kDownBatch = 8;    // groups in flight per wave
-
 template <int RQ>
 struct DownShared {
     int list[256];
     float half[RQ][64];
 };
 
-template <int RQ>
+// the eight activations that face a lane's 16-byte piece of a row, as they are stored
+template <typename AT> struct ActPiece;
+template <> struct ActPiece<bf16_t> {
+    u32x4 v;
+    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const u32x4 *>(p); }
+    __device__ __forceinline__ void dot(const u32x4 &w, float &acc0, float &acc1) const
+    {
+        acc0 = dot2_bf16(w.x, v.x, acc0);
+        acc1 = dot2_bf16(w.y, v.y, acc1);
+        acc0 = dot2_bf16(w.z, v.z, acc0);
+        acc1 = dot2_bf16(w.w, v.w, acc1);
+    }
+};
+template <> struct ActPiece<float> {
+    float4 a, b;
+    __device__ __forceinline__ void load(const float *p)
+    {
+        a = *reinterpret_cast<const float4 *>(p);
+        b = *reinterpret_cast<const float4 *>(p + 4);
+    }
+    __device__ __forceinline__ void dot(const u32x4 &w, float &acc0, float &acc1) const
+    {
+        acc0 = __builtin_fmaf(bf16_lo(w.x), a.x, acc0);
+        acc1 = __builtin_fmaf(bf16_hi(w.x), a.y, acc1);
+        acc0 = __builtin_fmaf(bf16_lo(w.y), a.z, acc0);
+        acc1 = __builtin_fmaf(bf16_hi(w.y), a.w, acc1);
+        acc0 = __builtin_fmaf(bf16_lo(w.z), b.x, acc0);
+        acc1 = __builtin_fmaf(bf16_hi(w.z), b.y, acc1);
+        acc0 = __builtin_fmaf(bf16_lo(w.w), b.z, acc0);
+        acc1 = __builtin_fmaf(bf16_hi(w.w), b.w, acc1);
+    }
+};
+
+// EXACT: d is a multiple of the workgroup's 4 RQ rows; otherwise rows past the end repeat the last one, unused.
+template <int RQ, typename AT, bool EXACT>
 __device__ __forceinline__ void down_t1_body(DownShared<RQ> &sh, int d, int G,
                                              const bf16_t *__restrict__ Wd,
                                              const uint8_t *__restrict__ mask,
-                                             const bf16_t *__restrict__ act, bf16_t *__restrict__ y,
+                                             const AT *__restrict__ act, bf16_t *__restrict__ y,
                                              int vblock)
 {
     constexpr int gs = 128;
@@ -277,31 +307,28 @@ __device__ __forceinline__ void down_t1_body(DownShared<RQ> &sh, int d, int G,
     const int rq = wave % RQ, half = wave / RQ;                     // row quad, even/odd groups
     const int row = (vblock * RQ + rq) * 4 + (lane >> 4);           // output index j
     const int piece = (lane & 15) * 8;                              // first neuron of this lane's piece
-    const bf16_t *wbase = Wd + (size_t)row * gs + piece;
+    const bf16_t *wbase = Wd + (size_t)(EXACT ? row : min(row, d - 1)) * gs + piece;
     const size_t gstride = (size_t)d * gs;
     float acc0 = 0.0f, acc1 = 0.0f;
-    constexpr int kB = kDownBatch / 2;                             // two half batches in flight
-    auto fetch = [&](u32x4 (&v)[kB], u32x4 (&a)[kB], int u0) {
+    // two half batches in flight: eight groups, six where the activation takes twice the registers
+    constexpr int kB = sizeof(AT) == 2 ? 4 : 3;
+    auto fetch = [&](u32x4 (&v)[kB], ActPiece<AT> (&a)[kB], int u0) {
 #pragma unroll
         for (int q = 0; q < kB; ++q) {
             const int u = u0 + 2 * q < count ? u0 + 2 * q : (count > 0 ? count - 1 : 0);   // an in-range duplicate
             v[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(wbase + sh.list[u] * gstride));
-            a[q] = *reinterpret_cast<const u32x4 *>(act + u * gs + piece);
+            a[q].load(act + u * gs + piece);
         }
     };
-    auto mac = [&](const u32x4 (&v)[kB], const u32x4 (&a)[kB], int u0) {
+    auto mac = [&](const u32x4 (&v)[kB], const ActPiece<AT> (&a)[kB], int u0) {
 #pragma unroll
         for (int q = 0; q < kB; ++q) {
-            if (u0 + 2 * q < count) {
-                acc0 = dot2_bf16(v[q].x, a[q].x, acc0);
-                acc1 = dot2_bf16(v[q].y, a[q].y, acc1);
-                acc0 = dot2_bf16(v[q].z, a[q].z, acc0);
-                acc1 = dot2_bf16(v[q].w, a[q].w, acc1);
-            }
+            if (u0 + 2 * q < count) a[q].dot(v[q], acc0, acc1);
         }
     };
     if (count > 0) {
-        u32x4 v0[kB], a0[kB], v1[kB], a1[kB];
+        u32x4 v0[kB], v1[kB];
+        ActPiece<AT> a0[kB], a1[kB];
         fetch(v0, a0, half);
         fetch(v1, a1, half + 2 * kB);
         int u0 = half;
@@ -322,27 +349,27 @@ __device__ __forceinline__ void down_t1_body(DownShared<RQ> &sh, int d, int G,
     v = dpp_add<0x140>(v);
     if (half == 1) sh.half[rq][lane] = v;
     __syncthreads();
-    if (half == 0 && (lane & 15) == 0) y[row] = f32_to_bf16(v + sh.half[rq][lane]);
+    if (half == 0 && (lane & 15) == 0 && (EXACT || row < d)) y[row] = f32_to_bf16(v + sh.half[rq][lane]);
 }
 
-// (Both down kernels are held to 128 vector registers: two workgroups must fit a compute unit, or the
+// (The down kernels are held to 128 vector registers: two workgroups must fit a compute unit, or the
 // extra workgroup of the `_mask` form waits for a free one and the launch takes half as long again.)
-template <int RQ>
+template <int RQ, typename AT, bool EXACT>
 __global__ __launch_bounds__(RQ * 128, 4) void down_t1(int d, int G, const bf16_t *__restrict__ Wd,
                                                     const uint8_t *__restrict__ mask,
-                                                    const bf16_t *__restrict__ act,
+                                                    const AT *__restrict__ act,
                                                     bf16_t *__restrict__ y)
 {
     __shared__ DownShared<RQ> sh;
-    down_t1_body<RQ>(sh, d, G, Wd, mask, act, y, blockIdx.x);
+    down_t1_body<RQ, AT, EXACT>(sh, d, G, Wd, mask, act, y, blockIdx.x);
 }
 
 // The down projection, with the second predictor layer + ranking + mask of the NEXT block in
 // workgroup 0 (it is the longest dependent chain, so it is dispatched first).
-template <int RQ>
+template <int RQ, typename AT, bool EXACT>
 __global__ __launch_bounds__(RQ * 128, 4) void down_mask_t1(int d, int G, const bf16_t *__restrict__ Wd,
                                                          const uint8_t *__restrict__ mask,
-                                                         const bf16_t *__restrict__ act,
+                                                         const AT *__restrict__ act,
                                                          bf16_t *__restrict__ y, AheadDev nx)
 {
     __shared__ DownShared<RQ> sh;
@@ -353,7 +380,7 @@ __global__ __launch_bounds__(RQ * 128, 4) void down_mask_t1(int d, int G, const 
                                                   nx.mask, nx.surv_idx, nx.n_surv);
         return;
     }
-    down_t1_body<RQ>(sh, d, G, Wd, mask, act, y, blockIdx.x - 1);
+    down_t1_body<RQ, AT, EXACT>(sh, d, G, Wd, mask, act, y, blockIdx.x - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -380,29 +407,59 @@ static hipError_t decode_generic(const WT *x, int T, int d, int G, int gs, const
 // dispatching the predictor's workgroups after the gate/up ones, are all slower.
 constexpr int kGateUpBlocks = 256;
 
-template <int NCH>
-static hipError_t decode_t1(const bf16_t *x, int G, int gs, const bf16_t *Wg, const bf16_t *Wu,
-                            const bf16_t *Wd, const uint8_t *mask, bf16_t *y,
-                            const DecodeScratch &ws, const AheadArgs *ah, hipStream_t s)
+template <int NCH, bool TAIL, typename AT>
+static void launch_gate_up_t1(const bf16_t *x, int d, int G, const bf16_t *Wg, const bf16_t *Wu, const uint8_t *mask,
+                              AT *act, const AheadArgs *ah, hipStream_t s)
 {
-    constexpr int d = NCH * 512;
+    const int n_pred = ah ? (ah->r + 3) / 4 : 0;
+    launch_timed(ah ? "gate_up_pred_t1" : "gate_up_t1", gate_up_pred_t1<NCH, TAIL, AT>, dim3(kGateUpBlocks + n_pred),
+                 dim3(256), s, x, d, G, Wg, Wu, mask, act, ah ? (const bf16_t *)ah->x_next : (const bf16_t *)nullptr,
+                 ah ? (const bf16_t *)ah->At : (const bf16_t *)nullptr, ah ? ah->r : 0, ah ? ah->h : (float *)nullptr, n_pred);
+}
+
+// Row lengths whose chunks are whole and whose rows divide over 256 workgroups: d = 1024 k, k = 2..8, and 5120
+// (LLaMA-family hidden sizes).  Their activation is bf16.
+bool t1_shape_supported(int d)
+{
+    return d == 5120 || (d % 1024 == 0 && d >= 2048 && d <= 8192);
+}
+
+static hipError_t decode_t1(const bf16_t *x, int d, int G, const bf16_t *Wg, const bf16_t *Wu, const bf16_t *Wd,
+                            const uint8_t *mask, bf16_t *y, const DecodeScratch &ws, const AheadArgs *ah, hipStream_t s)
+{
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
-    if (!ah) {
-        launch_timed("gate_up_t1", gate_up_t1<NCH>, dim3(kGateUpBlocks), dim3(256), s, x, G, gs, Wg, Wu,
-                     mask, act);
-    } else {
-        const int n_pred = (ah->r + 3) / 4;
-        launch_timed("gate_up_pred_t1", gate_up_pred_t1<NCH>, dim3(kGateUpBlocks + n_pred), dim3(256), s, x, G,
-                     gs, Wg, Wu, mask, act, (const bf16_t *)ah->x_next, (const bf16_t *)ah->At, ah->r, ah->h,
-                     n_pred);
+    switch (d) {
+    case 2048: launch_gate_up_t1<4, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    case 3072: launch_gate_up_t1<6, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    case 4096: launch_gate_up_t1<8, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    case 5120: launch_gate_up_t1<10, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    case 6144: launch_gate_up_t1<12, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    case 7168: launch_gate_up_t1<14, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
+    default: launch_gate_up_t1<16, false>(x, d, G, Wg, Wu, mask, act, ah, s); break;
     }
     return launch_down_t1(Wd, d, G, mask, act, y, s, ah);
 }
 
-// Row lengths of the one-token path: d = 1024 k, k = 2..8, and 5120 (LLaMA-family hidden sizes).
-bool t1_shape_supported(int d)
+// Any other row length up to 8192 (a multiple of 8): the same kernels with a clamped last part of the row, and the
+// activation kept in float32, as the plain path that served these lengths keeps it.  d = 3200, 68 groups: gate/up
+// 11.4 us and down 8.4 us with the next block's prediction on board; the plain path took 13.2 + 37.8, a launch of 4.9 for
+// the list of groups, and 5.3 + 6.0 for the prediction.  Longer rows would not fit a wave's registers twice.
+bool t1_any_supported(int d) { return d % 8 == 0 && d <= 8192; }
+
+static hipError_t decode_t1_any(const bf16_t *x, int d, int G, const bf16_t *Wg, const bf16_t *Wu, const bf16_t *Wd,
+                                const uint8_t *mask, bf16_t *y, const DecodeScratch &ws, const AheadArgs *ah, hipStream_t s)
 {
-    return d == 5120 || (d % 1024 == 0 && d >= 2048 && d <= 8192);
+    switch ((d + 1023) / 1024) {
+    case 1: launch_gate_up_t1<2, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 2: launch_gate_up_t1<4, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 3: launch_gate_up_t1<6, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 4: launch_gate_up_t1<8, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 5: launch_gate_up_t1<10, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 6: launch_gate_up_t1<12, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    case 7: launch_gate_up_t1<14, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    default: launch_gate_up_t1<16, true>(x, d, G, Wg, Wu, mask, ws.act, ah, s); break;
+    }
+    return launch_down_t1_any(Wd, d, G, mask, ws.act, y, s, ah);
 }
 
 hipError_t launch_down_t1(const bf16_t *Wd, int d, int G, const uint8_t *mask, const bf16_t *act, bf16_t *y,
@@ -412,9 +469,9 @@ hipError_t launch_down_t1(const bf16_t *Wd, int d, int G, const uint8_t *mask, c
 #define HALO_DOWN_CASE(D)                                                                                  \
     case D:                                                                                                \
         if (ahead)                                                                                         \
-            down_mask_t1<D / 1024><<<dim3(257), dim3(D / 1024 * 128), 0, s>>>(d, G, Wd, mask, act, y, nx); \
+            down_mask_t1<D / 1024, bf16_t, true><<<dim3(257), dim3(D / 1024 * 128), 0, s>>>(d, G, Wd, mask, act, y, nx); \
         else                                                                                               \
-            down_t1<D / 1024><<<dim3(256), dim3(D / 1024 * 128), 0, s>>>(d, G, Wd, mask, act, y);          \
+            down_t1<D / 1024, bf16_t, true><<<dim3(256), dim3(D / 1024 * 128), 0, s>>>(d, G, Wd, mask, act, y);          \
         break;
     switch (d) {
         HALO_DOWN_CASE(2048)
@@ -430,10 +487,23 @@ hipError_t launch_down_t1(const bf16_t *Wd, int d, int G, const uint8_t *mask, c
     return hipGetLastError();
 }
 
-hipError_t launch_down_generic_bf16(const float *act, int act_stride, int d, int gs, const bf16_t *Wd,
-                                    const int32_t *ulist, const int32_t *meta, bf16_t *y, hipStream_t s)
+// Any d: 16 rows to a workgroup, 8 below 4096 (a grid of 128 workgroups would leave half of the chip idle).
+hipError_t launch_down_t1_any(const bf16_t *Wd, int d, int G, const uint8_t *mask, const float *act, bf16_t *y,
+                              hipStream_t s, const AheadArgs *ahead)
 {
-    down_generic<bf16_t, 4><<<dim3((d + 3) / 4), dim3(256), 0, s>>>(act, act_stride, 1, d, gs, Wd, ulist, meta, y);
+    const AheadDev nx = ahead ? ahead_dev(*ahead) : AheadDev{};
+    const int rq = d < 4096 ? 2 : 4, blocks = (d + 4 * rq - 1) / (4 * rq);
+    if (ahead) {
+        if (rq == 2)
+            down_mask_t1<2, float, false><<<dim3(blocks + 1), dim3(256), 0, s>>>(d, G, Wd, mask, act, y, nx);
+        else
+            down_mask_t1<4, float, false><<<dim3(blocks + 1), dim3(512), 0, s>>>(d, G, Wd, mask, act, y, nx);
+    } else {
+        if (rq == 2)
+            down_t1<2, float, false><<<dim3(blocks), dim3(256), 0, s>>>(d, G, Wd, mask, act, y);
+        else
+            down_t1<4, float, false><<<dim3(blocks), dim3(512), 0, s>>>(d, G, Wd, mask, act, y);
+    }
     return hipGetLastError();
 }
 
@@ -455,18 +525,11 @@ hipError_t launch_ffn_decode(int dtype, const void *x, int T, int d, int G, int 
                                      (const float *)Wd, mask, (float *)y, ws, s);
     const bf16_t *bx = (const bf16_t *)x, *bg = (const bf16_t *)Wg, *bu = (const bf16_t *)Wu,
                  *bd = (const bf16_t *)Wd;
-    if (T == 1 && G <= 256 && gs == 128 && t1_shape_supported(d)) {
+    if (T == 1 && G <= 256 && gs == 128 && t1_any_supported(d)) {
         const AheadArgs *ah = (ahead && ahead_fused) ? ahead : nullptr;
         if (ah) *ahead_fused = true;
-        switch (d) {
-        case 2048: return decode_t1<4>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        case 3072: return decode_t1<6>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        case 4096: return decode_t1<8>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        case 5120: return decode_t1<10>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        case 6144: return decode_t1<12>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        case 7168: return decode_t1<14>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        default: return decode_t1<16>(bx, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
-        }
+        if (t1_shape_supported(d)) return decode_t1(bx, d, G, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
+        return decode_t1_any(bx, d, G, bg, bu, bd, mask, (bf16_t *)y, ws, ah, s);
     }
     if (mfma_path_supported(T, d, gs))
         return launch_ffn_mfma(bx, T, d, G, gs, bg, bu, bd, mask, (bf16_t *)y, ws, s, ahead, ahead_fused);

@@ -75,9 +75,10 @@ __global__ __launch_bounds__(256) void gate_up_ft(
         if (p < kPieces) *reinterpret_cast<u32x4 *>(sx + t * XR + e) = xp[j];
     }
     // the first two neurons' rows are on their way while the workgroup meets at the barrier
+    const RowLanes<NCH, false> rl(d, lane);
     RowPair<NCH> A, B;
-    if (busy) load_rows<NCH>(A, Wg, Wu, row_of(n0), lane);
-    if (n0 + 1 < n1) load_rows<NCH>(B, Wg, Wu, row_of(n0 + 1), lane);
+    if (busy) load_rows<NCH>(A, Wg, Wu, row_of(n0), lane, rl);
+    if (n0 + 1 < n1) load_rows<NCH>(B, Wg, Wu, row_of(n0 + 1), lane, rl);
     __syncthreads();
     if (!busy) return;                                       // no barrier below
     const bf16_t *xl = sx + lane * 8;

@@ -78,8 +78,9 @@ inline AheadDev ahead_dev(const AheadArgs &a)
 // the one-token down projection on its own (also the attention block's output projection)
 hipError_t launch_down_t1(const bf16_t *Wd, int d, int G, const uint8_t *mask, const bf16_t *act, bf16_t *y,
                           hipStream_t s, const AheadArgs *ahead = nullptr);
-hipError_t launch_down_generic_bf16(const float *act, int act_stride, int d, int gs, const bf16_t *Wd,
-                                    const int32_t *ulist, const int32_t *meta, bf16_t *y, hipStream_t s);
+// the same for any d (a multiple of 8), with the activation in float32
+hipError_t launch_down_t1_any(const bf16_t *Wd, int d, int G, const uint8_t *mask, const float *act, bf16_t *y,
+                              hipStream_t s, const AheadArgs *ahead = nullptr);
 
 hipError_t launch_ffn_decode(int dtype, const void *x, int T, int d, int G, int gs, const void *Wg,
                              const void *Wu, const void *Wd, const uint8_t *mask, void *y,

@@ -19,6 +19,7 @@
 // Only surviving heads' query rows, cache rows and output-projection blocks are read.
 #include "kernels.hpp"
 #include "mask_words.hpp"
+#include "row_stream.hpp"
 
 namespace halo {
 
@@ -36,31 +37,34 @@ struct RowRegs {
     u32x4 a[NCH], b[NCH];            // two independent rows
 };
 
-template <int NCH>
-__device__ __forceinline__ void load_two(RowRegs<NCH> &r, const bf16_t *pa, const bf16_t *pb, int lane)
+template <int NCH, bool TAIL>
+__device__ __forceinline__ void load_two(RowRegs<NCH> &r, const bf16_t *pa, const bf16_t *pb, const RowLanes<NCH, TAIL> &rl,
+                                         int lane)
 {
-    const u32x4 *qa = reinterpret_cast<const u32x4 *>(pa) + lane, *qb = reinterpret_cast<const u32x4 *>(pb) + lane;
+    const u32x4 *qa = reinterpret_cast<const u32x4 *>(pa), *qb = reinterpret_cast<const u32x4 *>(pb);
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        r.a[k] = __builtin_nontemporal_load(qa + k * kWave);
-        r.b[k] = __builtin_nontemporal_load(qb + k * kWave);
+        r.a[k] = __builtin_nontemporal_load(qa + rl.piece(k, lane));
+        r.b[k] = __builtin_nontemporal_load(qb + rl.piece(k, lane));
     }
 }
 
-template <int NCH>
-__device__ __forceinline__ void dot_two(const RowRegs<NCH> &r, const u32x4 (&xr)[NCH], float &ra, float &rb)
+template <int NCH, bool TAIL>
+__device__ __forceinline__ void dot_two(const RowRegs<NCH> &r, const u32x4 (&xr)[NCH], const RowLanes<NCH, TAIL> &rl,
+                                        float &ra, float &rb)
 {
     float a0 = 0.0f, b0 = 0.0f;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        a0 = dot2_bf16(r.a[k].x, xr[k].x, a0);
-        b0 = dot2_bf16(r.b[k].x, xr[k].x, b0);
-        a0 = dot2_bf16(r.a[k].y, xr[k].y, a0);
-        b0 = dot2_bf16(r.b[k].y, xr[k].y, b0);
-        a0 = dot2_bf16(r.a[k].z, xr[k].z, a0);
-        b0 = dot2_bf16(r.b[k].z, xr[k].z, b0);
-        a0 = dot2_bf16(r.a[k].w, xr[k].w, a0);
-        b0 = dot2_bf16(r.b[k].w, xr[k].w, b0);
+        const u32x4 a = rl.keep(r.a[k], k), b = rl.keep(r.b[k], k);
+        a0 = dot2_bf16(a.x, xr[k].x, a0);
+        b0 = dot2_bf16(b.x, xr[k].x, b0);
+        a0 = dot2_bf16(a.y, xr[k].y, a0);
+        b0 = dot2_bf16(b.y, xr[k].y, b0);
+        a0 = dot2_bf16(a.z, xr[k].z, a0);
+        b0 = dot2_bf16(b.z, xr[k].z, b0);
+        a0 = dot2_bf16(a.w, xr[k].w, a0);
+        b0 = dot2_bf16(b.w, xr[k].w, b0);
     }
     ra = wave_sum_fast(a0);
     rb = wave_sum_fast(b0);
@@ -79,52 +83,49 @@ struct QkvArgs {
 };
 
 // pairs of rows [p0, p1) of a job list whose row v comes from src(v) and goes to put(v, value)
-template <int NCH, typename Src, typename Put>
-__device__ __forceinline__ void sweep_pairs(int p0, int p1, const u32x4 (&xr)[NCH], int lane, Src src, Put put)
+template <int NCH, bool TAIL, typename Src, typename Put>
+__device__ __forceinline__ void sweep_pairs(int p0, int p1, const u32x4 (&xr)[NCH], const RowLanes<NCH, TAIL> &rl, int lane,
+                                            Src src, Put put)
 {
     if (p0 >= p1) return;
     RowRegs<NCH> A, B;
-    load_two<NCH>(A, src(2 * p0), src(2 * p0 + 1), lane);
-    int p = p0;
-    while (p + 2 < p1) {
-        load_two<NCH>(B, src(2 * p + 2), src(2 * p + 3), lane);
+    auto load = [&](RowRegs<NCH> &r, int p) { load_two<NCH, TAIL>(r, src(2 * p), src(2 * p + 1), rl, lane); };
+    auto finish = [&](const RowRegs<NCH> &r, int p) {
         float va, vb;
-        dot_two<NCH>(A, xr, va, vb);
+        dot_two<NCH, TAIL>(r, xr, rl, va, vb);
         put(2 * p, va);
         put(2 * p + 1, vb);
-        load_two<NCH>(A, src(2 * p + 4), src(2 * p + 5), lane);
-        dot_two<NCH>(B, xr, va, vb);
-        put(2 * p + 2, va);
-        put(2 * p + 3, vb);
+    };
+    load(A, p0);
+    int p = p0;
+    while (p + 2 < p1) {
+        load(B, p + 1);
+        finish(A, p);
+        load(A, p + 2);
+        finish(B, p + 1);
         p += 2;
     }
     if (p + 1 < p1) {
-        load_two<NCH>(B, src(2 * p + 2), src(2 * p + 3), lane);
-        float va, vb;
-        dot_two<NCH>(A, xr, va, vb);
-        put(2 * p, va);
-        put(2 * p + 1, vb);
-        dot_two<NCH>(B, xr, va, vb);
-        put(2 * p + 2, va);
-        put(2 * p + 3, vb);
+        load(B, p + 1);
+        finish(A, p);
+        finish(B, p + 1);
     } else {
-        float va, vb;
-        dot_two<NCH>(A, xr, va, vb);
-        put(2 * p, va);
-        put(2 * p + 1, vb);
+        finish(A, p);
     }
 }
 
-template <int NCH>
-__global__ __launch_bounds__(256) void qkv_rows(QkvArgs a)
+template <int NCH, bool TAIL>
+__global__ __launch_bounds__(256) void qkv_rows(QkvArgs a, int len)
 {
-    constexpr int d = NCH * 512, dh = kHeadDim;
+    constexpr int dh = kHeadDim;
+    const int d = TAIL ? len : NCH * 512;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const RowLanes<NCH, TAIL> rl(d, lane);
     if ((int)blockIdx.x < a.n_pred) {
         // paper Sec. III-B.3, Pred beside Load/Comp, one layer ahead: h_next = ReLU(x_next A)
         const int j = blockIdx.x * 4 + wave;
         if (j < a.r) {
-            const float p = dot_order64_fixed<d>(a.x_next, a.At_next + (size_t)j * d, lane);
+            const float p = dot_order64_row<NCH, TAIL>(a.x_next, a.At_next + (size_t)j * d, rl, lane);
             if (lane == 0) a.h_next[j] = p > 0.0f ? p : 0.0f;
         }
         return;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256) void qkv_rows(QkvArgs a)
     const MaskWords mw = load_mask_words(a.mask, a.H, lane);     // needed only further down
     u32x4 xr[NCH];
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) xr[k] = *reinterpret_cast<const u32x4 *>(a.x + (k * kWave + lane) * 8);
+    for (int k = 0; k < NCH; ++k) xr[k] = rl.keep(reinterpret_cast<const u32x4 *>(a.x)[rl.piece(k, lane)], k);
     // keys and values of every head: 2*H*dh rows, taken in pairs
     {
         const int hd = a.H * dh;
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(256) void qkv_rows(QkvArgs a)
                 *dst = f32_to_bf16(val);
             }
         };
-        sweep_pairs<NCH>(p0, p1, xr, lane, src, put);
+        sweep_pairs<NCH, TAIL>(p0, p1, xr, rl, lane, src, put);
     }
     // queries of the surviving heads: count*dh rows (an even number), compact by slot
     {
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(256) void qkv_rows(QkvArgs a)
         auto put = [&](int v, float val) {
             if (lane == 0) a.q[v] = val;
         };
-        sweep_pairs<NCH>(p0, p1, xr, lane, src, put);
+        sweep_pairs<NCH, TAIL>(p0, p1, xr, rl, lane, src, put);
     }
 }
 
@@ -373,7 +374,10 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
     if (H > 256) return hipErrorInvalidValue;                    // the mask-word helpers cover 256 heads
     const int chunks = pos / kAttnChunk + 1;
     if (chunks > kMaxChunks) return hipErrorInvalidValue;
-    const bool fast = d == 4096 || d == 5120 || d == 8192;
+    // row lengths up to 8192 are streamed; 4096, 5120 and 8192 by kernels without a clamped last part of the row and
+    // with the merged head outputs in bf16, the others with those in float32 (2048 cached rows, d = 3200: 26 us of
+    // kernels in four launches; the plain row kernels took 61 us in seven, d = 2048: 22 against 44)
+    const bool whole = d == 4096 || d == 5120 || d == 8192, fast = d <= 8192;
     const AheadArgs *ah = (fast && ahead && ahead_fused) ? ahead : nullptr;
     if (ah) *ahead_fused = true;
     const int n_pred = ah ? (ah->r + 3) / 4 : 0;
@@ -381,11 +385,23 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
                (bf16_t *)v_cache, ws.q, mask, H, max_len, pos,
                ah ? (const bf16_t *)ah->x_next : nullptr, ah ? (const bf16_t *)ah->At : nullptr,
                ah ? ah->h : nullptr, ah ? ah->r : 0, n_pred};
-    if (fast) {
+#define HALO_QKV(NCH, TAIL) launch_timed("qkv_rows", qkv_rows<NCH, TAIL>, dim3(256 + n_pred), dim3(256), s, qa, d)
+    if (whole) {
         switch (d) {
-        case 4096: launch_timed("qkv_rows", qkv_rows<8>, dim3(256 + n_pred), dim3(256), s, qa); break;
-        case 5120: launch_timed("qkv_rows", qkv_rows<10>, dim3(256 + n_pred), dim3(256), s, qa); break;
-        default: launch_timed("qkv_rows", qkv_rows<16>, dim3(256 + n_pred), dim3(256), s, qa); break;
+        case 4096: HALO_QKV(8, false); break;
+        case 5120: HALO_QKV(10, false); break;
+        default: HALO_QKV(16, false); break;
+        }
+    } else if (fast) {
+        switch ((d + 1023) / 1024) {
+        case 1: HALO_QKV(2, true); break;
+        case 2: HALO_QKV(4, true); break;
+        case 3: HALO_QKV(6, true); break;
+        case 4: HALO_QKV(8, true); break;
+        case 5: HALO_QKV(10, true); break;
+        case 6: HALO_QKV(12, true); break;
+        case 7: HALO_QKV(14, true); break;
+        default: HALO_QKV(16, true); break;
         }
     } else {
         hipError_t e = launch_union(mask, 1, H, ws.dec.ulist, ws.dec.meta, s);
@@ -393,18 +409,18 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
         launch_timed("qkv_rows_generic", qkv_rows_generic, dim3(512), dim3(256), s, qa, d,
                      (const int32_t *)ws.dec.ulist, (const int32_t *)ws.dec.meta);
     }
+#undef HALO_QKV
     attn_partial<<<dim3(chunks, H), dim3(256), 0, s>>>(ws.q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, mask,
                                                        H, max_len, pos, ws.part);
     // the output projection is the FFN's down projection with heads as groups
-    if (fast) {
+    if (whole) {
         attn_combine<bf16_t><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, chunks,
                                                            reinterpret_cast<bf16_t *>(ws.dec.act));
         return launch_down_t1((const bf16_t *)Wo, d, H, mask, reinterpret_cast<const bf16_t *>(ws.dec.act),
                               (bf16_t *)y, s, ah);
     }
     attn_combine<float><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, chunks, ws.dec.act);
-    return launch_down_generic_bf16(ws.dec.act, H * kHeadDim, d, kHeadDim, (const bf16_t *)Wo, ws.dec.ulist,
-                                    ws.dec.meta, (bf16_t *)y, s);
+    return launch_down_t1_any((const bf16_t *)Wo, d, H, mask, (const float *)ws.dec.act, (bf16_t *)y, s, ah);
 }
 
 }  // namespace halo

@@ -256,3 +256,16 @@ def test_mha_long_context_many_chunks():
     pd = H.halo_build_schedule(3, w.device_plr())
     _check_step(L, hs.mha_hidden(w, 0, hz.DEV), kc, vc, w.ctx, 3, pd, None)
     _check_step(L, hs.mha_hidden(w, 1, hz.DEV), kc, vc, 4095, 6, H.halo_build_schedule(6, w.device_plr()), None)
+
+
+@pytest.mark.parametrize("d,Hh,ctx", [(8, 1, 3), (1032, 5, 129), (2048, 16, 300), (3200, 25, 40), (7176, 3, 128), (8200, 2, 20)])
+def test_mha_of_any_row_length(d, Hh, ctx):
+    # rows that are not whole 512-element chunks, outputs that are not whole workgroups, and one row longer than the
+    # streaming kernels take
+    w = dataclasses.replace(hs.LLAMA7B_MHA_DECODE, name="case", d=d, n_heads=Hh, rank=40, ctx=ctx, max_len=ctx + 8, seed=37)
+    _say(f"mha any row length d={d} H={Hh} pos={ctx}")
+    L = MhaLayer(w)
+    kc, vc = hs.kv_cache(w, 0, hz.DEV)
+    for K in (max(1, Hh // 2), Hh):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        _check_step(L, hs.mha_hidden(w, K, hz.DEV), kc, vc, ctx, K, pd, hs.mha_drop_outcomes(w, 0, K))

@@ -595,3 +595,28 @@ def test_float32_tiles(T, d, G, gs):
         g = hz.gpu_forward(w, L, x, K, pd, drop)
         c = hz.oracle_forward(w, L, x, K, pd, drop)
         hz.assert_parity(g, c, TOL["f32"], f"f32 K={K}")
+
+
+@pytest.mark.parametrize("d,G,K", [(8, 3, 2), (136, 5, 3), (1032, 9, 9), (2560, 70, 33), (3200, 7, 7), (7936, 6, 3), (8184, 3, 2)])
+def test_one_token_of_any_row_length(d, G, K):
+    # rows whose last 512-element chunk is not whole, outputs that are not whole workgroups; the activation stays in
+    # float32 there: serial and overlapped form, the second equal to the first bit for bit
+    w = dataclasses.replace(hs.LLAMA7B_DECODE, name="case", d=d, ffn=G * 128, rank=40, seed=23)
+    _say(f"one token, any row length d={d} G={G}")
+    s = hz.shape_of(w)
+    L = hz.Layer(w)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    pdd = torch.from_numpy(pd).to(hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, 1, K), dtype=torch.uint8, device=hz.DEV)
+    for step in range(2):
+        x, xn = hs.hidden_states(w, step, hz.DEV), hs.hidden_states(w, step + 1, hz.DEV)
+        drop, dn = hs.drop_outcomes(w, 0, step), hs.drop_outcomes(w, 0, step + 1)
+        g = hz.gpu_forward(w, L, x, K, pd, drop)
+        hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"any d={d} step {step}")
+        gn = hz.gpu_forward(w, L, xn, K, pd, dn)
+        y = torch.full((1, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+        mn = torch.zeros((1, G), dtype=torch.uint8, device=hz.DEV)
+        H.halo_ffn_forward_ahead(s, x, L.Wg, L.Wu, L.Wd, torch.from_numpy(g["mask"]).to(hz.DEV), y, xn, L.At, L.Bt, K,
+                                 pdd, w.n_dev, torch.from_numpy(dn).to(hz.DEV), mn, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])

@@ -268,7 +268,7 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * of x, y and the predictor weights.  All pointers are device pointers, 16-byte aligned.
  * Everything else -- mask semantics, workspace, stream, errors -- is as in
  * halo_group_sparse_ffn / halo_ffn_forward.  Tuned paths (bf16 activations, n_groups <= 256): one
- * token with d in {4096, 8192} (every surviving code byte streamed once, float ALUs), and 2..16
+ * token with d <= 8192 (every surviving code byte streamed once, float ALUs), and 2..16
  * tokens with d a multiple of 1024 up to 8192 (matrix cores, codes expanded in registers); other
  * shapes and float32 activations take a plain path that dequantises element by element.  More than
  * 16 tokens (same shapes): with a workspace of halo_workspace_bytes_q4 the weights are expanded to bf16

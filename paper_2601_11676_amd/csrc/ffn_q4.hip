@@ -14,11 +14,12 @@
 // arithmetic stays far below the memory time: or-ing 0x4300 over a code gives the bf16 value
 // 128 + c exactly, the packed dot instruction multiplies two of those with two activations,
 // and the constant offset is taken out once per 32 elements: sum (c-8) x = sum (128+c) x -
-// 136 sum x.  Any other shape goes through plain kernels that dequantise element by element.
+// 136 sum x.  Shapes that no tuned path takes go through plain kernels that dequantise element by element.
 #include "kernels.hpp"
 #include "mask_device.hpp"
 #include "mask_words.hpp"
 #include "q4_codes.hpp"
+#include "row_stream.hpp"
 
 namespace halo {
 
@@ -52,44 +53,59 @@ __device__ __forceinline__ float sum32(const u32x4 (&x)[4])
 }
 
 // ---------------------------------------------------------------------------
-// one token, bf16 activations, d = NH * 2048, group size 128, G <= 256
+// one token, bf16 activations, d <= NH * 2048, group size 128, G <= 256
 // ---------------------------------------------------------------------------
 // gate/up: one wave per neuron at a time, NB neurons requested together.  A lane owns the 32
-// elements 2048 h + 32 lane .. + 31 of every half h: one 16-byte code piece per matrix row and
-// half, one scale (block 16 h + lane / 4), and the matching 64 bytes of x kept in registers.
+// elements 2048 h + 32 lane .. + 31 of every part h of the row: one 16-byte code piece per matrix row and
+// part, one scale (block 16 h + lane / 4), and the matching 64 bytes of x kept in registers.
 // Eight waves per workgroup, two per SIMD: unpacking the codes costs about three vector
 // instructions per two weights, which is not negligible beside the memory time of a quarter
 // of the bf16 bytes, so one wave's arithmetic has to overlap another's memory wait.
+// WHOLE: rows of exactly NH * 2048 elements, activation in bf16.  Otherwise any multiple of 128 above
+// (NH - 1) * 2048: lanes whose piece of the last part lies past the end read the row's first piece against zeros,
+// and the activation stays in float32, as in the plain path that served these lengths (13B shape: gate/up
+// 11.5 us and down 9.0 us per launch; the plain path took 19.7 and 44, and three more launches).
 constexpr int kQ4GateUpThreads = 512;
 constexpr int kQ4GateUpBlocks = 256;      // workgroups that do gate/up work (one per compute unit)
 
-template <int NH>
-__global__ __launch_bounds__(kQ4GateUpThreads, (NH == 2 ? 4 : 2)) void gate_up_q4_t1(
+// a predictor row beside such a row: its 16-byte pieces as RowLanes deals them
+template <int NH, bool WHOLE>
+__device__ __forceinline__ void q4_pred_row(const bf16_t *__restrict__ x_next, const bf16_t *__restrict__ At_next,
+                                            float *__restrict__ h_next, int d, int j, int lane)
+{
+    float p;
+    if (WHOLE || d > (NH * 4 - 2) * 512) {                       // uniform
+        const RowLanes<NH * 4, !WHOLE> rl(d, lane);
+        p = dot_order64_row<NH * 4, !WHOLE>(x_next, At_next + rl.row(j), rl, lane);
+    } else {
+        const RowLanes<NH * 4 - 2, true> rl(d, lane);
+        p = dot_order64_row<NH * 4 - 2, true>(x_next, At_next + rl.row(j), rl, lane);
+    }
+    if (lane == 0) h_next[j] = p > 0.0f ? p : 0.0f;
+}
+
+template <int NH, bool WHOLE, typename AT>
+__global__ __launch_bounds__(kQ4GateUpThreads, (NH <= 2 ? 4 : 2)) void gate_up_q4_t1(
     const bf16_t *__restrict__ x, int G, const uint32_t *__restrict__ Gq, const bf16_t *__restrict__ Gs,
     const uint32_t *__restrict__ Uq, const bf16_t *__restrict__ Us, const uint8_t *__restrict__ mask,
-    bf16_t *__restrict__ act, const bf16_t *__restrict__ x_next, const bf16_t *__restrict__ At_next, int r,
-    float *__restrict__ h_next, int n_pred, int pred_rows)
+    AT *__restrict__ act, const bf16_t *__restrict__ x_next, const bf16_t *__restrict__ At_next, int r,
+    float *__restrict__ h_next, int n_pred, int pred_rows, int len)
 {
-    constexpr int d = NH * 2048, gs = 128, NB = NH == 2 ? 3 : 2, WPB = kQ4GateUpThreads / 64;
-    constexpr int kWords = d / 8, kBlocks = d / kQ4Block;
+    constexpr int gs = 128, NB = NH <= 2 ? 3 : 2, WPB = kQ4GateUpThreads / 64;
+    const int d = WHOLE ? NH * 2048 : len;
+    const int kWords = d / 8, kBlocks = d / kQ4Block;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // pred_rows > 0 (then n_pred == 0): the predictor's rows are dealt evenly, pred_rows of them to the last
     // waves of every workgroup, row vblock + 256 k to wave 7 - k.  A row of At is as many bytes as two
     // neurons' codes, and a workgroup of predictor rows alone carried three quarters more bytes than its
     // neighbours' share of the codes: the compute units that held one finished 2 us after the others.
-    if (pred_rows > 0 && wave >= WPB - pred_rows) {
-        const int j = blockIdx.x + kQ4GateUpBlocks * (WPB - 1 - wave);
-        const float p = dot_order64_fixed<d>(x_next, At_next + (size_t)j * d, lane);
-        if (lane == 0) h_next[j] = p > 0.0f ? p : 0.0f;
-    }
+    if (pred_rows > 0 && wave >= WPB - pred_rows)
+        q4_pred_row<NH, WHOLE>(x_next, At_next, h_next, d, blockIdx.x + kQ4GateUpBlocks * (WPB - 1 - wave), lane);
     if ((int)blockIdx.x < n_pred) {
         // the first predictor layer of the NEXT block rides along (paper Sec. III-B.3, Pred beside
         // Load/Comp, one layer ahead): one row of At per wave, h_next = ReLU(x_next A)
         const int j = blockIdx.x * WPB + wave;
-        if (j < r) {
-            const float p = dot_order64_fixed<d>(x_next, At_next + (size_t)j * d, lane);
-            if (lane == 0) h_next[j] = p > 0.0f ? p : 0.0f;
-        }
+        if (j < r) q4_pred_row<NH, WHOLE>(x_next, At_next, h_next, d, j, lane);
         return;
     }
     const MaskWords mw = load_mask_words(mask, G, lane);
@@ -113,13 +129,19 @@ __global__ __launch_bounds__(kQ4GateUpThreads, (NH == 2 ? 4 : 2)) void gate_up_q
     if (n0 >= n1) return;
     const int u_first = n0 / gs, u_last = (n1 - 1) / gs;
     const int g_first = nth_group(mw, u_first, lane), g_last = nth_group(mw, u_last, lane);
+    // this lane's piece of the last part of a row: in words from the row's start, and its scale
+    const bool tail_ok = WHOLE || (NH - 1) * 2048 + lane * 32 < d;
+    const int tail_word = tail_ok ? (NH - 1) * 256 + lane * 4 : 0, tail_block = tail_ok ? (NH - 1) * 16 + (lane >> 2) : 0;
     u32x4 xr[NH][4];
     float xs[NH];
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            xr[h][j] = *reinterpret_cast<const u32x4 *>(x + h * 2048 + lane * 32 + j * 8);
+        for (int j = 0; j < 4; ++j) {
+            const bool tail = !WHOLE && h == NH - 1;
+            xr[h][j] = *reinterpret_cast<const u32x4 *>(x + (tail ? tail_word * 8 : h * 2048 + lane * 32) + j * 8);
+            if (tail && !tail_ok) xr[h][j] = u32x4{0u, 0u, 0u, 0u};
+        }
     }
     for (int nb = n0; nb < n1; nb += NB) {
         u32x4 cg[NB][NH], cu[NB][NH];
@@ -131,12 +153,12 @@ __global__ __launch_bounds__(kQ4GateUpThreads, (NH == 2 ? 4 : 2)) void gate_up_q
             const size_t row = (size_t)(u == u_first ? g_first : g_last) * gs + (n - u * gs);
 #pragma unroll
             for (int h = 0; h < NH; ++h) {
-                cg[i][h] = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4 *>(Gq + row * kWords + h * 256) + lane);
-                cu[i][h] = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4 *>(Uq + row * kWords + h * 256) + lane);
-                sg[i][h] = Gs[row * kBlocks + h * 16 + (lane >> 2)];
-                su[i][h] = Us[row * kBlocks + h * 16 + (lane >> 2)];
+                const bool tail = !WHOLE && h == NH - 1;
+                const int word = tail ? tail_word : h * 256 + lane * 4, block = tail ? tail_block : h * 16 + (lane >> 2);
+                cg[i][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(Gq + row * kWords + word));
+                cu[i][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(Uq + row * kWords + word));
+                sg[i][h] = Gs[row * kBlocks + block];
+                su[i][h] = Us[row * kBlocks + block];
             }
         }
         if (nb == n0) {
@@ -152,72 +174,143 @@ __global__ __launch_bounds__(kQ4GateUpThreads, (NH == 2 ? 4 : 2)) void gate_up_q
                 ag = __builtin_fmaf(bf16_bits_to_float(sg[i][h]), q4_dot32(cg[i][h], xr[h]) - xs[h], ag);
                 au = __builtin_fmaf(bf16_bits_to_float(su[i][h]), q4_dot32(cu[i][h], xr[h]) - xs[h], au);
             }
-            const float v = silu_mul_fast(wave_sum_fast(ag), wave_sum_fast(au));
-            if (lane == 0) act[nb + i] = f32_to_bf16(v);
+            ag = wave_sum_fast(ag);
+            au = wave_sum_fast(au);
+            const float v = WHOLE ? silu_mul_fast(ag, au) : silu_mul(ag, au);
+            if (lane == 0) store_out(act + nb + i, v);
         }
     }
 }
 
 // down: four lanes share an output row j (16 bytes each = 32 of the group's 128 neurons), a
 // wave covers 16 consecutive rows = 1 KiB of a group's codes, the workgroup's eight waves take
-// every eighth surviving group and meet in LDS.  A lane fetches what it multiplies straight from
-// memory -- its code piece, the row's scale and the 64 bytes of the activation that face the piece
-// (the same 64 bytes for the 16 rows of a wave: one request per wave instruction) -- for four groups
-// at a time, and takes the sum of those 32 activations itself (for the constant offset of the
-// codes): nothing is staged through LDS, so no barrier stands between the mask and the first codes
-// (with the activation staged once per workgroup the kernel spent 3.2 of its 5.3 us getting ready).
-constexpr int kDownQ4Batch = 4;
+// every eighth surviving group and meet in LDS.  All of a wave's groups (up to eight at a time) are requested
+// together: the codes and the rows' scales, and beside them the activations that face them, coalesced, which the
+// wave then parks in LDS for itself -- no barrier stands between the mask and the codes -- and reads back in
+// operand order.  What bounds it is the chain mask -> group ids -> codes -> sums, so it is built for few
+// requests and one memory round trip per eight groups: with the activations fetched straight into every lane
+// (four more requests per group, two batches of four groups, group ids from a search per group) it took 6.8 us per
+// launch at the 7B shape, now 5.9; the same form in float32 at the 13B shape 30 us, now 9.0.
+// AT: bf16, or float for row lengths other than 4096 and 8192.
+constexpr int kDownQ4Batch = 8;
 
 struct DownQ4Shared {
     float part[8][16];
 };
 
+// the 32 activations at LDS address a (bytes) against a lane's 32 codes: sum (c - 8) a.  The offset's sum comes from
+// two of the 32 per lane, added over the 16 lanes (same lane % 4) that face the same 32.
+__device__ __forceinline__ float q4_down_dot(const u32x4 &c, const bf16_t *a, int lane)
+{
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const u32x4 *>(a + k * 8);
+    float sum = dot2_bf16(0x3F803F80u, *reinterpret_cast<const uint32_t *>(a + (lane >> 2) * 2), 0.0f);
+    sum = xor_add<4>(sum);
+    sum = xor_add<8>(sum);
+    sum = xor_add<16>(sum);
+    sum = xor_add<32>(sum);
+    return q4_dot32(c, v) - 136.0f * sum;
+}
+__device__ __forceinline__ float q4_down_dot(const u32x4 &c, const float *a, int lane)
+{
+    const float2 own = *reinterpret_cast<const float2 *>(a + (lane >> 2) * 2);
+    float sum = own.x + own.y;
+    sum = xor_add<4>(sum);
+    sum = xor_add<8>(sum);
+    sum = xor_add<16>(sum);
+    sum = xor_add<32>(sum);
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float4 v = *reinterpret_cast<const float4 *>(a + j * 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            // elements 4 j + 2 i and 4 j + 2 i + 1 as 128 + c
+            const uint32_t pair = q4_pair(w[j >> 1], 2 * (j & 1) + i);
+            acc[2 * i] = __builtin_fmaf(bf16_lo(pair), i ? v.z : v.x, acc[2 * i]);
+            acc[2 * i + 1] = __builtin_fmaf(bf16_hi(pair), i ? v.w : v.y, acc[2 * i + 1]);
+        }
+    }
+    return ((acc[0] + acc[1]) + (acc[2] + acc[3])) - 136.0f * sum;
+}
+
 // With ahead != 0 workgroup 0 is the mask workgroup of the NEXT block (second predictor layer,
 // ranking, mask); it is dispatched first because it is the longest dependent chain.  A
 // workgroup is one or the other, so the two LDS layouts share their bytes and two workgroups
 // fit a compute unit (the mask workgroup must run beside a down-projection one, not after).
+template <typename AT>
 __global__ __launch_bounds__(512, 4) void down_q4_t1(int d, int G, const uint32_t *__restrict__ Dq,
                                                       const bf16_t *__restrict__ Ds,
                                                       const uint8_t *__restrict__ mask,
-                                                      const bf16_t *__restrict__ act, bf16_t *__restrict__ y,
+                                                      const AT *__restrict__ act, bf16_t *__restrict__ y,
                                                       int ahead, AheadDev nx)
 {
     constexpr int gs = 128, kB = kDownQ4Batch;
-    constexpr size_t kLds = sizeof(DownQ4Shared) > sizeof(MaskShared) ? sizeof(DownQ4Shared) : sizeof(MaskShared);
+    constexpr int kPer = 1024 / (gs * sizeof(AT)), kLoads = kB / kPer;     // groups per activation load, loads per batch
+    constexpr size_t kActBytes = kB * gs * sizeof(AT);                     // a wave's activations of a batch
+    constexpr size_t kProj = sizeof(DownQ4Shared) + 8 * kActBytes;
+    constexpr size_t kLds = kProj > sizeof(MaskShared) ? kProj : sizeof(MaskShared);
     __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
     if (ahead && blockIdx.x == 0) {
         mask_scores_block<512, bf16_t, true>(*reinterpret_cast<MaskShared *>(lds), tid, nx.h, nx.Bt, nx.r,
                                              nx.scores, G, nx.K, nx.prio_dev, nx.n_dev, nx.drop, nx.order,
                                              nx.group_dev, nx.mask, nx.surv_idx, nx.n_surv);
         return;
     }
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     DownQ4Shared &sh = *reinterpret_cast<DownQ4Shared *>(lds);
+    AT *mine = reinterpret_cast<AT *>(lds + sizeof(DownQ4Shared) + wave * kActBytes);
     const int vblock = blockIdx.x - (ahead ? 1 : 0);
     const MaskWords mw = load_mask_words(mask, G, lane);
-    const int count = mw.count;
+    // this wave's groups: positions wave, wave + 8, ... of the surviving list, at most 32 of them, one to a lane.
+    // A lane that holds a surviving group knows its position and hands the group to lane position / 8 of this wave
+    // if it is one of the wave's; the others hand theirs to lane 63, which nobody asks.
+    int my_group = 0;
+    {
+        int base = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int pos = base + __popcll(mw.w[k] & ((1ull << lane) - 1ull));
+            const bool ours = ((mw.w[k] >> lane) & 1ull) && (pos & 7) == wave;
+            my_group |= __builtin_amdgcn_ds_permute((ours ? pos >> 3 : 63) * 4, ours ? k * kWave + lane : 0);
+            base += __popcll(mw.w[k]);
+        }
+    }
+    const int slots = (mw.count - wave + 7) >> 3;
     const int j = vblock * 16 + (lane >> 2);                       // output row of this lane
     const int p = lane & 3;                                        // which 32 neurons of the group
     float acc = 0.0f;
-    const size_t gstride = (size_t)d * 16;                         // words per group
-    // this wave's groups: positions wave, wave + 8, ... of the surviving list (at most 32 of them)
-    for (int u0 = wave; u0 < count; u0 += 8 * kB) {
-        u32x4 c[kB], a[kB][4];
+    const size_t gwords = (size_t)d * 16;                          // words per group
+    for (int s0 = 0; s0 < slots; s0 += kB) {                       // uniform
+        u32x4 c[kB], a[kLoads];
         uint16_t s[kB];
 #pragma unroll
         for (int q = 0; q < kB; ++q) {
-            const int u = u0 + 8 * q < count ? u0 + 8 * q : u0;      // past the end: an in-range duplicate
-            const int g = nth_group(mw, u, lane);
-            c[q] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4 *>(Dq + g * gstride + (size_t)j * 16) + p);
-            s[q] = Ds[(size_t)g * d + j];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a[q][k] = *reinterpret_cast<const u32x4 *>(act + u * gs + p * 32 + k * 8);
+            if (s0 + q < slots) {
+                const int g = __builtin_amdgcn_readlane(my_group, s0 + q);
+                c[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(Dq + g * gwords + (size_t)j * 16) + p);
+                s[q] = Ds[(size_t)g * d + j];
+            }
         }
+        // activation load n: groups s0 + n kPer .. of the wave, 16 bytes a lane (past the last one: repeats it)
+        constexpr int kLanes = kWave / kPer;
+#pragma unroll
+        for (int n = 0; n < kLoads; ++n)
+            if (s0 + n * kPer < slots) {
+                const int u = wave + 8 * min(s0 + n * kPer + lane / kLanes, slots - 1);
+                a[n] = *reinterpret_cast<const u32x4 *>(act + u * gs + (lane % kLanes) * (16 / (int)sizeof(AT)));
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < kLoads; ++n)
+            if (s0 + n * kPer < slots) *reinterpret_cast<u32x4 *>(reinterpret_cast<unsigned char *>(mine) + n * 1024 + lane * 16) = a[n];
+        // (the region is the wave's own, and a wave's LDS operations complete in order)
 #pragma unroll
         for (int q = 0; q < kB; ++q) {
-            if (u0 + 8 * q < count)
-                acc = __builtin_fmaf(bf16_bits_to_float(s[q]), q4_dot32(c[q], a[q]) - 136.0f * sum32(a[q]), acc);
+            if (s0 + q < slots) acc = __builtin_fmaf(bf16_bits_to_float(s[q]), q4_down_dot(c[q], mine + q * gs + p * 32, lane), acc);
         }
     }
     // the four lanes of a row, then the eight waves
@@ -413,6 +506,36 @@ static hipError_t expand_q4(const uint32_t *codes, const bf16_t *scales, bf16_t 
     return hipGetLastError();
 }
 
+template <typename AT>
+static hipError_t q4_one_token(const bf16_t *x, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *y, AT *act,
+                               hipStream_t s, const AheadArgs *ahead, bool *ahead_fused)
+{
+    constexpr bool kWhole = sizeof(AT) == 2;
+    const AheadArgs *ah = (ahead && ahead_fused) ? ahead : nullptr;
+    if (ah) *ahead_fused = true;
+    // predictors of 256 or 512 rows: one or two rows in every gate/up workgroup; else workgroups of their own
+    const int pred_rows = (ah && (ah->r == kQ4GateUpBlocks || ah->r == 2 * kQ4GateUpBlocks)) ? ah->r / kQ4GateUpBlocks : 0;
+    const int n_pred = (ah && pred_rows == 0) ? (ah->r + 7) / 8 : 0;
+    const bf16_t *xn = ah ? (const bf16_t *)ah->x_next : nullptr, *an = ah ? (const bf16_t *)ah->At : nullptr;
+    float *hn = ah ? ah->h : nullptr;
+    const int r = ah ? ah->r : 0;
+#define HALO_Q4_T1(NH)                                                                                                  \
+    launch_timed("gate_up_q4_t1", gate_up_q4_t1<NH, kWhole, AT>, dim3(kQ4GateUpBlocks + n_pred), dim3(kQ4GateUpThreads), \
+                 s, x, G, w.gate_codes, w.gate_scales, w.up_codes, w.up_scales, mask, act, xn, an, r, hn, n_pred,       \
+                 pred_rows, d)
+    switch ((d + 2047) / 2048) {
+    case 1: if constexpr (!kWhole) HALO_Q4_T1(1); break;
+    case 2: HALO_Q4_T1(2); break;
+    case 3: if constexpr (!kWhole) HALO_Q4_T1(3); break;
+    default: HALO_Q4_T1(4); break;
+    }
+#undef HALO_Q4_T1
+    const AheadDev nx = ah ? ahead_dev(*ah) : AheadDev{};
+    down_q4_t1<AT><<<dim3(d / 16 + (ah ? 1 : 0)), dim3(512), 0, s>>>(d, G, w.down_codes, w.down_scales, mask, (const AT *)act,
+                                                                 y, ah ? 1 : 0, nx);
+    return hipGetLastError();
+}
+
 hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, const Q4Weights &w,
                          const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s, int rank,
                          const AheadArgs *ahead, bool *ahead_fused)
@@ -422,28 +545,10 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
         return q4_generic<float>((const float *)x, T, d, G, gs, w, mask, (float *)y, ws, s);
     const bf16_t *bx = (const bf16_t *)x;
     bf16_t *by = (bf16_t *)y;
-    if (T == 1 && G <= 256 && (d == 4096 || d == 8192)) {
-        bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
-        const AheadArgs *ah = (ahead && ahead_fused) ? ahead : nullptr;
-        if (ah) *ahead_fused = true;
-        // predictors of 256 or 512 rows: one or two rows in every gate/up workgroup; else workgroups of their own
-        const int pred_rows = (ah && (ah->r == kQ4GateUpBlocks || ah->r == 2 * kQ4GateUpBlocks)) ? ah->r / kQ4GateUpBlocks : 0;
-        const int n_pred = (ah && pred_rows == 0) ? (ah->r + 7) / 8 : 0;
-        const bf16_t *xn = ah ? (const bf16_t *)ah->x_next : nullptr, *an = ah ? (const bf16_t *)ah->At : nullptr;
-        float *hn = ah ? ah->h : nullptr;
-        const int r = ah ? ah->r : 0;
-        if (d == 4096)
-            launch_timed("gate_up_q4_t1", gate_up_q4_t1<2>, dim3(kQ4GateUpBlocks + n_pred), dim3(kQ4GateUpThreads), s, bx, G, w.gate_codes,
-                         w.gate_scales, w.up_codes, w.up_scales, mask, act, xn, an, r, hn, n_pred, pred_rows);
-        else
-            launch_timed("gate_up_q4_t1", gate_up_q4_t1<4>, dim3(kQ4GateUpBlocks + n_pred), dim3(kQ4GateUpThreads), s, bx, G, w.gate_codes,
-                         w.gate_scales, w.up_codes, w.up_scales, mask, act, xn, an, r, hn, n_pred, pred_rows);
-        AheadDev nx{};
-        if (ah) nx = ahead_dev(*ah);
-        down_q4_t1<<<dim3(d / 16 + (ah ? 1 : 0)), dim3(512), 0, s>>>(d, G, w.down_codes, w.down_scales, mask, act,
-                                                                     by, ah ? 1 : 0, nx);
-        return hipGetLastError();
-    }
+    if (T == 1 && G <= 256 && d <= 8192)
+        return d == 4096 || d == 8192
+                   ? q4_one_token<bf16_t>(bx, d, G, w, mask, by, reinterpret_cast<bf16_t *>(ws.act), s, ahead, ahead_fused)
+                   : q4_one_token<float>(bx, d, G, w, mask, by, ws.act, s, ahead, ahead_fused);
     if (q4_mfma_path_supported(T, d, G, gs))
         return launch_ffn_q4_mfma(bx, T, d, G, w, mask, by, ws, s, rank, ahead, ahead_fused);
     if (ws.q4_w && q4_expand_supported(T, dtype, d, G, gs)) {

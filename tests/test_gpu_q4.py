@@ -285,3 +285,28 @@ def test_q4_stack_teacher_forced(wl, keep, layers):
     h = hz.run_stack_gpu(wl, keep, layers=layers, check_layers=check, on_layer=on_layer, q4=True)
     assert torch.isfinite(h).all() and seen == check
 
+
+
+@pytest.mark.parametrize("d,G,K,r", [(128, 3, 2, 40), (1152, 9, 9, 256), (2048, 70, 33, 64), (2560, 7, 4, 512), (5120, 86, 43, 256),
+                                     (6272, 6, 3, 256), (8064, 40, 30, 128)])
+def test_q4_one_token_of_any_row_length(d, G, K, r):
+    # rows that are not whole 2048-element parts; the activation stays in float32 there: serial and overlapped form,
+    # the second equal to the first bit for bit
+    w = dataclasses.replace(hs.LLAMA7B_DECODE, name="case", d=d, ffn=G * 128, rank=r, seed=24)
+    _say(f"q4 one token, any row length d={d} G={G} r={r}")
+    s = hz.shape_of(w)
+    L = hz.Q4Layer(w)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    pdd = torch.from_numpy(pd).to(hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, 1, K), dtype=torch.uint8, device=hz.DEV)
+    x, xn = hs.hidden_states(w, 0, hz.DEV), hs.hidden_states(w, 1, hz.DEV)
+    drop, dn = hs.drop_outcomes(w, 0, 0), hs.drop_outcomes(w, 0, 1)
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop)
+    hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"q4 any d={d}")
+    gn = hz.gpu_forward_q4(w, L, xn, K, pd, dn)
+    y = torch.full((1, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+    mn = torch.zeros((1, G), dtype=torch.uint8, device=hz.DEV)
+    H.halo_ffn_forward_ahead_q4(s, x, L.q4, torch.from_numpy(g["mask"]).to(hz.DEV), y, xn, L.At, L.Bt, K, pdd, w.n_dev,
+                                torch.from_numpy(dn).to(hz.DEV), mn, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])

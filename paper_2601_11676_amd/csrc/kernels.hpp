@@ -28,7 +28,7 @@ struct DecodeScratch {
                         // (the matrix-core paths store bf16 in the same buffer)
     int32_t *tok_list;  // [G][T] prefill: tokens that keep each group, ascending
     int32_t *tok_cnt;   // [G]
-    int32_t *slot;      // [T][G] position of the token in its group's list, -1 = not kept
+    int32_t *slot;      // [T][G] words: prefill's row table (16 bits, group-major), or positions in the lists, -1 = not kept
     float *partial;     // [splits][T][d] prefill: the down projection's sums per range of groups
     bf16_t *q4_w = nullptr;   // 4-bit callers with many tokens: room for Wg, Wu [ffn][d] and Wd [G][d][gs] as bf16, or null
 };
@@ -109,7 +109,7 @@ hipError_t launch_gate_up_few(const bf16_t *x, int T, int d, int G, int gs, cons
 
 // ffn_prefill.hip : bf16 matrix-core path for many tokens
 bool prefill_path_supported(int T, int d, int gs);
-int prefill_down_splits(int T, int d, int G);   // ranges of groups in the down projection (0: one pass, no ranges)
+int prefill_down_splits(int T, int d, int G);   // ranges of groups in the down projection (0: no ring kernel)
 hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg,
                               const bf16_t *Wu, const bf16_t *Wd, const uint8_t *mask, bf16_t *y,
                               const DecodeScratch &ws, hipStream_t s);
@@ -131,6 +131,11 @@ bool q4_expand_supported(int T, int dtype, int d, int G, int gs);
 hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, const Q4Weights &w,
                          const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s, int rank,
                          const AheadArgs *ahead = nullptr, bool *ahead_fused = nullptr);
+
+// ffn_prefill.hip : many tokens over 4-bit weights, expanded on their way into LDS
+bool prefill_q4_supported(int T, int d, int G, int gs);
+hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *y,
+                                 const DecodeScratch &ws, hipStream_t s);
 
 // ffn_q4_mt.hip : 4-bit weights, 2..16 tokens, matrix cores
 bool q4_mfma_path_supported(int T, int d, int G, int gs);

@@ -620,3 +620,26 @@ def test_one_token_of_any_row_length(d, G, K):
                                  pdd, w.n_dev, torch.from_numpy(dn).to(hz.DEV), mn, ws)
         torch.cuda.synchronize()
         assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])
+
+
+@pytest.mark.parametrize("T,d,G,K", [
+    (17, 128, 3, 2),           # one block of two stages, one group range per group
+    (128, 256, 5, 2),          # a full half tile of tokens in the down projection
+    (129, 640, 40, 20),        # half tiles in gate/up, a whole tile with half of it empty in down
+    (256, 384, 70, 60),        # two half tiles for the groups that most tokens keep
+    (257, 1024, 6, 6),         # dense: no token needs a row of zeros
+    (300, 256, 300, 30),       # more than 256 groups
+    (515, 4224, 9, 4),         # three token tiles, the last with three tokens
+])
+def test_many_token_rings(T, d, G, K):
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=81)
+    _say(f"many-token rings T={T} d={d} G={G} K={K}")
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    drop[0] = 1                                                # a token with no survivor
+    for dr in (drop, None):
+        g = hz.gpu_forward(w, L, x, K, pd, dr)
+        c = hz.oracle_forward(w, L, x, K, pd, dr)
+        hz.assert_parity(g, c, TOL["bf16"], f"rings T={T}")

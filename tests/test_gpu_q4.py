@@ -310,3 +310,31 @@ def test_q4_one_token_of_any_row_length(d, G, K, r):
                                 torch.from_numpy(dn).to(hz.DEV), mn, ws)
     torch.cuda.synchronize()
     assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])
+
+
+@pytest.mark.parametrize("T,d,G,K", [
+    (17, 128, 3, 2),           # one block of codes per row
+    (128, 640, 5, 2),          # an odd number of blocks per row: the scales' words straddle rows
+    (200, 384, 70, 60),        # half tiles in gate/up, whole ones in down
+    (257, 1024, 6, 6),         # dense: no token needs a row of zeros
+    (300, 256, 300, 30),       # more groups than the few-token kernels take
+    (515, 4224, 9, 4),         # three token tiles, the last with three tokens
+])
+def test_q4_many_token_rings(T, d, G, K):
+    # the codes expanded on their way into LDS give what the bf16 kernels give on the expanded weights, bit for bit
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=82)
+    _say(f"q4 many-token rings T={T} d={d} G={G} K={K}")
+    s = hz.shape_of(w)
+    L = hz.Q4Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    drop[0] = 1
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop)
+    hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"q4 rings T={T}")
+    Wg, Wu, WdT = (torch.from_numpy(np.ascontiguousarray(a)).to(torch.bfloat16).to(hz.DEV) for a in L.host()[2:])
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, K), dtype=torch.uint8, device=hz.DEV)
+    H.halo_group_sparse_ffn(s, x, Wg, Wu, H.pack_down_proj(WdT, 128), torch.from_numpy(g["mask"]).to(hz.DEV), y, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"])

@@ -229,6 +229,18 @@ __device__ __forceinline__ void mfma16_inplace(f32x4_t &acc, const u32x4 &a, con
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
+// Zeros in the accumulators.  (They are carried by the loop over the stages, so the writes stand in front of it, far from
+// the first matrix instruction; in front of a peeled first step the compiler puts them right before the statements
+// that read them, and it cannot know that those need a distance.)
+template <int MT, int TT>
+__device__ __forceinline__ void clear_accumulators(f32x4_t (&acc)[MT][TT])
+{
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < TT; ++n) acc[m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+}
+
 // Token tiles are numbered group by group (group g has ceil(cnt[g] / tile_tokens) of them), and only
 // tiles that exist get a number, so the working workgroups are consecutive.  Called by whole waves;
 // results are the same in every lane.
@@ -242,25 +254,27 @@ __device__ __forceinline__ int wave_inclusive_sum(int n, int lane)
     return n;
 }
 
-__device__ __forceinline__ int count_tiles(const int32_t *__restrict__ tok_cnt, int G, int tile_tokens, int lane)
+// tiles(n): the tiles of a group that n tokens keep
+template <typename Tiles>
+__device__ __forceinline__ int count_tiles(const int32_t *__restrict__ tok_cnt, int G, int lane, Tiles tiles)
 {
     int total = 0;
     for (int g0 = 0; g0 < G; g0 += 64) {
         const int g = g0 + lane;
-        const int n = g < G ? (tok_cnt[g] + tile_tokens - 1) / tile_tokens : 0;
+        const int n = g < G ? tiles(tok_cnt[g]) : 0;
         total += __shfl(wave_inclusive_sum(n, lane), 63);
     }
     return total;
 }
 
 // group and tile within the group of tile number `target` (< count_tiles)
-__device__ __forceinline__ int2 find_tile(const int32_t *__restrict__ tok_cnt, int G, int tile_tokens, int target,
-                                          int lane)
+template <typename Tiles>
+__device__ __forceinline__ int2 find_tile(const int32_t *__restrict__ tok_cnt, int G, int target, int lane, Tiles tiles)
 {
     int base = 0;
     for (int g0 = 0; g0 < G; g0 += 64) {
         const int g = g0 + lane;
-        const int n = g < G ? (tok_cnt[g] + tile_tokens - 1) / tile_tokens : 0;
+        const int n = g < G ? tiles(tok_cnt[g]) : 0;
         const int incl = wave_inclusive_sum(n, lane);
         const int total = __shfl(incl, 63);
         if (target < base + total) {
@@ -403,13 +417,14 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     // workgroups of a die walk K from the same starting stage, so those rows are found in the die's
     // own L2.  Numbering only the tiles that exist also spreads the work evenly over the dies (with
     // a (group, chunk) grid the empty chunks left some dies with more workgroups than compute units).
-    const int n_items = 2 * count_tiles(tok_cnt, G, NTOK, lane);
+    auto tiles_of = [](int n) { return (n + NTOK - 1) / NTOK; };
+    const int n_items = 2 * count_tiles(tok_cnt, G, lane, tiles_of);
     const int per_die = (n_items + 7) >> 3;
     const int die = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int item = __builtin_amdgcn_readfirstlane(die * per_die + slot);
     if (slot >= per_die || item >= n_items) return;              // uniform for the workgroup
     const int nt = item & 1;
-    const int2 tile = find_tile(tok_cnt, G, NTOK, item >> 1, lane);
+    const int2 tile = find_tile(tok_cnt, G, item >> 1, lane, tiles_of);
     const int g = __builtin_amdgcn_readfirstlane(tile.x);
     const int cnt = tok_cnt[g];
     const int c0 = __builtin_amdgcn_readfirstlane(tile.y) * NTOK;
@@ -470,10 +485,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     // operand reads: tile row (or token row) i16 of a tile, piece (4 ks + q) at its swizzled position
     const int loff = i16 * 128 + (((4 * part.ks + q) ^ (i16 & 7)) * 16);
     f32x4_t acc[MT][TT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) acc[m][tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    clear_accumulators(acc);
 
     // Stage s lives in ring buffer s % 3 (converted weights: s % 2).  At the top of step s the fragments of stage s are
     // in registers.  The barrier of step s says: everybody's part of stage s+1 has landed and everybody
@@ -545,6 +557,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     wait_loads<0>();                                             // (of loads that move nothing)
     __syncthreads();                                             // every wave is done with the rings
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");           // the last matrix results are in the registers
+    __builtin_amdgcn_sched_barrier(0);                           // (nothing that reads them moves above the pause)
 
     bf16_t *act_row0 = act + (size_t)g * T * gs + nt * 64;
     const int sl0 = c0 + part.tq * 64 + i16;
@@ -566,6 +579,160 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         exchange_halves<0, MT, TT>(acc, ring, wave, lane, put);
     else
         exchange_halves<1, MT, TT>(acc, ring, wave, lane, put);
+}
+
+// ---------------------------------------------------------------------------
+// the same over whole tiles of 256 weight rows x 256 tokens (bf16)
+// ---------------------------------------------------------------------------
+// What a compute unit can have in flight bounds gate_up_pf_ring: it moves 96 KiB into LDS per 256 x 256 x 64 of matrix
+// work, this kernel 64.  (us per launch against gate_up_pf_ring, half of the tokens keeping a group: 1000 tokens of the 70B
+// shape 495 against 525, of the 13B shape 135 against 168, 1024 tokens of the 7B shape 108 against 125.)  The eight waves are
+// two halves of the rows times four shares of the 16-token tiles over the whole K range: no exchange at the end.
+// Groups end in a tile of any length (their token counts differ widely), so a wave's tiles are every fourth one and a tile
+// of one, two or three quarters runs with as many per wave: 1000 tokens of the 70B shape 523 -> 495.  (Taking all whole
+// tiles first and the short ones behind them evened out the last round, but then no two tiles of a group share their
+// weight rows in a die's L2: 13B shape 138 -> 192.)
+// Two stages of 64 KiB fit, so a step is cut in two: half kk of the 64 elements of stage s is multiplied while the
+// fragments of the next half are read.  The barrier sits in front of the second half, when everybody has read all of
+// stage s: its buffers go to the stages that follow, token rows one step ahead, weight rows (three buffers: they come from
+// memory, not from a neighbour's L2 lines) two.
+constexpr int kBigStage = 256 * 128;                             // bytes of a stage of weight rows, or of token rows
+
+__global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gate_up_pf_big(
+    const bf16_t *__restrict__ x, int T, int d, int G, const bf16_t *__restrict__ Wg, const bf16_t *__restrict__ Wu,
+    const int32_t *__restrict__ tok_list, const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];      // two stages of token rows, three of weight rows
+    constexpr int gs = 128, kWBase = 2 * kBigStage;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rh = wave & 1, tq = wave >> 1;
+    const int i16 = lane & 15, q = lane >> 4;
+    // one item per token tile; numbered as in gate_up_pf_ring
+    auto tiles_of = [](int n) { return (n + 255) / 256; };
+    const int n_items = count_tiles(tok_cnt, G, lane, tiles_of);
+    const int per_die = (n_items + 7) >> 3;
+    const int die = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int item = __builtin_amdgcn_readfirstlane(die * per_die + slot);
+    if (slot >= per_die || item >= n_items) return;              // uniform for the workgroup
+    const int2 tile = find_tile(tok_cnt, G, item, lane, tiles_of);
+    const int g = __builtin_amdgcn_readfirstlane(tile.x);
+    const int cnt = tok_cnt[g];
+    const int c0 = __builtin_amdgcn_readfirstlane(tile.y) * 256;
+    const int quarters = min((cnt - c0 + 63) / 64, 4);
+    const int32_t *list = tok_list + (size_t)g * T;
+
+    const int ns = d / 64, stage0 = (die * ns) >> 3;
+    const int br = lane >> 3, piece = (lane & 7) ^ br;
+    // a stage's 32 blocks of 8 token rows and 32 of weight rows (gate rows, then up rows): wave w takes blocks w + 8 j
+    uint32_t off_x[4], off_w[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int sl = c0 + (wave + 8 * j) * 8 + br;
+        off_x[j] = sl < cnt ? (uint32_t)(list[sl] * d + piece * 8) * 2u : kNoRow;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) off_w[j] = (uint32_t)(((wave + 8 * j) * 8 + br) * d + piece * 8) * 2u;
+    const uint32_t ring0 = (uint32_t)(size_t)ring + wave * 1024;
+    const srd_t srd_g = make_srd(Wg + (size_t)g * gs * d, true), srd_u = make_srd(Wu + (size_t)g * gs * d, true);
+    const srd_t srd_x = make_srd(x, true);
+    auto if_exists = [](srd_t v, bool yes) {
+        v.z = (uint32_t)__builtin_amdgcn_readfirstlane(yes ? v.z : 0u);
+        return v;
+    };
+    auto byte_of = [&](int s) { return (uint32_t)(stage0 + s >= ns ? stage0 + s - ns : stage0 + s) * 128u; };
+    auto load_x = [&](int j, int s) {
+        const bool yes = s < ns;
+        load_to_lds16(if_exists(srd_x, yes), off_x[j], byte_of(yes ? s : 0), ring0 + (s & 1) * kBigStage + j * 8192);
+    };
+    auto load_w = [&](int j, int s, int b) {                     // b = s % 3
+        const bool yes = s < ns;
+        load_to_lds16<true>(if_exists(j < 2 ? srd_g : srd_u, yes), off_w[j & 1], byte_of(yes ? s : 0),
+                            ring0 + kWBase + b * kBigStage + j * 8192);
+    };
+    // the wave's row tiles: four of the gate rows and the four of the up rows that face them; its 16-token tiles: tq + 4 n
+    auto row_tile = [&](int m) { return m < 4 ? 4 * rh + m : 8 + 4 * rh + (m - 4); };
+    const int loff0 = i16 * 128 + ((q ^ (i16 & 7)) * 16), loff1 = loff0 ^ 64;       // piece 4 kk + q
+
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_x(j, s);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_w(j, s, s);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load_w(j, 2, 2);
+    wait_loads<12>();                                            // stage 0
+    __syncthreads();
+
+    auto tile_of = [&](auto quarters_c) __attribute__((always_inline)) {
+        constexpr int N = decltype(quarters_c)::value;           // 16-token tiles of a wave
+        f32x4_t acc[8][N];
+        clear_accumulators(acc);
+        u32x4 fa[8], f0[N], f1[N];
+        int wb = 0;                                              // weight buffer of stage s
+        auto wbuf = [&](int ahead) { return wb + ahead >= 3 ? wb + ahead - 3 : wb + ahead; };
+        auto read_a = [&](int m, int b, int off) __attribute__((always_inline)) {
+            fa[m] = *reinterpret_cast<const u32x4 *>(ring + kWBase + b * kBigStage + off + row_tile(m) * 2048);
+        };
+        auto read_b = [&](u32x4 (&f)[N], int n, int s, int off) __attribute__((always_inline)) {
+            f[n] = *reinterpret_cast<const u32x4 *>(ring + (s & 1) * kBigStage + off + (tq + 4 * n) * 2048);
+        };
+#pragma unroll
+        for (int m = 0; m < 8; ++m) read_a(m, 0, loff0);
+#pragma unroll
+        for (int n = 0; n < N; ++n) read_b(f0, n, 0, loff0);
+        for (int s = 0; s < ns; ++s) {
+            ring_multiply<8, N>(
+                acc, fa, f0, [&](int n) __attribute__((always_inline)) { if (n < N) read_b(f1, n, s, loff1); },
+                [&](int m) __attribute__((always_inline)) { read_a(m, wb, loff1); });
+            wait_loads<4>();                                     // all but stage s+2's weight rows
+            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+            // (in the last step the fragments of a stage that does not exist, unused)
+            ring_multiply<8, N>(
+                acc, fa, f1,
+                [&](int n) __attribute__((always_inline)) {
+                    if (n < N) read_b(f0, n, s + 1, loff0);
+                    constexpr int every = N < 3 ? N : 3;
+                    const int k = n / every;
+                    if (n % every == every - 1 && k < 8) {
+                        if (k < 4)
+                            load_x(k, s + 2);
+                        else
+                            load_w(k - 4, s + 3, wb);
+                    }
+                },
+                [&](int m) __attribute__((always_inline)) { read_a(m, wbuf(1), loff0); });
+            wb = wbuf(1);
+        }
+        wait_loads<0>();                                         // (of loads that move nothing)
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");       // the last matrix results are in the registers
+        __builtin_amdgcn_sched_barrier(0);                       // (nothing that reads them moves above the pause)
+
+        bf16_t *act_row0 = act + (size_t)g * T * gs;
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int sl = c0 + (tq + 4 * n) * 16 + i16;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const f32x4_t gt = acc[m][n], up = acc[m + 4][n];
+                const uint32_t lo = (uint32_t)f32_to_bf16(silu_mul_fast(gt[0], up[0])) | ((uint32_t)f32_to_bf16(silu_mul_fast(gt[1], up[1])) << 16);
+                const uint32_t hi = (uint32_t)f32_to_bf16(silu_mul_fast(gt[2], up[2])) | ((uint32_t)f32_to_bf16(silu_mul_fast(gt[3], up[3])) << 16);
+                if (sl < cnt) *reinterpret_cast<uint2 *>(act_row0 + (size_t)sl * 128 + (4 * rh + m) * 16 + 4 * q) = make_uint2(lo, hi);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    if (quarters == 4)
+        tile_of(std::integral_constant<int, 4>{});
+    else if (quarters == 3)
+        tile_of(std::integral_constant<int, 3>{});
+    else if (quarters == 2)
+        tile_of(std::integral_constant<int, 2>{});
+    else
+        tile_of(std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -721,17 +888,46 @@ template <bool Q4, int NTOK>
 __host__ __device__ constexpr int down_ring_bytes() { return Ring<Q4, NTOK>::kBytes + kTabGroups * kTabBytes; }
 static_assert(down_ring_bytes<true, 256>() <= 160 * 1024 && down_ring_bytes<false, 256>() <= 160 * 1024, "fits a compute unit");
 
-// tokens of a tile of the down projection: half tiles when one of them holds all tokens
-inline int down_tile_tokens(int T) { return T <= 128 ? 128 : 256; }
+// Number of group ranges, the cheapest by a plain account in us: rounds of one workgroup per compute unit, each 10 and 1.3
+// per group, and with several ranges the reduction's launch, write and read.
+// 1000 tokens of the 13B shape in three ranges 130 + 12 us against 166 + 9 in two, 600 tokens of the 70B shape in four
+// 309 + 15 against 318 in one.
+static int down_splits(int T, int d, int G)
+{
+    const long long tiles = (long long)(d / 128) * ((T + 255) / 256);
+    int best = 1;
+    float least = 0.f;
+    for (int n = 1; n <= kDownMaxSplits && n <= G; ++n) {
+        const float rounds = (float)((tiles * n + 255) / 256), reduce = n > 1 ? 5.f + 1.2e-6f * n * T * d : 0.f;
+        const float us = rounds * (10.f + 1.3f * ((G + n - 1) / n)) + reduce;
+        if (n == 1 || us < least) best = n, least = us;
+    }
+    return best;
+}
 
-// number of group ranges for the ring kernel, 0 = shape not covered by it (the row table holds 16 bits)
-int prefill_down_splits(int T, int d, int G)
+// the ranges that this shape is cut into where the scratch has room for their sums, 0 = shape not covered by
+// the ring kernels (the row table holds 16 bits)
+int prefill_down_splits(int T, int d, int G) { return d % 128 != 0 || T > 32767 ? 0 : down_splits(T, d, G); }
+
+// The ranges whose sums every workspace has room for.  They give a workspace its size, and so decide which calls the fixed
+// scratch array takes: the line is an agreed one (ranges of at most 32 groups, none for shapes that would need
+// more than kDownMaxSplits to fill the chip) and does not follow the kernels.
+int prefill_down_splits_reserved(int T, int d, int G)
 {
     if (d % 128 != 0 || T > 32767) return 0;
-    const int tok = down_tile_tokens(T), tiles = (d / 128) * ((T + tok - 1) / tok);
-    int splits = (256 + tiles / 2) / tiles;                      // about one workgroup per compute unit
-    splits = splits < 1 ? 1 : splits > kDownMaxSplits ? kDownMaxSplits : splits;
-    return splits > G ? G : splits;
+    const int tiles = (d / 128) * ((T + 255) / 256), need = (G + 31) / 32;
+    int splits = (256 + tiles / 2) / tiles;
+    splits = splits < need ? need : splits;
+    splits = splits < 1 ? 1 : splits;
+    splits = splits > G ? G : splits;
+    return splits > kDownMaxSplits || (G + splits - 1) / splits > 32 ? 0 : splits;
+}
+
+// the wanted ranges, or as many as the call's scratch holds (a small workspace of a narrow layer)
+static int splits_in_room(int splits, int T, int d, const DecodeScratch &ws)
+{
+    const size_t room = ws.partial_elems / ((size_t)T * d);
+    return room >= (size_t)splits ? splits : room < 1 ? 1 : (int)room;
 }
 
 // Wd: bf16 [G][d][128], or (Q4) code words [G][d][16] with scales Sd [G][d]; rows: the row table
@@ -823,10 +1019,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     };
     const int loff = i16 * 128 + (((4 * part.ks + q) ^ (i16 & 7)) * 16);
     f32x4_t acc[MT][TT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) acc[m][tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    clear_accumulators(acc);
 
 #pragma unroll
     for (int gi = 0; gi < kTabGroups; ++gi) request_table(gi, gi < ng);
@@ -908,6 +1101,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     wait_loads<0>();                                             // (of loads that move nothing)
     __syncthreads();                                             // every wave is done with the rings
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");           // the last matrix results are in the registers
+    __builtin_amdgcn_sched_barrier(0);                           // (nothing that reads them moves above the pause)
 
     float *out = partial ? partial + (size_t)split * T * d : nullptr;
     auto put = [&](auto first) {
@@ -983,20 +1177,37 @@ static hipError_t launch_gate_up_ring(const bf16_t *x, int T, int d, int G, cons
     return hipSuccess;
 }
 
+static void launch_reduce(const float *partial, int splits, int T, int d, bf16_t *y, hipStream_t s)
+{
+    const size_t n = (size_t)T * d;
+    reduce_partials<<<dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s>>>(partial, splits, n, y);
+}
+
 template <bool Q4, int NTOK>
-static hipError_t launch_down_ring(int T, int d, int G, const void *Wd, const bf16_t *Sd, const DecodeScratch &ws,
+static hipError_t launch_down_ring(int T, int d, int G, int splits, const void *Wd, const bf16_t *Sd, const DecodeScratch &ws,
                                    const bf16_t *act, bf16_t *y, hipStream_t s)
 {
     constexpr int bytes = down_ring_bytes<Q4, NTOK>();
     static const hipError_t lds_ok = allow_lds(down_pf_ring<Q4, NTOK>, bytes);
     if (lds_ok != hipSuccess) return lds_ok;
-    const int splits = prefill_down_splits(T, d, G), items = (d / 128) * ((T + NTOK - 1) / NTOK) * splits;
+    const int items = (d / 128) * ((T + NTOK - 1) / NTOK) * splits;
     down_pf_ring<Q4, NTOK><<<dim3((items + 7) / 8 * 8), dim3(kRingWaves * 64), bytes, s>>>(
         T, d, G, splits, Wd, Sd, reinterpret_cast<const int16_t *>(ws.slot), act, splits > 1 ? ws.partial : (float *)nullptr, y);
-    if (splits > 1) {
-        const size_t n = (size_t)T * d;
-        reduce_partials<<<dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s>>>(ws.partial, splits, n, y);
-    }
+    if (splits > 1) launch_reduce(ws.partial, splits, T, d, y, s);
+    return hipSuccess;
+}
+
+// Whole tiles of 256 x 256 in gate/up when half of the tokens keeping a group (the lists are not known here; each
+// ends in half a tile on average) gives more than 150 of them: gate_up_pf_ring's half rows then take a second round.
+static bool gate_up_big_tiles(int T, int G) { return (long long)G * (T + 256) > 512 * 150; }
+
+static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const bf16_t *Wg, const bf16_t *Wu,
+                                     const DecodeScratch &ws, bf16_t *act, hipStream_t s)
+{
+    static const hipError_t lds_ok = allow_lds(gate_up_pf_big, 5 * kBigStage);
+    if (lds_ok != hipSuccess) return lds_ok;
+    launch_timed_lds("gate_up_pf_big", gate_up_pf_big, dim3((G * ((T + 255) / 256) + 7) / 8 * 8),
+                     dim3(kRingWaves * 64), 5 * kBigStage, s, x, T, d, G, Wg, Wu, (const int32_t *)ws.tok_list, (const int32_t *)ws.tok_cnt, act);
     return hipSuccess;
 }
 
@@ -1004,16 +1215,26 @@ static hipError_t launch_down_ring(int T, int d, int G, const void *Wd, const bf
 // the next tile of a group's weights is found in the die's L2.  7B shape, bf16,
 // 128 tokens 44.7 us in gate/up and 25.7 us in down against 50.8 and 28.2 with whole tiles; 256 tokens 49.8 against 60.1
 // in gate/up, but 32.9 against 31.8 in down; 400 tokens 85 against 63 and 56 against 45.
+// In the down projection also where whole tiles times ranges would fill less than half of the chip: 200 tokens of d 2048, one
+// range, 41.7 us against 63.4; 200 tokens of d 1024 10.0 against 13.6.
 template <bool Q4>
 static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const void *Wd,
                                const bf16_t *Sg, const bf16_t *Su, const bf16_t *Sd, const DecodeScratch &ws, bf16_t *act,
                                bf16_t *y, hipStream_t s)
 {
-    hipError_t e = T <= 256 ? launch_gate_up_ring<Q4, 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s)
-                            : launch_gate_up_ring<Q4, 256>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
+    hipError_t e;
+    if (!Q4 && gate_up_big_tiles(T, G))
+        e = launch_gate_up_big(x, T, d, G, (const bf16_t *)Wg, (const bf16_t *)Wu, ws, act, s);
+    else if (T <= 256)
+        e = launch_gate_up_ring<Q4, 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
+    else
+        e = launch_gate_up_ring<Q4, 256>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
     if (e != hipSuccess) return e;
-    e = down_tile_tokens(T) == 128 ? launch_down_ring<Q4, 128>(T, d, G, Wd, Sd, ws, act, y, s)
-                                   : launch_down_ring<Q4, 256>(T, d, G, Wd, Sd, ws, act, y, s);
+    const int splits = splits_in_room(down_splits(T, d, G), T, d, ws);
+    if (T <= 128 || (d / 128) * ((T + 255) / 256) * splits < 128)
+        e = launch_down_ring<Q4, 128>(T, d, G, splits, Wd, Sd, ws, act, y, s);
+    else
+        e = launch_down_ring<Q4, 256>(T, d, G, splits, Wd, Sd, ws, act, y, s);
     return e == hipSuccess ? hipGetLastError() : e;
 }
 

@@ -2,6 +2,7 @@
 // See include/halo.h for the contract of every entry point.
 #include "../../include/halo.h"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -70,19 +71,24 @@ struct Workspace {
         dec.slot = reinterpret_cast<int32_t *>(take(G * t * sizeof(int32_t)));
         // partial sums of the prefill down projection: the number of ranges falls as T grows, so the
         // size is taken as the largest need of any token count up to T (a workspace sized for T then
-        // also serves every smaller call); the need is largest at the upper end of a token tile
-        size_t partial_elems = 0;
+        // also serves every smaller call); the need is largest at the upper end of a token tile.
+        // Beyond the reserved ranges the kernels take what room there is: never so much that a call
+        // which the fixed scratch array takes would outgrow it.
+        size_t reserved = 0, wanted = 0;
         if (s.dtype == HALO_BF16) {
             for (int t1 = 256; t1 - 256 < T; t1 += 256) {
                 const int tt = t1 < T ? t1 : T;
                 if (!prefill_path_supported(tt, s.d, s.group_size) || mfma_path_supported(tt, s.d, s.group_size))
                     continue;
-                const int splits = prefill_down_splits(tt, s.d, s.n_groups);
-                const size_t need = splits > 1 ? (size_t)splits * tt * s.d : 0;
-                partial_elems = need > partial_elems ? need : partial_elems;
+                auto need = [&](int splits) { return splits > 1 ? (size_t)splits * tt * s.d : 0; };
+                reserved = std::max(reserved, need(prefill_down_splits_reserved(tt, s.d, s.n_groups)));
+                wanted = std::max(wanted, need(prefill_down_splits(tt, s.d, s.n_groups)));
             }
         }
-        dec.partial = reinterpret_cast<float *>(take(partial_elems * sizeof(float)));
+        if (off + align_up(reserved * sizeof(float)) <= kStaticScratchBytes)
+            wanted = std::min(wanted, (kStaticScratchBytes - off) / sizeof(float));
+        dec.partial_elems = std::max(reserved, wanted);
+        dec.partial = reinterpret_cast<float *>(take(dec.partial_elems * sizeof(float)));
         // appended last: the layout in front of it is the same with and without
         if (q4_room && q4_expand_supported(T, s.dtype, s.d, s.n_groups, s.group_size))
             dec.q4_w = reinterpret_cast<bf16_t *>(take((size_t)3 * s.ffn * s.d * sizeof(bf16_t)));

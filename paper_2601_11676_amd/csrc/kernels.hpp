@@ -30,6 +30,7 @@ struct DecodeScratch {
     int32_t *tok_cnt;   // [G]
     int32_t *slot;      // [T][G] words: prefill's row table (16 bits, group-major), or positions in the lists, -1 = not kept
     float *partial;     // [splits][T][d] prefill: the down projection's sums per range of groups
+    size_t partial_elems;   // ... and the room there
     bf16_t *q4_w = nullptr;   // 4-bit callers with many tokens: room for Wg, Wu [ffn][d] and Wd [G][d][gs] as bf16, or null
 };
 // The next block's prediction (predictor + mask from x_next), see halo_ffn_forward_ahead.
@@ -109,7 +110,8 @@ hipError_t launch_gate_up_few(const bf16_t *x, int T, int d, int G, int gs, cons
 
 // ffn_prefill.hip : bf16 matrix-core path for many tokens
 bool prefill_path_supported(int T, int d, int gs);
-int prefill_down_splits(int T, int d, int G);   // ranges of groups in the down projection (0: no ring kernel)
+int prefill_down_splits(int T, int d, int G);   // most ranges of groups the down projection takes (0: no ring kernel)
+int prefill_down_splits_reserved(int T, int d, int G);   // ranges that a workspace has room for whatever its size
 hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg,
                               const bf16_t *Wu, const bf16_t *Wd, const uint8_t *mask, bf16_t *y,
                               const DecodeScratch &ws, hipStream_t s);

@@ -79,6 +79,18 @@ def test_workspace_bytes():
     assert H.halo_workspace_bytes(H.Shape(4090, 11008, 128, 256), 1, 4) == 0
 
 
+@pytest.mark.parametrize("d,G,T", [(128, 24, 643), (512, 24, 643), (1152, 108, 145), (2048, 24, 256), (4096, 86, 47),
+                                   (8192, 224, 24)])
+def test_many_token_calls_that_the_fixed_scratch_takes(d, G, T):
+    # room for more ranges of the down projection never pushes a call out of the fixed scratch array, nor lets one in: T is
+    # the most tokens (by the sizes without that room, or with the reserved eight ranges of d 4096 and 8192)
+    s = H.Shape(d, G * 128, 128, 64, "bf16", n_groups=G)
+    limit = H.halo_static_scratch_bytes()
+    sizes = [H.halo_workspace_bytes(s, t, G // 2) for t in range(1, 1000)]
+    assert [t + 1 for t, n in enumerate(sizes) if n <= limit] == list(range(1, T + 1))
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_workspace_bytes_q4():
     # the bound for callers of the 4-bit entry points: the plain one, plus one block's weights as bf16 once
     # more than 16 tokens can run on the bf16 kernels; never smaller, never falling as T grows

@@ -643,3 +643,22 @@ def test_many_token_rings(T, d, G, K):
         g = hz.gpu_forward(w, L, x, K, pd, dr)
         c = hz.oracle_forward(w, L, x, K, pd, dr)
         hz.assert_parity(g, c, TOL["bf16"], f"rings T={T}")
+
+
+@pytest.mark.parametrize("T,d,G,K", [
+    (1100, 384, 180, 60),      # 256 x 256 tiles: several per group, tails of every length, rows of six stages
+    (520, 128, 100, 45),       # ... rows of two stages
+    (300, 1152, 150, 70),      # ... groups of less than a tile; an odd number of stages per die
+    (200, 2048, 48, 24),       # the scratch has no room for a second range in the down projection: half tiles
+    (2050, 256, 97, 4),        # groups of few tokens among many
+])
+def test_many_token_whole_tiles(T, d, G, K):
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=83)
+    _say(f"whole tiles T={T} d={d} G={G} K={K}")
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    g = hz.gpu_forward(w, L, x, K, pd, drop)
+    c = hz.oracle_forward(w, L, x, K, pd, drop)
+    hz.assert_parity(g, c, TOL["bf16"], f"whole tiles T={T}")

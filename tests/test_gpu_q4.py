@@ -321,7 +321,8 @@ def test_q4_one_token_of_any_row_length(d, G, K, r):
     (515, 4224, 9, 4),         # three token tiles, the last with three tokens
 ])
 def test_q4_many_token_rings(T, d, G, K):
-    # the codes expanded on their way into LDS give what the bf16 kernels give on the expanded weights, bit for bit
+    # the codes expanded on their way into LDS give what the bf16 kernels give on the expanded weights, bit for bit (where those
+    # are the same kernels: with many groups the bf16 call runs on 256 x 256 tiles, which add a row up in one chain)
     w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=82)
     _say(f"q4 many-token rings T={T} d={d} G={G} K={K}")
     s = hz.shape_of(w)
@@ -332,6 +333,8 @@ def test_q4_many_token_rings(T, d, G, K):
     drop[0] = 1
     g = hz.gpu_forward_q4(w, L, x, K, pd, drop)
     hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"q4 rings T={T}")
+    if G * (T + 256) > 512 * 150:
+        return
     Wg, Wu, WdT = (torch.from_numpy(np.ascontiguousarray(a)).to(torch.bfloat16).to(hz.DEV) for a in L.host()[2:])
     y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
     ws = torch.empty(H.halo_workspace_bytes(s, T, K), dtype=torch.uint8, device=hz.DEV)

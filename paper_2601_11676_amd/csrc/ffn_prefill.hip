@@ -11,6 +11,7 @@
 //                  of the group's tokens (x rows gathered by the token list); the operands
 //                  travel straight from memory into rings of K stages in LDS.
 //                  act[g][slot][m] = SiLU(gate) * up in bf16.
+//   gate_up_pf_big : the same with whole groups of rows and 256 tokens, where there are tiles enough (bf16).
 //   down_pf_ring : one workgroup = 128 outputs x 256 tokens over a range of groups, same rings;
 //                  a token that does not keep a group reads the group's zero row, so it
 //                  contributes exactly nothing.  With several ranges the fp32 partial sums are

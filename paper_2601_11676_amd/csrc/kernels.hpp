@@ -7,6 +7,8 @@
 namespace halo {
 
 // predictor.hip
+bool scores_apart(int T, int r, int G);   // bf16: scores of many tokens as a launch of their own
+hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, int G, float *scores, hipStream_t s);
 hipError_t launch_predictor(int dtype, const void *x, int T, int d, int r, int G, const void *At,
                             const void *Bt, float *h, float *scores, hipStream_t s);
 

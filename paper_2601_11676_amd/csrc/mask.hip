@@ -37,6 +37,8 @@ hipError_t launch_group_mask(const float *scores, int T, int G, int K, const int
     return hipGetLastError();
 }
 
+// Many scores: computed on the matrix cores in a launch of their own (a token's workgroup reads all of Bt for itself).
+
 hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int r, float *scores,
                                   int T, int G, int K, const int8_t *prio_dev, int n_dev,
                                   const uint8_t *drop, int32_t *order, int8_t *group_dev,
@@ -46,7 +48,12 @@ hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int
         mask_scores_kernel<float, true><<<dim3(T), dim3(kMaskThreads), 0, s>>>(
             h, (const float *)Bt, r, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask,
             surv_idx, n_surv);
-    else if (T >= 64)
+    else if (scores_apart(T, r, G)) {
+        const hipError_t e = launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
+        if (e != hipSuccess) return e;
+        mask_scores_kernel<float, false, 512><<<dim3(T), dim3(512), 0, s>>>(
+            nullptr, nullptr, 0, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv);
+    } else if (T >= 64)
         // many tokens: workgroups of 512 threads, more of them resident per compute unit (measured at
         // 512 tokens of the 7B shape: 11.5 us against 13.6 us with 1024 threads and 14.7 us with 256)
         mask_scores_kernel<bf16_t, true, 512><<<dim3(T), dim3(512), 0, s>>>(

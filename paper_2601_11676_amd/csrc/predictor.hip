@@ -171,6 +171,85 @@ static void launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_
     hidden_mfma_kernel<TT, JT, WAVES><<<dim3((n_tt * n_jt + 7) / 8 * 8), dim3(WAVES * 64), 0, s>>>(x, At, h, T, d, r, n_tt, n_jt);
 }
 
+// The second layer for many tokens: scores[t][g] = h[t] . Bt[g], the same instruction and order.  The rows are short (one
+// or two pieces per lane), so a 16 x 16 tile is all a workgroup does and its lanes take their pieces straight from memory,
+// nothing is staged.  Eight waves: two values of l each.  Bound by the launch and one memory round trip
+// (1000 x 512 x 224: 9.7 us).
+constexpr int kScoreWaves = 8;
+
+__global__ __launch_bounds__(kScoreWaves * 64) void scores_mfma_kernel(
+    const float *__restrict__ H, const bf16_t *__restrict__ Bt, float *__restrict__ scores, int T, int r, int G)
+{
+    constexpr int kL = 16 / kScoreWaves;
+    __shared__ __attribute__((aligned(16))) f32x4_t sums[16 * 64];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, b = lane >> 4;
+    const int t0 = blockIdx.y * 16, g0 = blockIdx.x * 16;
+    const float *hrow = H + (size_t)min(t0 + i, T - 1) * r;      // rows past the end repeat the last one (never stored)
+    const bf16_t *brow = Bt + (size_t)min(g0 + i, G - 1) * r;
+    const int nk = (r + 511) / 512;
+    f32x16_t acc[kL];
+#pragma unroll
+    for (int l = 0; l < kL; ++l)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[l][e] = 0.0f;
+    float hv[kL][8], bv[kL][8];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int l = 0; l < kL; ++l) {
+            const int e0 = (64 * k + kL * wave + l + 16 * b) * 8;
+            const bool ok = e0 < r;                              // (r is a multiple of 8)
+            load8(hrow + (ok ? e0 : 0), hv[l]);
+            load8(brow + (ok ? e0 : 0), bv[l]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                hv[l][e] = ok ? hv[l][e] : 0.0f;                 // 0 * 0 leaves a chain as it is
+                bv[l][e] = ok ? bv[l][e] : 0.0f;
+            }
+        }
+    };
+    for (int k = 0; k < nk; ++k) {
+        fetch(k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int l = 0; l < kL; ++l) acc[l] = __builtin_amdgcn_mfma_f32_16x16x1f32(bv[l][e], hv[l][e], acc[l], 0, 0, 0);
+    }
+    // as in hidden_mfma_kernel: distances 32 and 16 are a lane's own blocks
+#pragma unroll
+    for (int l = 0; l < kL; ++l) {
+        f32x4_t s;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) s[m] = (acc[l][m] + acc[l][8 + m]) + (acc[l][4 + m] + acc[l][12 + m]);
+        sums[(kL * wave + l) * 64 + lane] = s;
+    }
+    __syncthreads();
+    // distances 8, 4, 2, 1: a thread per score, token c of the tile, group row
+    if (tid < 256) {
+        const int c = tid >> 4, row = tid & 15;
+        const float *one = reinterpret_cast<const float *>(sums) + ((row >> 2) * 16 + c) * 4 + (row & 3);
+        float p[16];
+#pragma unroll
+        for (int l = 0; l < 16; ++l) p[l] = one[l * 256];
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+            for (int l = 0; l < 8; ++l)
+                if (l < off) p[l] = p[l] + p[l + off];
+        if (t0 + c < T && g0 + row < G) scores[(size_t)(t0 + c) * G + g0 + row] = p[0];
+    }
+}
+
+// whether a launch of their own pays: inside the mask kernel a token's workgroup reads all of Bt for itself and spends most
+// instructions on lane-crossing sums, but the second launch costs a few microseconds.  us, both kernels against the one (T x r x G): 1000 x 512 x 224 22.0 against 36.8,
+// 700 x 512 x 120 12.0 against 16.2, 2000 x 256 x 86 16.5 against 20.6; 512 x 256 x 86 11.4 against 9.3.
+bool scores_apart(int T, int r, int G) { return T >= 64 && (long long)T * r * G >= 40ll << 20; }
+
+hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, int G, float *scores, hipStream_t s)
+{
+    scores_mfma_kernel<<<dim3((G + 15) / 16, (T + 15) / 16), dim3(kScoreWaves * 64), 0, s>>>(h, Bt, scores, T, r, G);
+    return hipGetLastError();
+}
+
 // The largest tile that still gives every compute unit a workgroup: the bytes staged per result fall with the
 // tile (2 x 2: 64 rows per 1024 results, 1 x 1: 32 per 256), but a unit without a workgroup does nothing.  Fewer
 // than 16 tokens do not fill a tile and stay with a wave per result (2..8 tokens: 7-13 us).
@@ -195,6 +274,7 @@ static hipError_t predict_t(const WT *x, int T, int d, int r, int G, const WT *A
     long long n1 = (long long)T * r, n2 = (long long)T * G;
     if (!hidden_rows_tiled(x, T, d, r, At, h, s))
         dot_rows_kernel<WT, WT, true><<<dim3((unsigned)((n1 + 3) / 4)), dim3(256), 0, s>>>(x, At, h, T, r, d);
+    if (scores && sizeof(WT) == 2 && scores_apart(T, r, G)) return launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
     if (scores)
         dot_rows_kernel<float, WT, false><<<dim3((unsigned)((n2 + 3) / 4)), dim3(256), 0, s>>>(h, Bt, scores, T, G, r);
     return hipGetLastError();

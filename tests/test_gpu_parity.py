@@ -576,6 +576,26 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     assert same.all()
 
 
+@pytest.mark.parametrize("T,r,G", [
+    (5300, 8, 1000),           # one piece per row, ragged tiles both ways
+    (530, 264, 310),           # half of the pieces
+    (2100, 520, 40),           # a second step of one piece
+    (300, 512, 300),
+])
+def test_scores_of_many_tokens_keep_the_fixed_order(T, r, G):
+    w = dataclasses.replace(hs.LLAMA7B_DECODE, name="case", d=128, ffn=G * 128, rank=r, T=T, seed=62)
+    _say(f"scores of many tokens T={T} r={r} G={G}")
+    s = hz.shape_of(w)
+    At, Bt = hs.predictor_weights(w, 0, hz.DEV)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    x[T - 1] *= 1e-38
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    sc = torch.empty((T, G), dtype=torch.float32, device=hz.DEV)
+    H.halo_predict_scores(s, x, At, Bt, sc, ws)
+    c = ref.predict_scores(hz.to_np32(x), hz.to_np32(At), hz.to_np32(Bt))
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), c.view(np.uint32))
+
+
 @pytest.mark.parametrize("T,d,G,gs", [
     (1, 8, 1, 16),             # the smallest: half a piece of the row, one tile of one group
     (1, 1000, 24, 128),        # a last tile of eight outputs

@@ -111,11 +111,11 @@ size_t halo_workspace_bytes(const halo_shape *shape, int32_t T, int32_t k_keep);
 
 /*
  * The same, for callers of the `_q4` entry points further down: for more than 16 tokens (bf16) the bound
- * also holds one block's FFN weights as bf16 (3 * ffn * d * 2 bytes).  Up to 32767 tokens a `_q4` call expands the
- * codes on their way into the matrix-core kernels and does not use that room; above that it expands the 4-bit
- * weights once into it and runs the bf16 kernels, and with only halo_workspace_bytes walks the
- * tokens 16 at a time instead (several times slower).  Never smaller than halo_workspace_bytes; 0 for invalid
- * arguments.
+ * also holds one block's FFN weights as bf16 (3 * ffn * d * 2 bytes).  With that room a many-token call runs on
+ * the many-token matrix-core kernels over the weights rounded to bf16: up to 32767 tokens the codes are expanded
+ * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  A `_q4` call
+ * given only halo_workspace_bytes works all the same and walks the tokens 16 at a time instead (several times
+ * slower; the scale is then applied in float32).  Never smaller than halo_workspace_bytes; 0 for invalid arguments.
  */
 size_t halo_workspace_bytes_q4(const halo_shape *shape, int32_t T, int32_t k_keep);
 
@@ -270,10 +270,10 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * Everything else -- mask semantics, workspace, stream, errors -- is as in
  * halo_group_sparse_ffn / halo_ffn_forward.  Tuned paths (bf16 activations, n_groups <= 256): one
  * token with d <= 8192 (every surviving code byte streamed once, float ALUs), 2..16
- * tokens with d a multiple of 1024 up to 8192 (matrix cores, codes expanded in registers), and 17..32767 tokens
- * (any d a multiple of 128, any n_groups; the many-token matrix-core kernels, each value s * (c - 8) rounded to
- * bf16, to nearest even, on its way into LDS); other shapes and float32 activations take a plain path that
- * dequantises element by element.  More than 32767 tokens: see halo_workspace_bytes_q4.
+ * tokens with d a multiple of 1024 up to 8192 (matrix cores, codes expanded in registers); other shapes and float32
+ * activations take a plain path that dequantises element by element.  More than 16 tokens (any d a multiple of
+ * 128, any n_groups): with a workspace of halo_workspace_bytes_q4 the many-token matrix-core kernels, each value
+ * s * (c - 8) rounded to bf16, to nearest even; with less, the paths above, 16 tokens at a time.
  */
 int halo_group_sparse_ffn_q4(const halo_shape *shape, const void *x, int32_t T, const void *Wg_codes,
                              const void *Wg_scales, const void *Wu_codes, const void *Wu_scales,

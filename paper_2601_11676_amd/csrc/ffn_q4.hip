@@ -551,9 +551,11 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
                    : q4_one_token<float>(bx, d, G, w, mask, by, ws.act, s, ahead, ahead_fused);
     if (q4_mfma_path_supported(T, d, G, gs))
         return launch_ffn_q4_mfma(bx, T, d, G, w, mask, by, ws, s, rank, ahead, ahead_fused);
-    if (prefill_q4_supported(T, d, G, gs)) return launch_ffn_prefill_q4(bx, T, d, G, w, mask, by, ws, s);
+    // The many-token kernels multiply by values rounded to bf16, the few-token kernels scale in float: which of the two a
+    // call of many tokens gets is the caller's choice, by the workspace.
+    if (ws.q4_w && prefill_q4_supported(T, d, G, gs)) return launch_ffn_prefill_q4(bx, T, d, G, w, mask, by, ws, s);
     if (ws.q4_w && q4_expand_supported(T, dtype, d, G, gs)) {
-        // Many tokens and room for a block's weights as bf16: the weights are expanded once (a stream of
+        // More tokens than the row table's 16 bits hold, and room for a block's weights as bf16: the weights are expanded once (a stream of
         // 0.5 + 2 bytes per element) and the bf16 matrix-core kernels do the rest, every weight used for
         // all the tokens that keep its group.
         const size_t ffn = (size_t)G * gs;

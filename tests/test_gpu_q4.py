@@ -331,7 +331,7 @@ def test_q4_many_token_rings(T, d, G, K):
     pd = H.halo_build_schedule(K, w.device_plr())
     drop = hs.drop_outcomes(w, T=T)
     drop[0] = 1
-    g = hz.gpu_forward_q4(w, L, x, K, pd, drop)
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop, big_workspace=True)
     hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"q4 rings T={T}")
     if G * (T + 256) > 512 * 150:
         return

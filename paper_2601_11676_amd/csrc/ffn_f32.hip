@@ -38,6 +38,19 @@ __device__ __forceinline__ f32x4_t pairwise_sum(f32x4_t (&p)[N])
 
 constexpr int kGateUpF32Waves = 8, kDownF32Waves = 16;
 
+// Where the lanes of group q load the four elements of piece p that they hold, in elements from the row's start.  The last
+// piece may hold 8 elements, and the only one of a row of 8 as well: lanes past the end take the row's first four, unused.
+__host__ __device__ constexpr bool in_row(int p, int q, int d) { return p * 16 + 4 * q < d; }
+__host__ __device__ constexpr int piece_at(int p, int q, int d) { return in_row(p, q, d) ? p * 16 + 4 * q : 0; }
+constexpr bool loads_stay_in_row(int d)
+{
+    for (int p = 0; p < (d + 15) / 16; ++p)
+        for (int q = 0; q < 4; ++q)
+            if (piece_at(p, q, d) < 0 || piece_at(p, q, d) + 4 > d) return false;
+    return true;
+}
+static_assert(loads_stay_in_row(8) && loads_stay_in_row(16) && loads_stay_in_row(24) && loads_stay_in_row(520), "d is a multiple of 8");
+
 // NT: token tiles of 16 per workgroup.  grid (ffn / 16, ceil(T / (16 NT)))
 template <int NT>
 __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
@@ -51,10 +64,10 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
     const int n0 = blockIdx.x * 16, g = n0 / gs, t0 = blockIdx.y * 16 * NT;
     const uint8_t mine = mask[(size_t)min(t0 + min(lane, 16 * NT - 1), T - 1) * G + g];
     if (__ballot(mine != 0) == 0ull) return;                     // uniform: the same bytes in every wave
-    const float *wg = Wg + (size_t)(n0 + i) * d + 4 * q, *wu = Wu + (size_t)(n0 + i) * d + 4 * q;
+    const float *wg = Wg + (size_t)(n0 + i) * d, *wu = Wu + (size_t)(n0 + i) * d;
     const float *xr[NT];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) xr[n] = x + (size_t)min(t0 + 16 * n + i, T - 1) * d + 4 * q;
+    for (int n = 0; n < NT; ++n) xr[n] = x + (size_t)min(t0 + 16 * n + i, T - 1) * d;
     const int np = (d + 15) / 16;                                // pieces of 16; the last one may hold 8
     struct Batch {
         f32x4_t g[U], u[U], x[NT][U];
@@ -64,8 +77,8 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
         for (int k = 0; k < U; ++k) {
             const int p = p0 + W * k;
             if (p < np) {                                        // uniform
-                const bool ok = p * 16 + 4 * q < d;
-                const int at = ok ? p * 16 : 0;
+                const bool ok = in_row(p, q, d);
+                const int at = piece_at(p, q, d);
                 b.g[k] = *reinterpret_cast<const f32x4_t *>(wg + at);
                 b.u[k] = *reinterpret_cast<const f32x4_t *>(wu + at);
 #pragma unroll

@@ -598,6 +598,7 @@ def test_scores_of_many_tokens_keep_the_fixed_order(T, r, G):
 
 @pytest.mark.parametrize("T,d,G,gs", [
     (1, 8, 1, 16),             # the smallest: half a piece of the row, one tile of one group
+    (40, 8, 3, 32),            # rows shorter than a piece, four token tiles
     (1, 1000, 24, 128),        # a last tile of eight outputs
     (17, 264, 5, 48),          # two token tiles, a half piece at the end of the row
     (33, 512, 9, 128),         # four token tiles, one of them empty

@@ -349,7 +349,7 @@ static void launch_down_mt(int T, int d, int G, const bf16_t *Wd, const uint8_t 
 // ---------------------------------------------------------------------------
 bool mfma_path_supported(int T, int d, int gs)
 {
-    return T >= 2 && T <= 16 && d % 128 == 0 && gs == 128;
+    return T >= 2 && T <= kFewTokens && d % 128 == 0 && gs == 128;
 }
 
 hipError_t launch_ffn_mfma(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg,

@@ -25,6 +25,7 @@
 // v_mfma_f32_16x16x32_bf16 operand layout as in ffn_mfma.hip: A lane l = row l%16, elements
 // 8*(l/16)..+7; B lane l = column l%16, same elements; D lane l = column l%16, rows 4*(l/16)..+3.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -906,8 +907,11 @@ static int down_splits(int T, int d, int G)
     return best;
 }
 
+// the row table holds 16 bits, and x is addressed with 32-bit byte offsets
+int prefill_ring_tokens(int d) { return (int)std::min<long long>(32767, ((1ll << 31) - 1) / ((long long)d * 2)); }
+
 // the ranges that this shape is cut into where the scratch has room for their sums, 0 = shape not covered by
-// the ring kernels (the row table holds 16 bits)
+// the ring kernels.  With the tiles fixed it falls as T grows (the reduction's part of the account is n T d), never rises.
 int prefill_down_splits(int T, int d, int G) { return d % 128 != 0 || T > 32767 ? 0 : down_splits(T, d, G); }
 
 // The ranges whose sums every workspace has room for.  They give a workspace its size, and so decide which calls the fixed

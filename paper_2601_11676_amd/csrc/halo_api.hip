@@ -69,20 +69,20 @@ struct Workspace {
         dec.tok_list = reinterpret_cast<int32_t *>(take(G * t * sizeof(int32_t)));
         dec.tok_cnt = reinterpret_cast<int32_t *>(take(G * sizeof(int32_t)));
         dec.slot = reinterpret_cast<int32_t *>(take(G * t * sizeof(int32_t)));
-        // partial sums of the prefill down projection: the number of ranges falls as T grows, so the
-        // size is taken as the largest need of any token count up to T (a workspace sized for T then
-        // also serves every smaller call); the need is largest at the upper end of a token tile.
+        // partial sums of the prefill down projection: the number of ranges falls as T grows, also inside a token tile,
+        // so the size is an upper bound that rises with T -- in every tile the ranges of the tile's first token count for
+        // all of its tokens up to T -- and a workspace sized for T also serves every smaller call.
         // Beyond the reserved ranges the kernels take what room there is: never so much that a call
         // which the fixed scratch array takes would outgrow it.
         size_t reserved = 0, wanted = 0;
-        if (s.dtype == HALO_BF16) {
-            for (int t1 = 256; t1 - 256 < T; t1 += 256) {
-                const int tt = t1 < T ? t1 : T;
-                if (!prefill_path_supported(tt, s.d, s.group_size) || mfma_path_supported(tt, s.d, s.group_size))
-                    continue;
-                auto need = [&](int splits) { return splits > 1 ? (size_t)splits * tt * s.d : 0; };
-                reserved = std::max(reserved, need(prefill_down_splits_reserved(tt, s.d, s.n_groups)));
-                wanted = std::max(wanted, need(prefill_down_splits(tt, s.d, s.n_groups)));
+        if (s.dtype == HALO_BF16 && prefill_path_supported(kFewTokens + 1, s.d, s.group_size)) {
+            const int last = std::min(T, prefill_ring_tokens(s.d));
+            for (int first = kFewTokens + 1, end; first <= last; first = end + 1) {
+                end = (first + 255) / 256 * 256;
+                const size_t tokens = (size_t)std::min(end, last);
+                auto need = [&](int splits) { return splits > 1 ? splits * tokens * s.d : 0; };
+                reserved = std::max(reserved, need(prefill_down_splits_reserved(first, s.d, s.n_groups)));
+                wanted = std::max(wanted, need(prefill_down_splits(first, s.d, s.n_groups)));
             }
         }
         if (off + align_up(reserved * sizeof(float)) <= kStaticScratchBytes)

@@ -98,6 +98,7 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
                           const uint8_t *mask, float *y, float *act, hipStream_t s);
 
 // ffn_mfma.hip : bf16 matrix-core path for a few tokens (2 <= T <= 16)
+constexpr int kFewTokens = 16;
 bool mfma_path_supported(int T, int d, int gs);
 hipError_t launch_ffn_mfma(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg,
                            const bf16_t *Wu, const bf16_t *Wd, const uint8_t *mask, bf16_t *y,
@@ -112,6 +113,7 @@ hipError_t launch_gate_up_few(const bf16_t *x, int T, int d, int G, int gs, cons
 
 // ffn_prefill.hip : bf16 matrix-core path for many tokens
 bool prefill_path_supported(int T, int d, int gs);
+int prefill_ring_tokens(int d);                 // most tokens that the ring kernels take
 int prefill_down_splits(int T, int d, int G);   // most ranges of groups the down projection takes (0: no ring kernel)
 int prefill_down_splits_reserved(int T, int d, int G);   // ranges that a workspace has room for whatever its size
 hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg,

@@ -91,6 +91,25 @@ def test_many_token_calls_that_the_fixed_scratch_takes(d, G, T):
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
 
 
+def test_workspace_never_falls_as_the_tokens_grow():
+    # the ranges of the down projection change inside a token tile, from shape to shape at another token count; and a
+    # call of more tokens than the row table holds has none
+    rng = np.random.default_rng(5)
+    shapes = [(1024, 36, 256), (5504, 64, 256), (768, 36, 256), (640, 20, 256), (640, 25, 256), (4608, 450, 256), (6144, 63, 256)]
+    shapes += [(128 * int(rng.integers(1, 65)), int(rng.integers(1, 1025)), int(rng.choice([8, 64, 512]))) for _ in range(80)]
+    shapes += [(d, max(1, int(d / 128 * rng.uniform(2, 4))), 256) for d in range(128, 8193, 128)]
+    for d, G, r in shapes:
+        s = H.Shape(d, G * 128, 128, r, "bf16", n_groups=G)
+        for K in (0, G):
+            sizes = [H.halo_workspace_bytes(s, T, K) for T in range(1, 1100)]
+            fall = [T + 2 for T, (a, b) in enumerate(zip(sizes, sizes[1:])) if b < a]
+            assert not fall, (d, G, r, K, fall)
+    for d, G in [(8192, 1), (8192, 8), (128, 1000), (1024, 24)]:
+        s = H.Shape(d, G * 128, 128, 8, "bf16", n_groups=G)
+        sizes = [H.halo_workspace_bytes(s, T, 0) for T in (32000, 32512, 32513, 32767, 32768, 32769, 33000, 40000)]
+        assert sizes == sorted(sizes), (d, G)
+
+
 def test_workspace_bytes_q4():
     # the bound for callers of the 4-bit entry points: the plain one, plus one block's weights as bf16 once
     # more than 16 tokens can run on the bf16 kernels; never smaller, never falling as T grows

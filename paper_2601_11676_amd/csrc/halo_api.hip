@@ -89,8 +89,9 @@ struct Workspace {
             wanted = std::min(wanted, (kStaticScratchBytes - off) / sizeof(float));
         dec.partial_elems = std::max(reserved, wanted);
         dec.partial = reinterpret_cast<float *>(take(dec.partial_elems * sizeof(float)));
-        // appended last: the layout in front of it is the same with and without
-        if (q4_room && q4_expand_supported(T, s.dtype, s.d, s.n_groups, s.group_size))
+        // appended last: the layout in front of it is the same with and without.  Also for more tokens than the
+        // many-token kernels address (T * d * 2 bytes of x below 2^31): the size of the larger call serves the smaller
+        if (q4_room && T > kFewTokens && q4_expand_supported(kFewTokens + 1, s.dtype, s.d, s.n_groups, s.group_size))
             dec.q4_w = reinterpret_cast<bf16_t *>(take((size_t)3 * s.ffn * s.d * sizeof(bf16_t)));
         bytes = off;
     }

@@ -120,6 +120,9 @@ def test_workspace_bytes_q4():
         assert H.halo_workspace_bytes_q4(s, T, 43) == H.halo_workspace_bytes(s, T, 43) + 3 * 11008 * 4096 * 2
     sizes = [H.halo_workspace_bytes_q4(s, T, 43) for T in range(1, 2200, 7)]
     assert all(b >= a > 0 for a, b in zip(sizes, sizes[1:]))
+    # also past the most tokens that the many-token kernels address (2^31 bytes of x: 262144 tokens)
+    sizes = [H.halo_workspace_bytes_q4(s, T, 43) for T in range(262141, 262148)]
+    assert all(b >= a > 0 for a, b in zip(sizes, sizes[1:]))
     assert H.halo_workspace_bytes_q4(s, 1, 87) == 0 and H.halo_workspace_bytes_q4(s, -1, 4) == 0
     f = H.Shape(4096, 11008, 128, 256, "f32")                  # float32 activations: the plain path, no extra room
     assert H.halo_workspace_bytes_q4(f, 512, 43) == H.halo_workspace_bytes(f, 512, 43)

@@ -61,7 +61,8 @@ struct Workspace {
         order = reinterpret_cast<int32_t *>(take(t * G * sizeof(int32_t)));
         group_dev = reinterpret_cast<int8_t *>(take(t * G));
         mask = reinterpret_cast<uint8_t *>(take(t * G));
-        surv_idx = reinterpret_cast<int32_t *>(take(t * (size_t)(K > 0 ? K : 1) * sizeof(int32_t)));
+        auto surv_bytes = [&](int k) { return align_up(t * (size_t)(k > 0 ? k : 1) * sizeof(int32_t)); };
+        surv_idx = reinterpret_cast<int32_t *>(take(surv_bytes(K)));
         n_surv = reinterpret_cast<int32_t *>(take(t * sizeof(int32_t)));
         dec.ulist = reinterpret_cast<int32_t *>(take(G * sizeof(int32_t)));
         dec.meta = reinterpret_cast<int32_t *>(take(256 * sizeof(int32_t)));
@@ -72,8 +73,7 @@ struct Workspace {
         // partial sums of the prefill down projection: the number of ranges falls as T grows, also inside a token tile,
         // so the size is an upper bound that rises with T -- in every tile the ranges of the tile's first token count for
         // all of its tokens up to T -- and a workspace sized for T also serves every smaller call.
-        // Beyond the reserved ranges the kernels take what room there is: never so much that a call
-        // which the fixed scratch array takes would outgrow it.
+        // Room for more than the reserved ranges never makes a call outgrow the fixed scratch array that takes it.
         size_t reserved = 0, wanted = 0;
         if (s.dtype == HALO_BF16 && prefill_path_supported(kFewTokens + 1, s.d, s.group_size)) {
             const int last = std::min(T, prefill_ring_tokens(s.d));
@@ -85,10 +85,17 @@ struct Workspace {
                 wanted = std::max(wanted, need(prefill_down_splits(first, s.d, s.n_groups)));
             }
         }
-        if (off + align_up(reserved * sizeof(float)) <= kStaticScratchBytes)
-            wanted = std::min(wanted, (kStaticScratchBytes - off) / sizeof(float));
-        dec.partial_elems = std::max(reserved, wanted);
-        dec.partial = reinterpret_cast<float *>(take(dec.partial_elems * sizeof(float)));
+        auto room = [&](size_t at) {                             // ... for a carving that has come to `at`
+            if (at + align_up(reserved * sizeof(float)) > kStaticScratchBytes) return std::max(reserved, wanted);
+            return std::max(reserved, std::min(wanted, (kStaticScratchBytes - at) / sizeof(float)));
+        };
+        // What the kernels may use of it is a matter of the shape and T alone, so that the FFN on its own (no k_keep) adds
+        // up in the same order as the whole pass: the least room that any k_keep leaves.  (The carving differs
+        // by k_keep in surv_idx only.  Where the array takes some k_keep and not others that is the reserved room.)
+        const size_t off_least = off - surv_bytes(K) + surv_bytes(0), off_most = off - surv_bytes(K) + surv_bytes(s.n_groups);
+        const size_t fits = kStaticScratchBytes - std::min(kStaticScratchBytes, align_up(reserved * sizeof(float)));
+        dec.partial_elems = off_least <= fits && off_most > fits ? reserved : room(off_most);
+        dec.partial = reinterpret_cast<float *>(take(room(off) * sizeof(float)));
         // appended last: the layout in front of it is the same with and without.  Also for more tokens than the
         // many-token kernels address (T * d * 2 bytes of x below 2^31): the size of the larger call serves the smaller
         if (q4_room && T > kFewTokens && q4_expand_supported(kFewTokens + 1, s.dtype, s.d, s.n_groups, s.group_size))

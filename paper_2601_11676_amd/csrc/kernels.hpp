@@ -32,7 +32,7 @@ struct DecodeScratch {
     int32_t *tok_cnt;   // [G]
     int32_t *slot;      // [T][G] words: prefill's row table (16 bits, group-major), or positions in the lists, -1 = not kept
     float *partial;     // [splits][T][d] prefill: the down projection's sums per range of groups
-    size_t partial_elems;   // ... and the room there
+    size_t partial_elems;   // ... and the room there that this shape may use
     bf16_t *q4_w = nullptr;   // 4-bit callers with many tokens: room for Wg, Wu [ffn][d] and Wd [G][d][gs] as bf16, or null
 };
 // The next block's prediction (predictor + mask from x_next), see halo_ffn_forward_ahead.

@@ -683,3 +683,21 @@ def test_many_token_whole_tiles(T, d, G, K):
     g = hz.gpu_forward(w, L, x, K, pd, drop)
     c = hz.oracle_forward(w, L, x, K, pd, drop)
     hz.assert_parity(g, c, TOL["bf16"], f"whole tiles T={T}")
+
+
+@pytest.mark.parametrize("T", [629, 633, 645])
+def test_staged_ffn_equals_the_whole_pass_near_the_scratch_line(T):
+    # the FFN on its own (no k_keep in its workspace) adds the down projection's ranges up in the same order: around the
+    # most tokens of the shape that the fixed scratch array takes
+    d, G, K = 1152, 23, 11
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=256, T=T, seed=84)
+    _say(f"staged and fused T={T}")
+    s = hz.shape_of(w)
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    g = hz.gpu_forward(w, L, x, K, H.halo_build_schedule(K, w.device_plr()), hs.drop_outcomes(w, T=T))
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    H.halo_group_sparse_ffn(s, x, L.Wg, L.Wu, L.Wd, torch.from_numpy(g["mask"]).to(hz.DEV), y, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"])

@@ -1,0 +1,31 @@
+"""What the entry points launch, checked without a GPU (tests/launches.py)."""
+import numpy as np
+
+from tests.launches import record
+
+BF16, F32 = 1, 0
+
+
+def test_staged_and_fused_ffn_launch_the_same():
+    # the ranges of the down projection, and with them the order of its sums, follow the shape and T, not the room that the
+    # rest of a workspace leaves: T around the most tokens that the fixed scratch array takes
+    rng = np.random.default_rng(9)
+    cases = [(1152, 23, T, 256) for T in range(617, 650, 4)]
+    for _ in range(60):
+        d, G = 128 * int(rng.integers(1, 33)), int(rng.integers(8, 97))
+        line = (8 << 20) / (G * 128 * 4 + G * 25 + 64)
+        cases += [(d, G, max(17, int(line * f)), 64) for f in (0.5, 0.9, 0.95, 0.98, 1.0, 1.05)]
+    calls = []
+    for d, G, T, r in cases:
+        shape = (d, G, 128, r, BF16)
+        calls += [dict(fn="group_sparse_ffn", shape=shape, T=T)]
+        calls += [dict(fn="ffn_forward", shape=shape, T=T, K=K) for K in (1, G // 2, G)]
+        calls += [dict(fn="group_sparse_ffn_q4", shape=shape, T=T), dict(fn="ffn_forward_q4", shape=shape, T=T, K=G)]
+    got = iter(record(calls))
+    for case in cases:
+        for n in (4, 2):                                         # the bf16 calls, the 4-bit calls
+            runs = [next(got) for _ in range(n)]
+            assert all(rc == 0 for rc, _, _ in runs), case
+            staged = runs[0][2]
+            for _, _, launches in runs[1:]:
+                assert launches[-len(staged):] == staged, case

@@ -291,7 +291,7 @@ static void launch_down(const float *act, int T, int d, int G, int gs, const flo
 // The weights are read once per range of tokens (from L2 after the first), so a range takes as many tokens as the
 // registers of its waves allow: 64 in gate/up, 32 in down (sixteen waves).  A range of down lies within one of gate/up,
 // so the groups it walks have been written.
-hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
+static void launch_blocks(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
                           const uint8_t *mask, float *y, float *act, hipStream_t s)
 {
     if (T <= 16)
@@ -304,7 +304,18 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
         launch_down<1>(act, T, d, G, gs, Wd, mask, y, s);
     else
         launch_down<2>(act, T, d, G, gs, Wd, mask, y, s);
-    return hipGetLastError();
+}
+
+hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
+                          const uint8_t *mask, float *y, float *act, hipStream_t s)
+{
+    constexpr int kRun = 1 << 20;                                // ranges of tokens are a grid's y, which ends at 65535
+    for (int t0 = 0;; t0 += kRun) {
+        const size_t t = (size_t)t0;
+        launch_blocks(x + t * d, T - t0 < kRun ? T - t0 : kRun, d, G, gs, Wg, Wu, Wd, mask + t * G, y + t * d,
+                      act + t * G * gs, s);
+        if (T - t0 <= kRun) return hipGetLastError();
+    }
 }
 
 }  // namespace halo

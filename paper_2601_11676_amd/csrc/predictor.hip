@@ -246,8 +246,13 @@ bool scores_apart(int T, int r, int G) { return T >= 64 && (long long)T * r * G 
 
 hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, int G, float *scores, hipStream_t s)
 {
-    scores_mfma_kernel<<<dim3((G + 15) / 16, (T + 15) / 16), dim3(kScoreWaves * 64), 0, s>>>(h, Bt, scores, T, r, G);
-    return hipGetLastError();
+    constexpr int kRun = 65535 * 16;                             // tokens of a launch: a grid's y ends at 65535
+    for (int t0 = 0;; t0 += kRun) {
+        const int n = T - t0 < kRun ? T - t0 : kRun;
+        scores_mfma_kernel<<<dim3((G + 15) / 16, (n + 15) / 16), dim3(kScoreWaves * 64), 0, s>>>(
+            h + (size_t)t0 * r, Bt, scores + (size_t)t0 * G, n, r, G);
+        if (T - t0 <= kRun) return hipGetLastError();
+    }
 }
 
 // The largest tile that still gives every compute unit a workgroup: the bytes staged per result fall with the

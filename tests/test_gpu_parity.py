@@ -701,3 +701,37 @@ def test_staged_ffn_equals_the_whole_pass_near_the_scratch_line(T):
     H.halo_group_sparse_ffn(s, x, L.Wg, L.Wu, L.Wd, torch.from_numpy(g["mask"]).to(hz.DEV), y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"])
+
+
+def test_more_tokens_than_one_grid_takes():
+    # the scores kernel's grid ends at 1048560 tokens, the float32 kernels are launched 2^20 tokens at a time: rows around
+    # the seam against the same rows in a small call (scores, bit for bit) and against 64 bits (float32: sums of 8 and 32 terms)
+    _say("more tokens than one grid takes")
+    g = torch.Generator(device=hz.DEV)
+    g.manual_seed(3)
+    normal = lambda shape, dt: torch.empty(shape, dtype=dt, device=hz.DEV).normal_(0.0, 1.0, generator=g)
+    T, G = 65535 * 16 + 37, 8
+    s = H.Shape(8, G * 16, 16, 8, "bf16", n_groups=G)
+    x, At, Bt = normal((T, 8), torch.bfloat16), normal((8, 8), torch.bfloat16), normal((G, 8), torch.bfloat16)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    sc = torch.full((T, G), float("nan"), dtype=torch.float32, device=hz.DEV)
+    H.halo_predict_scores(s, x, At, Bt, sc, ws)
+    few = torch.empty((64, G), dtype=torch.float32, device=hz.DEV)
+    for t0 in (0, T - 64):
+        H.halo_predict_scores(s, x[t0:t0 + 64].contiguous(), At, Bt, few, ws)
+        assert torch.equal(sc[t0:t0 + 64], few)
+    T, G, gs = (1 << 20) + 40, 2, 16
+    s = H.Shape(8, G * gs, gs, 8, "f32", n_groups=G)
+    x, Wg, Wu, Wd = (normal(n, torch.float32) for n in ((T, 8), (G * gs, 8), (G * gs, 8), (G, 8, gs)))
+    mask = (torch.rand((T, G), generator=g, device=hz.DEV) < 0.6).to(torch.uint8)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    y = torch.full((T, 8), float("nan"), dtype=torch.float32, device=hz.DEV)
+    H.halo_group_sparse_ffn(s, x, Wg, Wu, Wd, mask, y, ws)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all()
+    rows = [0, 1, 31, 500000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, T - 1]
+    xd = x[rows].double().cpu()
+    gate, up = xd @ Wg.double().cpu().T, xd @ Wu.double().cpu().T
+    act = gate * torch.sigmoid(gate) * up * mask[rows].double().cpu().repeat_interleave(gs, dim=1)
+    ref64 = act @ Wd.double().cpu().permute(0, 2, 1).reshape(G * gs, 8)
+    assert (y[rows].double().cpu() - ref64).norm() <= 2e-6 * ref64.norm()

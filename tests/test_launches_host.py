@@ -29,3 +29,16 @@ def test_staged_and_fused_ffn_launch_the_same():
             staged = runs[0][2]
             for _, _, launches in runs[1:]:
                 assert launches[-len(staged):] == staged, case
+
+
+def test_grids_of_very_many_tokens_stay_within_the_limits():
+    # the recorder refuses more than 65535 workgroups in y, as a device may
+    scores, ffn = [1048560, 1048561, 1048576, 5000000], [2097121, 2100000, 4194304, 4200000]
+    calls = [dict(fn="predict_scores", shape=(8, 8, 128, 8, BF16), T=T) for T in scores]
+    calls += [dict(fn="group_sparse_ffn", shape=(8, 2, 16, 8, F32), T=T) for T in ffn]
+    for c, (rc, _, launches) in zip(calls, record(calls)):
+        assert rc == 0, (c, launches)
+        # every token is covered: rows per workgroup of the kernels
+        for name, rows in [("scores_mfma", 16), ("gate_up_f32", 64), ("down_f32", 32)]:
+            runs = [y for n, _, y, _, _ in launches if name in n]
+            assert not runs or (sum(runs) - 1) * rows < c["T"] <= sum(runs) * rows, (c, launches)

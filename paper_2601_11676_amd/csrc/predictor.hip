@@ -257,10 +257,14 @@ hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, in
 
 // The largest tile that still gives every compute unit a workgroup: the bytes staged per result fall with the
 // tile (2 x 2: 64 rows per 1024 results, 1 x 1: 32 per 256), but a unit without a workgroup does nothing.  Fewer
-// than 16 tokens do not fill a tile and stay with a wave per result (2..8 tokens: 7-13 us).
+// than 16 tokens do not fill a tile and stay with a wave per result (2..8 tokens: 7-13 us), and so do few results: a
+// tile's workgroup walks its row in steps of 512 with a barrier each, while a wave per result has all of it under
+// way.  Both layers in us, wave against tile: 16 x 64 results d 1024 4.7 against 6.6, d 8192 6.9 against 17.6; 48 x 256
+// d 4096 10.4 against 11.5; 64 x 256 d 4096 12.3 against 11.5; 32 x 512 d 8192 19.9 against 17.7.  The two meet between
+// 12800 and 16384 results at every d from 128 to 8192.
 static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
-    if (T < 16) return false;
+    if (T < 16 || (long long)T * r < 14 * 1024) return false;
     const int n_tt = (T + 31) / 32;
     if (n_tt * ((r + 31) / 32) >= 256)
         launch_hidden_mfma<2, 2, 8>(x, T, d, r, At, h, s);

@@ -552,8 +552,10 @@ def test_stack_glue_and_ceiling_aids():
 
 
 @pytest.mark.parametrize("T,d,r,G", [
-    (16, 520, 40, 9),          # one 16 x 16 tile per workgroup, a ragged last step of the row, rows past the end
-    (33, 4096, 256, 86),       # a token tile with one token in it
+    (16, 520, 40, 9),          # few results: a wave each
+    (33, 4096, 256, 86),
+    (57, 520, 264, 9),         # one 16 x 16 tile per workgroup, a ragged last step of the row, rows past the end
+    (33, 4096, 512, 86),       # a token tile with one token in it
     (300, 2048, 264, 70),
     (512, 1032, 256, 8),       # two token tiles x one row tile per workgroup
     (530, 640, 512, 33),       # two x two, both ragged

@@ -42,3 +42,15 @@ def test_grids_of_very_many_tokens_stay_within_the_limits():
         for name, rows in [("scores_mfma", 16), ("gate_up_f32", 64), ("down_f32", 32)]:
             runs = [y for n, _, y, _, _ in launches if name in n]
             assert not runs or (sum(runs) - 1) * rows < c["T"] <= sum(runs) * rows, (c, launches)
+
+
+def test_first_predictor_layer_by_the_number_of_results():
+    # few results (T * rank below 14 Ki), or fewer than 16 tokens, are a wave each; the others go to tiles
+    cases = [(16, 64, False), (16, 512, False), (100, 128, False), (256, 48, False), (15, 1024, False), (28, 512, True), (64, 256, True),
+             (300, 64, True)]
+    calls = [dict(fn="predict_scores", shape=(d, 32, 128, r, BF16), T=T) for T, r, _ in cases for d in (128, 1024, 8192)]
+    got = iter(record(calls))
+    for T, r, tiles in cases:
+        for _ in range(3):
+            rc, _, launches = next(got)
+            assert rc == 0 and ("hidden_mfma" in launches[0][0]) == tiles, (T, r, launches)

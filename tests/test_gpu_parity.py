@@ -737,3 +737,21 @@ def test_more_tokens_than_one_grid_takes():
     act = gate * torch.sigmoid(gate) * up * mask[rows].double().cpu().repeat_interleave(gs, dim=1)
     ref64 = act @ Wd.double().cpu().permute(0, 2, 1).reshape(G * gs, 8)
     assert (y[rows].double().cpu() - ref64).norm() <= 2e-6 * ref64.norm()
+
+
+@pytest.mark.parametrize("G,K", [(2, 1), (3, 2)])
+def test_more_tokens_than_the_row_table_holds(G, K):
+    # 32768 tokens: positions of 32 bits and the output-stationary down projection, an even and an odd number of groups
+    T, d = 32768, 128
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=8, T=T, seed=85)
+    _say(f"past the row table G={G}")
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    drop[0] = 1                                                # a token with no survivor
+    g = hz.gpu_forward(w, L, x, K, pd, drop)
+    rows = np.r_[0:130, 16300:16500, T - 130:T]
+    c = hz.oracle_forward(w, L, x[torch.from_numpy(rows).to(hz.DEV)], K, pd, drop[rows])
+    hz.assert_parity({k: v[rows] for k, v in g.items()}, c, TOL["bf16"], "past the row table")
+    assert np.isfinite(g["y"]).all()

@@ -341,3 +341,20 @@ def test_q4_many_token_rings(T, d, G, K):
     H.halo_group_sparse_ffn(s, x, Wg, Wu, H.pack_down_proj(WdT, 128), torch.from_numpy(g["mask"]).to(hz.DEV), y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"])
+
+
+@pytest.mark.parametrize("G,K", [(2, 1), (3, 2)])
+def test_q4_more_tokens_than_the_row_table_holds(G, K):
+    # 32768 tokens: the codes are expanded into the workspace and the bf16 kernels run on them
+    T, d = 32768, 128
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=8, T=T, seed=86)
+    _say(f"q4 past the row table G={G}")
+    L = hz.Q4Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop, big_workspace=True)
+    rows = np.r_[0:130, 16300:16500, T - 130:T]
+    c = hz.oracle_forward(w, L, x[torch.from_numpy(rows).to(hz.DEV)], K, pd, drop[rows])
+    hz.assert_parity({k: v[rows] for k, v in g.items()}, c, TOL["bf16"], "q4 past the row table")
+    assert np.isfinite(g["y"]).all()

@@ -54,3 +54,14 @@ def test_first_predictor_layer_by_the_number_of_results():
         for _ in range(3):
             rc, _, launches = next(got)
             assert rc == 0 and ("hidden_mfma" in launches[0][0]) == tiles, (T, r, launches)
+
+
+def test_kernels_past_the_row_table():
+    shape = (128, 3, 128, 8, BF16)
+    for T, q4, names in [(32767, False, ["group_tokens", "gate_up_pf_big", "down_pf_ring"]),
+                         (32768, False, ["group_tokens", "gate_up_pf_ring", "7down_pf"]),
+                         (32767, True, ["group_tokens", "gate_up_pf_ring", "down_pf_ring"]),
+                         (32768, True, ["expand_q4"] * 3 + ["group_tokens", "gate_up_pf_ring", "7down_pf"])]:
+        (rc, _, launches), = record([dict(fn="group_sparse_ffn" + ("_q4" if q4 else ""), shape=shape, T=T)])
+        kernels = [n for n, *_ in launches if "reduce" not in n]
+        assert rc == 0 and len(kernels) == len(names) and all(a in b for a, b in zip(names, kernels)), (T, q4, launches)

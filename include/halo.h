@@ -113,9 +113,12 @@ size_t halo_workspace_bytes(const halo_shape *shape, int32_t T, int32_t k_keep);
  * The same, for callers of the `_q4` entry points further down: for more than 16 tokens (bf16) the bound
  * also holds one block's FFN weights as bf16 (3 * ffn * d * 2 bytes).  With that room a many-token call runs on
  * the many-token matrix-core kernels over the weights rounded to bf16: up to 32767 tokens the codes are expanded
- * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  A `_q4` call
- * given only halo_workspace_bytes works all the same and walks the tokens 16 at a time instead (several times
- * slower; the scale is then applied in float32).  Never smaller than halo_workspace_bytes; 0 for invalid arguments.
+ * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  (It is
+ * how a caller chooses the rounded weights: a smaller sign would let the slack of a workspace that was sized for more
+ * tokens change the arithmetic.)  A `_q4` call given only halo_workspace_bytes works all the same, several times slower,
+ * with the scale applied in float32: 16 tokens at a time on the 2..16-token kernels where these take the shape (d a
+ * multiple of 1024 up to 8192, n_groups <= 256), else all tokens on the plain path.  Never smaller than
+ * halo_workspace_bytes; 0 for invalid arguments.
  */
 size_t halo_workspace_bytes_q4(const halo_shape *shape, int32_t T, int32_t k_keep);
 
@@ -236,11 +239,11 @@ int halo_ffn_forward_static(const halo_shape *shape, const void *x, const void *
  *   - predictor + group mask of the next block from x_pred_next with that block's
  *     predictor weights -> mask_next (and the optional outputs, same meaning as in
  *     halo_build_group_mask; NULL = not produced).
- * For one token (bf16, group size 128, n_groups <= 256, d <= 8192) and for 2..16 tokens (bf16, d a multiple of 128, group size 128, n_groups <= 256) the
- * prediction occupies spare
- * workgroups of the FFN's own two launches (first predictor layer beside gate/up, second
- * layer + ranking + mask beside the down projection), so it costs no launch and little or no
- * time on the critical path; for other shapes it is enqueued after the FFN.  Results are
+ * For one token (bf16, group size 128, n_groups <= 256, d <= 8192) and for 2..16 tokens (bf16, group size
+ * 128, n_groups <= 256, d a multiple of 128) the prediction occupies spare workgroups of the FFN's own two
+ * launches (first predictor layer beside gate/up, second layer + ranking + mask beside the down
+ * projection), so it costs no launch and little or no time on the critical path; for other shapes it is
+ * enqueued after the FFN.  Results are
  * identical to the separate calls either way.  x_pred_next may be x (predicting from this
  * block's input, as the paper does) but must not be y; mask_next must not alias mask_cur.
  */
@@ -273,7 +276,8 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * tokens with d a multiple of 1024 up to 8192 (matrix cores, codes expanded in registers); other shapes and float32
  * activations take a plain path that dequantises element by element.  More than 16 tokens (any d a multiple of
  * 128, any n_groups): with a workspace of halo_workspace_bytes_q4 the many-token matrix-core kernels, each value
- * s * (c - 8) rounded to bf16, to nearest even; with less, the paths above, 16 tokens at a time.
+ * s * (c - 8) rounded to bf16, to nearest even; with less, the 2..16-token kernels 16 tokens at a time where they take
+ * the shape, else the plain path.
  */
 int halo_group_sparse_ffn_q4(const halo_shape *shape, const void *x, int32_t T, const void *Wg_codes,
                              const void *Wg_scales, const void *Wu_codes, const void *Wu_scales,

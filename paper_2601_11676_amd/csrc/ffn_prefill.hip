@@ -219,12 +219,14 @@ __device__ __forceinline__ void wait_loads()
 }
 
 // acc += a * b with the accumulator pinned to the accumulation registers and updated in place.
-// (Left to itself the compiler gives the 64 tiles of this kernel rotating destination registers and
+// (Left to itself the compiler gives the tiles of these kernels rotating destination registers and
 // moves a few hundred registers between the two files per step to make that work.)  A statement the
 // compiler cannot look into also gets none of its matrix-pipeline wait states, which is safe here:
-// a tile is touched again 63 matrix instructions later (a 16x16x32 bf16 instruction occupies the
-// pipeline for 8 passes of 4 cycles, so its result is long written back by then), and the first
-// ordinary read of the accumulators comes after a barrier and an explicit pause of 2 x 16 idle
+// a wave goes through all of its tiles before it touches one again, 32 in the 256-token rings, 16 in the 128-token
+// rings, 8 N in gate_up_pf_big (N = 1: seven matrix instructions lie between; ring_multiply asserts the 8).  A
+// 16x16x32 bf16 instruction occupies the pipeline for 8 passes and they issue in order, so one instruction
+// in between is already more than the few cycles a result takes after its last pass.  The first
+// ordinary read of the accumulators comes after an explicit pause of 2 x 16 idle
 // cycles, more than the 18 cycles the last instruction can still be in flight.
 __device__ __forceinline__ void mfma16_inplace(f32x4_t &acc, const u32x4 &a, const u32x4 &b)
 {
@@ -365,6 +367,7 @@ template <int MT, int TT, typename Beside, typename Refill>
 __device__ __forceinline__ void ring_multiply(f32x4_t (&acc)[MT][TT], const u32x4 (&a)[MT], const u32x4 (&b)[TT], Beside beside,
                                               Refill refill)
 {
+    static_assert(MT * TT >= 8, "the distance that mfma16_inplace relies on");
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
 #pragma unroll
@@ -1204,6 +1207,10 @@ static hipError_t launch_down_ring(int T, int d, int G, int splits, const void *
 
 // Whole tiles of 256 x 256 in gate/up when half of the tokens keeping a group (the lists are not known here; each
 // ends in half a tile on average) gives more than 150 of them: gate_up_pf_ring's half rows then take a second round.
+// Whole FFN in us, ring against whole tiles, half of the tokens keeping a group: below the line 7B 500 tokens 115 against 138,
+// 13B 400 148 against 175; above it 7B 700 196 against 163, 13B 600 260 against 221, 70B 256 385 against 294.  With other
+// shares the line lies elsewhere: at 0.3 these three run in 157 (ring 133), 197 (171) and 275 (286), at 0.7 the two below
+// the line in 170 (whole tiles 143) and 234 (194).
 static bool gate_up_big_tiles(int T, int G) { return (long long)G * (T + 256) > 512 * 150; }
 
 static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const bf16_t *Wg, const bf16_t *Wu,

@@ -37,8 +37,6 @@ hipError_t launch_group_mask(const float *scores, int T, int G, int K, const int
     return hipGetLastError();
 }
 
-// Many scores: computed on the matrix cores in a launch of their own (a token's workgroup reads all of Bt for itself).
-
 hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int r, float *scores,
                                   int T, int G, int K, const int8_t *prio_dev, int n_dev,
                                   const uint8_t *drop, int32_t *order, int8_t *group_dev,
@@ -49,6 +47,7 @@ hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int
             h, (const float *)Bt, r, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask,
             surv_idx, n_surv);
     else if (scores_apart(T, r, G)) {
+        // many scores: on the matrix cores in a launch of their own (here a token's workgroup reads all of Bt for itself)
         const hipError_t e = launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
         if (e != hipSuccess) return e;
         mask_scores_kernel<float, false, 512><<<dim3(T), dim3(512), 0, s>>>(

@@ -240,8 +240,12 @@ __global__ __launch_bounds__(kScoreWaves * 64) void scores_mfma_kernel(
 }
 
 // whether a launch of their own pays: inside the mask kernel a token's workgroup reads all of Bt for itself and spends most
-// instructions on lane-crossing sums, but the second launch costs a few microseconds.  us, both kernels against the one (T x r x G): 1000 x 512 x 224 22.0 against 36.8,
-// 700 x 512 x 120 12.0 against 16.2, 2000 x 256 x 86 16.5 against 20.6; 512 x 256 x 86 11.4 against 9.3.
+// instructions on lane-crossing sums, but the second launch costs a few microseconds.  us, both kernels against the one
+// (T x r x G): 1000 x 512 x 224 22.0 against 36.8, 700 x 512 x 120 12.0 against 16.2, 2000 x 256 x 86 16.5 against 20.6;
+// 512 x 256 x 86 11.4 against 9.3.  Every shape measured from 40 Mi on gains (2 to 90 us of a pass).  Below, the two cross
+// at 10 to 20 Mi where there are 86 to 160 groups (900 x 256 x 86, 19 Mi: level; 512 x 256 x 86, 11 Mi: 1.3 lost), lower with
+// more groups or ranks of 64 and less (200 x 512 x 224, 22 Mi: 3.5 to be had; 1500 x 64 x 224, 21 Mi: 9), and at 28 Mi with
+// 64 groups.
 bool scores_apart(int T, int r, int G) { return T >= 64 && (long long)T * r * G >= 40ll << 20; }
 
 hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, int G, float *scores, hipStream_t s)

@@ -237,7 +237,7 @@ def test_q4_full_size_single_layer_of_the_stacks(wl):
 @pytest.mark.parametrize("big_workspace", [False, True])
 def test_q4_llama7b_prefill_all_tokens(big_workspace):
     # 512 tokens over 4-bit weights: with the plain workspace the few-token kernels walk the tokens 16 at a
-    # time; with room for a block's weights as bf16 they are expanded once and the bf16 kernels run
+    # time; with room for a block's weights as bf16 the many-token kernels run on weights rounded to bf16
     w = hs.LLAMA7B_PREFILL
     _say(f"q4 7B prefill, 512 tokens, every token, big workspace {big_workspace}")
     s = hz.shape_of(w)
@@ -255,7 +255,7 @@ def test_q4_llama7b_prefill_all_tokens(big_workspace):
 
 @pytest.mark.parametrize("T,d,G", [(17, 1024, 9), (40, 2048, 12), (300, 1024, 20)])
 def test_q4_many_tokens_on_expanded_weights(T, d, G):
-    # small shapes through the expansion to bf16 (workspace of halo_workspace_bytes_q4)
+    # small shapes on weights rounded to bf16 (workspace of halo_workspace_bytes_q4)
     w = dataclasses.replace(hs.LLAMA13B_STACK, name="case", d=d, ffn=G * 128, rank=64, T=T, layers=1, seed=19)
     _say(f"q4 many tokens, expanded weights T={T} d={d} G={G}")
     L = hz.Q4Layer(w)
@@ -315,10 +315,12 @@ def test_q4_one_token_of_any_row_length(d, G, K, r):
 @pytest.mark.parametrize("T,d,G,K", [
     (17, 128, 3, 2),           # one block of codes per row
     (128, 640, 5, 2),          # an odd number of blocks per row: the scales' words straddle rows
-    (200, 384, 70, 60),        # half tiles in gate/up, whole ones in down
+    (200, 384, 70, 60),        # half tiles, many groups of three blocks
+    (129, 4096, 40, 20),       # half tiles in gate/up, a whole tile with half of it empty in down
     (257, 1024, 6, 6),         # dense: no token needs a row of zeros
     (300, 256, 300, 30),       # more groups than the few-token kernels take
-    (515, 4224, 9, 4),         # three token tiles, the last with three tokens
+    (515, 4224, 9, 4),         # whole tiles in gate/up, five half tiles in down, one range
+    (515, 4224, 40, 10),       # three whole tiles in down, the last with three tokens
 ])
 def test_q4_many_token_rings(T, d, G, K):
     # the codes expanded on their way into LDS give what the bf16 kernels give on the expanded weights, bit for bit (where those

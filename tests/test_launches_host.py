@@ -65,3 +65,17 @@ def test_kernels_past_the_row_table():
         (rc, _, launches), = record([dict(fn="group_sparse_ffn" + ("_q4" if q4 else ""), shape=shape, T=T)])
         kernels = [n for n, *_ in launches if "reduce" not in n]
         assert rc == 0 and len(kernels) == len(names) and all(a in b for a, b in zip(names, kernels)), (T, q4, launches)
+
+
+def test_many_token_cases_run_on_the_kernels_they_are_for():
+    # the forms of the ring kernels that the parity cases are chosen to reach: tokens per tile, in gate/up and down
+    for T, d, G, gate_up, down in [(17, 128, 3, 128, 128), (129, 640, 40, 128, 128), (129, 4096, 40, 128, 256),
+                                   (257, 1024, 6, 256, 128), (515, 4224, 9, 256, 128), (515, 4224, 40, 256, 256)]:
+        for q4 in (0, 1):
+            (rc, _, launches), = record([dict(fn="ffn_forward" + ("_q4" if q4 else ""), shape=(d, G, 128, 64, BF16), T=T, K=G // 2)])
+            names = [n for n, *_ in launches]
+            for kernel, tokens in (("gate_up_pf_ring", gate_up), ("down_pf_ring", down)):
+                assert rc == 0 and sum(f"{kernel}ILb{q4}ELi{tokens}E" in n for n in names) == 1, (T, d, G, q4, names)
+    for T, d, G in [(300, 256, 300), (1100, 384, 180), (520, 128, 100), (300, 1152, 150), (2050, 256, 97)]:
+        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, G, 128, 64, BF16), T=T, K=G // 3)])
+        assert rc == 0 and any("gate_up_pf_big" in n for n, *_ in launches), (T, d, G, launches)

@@ -5,9 +5,10 @@
 // the matrix instruction is only a cheap way to apply one 16-byte weight piece to all
 // tokens at once (v_mfma_f32_16x16x32_bf16: 16 weight rows x 16 tokens x 32 elements).
 //
-//   gate/up : each wave owns a contiguous run of the union's neurons (runs differ by at
-//             most one), cut into tiles of <= 16 rows, and sweeps the rows in 512-element
-//             chunks; the token fragments are read from x directly (it is small and stays
+//   gate/up : (here for rows longer than 8192 or more than 256 groups; the others are in
+//             ffn_few.hip and ffn_stream.hip) each wave owns a contiguous run of the union's
+//             neurons (runs differ by at most one), cut into tiles of <= 16 rows, and sweeps the
+//             rows in 512-element chunks; the token fragments are read from x directly (it is small and stays
 //             in cache).  act[t][n] = mask ? SiLU(gate)*up : 0 is stored in bf16.
 //   down    : Wd is group-blocked, Wd[g][j][m]; a workgroup owns a run of consecutive output
 //             rows j (one workgroup per compute unit where the row count allows), its four
@@ -62,12 +63,7 @@ __global__ __launch_bounds__(256) void gate_up_mt(
     if ((int)blockIdx.x < ap.n_pred) {
         // paper Sec. III-B.3, Pred beside Load/Comp, one layer ahead: the next block's first layer
         const int j = blockIdx.x * 4 + wave;
-        switch (d) {
-        case 4096: predictor_row_tokens<4096>(ap.x_next, ap.At, ap.h, T, d, ap.r, j, lane); break;
-        case 5120: predictor_row_tokens<5120>(ap.x_next, ap.At, ap.h, T, d, ap.r, j, lane); break;
-        case 8192: predictor_row_tokens<8192>(ap.x_next, ap.At, ap.h, T, d, ap.r, j, lane); break;
-        default: predictor_row_tokens<0>(ap.x_next, ap.At, ap.h, T, d, ap.r, j, lane); break;
-        }
+        predictor_row_tokens<0>(ap.x_next, ap.At, ap.h, T, d, ap.r, j, lane);
         return;
     }
     bf16_t *my = sW[wave];
@@ -372,6 +368,11 @@ hipError_t launch_ffn_mfma(const bf16_t *x, int T, int d, int G, int gs, const b
         if (few_path_supported(T, d, G, gs)) {
             // up to four tokens: rows streamed as in the one-token path
             hipError_t e = launch_gate_up_few(x, T, d, G, gs, Wg, Wu, mask, act, ffn, s, ap);
+            if (e != hipSuccess) return e;
+        } else if (stream_path_supported(T, d, G, gs)) {
+            // one K slice of all rows per wave: d 2432, 8 tokens 26.2 -> 18.2 us, d 1152, 5 tokens 17.1 -> 9.5, 70B shape, 8 tokens
+            // 151.5 -> 142.4; where the float ALUs above apply they are level or ahead (7B shape, 2 tokens 23.0 against 24.0)
+            const hipError_t e = launch_gate_up_stream(x, T, d, G, Wg, Wu, mask, act, s, ap);
             if (e != hipSuccess) return e;
         } else {
             launch_timed("gate_up_mt", gate_up_mt<true>, dim3(256 + ap.n_pred), dim3(256), s, x, T, d, G, gs, Wg, Wu,

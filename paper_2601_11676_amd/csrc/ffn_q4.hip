@@ -537,7 +537,7 @@ static hipError_t q4_one_token(const bf16_t *x, int d, int G, const Q4Weights &w
 }
 
 hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, const Q4Weights &w,
-                         const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s, int rank,
+                         const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s,
                          const AheadArgs *ahead, bool *ahead_fused)
 {
     if (ahead_fused) *ahead_fused = false;
@@ -549,8 +549,7 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
         return d == 4096 || d == 8192
                    ? q4_one_token<bf16_t>(bx, d, G, w, mask, by, reinterpret_cast<bf16_t *>(ws.act), s, ahead, ahead_fused)
                    : q4_one_token<float>(bx, d, G, w, mask, by, ws.act, s, ahead, ahead_fused);
-    if (q4_mfma_path_supported(T, d, G, gs))
-        return launch_ffn_q4_mfma(bx, T, d, G, w, mask, by, ws, s, rank, ahead, ahead_fused);
+    if (stream_path_supported(T, d, G, gs)) return launch_ffn_q4_mfma(bx, T, d, G, w, mask, by, ws, s, ahead, ahead_fused);
     // The many-token kernels multiply by values rounded to bf16, the few-token kernels scale in float: which of the two a
     // call of many tokens gets is the caller's choice, by the workspace.
     if (ws.q4_w && prefill_q4_supported(T, d, G, gs)) return launch_ffn_prefill_q4(bx, T, d, G, w, mask, by, ws, s);
@@ -566,7 +565,7 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
         if (e != hipSuccess) return e;
         return launch_ffn_decode(dtype, x, T, d, G, gs, Wg, Wu, Wd, mask, y, ws, s);
     }
-    if (T > 16 && q4_mfma_path_supported(16, d, G, gs)) {
+    if (T > 16 && stream_path_supported(16, d, G, gs)) {
         // Many tokens: the matrix-core kernels over tiles of up to 16 tokens, one tile after the other on
         // the stream (each streams the union of its own tokens' groups; the activation scratch is reused).
         // No kernel of its own for this case yet: a tile pair of launches is 30-90 us, where the plain path
@@ -576,7 +575,7 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
             int n = T - t0 > 16 ? 16 : T - t0;
             if (T - t0 == 17) n = 15;
             const hipError_t e = launch_ffn_q4_mfma(bx + (size_t)t0 * d, n, d, G, w, mask + (size_t)t0 * G,
-                                                    by + (size_t)t0 * d, ws, s, rank, nullptr, nullptr);
+                                                    by + (size_t)t0 * d, ws, s, nullptr, nullptr);
             if (e != hipSuccess) return e;
             t0 += n;
         }

@@ -132,10 +132,8 @@ struct Q4Weights {
 bool q4_shape_supported(int d, int gs);
 // many tokens over 4-bit weights can run on the bf16 matrix-core kernels once the weights are expanded
 bool q4_expand_supported(int T, int dtype, int d, int G, int gs);
-// rank: the predictor's size; the few-token kernel shapes its work around the predictor rows it carries when
-// one step is overlapped with the next, and shapes it the same way when it carries none (same bits either way)
 hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, const Q4Weights &w,
-                         const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s, int rank,
+                         const uint8_t *mask, void *y, const DecodeScratch &ws, hipStream_t s,
                          const AheadArgs *ahead = nullptr, bool *ahead_fused = nullptr);
 
 // ffn_prefill.hip : many tokens over 4-bit weights, expanded on their way into LDS
@@ -144,10 +142,19 @@ hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4W
                                  const DecodeScratch &ws, hipStream_t s);
 
 // ffn_q4_mt.hip : 4-bit weights, 2..16 tokens, matrix cores
-bool q4_mfma_path_supported(int T, int d, int G, int gs);
 hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask,
-                              bf16_t *y, const DecodeScratch &ws, hipStream_t s, int rank,
-                              const AheadArgs *ahead = nullptr, bool *ahead_fused = nullptr);
+                              bf16_t *y, const DecodeScratch &ws, hipStream_t s, const AheadArgs *ahead = nullptr,
+                              bool *ahead_fused = nullptr);
+
+// ffn_stream.hip : 2..16 tokens, bf16 or 4-bit weights, rows of any multiple of 128 up to 8192, up to 256 groups
+bool stream_path_supported(int T, int d, int G, int gs);
+hipError_t launch_gate_up_stream(const bf16_t *x, int T, int d, int G, const bf16_t *Wg, const bf16_t *Wu, const uint8_t *mask,
+                                 bf16_t *act, hipStream_t s, const AheadPredDev &ap);
+// plane: 0 = activations as one bf16 value each; otherwise as the sum of two, the second `plane` elements behind the first
+hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *act,
+                                    size_t plane, hipStream_t s, const AheadPredDev &ap);
+hipError_t launch_down_q4_planes(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const bf16_t *act, size_t plane,
+                                 bf16_t *y, const AheadArgs *ah, hipStream_t s);
 
 // mha_decode.hip : head-sparse attention for one new token (bf16, head dimension 128)
 struct MhaScratch {

@@ -169,6 +169,46 @@ def test_q4_few_tokens_with_handmade_masks(T, d, G):
                 assert np.linalg.norm(yg[t] - yc[t]) / np.linalg.norm(yc[t]) <= TOL["bf16"], t
 
 
+@pytest.mark.parametrize("q4", [True, False])
+@pytest.mark.parametrize("T,d,G,r", [
+    (2, 128, 3, 40),           # 4-bit: half a unit, seven of eight waves without one; bf16: two units
+    (8, 1152, 27, 264),        # the most tokens of a folded operand; an odd number of blocks
+    (9, 2176, 5, 64),          # one more: two operands; the last wave's second unit is half a unit
+    (16, 3200, 40, 512),       # four passes of two predictor rows
+    (3, 5248, 200, 256),       # three rows of eight outputs to a workgroup
+    (13, 6784, 6, 64),         # bf16: thirteen or fourteen units to a wave
+    (5, 7936, 9, 256),         # ... fifteen or sixteen
+    (16, 8064, 256, 64),       # the most groups: every neuron of a workgroup's run in one group
+])
+def test_few_tokens_of_any_row_length(q4, T, d, G, r):
+    # against the oracle, and the overlapped form equal to the serial one bit for bit
+    w = dataclasses.replace(hs.LLAMA13B_STACK, name="case", d=d, ffn=G * 128, rank=r, T=T, layers=1, seed=28)
+    _say(f"few tokens, any row length q4={q4} T={T} d={d} G={G}")
+    s, L = hz.shape_of(w), (hz.Q4Layer if q4 else hz.Layer)(w)
+    forward = hz.gpu_forward_q4 if q4 else hz.gpu_forward
+    x, xn = hs.hidden_states(w, 0, hz.DEV), hs.hidden_states(w, 1, hz.DEV)
+    for K in sorted({max(1, G // 2), G}):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        drop, dn = hs.drop_outcomes(w, 0, 0, T=T), hs.drop_outcomes(w, 0, 1, T=T)
+        if K < G:
+            drop[T - 1] = 1                    # one token loses every device: exact zeros expected
+        g = forward(w, L, x, K, pd, drop)
+        if G < 200 or K < G:
+            hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"K={K}")
+        gn = forward(w, L, xn, K, pd, dn)
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+        mn = torch.zeros((T, G), dtype=torch.uint8, device=hz.DEV)
+        ws = torch.empty(H.halo_workspace_bytes(s, T, K), dtype=torch.uint8, device=hz.DEV)
+        rest = (torch.from_numpy(g["mask"]).to(hz.DEV), y, xn, L.At, L.Bt, K, torch.from_numpy(pd).to(hz.DEV), w.n_dev,
+                torch.from_numpy(dn).to(hz.DEV), mn, ws)
+        if q4:
+            H.halo_ffn_forward_ahead_q4(s, x, L.q4, *rest)
+        else:
+            H.halo_ffn_forward_ahead(s, x, L.Wg, L.Wu, L.Wd, *rest)
+        torch.cuda.synchronize()
+        assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])
+
+
 @pytest.mark.parametrize("d,T,r,G,K", [
     (4096, 1, 256, 20, 10), (8192, 1, 256, 20, 10), (512, 3, 256, 20, 10), (5120, 4, 256, 20, 10),
     (8192, 8, 256, 20, 10), (384, 3, 256, 20, 10),

@@ -205,6 +205,20 @@ __device__ __forceinline__ void predictor_row_tokens(const bf16_t *__restrict__ 
     }
 }
 
+// Loads through a buffer descriptor: an offset of kOutOfRange (plus anything small) is past its end, and every offset is past the
+// end of one of 0 bytes; such a load moves nothing and gives zeros, so no load has to stand behind a condition.
+constexpr uint32_t kOutOfRange = 0x80000000u;
+constexpr int kNt = 2;                       // cache policy: non-temporal
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int bytes = 0x7fffffff)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
+}
+template <int POLICY>
+__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t b, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, voff, soff, POLICY));
+}
+
 // Wave-wide sum through the DPP cross-lane paths (no LDS traffic); result is uniform.
 // Used where the summation order is free (FFN dot products), not by the predictor.
 __device__ __forceinline__ float wave_sum_fast(float v)

@@ -517,7 +517,7 @@ hipError_t launch_ffn_decode(int dtype, const void *x, int T, int d, int G, int 
                              bool *ahead_fused)
 {
     if (ahead_fused) *ahead_fused = false;
-    if (dtype == 0 && f32_path_supported(gs))
+    if (dtype == 0 && f32_path_supported(d, gs))
         return launch_ffn_f32((const float *)x, T, d, G, gs, (const float *)Wg, (const float *)Wu, (const float *)Wd, mask,
                               (float *)y, ws.act, s);
     if (dtype == 0)                                              // groups that are not whole 16-row tiles

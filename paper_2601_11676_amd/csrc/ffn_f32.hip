@@ -6,14 +6,14 @@
 // front of each result, not bytes or flops, so both kernels cut the reduction dimension over the waves of a
 // workgroup until a wave's share is a handful of loads that are all requested together, and meet in LDS once.
 //   gate/up : workgroup = 16 neurons of one group x up to 64 tokens; leaves at once when none of its tokens
-//             keeps the group, so no list of groups is needed.  act[t][ffn] = mask ? SiLU(gate) * up : 0.
-//   down    : workgroup = 16 outputs x up to 32 tokens, its waves share the pieces of the union's groups.
+//             keeps the group, so no list of groups is needed.  act = mask ? SiLU(gate) * up : 0.
+//   down    : workgroup = 16 outputs x up to 16 tokens, its waves share the pieces of the union's groups.
 // WHICH 4 of a 16-element piece an instruction's lane group multiplies is free as long as both operands agree:
 // lane (i, q) = (l % 16, l / 16) holds elements 4 q .. 4 q + 3 of row i in one 16-byte load, and instruction e
 // multiplies element 4 q + e of every lane group.  D: lane l holds column (token) l % 16, rows 4 (l / 16) .. + 3.
-// Tiny block: gate/up 4.6 us and down 6.9 us per launch, against 10.0 and 68 us for a wave per neuron / per output
-// row that walked its groups one 4-byte load at a time; the pass called from Python 21 us (89).  1000 x 24 groups, one
-// token: 28 us (265).  Error against 64 bits over d 128..1024, 4..24 groups, 1..64 tokens: 0.89..1.01 times theirs.
+// Tiny block: gate/up 4.7 us and down 5.8 us per launch, the pass called from Python 19 us; a wave per neuron / per output
+// row that walked its groups one 4-byte load at a time took 10, 68 and 89.  Error against 64 bits over d 128..1024, 4..24 groups,
+// 1..64 tokens: 0.89..1.01 times theirs.
 #include "kernels.hpp"
 
 namespace halo {
@@ -37,105 +37,98 @@ __device__ __forceinline__ f32x4_t pairwise_sum(f32x4_t (&p)[N])
 }
 
 constexpr int kGateUpF32Waves = 8, kDownF32Waves = 16;
+constexpr int kRowF32 = 128 + 4;                                 // padded LDS row of a chunk of 128 elements
 
-// Where the lanes of group q load the four elements of piece p that they hold, in elements from the row's start.  The last
-// piece may hold 8 elements, and the only one of a row of 8 as well: lanes past the end take the row's first four, unused.
-__host__ __device__ constexpr bool in_row(int p, int q, int d) { return p * 16 + 4 * q < d; }
-__host__ __device__ constexpr int piece_at(int p, int q, int d) { return in_row(p, q, d) ? p * 16 + 4 * q : 0; }
-constexpr bool loads_stay_in_row(int d)
+__device__ __forceinline__ f32x4_t load4(__amdgpu_buffer_rsrc_t b, uint32_t voff, uint32_t soff)
 {
-    for (int p = 0; p < (d + 15) / 16; ++p)
-        for (int q = 0; q < 4; ++q)
-            if (piece_at(p, q, d) < 0 || piece_at(p, q, d) + 4 > d) return false;
-    return true;
+    return __builtin_bit_cast(f32x4_t, buffer_load16<0>(b, voff, soff));
 }
-static_assert(loads_stay_in_row(8) && loads_stay_in_row(16) && loads_stay_in_row(24) && loads_stay_in_row(520), "d is a multiple of 8");
 
-// NT: token tiles of 16 per workgroup.  grid (ffn / 16, ceil(T / (16 NT)))
+// Sums of products over pieces of 16 elements, taken in pairs: a sum per instruction of a piece, folded pairwise after every
+// second piece, so that no chain is longer than 8 products, as in a wave per row (one running sum per wave was up to twice as
+// far from 64 bits, chains of 16 up to 1.1 times).
 template <int NT>
-__global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
-    const float *__restrict__ x, int T, int d, int G, int gs, const float *__restrict__ Wg, const float *__restrict__ Wu,
-    const uint8_t *__restrict__ mask, float *__restrict__ act, int ffn)
-{
-    constexpr int W = kGateUpF32Waves, U = NT == 4 ? 1 : 2;      // pieces per batch and wave
-    __shared__ f32x4_t part[W][2][NT][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * 16, g = n0 / gs, t0 = blockIdx.y * 16 * NT;
-    const uint8_t mine = mask[(size_t)min(t0 + min(lane, 16 * NT - 1), T - 1) * G + g];
-    if (__ballot(mine != 0) == 0ull) return;                     // uniform: the same bytes in every wave
-    const float *wg = Wg + (size_t)(n0 + i) * d, *wu = Wu + (size_t)(n0 + i) * d;
-    const float *xr[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) xr[n] = x + (size_t)min(t0 + 16 * n + i, T - 1) * d;
-    const int np = (d + 15) / 16;                                // pieces of 16; the last one may hold 8
-    struct Batch {
-        f32x4_t g[U], u[U], x[NT][U];
-    };
-    auto fetch = [&](Batch &b, int p0) {
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int p = p0 + W * k;
-            if (p < np) {                                        // uniform
-                const bool ok = in_row(p, q, d);
-                const int at = piece_at(p, q, d);
-                b.g[k] = *reinterpret_cast<const f32x4_t *>(wg + at);
-                b.u[k] = *reinterpret_cast<const f32x4_t *>(wu + at);
-#pragma unroll
-                for (int n = 0; n < NT; ++n) b.x[n][k] = *reinterpret_cast<const f32x4_t *>(xr[n] + at);
-                if (!ok) {
-                    b.g[k] = b.u[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int n = 0; n < NT; ++n) b.x[n][k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-        }
-    };
-    f32x4_t cg[NT], cu[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) cg[n] = cu[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // A batch has a sum per instruction of a piece, folded pairwise at its end: no chain is longer than 8 products, as in
-    // a wave per row (one running sum per wave was up to twice as far from 64 bits, chains of 16 up to 1.1 times).
-    f32x4_t bg[NT][4], bu[NT][4];
-    auto multiply = [&](const Batch &b, int p0) {
-#pragma unroll
-        for (int k = 0; k < U; ++k)
-            if (p0 + W * k < np) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int n = 0; n < NT; ++n) {
-                        bg[n][e] = mfma4(b.g[k][e], b.x[n][k][e], bg[n][e]);
-                        bu[n][e] = mfma4(b.u[k][e], b.x[n][k][e], bu[n][e]);
-                    }
-            }
-    };
-    Batch A, B;
-    fetch(A, wave);
-    auto clear = [&]() {
+struct PairSum {
+    f32x4_t s[NT][4];
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
         for (int n = 0; n < NT; ++n)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bg[n][e] = bu[n][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    };
-    auto fold = [&]() {
+            for (int e = 0; e < 4; ++e) s[n][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void add(const f32x4_t &w, const f32x4_t (&x)[NT])
+    {
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            cg[n] += (bg[n][0] + bg[n][1]) + (bg[n][2] + bg[n][3]);
-            cu[n] += (bu[n][0] + bu[n][1]) + (bu[n][2] + bu[n][3]);
-        }
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) s[n][e] = mfma4(w[e], x[n][e], s[n][e]);
+    }
+    __device__ __forceinline__ void fold(f32x4_t (&c)[NT])
+    {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) c[n] += (s[n][0] + s[n][1]) + (s[n][2] + s[n][3]);
+    }
+};
+
+// NT: token tiles of 16 per workgroup.  grid (ffn / 16, ceil(T / (16 NT)))
+// A wave takes every eighth pair of pieces, 128 bytes of a row: with single pieces dealt out, two waves asked for the halves
+// of every cache line.  DEPTH pieces are in flight, the first ones requested beside the mask bytes that say whether anybody
+// wants them, and no load stands behind a condition.  (d 616, 13 groups, 36 tokens 13.2 -> 7.4 us, half of it because two token
+// tiles to a workgroup, not four, leave no compute unit idle; d 1000, 24 groups, 60 tokens 16.6 -> 16.2, either number of tiles.
+// Chunks of 128 elements through LDS, as in the down projection: 4.5 us at the tiny block, but 10 and 21 at these two.)
+template <int NT>
+__global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
+    const float *__restrict__ x, int T, int d, int G, int gs, const float *__restrict__ Wg, const float *__restrict__ Wu,
+    const uint8_t *__restrict__ mask, float *__restrict__ act, size_t group_stride, int token_stride)
+{
+    constexpr int W = kGateUpF32Waves, DEPTH = NT == 1 ? 4 : 2;
+    __shared__ f32x4_t part[W][2][NT][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * 16, g = n0 / gs, t0 = blockIdx.y * 16 * NT;
+    const uint8_t mine = mask[(size_t)min(t0 + min(lane, 16 * NT - 1), T - 1) * G + g];
+    // (descriptors of the workgroup's own rows: the offsets stay small whatever the matrices' sizes)
+    const __amdgpu_buffer_rsrc_t bg = buffer_of(Wg + (size_t)n0 * d), bu = buffer_of(Wu + (size_t)n0 * d),
+                                 bx = buffer_of(x + (size_t)t0 * d);
+    const uint32_t at_w = (uint32_t)(i * d + 4 * q) * 4;
+    uint32_t at_x[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) at_x[n] = (uint32_t)(min(16 * n + i, T - 1 - t0) * d + 4 * q) * 4;
+    const int np = (d + 15) / 16;                                // pieces of 16; the last one may hold 8
+    struct Piece {
+        f32x4_t g, u, x[NT];
     };
-    for (int p0 = wave; p0 < np; p0 += 2 * W * U) {
-        clear();
-        fetch(B, p0 + W * U);
-        multiply(A, p0);
-        if (U > 1) {
-            fold();
-            clear();
+    auto fetch = [&](Piece &b, int p) {                          // zeros past the end of the row
+        const bool ok = p * 16 + 4 * q < d;
+        b.g = load4(bg, ok ? at_w : kOutOfRange, p * 64);
+        b.u = load4(bu, ok ? at_w : kOutOfRange, p * 64);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) b.x[n] = load4(bx, ok ? at_x[n] : kOutOfRange, p * 64);
+    };
+    Piece b[DEPTH];
+#pragma unroll
+    for (int k = 0; k < DEPTH; ++k) fetch(b[k], 2 * (wave + W * (k / 2)) + k % 2);
+    if (__ballot(mine != 0) == 0ull) return;                     // uniform: the same bytes in every wave
+    f32x4_t cg[NT], cu[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) cg[n] = cu[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    PairSum<NT> sg, su;
+    for (int p = 2 * wave; p < np; p += W * DEPTH) {
+#pragma unroll
+        for (int k = 0; k < DEPTH; ++k) {
+            if (k % 2 == 0) {
+                sg.clear();
+                su.clear();
+            }
+            sg.add(b[k].g, b[k].x);
+            su.add(b[k].u, b[k].x);
+            fetch(b[k], p + W * (k / 2 * 2 + DEPTH) + k % 2);
+            if (k % 2 == 1) {
+                sg.fold(cg);
+                su.fold(cu);
+            }
         }
-        fetch(A, p0 + 2 * W * U);
-        multiply(B, p0 + W * U);
-        fold();
     }
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -150,19 +143,120 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
             pg[w] = part[w][0][wave][lane];
             pu[w] = part[w][1][wave][lane];
         }
-        const f32x4_t sg = pairwise_sum(pg), su = pairwise_sum(pu);
+        const f32x4_t g_ = pairwise_sum(pg), u_ = pairwise_sum(pu);
         const int t = t0 + 16 * wave + i;
+        const bool wanted = __shfl(mine, 16 * wave + i) != 0;
         if (t < T) {
-            const bool keep = mask[(size_t)t * G + g] != 0;
             f32x4_t v;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) v[m] = keep ? silu_mul(sg[m], su[m]) : 0.0f;
-            *reinterpret_cast<f32x4_t *>(act + (size_t)t * ffn + n0 + 4 * q) = v;
+            for (int m = 0; m < 4; ++m) v[m] = wanted ? silu_mul(g_[m], u_[m]) : 0.0f;
+            *reinterpret_cast<f32x4_t *>(act + g * group_stride + (size_t)t * token_stride + (n0 - g * gs) + 4 * q) = v;
         }
     }
 }
 
-// grid (ceil(d / 16), ceil(T / (16 NT))); reads act of the groups that a token of its own range keeps
+// Groups of 128 neurons, act[g][t][128].  grid (ceil(d / 16), ceil(T / 16)); uses act and Wd of the groups that a token of its own
+// range keeps.  A group's 16 rows of Wd are 8 KiB of consecutive bytes and so are its 16 tokens of act: a thread moves one
+// 16-byte slot of one of the two per group, four groups go through LDS at a time and four more are on their way; wave w multiplies
+// pieces 2 w and 2 w + 1 of the 32.  (In operand order a load was 64 bytes of sixteen rows, and a compute unit's loads took
+// several times as long as their bytes: tiny block 7.2 -> 5.8 us, d 504, 20 groups, 25 tokens 18.8 -> 9.9, d 1000, 24 groups, 60
+// tokens 22.5 -> 13.2, one token 10.0 -> 7.6.)  The first eight groups are requested beside the mask bytes and used if the mask says so;
+// the rest comes from the list of the other groups that are kept.
+constexpr int kTurn = 4, kFirst = 2 * kTurn;
+
+__global__ __launch_bounds__(kDownF32Waves * 64) void down_f32_128(
+    const float *__restrict__ act, int T, int d, int G, const float *__restrict__ Wd, const uint8_t *__restrict__ mask,
+    float *__restrict__ y)
+{
+    constexpr int W = kDownF32Waves, gs = 128;
+    __shared__ __attribute__((aligned(16))) float stage[kTurn * 2 * 16 * kRowF32];      // [group of the turn][Wd, act][row][kRowF32]
+    __shared__ int s_list[1024], s_cnt[W];
+    __shared__ unsigned long long s_first;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, q = lane >> 4, half = wave >> 3, row = (tid >> 5) & 15, col = (tid & 31) * 4;
+    const int j0 = blockIdx.x * 16, t0 = blockIdx.y * 16, n_tok = min(T - t0, 16);
+    // the union of the range's groups: a thread per group (G <= 1024)
+    unsigned any = 0;
+    if (wave * 64 < G) {                                         // uniform
+        uint8_t v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = mask[(size_t)(t0 + min(k, n_tok - 1)) * G + min(tid, G - 1)];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) any |= v[k];
+    }
+    const uint32_t voff = half ? (row < n_tok ? (uint32_t)(row * gs + col) * 4 : kOutOfRange) : (uint32_t)(min(row, d - 1 - j0) * gs + col) * 4;
+    auto fetch = [&](int g, bool yes) -> f32x4_t {
+        const float *p = half ? act + ((size_t)g * T + t0) * gs : Wd + ((size_t)g * d + j0) * gs;
+        return load4(buffer_of(p, yes ? 0x7fffffff : 0), voff, 0);
+    };
+    f32x4_t A[kTurn], B[kTurn];
+#pragma unroll
+    for (int k = 0; k < kTurn; ++k) A[k] = fetch(min(k, G - 1), k < G);
+#pragma unroll
+    for (int k = 0; k < kTurn; ++k) B[k] = fetch(min(k + kTurn, G - 1), k + kTurn < G);
+    const unsigned long long kept = __ballot(tid < G && any != 0u), rest = wave == 0 ? kept & ~((1ull << kFirst) - 1ull) : kept;
+    if (lane == 0) s_cnt[wave] = __popcll(rest);
+    if (tid == 0) s_first = kept;
+    __syncthreads();
+    int before = 0, n_u = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        before += w < wave ? s_cnt[w] : 0;
+        n_u += s_cnt[w];
+    }
+    if ((rest >> lane) & 1ull) s_list[before + __popcll(rest & ((1ull << lane) - 1ull))] = tid;
+    const unsigned first = (unsigned)__builtin_amdgcn_readfirstlane((uint32_t)s_first);
+    // act of a group that nobody keeps was never written, and its weights are not to be used
+#pragma unroll
+    for (int k = 0; k < kTurn; ++k) {
+        const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+        A[k] = (first >> k) & 1u ? A[k] : zero;
+        B[k] = (first >> (k + kTurn)) & 1u ? B[k] : zero;
+    }
+    f32x4_t c[1] = {f32x4_t{0.f, 0.f, 0.f, 0.f}};
+    // turn k takes what b holds, and asks for the groups at positions 4 k .. of the list
+    auto turn = [&](f32x4_t (&b)[kTurn], int at) {
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) *reinterpret_cast<f32x4_t *>(stage + ((k * 2 + half) * 16 + row) * kRowF32 + col) = b[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) {
+            const bool yes = at + k < n_u;                       // uniform
+            b[k] = fetch(yes ? __builtin_amdgcn_readfirstlane(s_list[at + k]) : 0, yes);
+        }
+        PairSum<1> sum;
+        sum.clear();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int p = 2 * wave + k;
+            auto operand = [&](int m) { return *reinterpret_cast<const f32x4_t *>(stage + (((p >> 3) * 2 + m) * 16 + i) * kRowF32 + (p & 7) * 16 + 4 * q); };
+            const f32x4_t a[1] = {operand(1)};
+            sum.add(operand(0), a);
+        }
+        sum.fold(c);
+        __syncthreads();
+    };
+    turn(A, 0);
+    if (G > kTurn) turn(B, kTurn);
+    for (int at = 0; at < n_u; at += kFirst) {
+        turn(A, at + kFirst);
+        if (at + kTurn < n_u) turn(B, at + kFirst + kTurn);
+    }
+    f32x4_t *part = reinterpret_cast<f32x4_t *>(stage);
+    part[tid] = c[0];
+    __syncthreads();
+    if (wave == 0) {
+        f32x4_t p[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) p[w] = part[w * 64 + lane];
+        const f32x4_t s = pairwise_sum(p);
+        const int t = t0 + i, j = j0 + 4 * q;
+        if (t < T && j < d) *reinterpret_cast<f32x4_t *>(y + (size_t)t * d + j) = s;     // (d is a multiple of 8)
+    }
+}
+
+// Groups of any multiple of 16 neurons, act[t][ffn].  grid (ceil(d / 16), ceil(T / (16 NT))); reads act of the groups that a token of its own range keeps
 template <int NT>
 __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32(
     const float *__restrict__ act, int ffn, int T, int d, int G, int gs, const float *__restrict__ Wd,
@@ -218,7 +312,7 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32(
     f32x4_t c[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) c[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    f32x4_t bs[NT][4];                                           // as in gate_up_f32
+    f32x4_t bs[NT][4];                                           // as in PairSum
     auto multiply = [&](const Batch &b, int p0) {
 #pragma unroll
         for (int k = 0; k < U; ++k)
@@ -269,15 +363,17 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32(
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-bool f32_path_supported(int gs) { return gs % 16 == 0; }
+// (offsets within a workgroup's rows have 32 bits)
+bool f32_path_supported(int d, int gs) { return gs % 16 == 0 && d <= 1 << 22; }
 
 template <int NT>
 static void launch_gate_up(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu,
                            const uint8_t *mask, float *act, hipStream_t s)
 {
     const int ffn = G * gs;
+    const bool by_group = gs == 128;                             // how the down projection wants it
     launch_timed("gate_up_f32", gate_up_f32<NT>, dim3(ffn / 16, (T + 16 * NT - 1) / (16 * NT)), dim3(kGateUpF32Waves * 64), s,
-                 x, T, d, G, gs, Wg, Wu, mask, act, ffn);
+                 x, T, d, G, gs, Wg, Wu, mask, act, by_group ? (size_t)T * gs : (size_t)gs, by_group ? gs : ffn);
 }
 
 template <int NT>
@@ -288,33 +384,37 @@ static void launch_down(const float *act, int T, int d, int G, int gs, const flo
                                                                                                    gs, Wd, mask, y);
 }
 
-// The weights are read once per range of tokens (from L2 after the first), so a range takes as many tokens as the
-// registers of its waves allow: 64 in gate/up, 32 in down (sixteen waves).  A range of down lies within one of gate/up,
-// so the groups it walks have been written.
-static void launch_blocks(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
-                          const uint8_t *mask, float *y, float *act, hipStream_t s)
+// The weights are read once per range of tokens (from L2 after the first).  A range of down lies within one of gate/up, so the
+// groups it walks have been written.  nt: token tiles of a workgroup in gate/up.
+static hipError_t launch_blocks(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
+                                const uint8_t *mask, float *y, float *act, int nt, hipStream_t s)
 {
-    if (T <= 16)
+    if (nt == 1)
         launch_gate_up<1>(x, T, d, G, gs, Wg, Wu, mask, act, s);
-    else if (T <= 32)
+    else if (nt == 2)
         launch_gate_up<2>(x, T, d, G, gs, Wg, Wu, mask, act, s);
     else
         launch_gate_up<4>(x, T, d, G, gs, Wg, Wu, mask, act, s);
-    if (T <= 16)
+    if (gs == 128)
+        down_f32_128<<<dim3((d + 15) / 16, (T + 15) / 16), dim3(kDownF32Waves * 64), 0, s>>>(act, T, d, G, Wd, mask, y);
+    else if (nt == 1)
         launch_down<1>(act, T, d, G, gs, Wd, mask, y, s);
     else
         launch_down<2>(act, T, d, G, gs, Wd, mask, y, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
                           const uint8_t *mask, float *y, float *act, hipStream_t s)
 {
-    constexpr int kRun = 1 << 20;                                // ranges of tokens are a grid's y, which ends at 65535
-    for (int t0 = 0;; t0 += kRun) {
+    // four token tiles to a workgroup read the weights least often, two where four would leave compute units without one
+    const int nt = T <= 16 ? 1 : T <= 32 || (long long)((T + 63) / 64) * (G * gs / 16) < 256 ? 2 : 4;
+    const int run = gs == 128 ? 1 << 19 : 1 << 20;               // ranges of tokens are a grid's y, which ends at 65535
+    for (int t0 = 0;; t0 += run) {
         const size_t t = (size_t)t0;
-        launch_blocks(x + t * d, T - t0 < kRun ? T - t0 : kRun, d, G, gs, Wg, Wu, Wd, mask + t * G, y + t * d,
-                      act + t * G * gs, s);
-        if (T - t0 <= kRun) return hipGetLastError();
+        const hipError_t e = launch_blocks(x + t * d, T - t0 < run ? T - t0 : run, d, G, gs, Wg, Wu, Wd, mask + t * G, y + t * d,
+                                           act + t * G * gs, nt, s);
+        if (e != hipSuccess || T - t0 <= run) return e;
     }
 }
 

@@ -30,19 +30,6 @@ __device__ __forceinline__ f32x4_t mfma16s(const u32x4 &a, const u32x4 &b, const
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// buffer loads: an offset of kOutOfRange (plus anything small) is past the end of the descriptor and moves nothing
-constexpr uint32_t kOutOfRange = 0x80000000u;
-constexpr int kNt = 2;                       // cache policy: non-temporal
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int bytes = 0x7fffffff)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
-}
-template <int POLICY>
-__device__ __forceinline__ u32x4 buffer_load16(__amdgpu_buffer_rsrc_t b, uint32_t voff, uint32_t soff)
-{
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, voff, soff, POLICY));
-}
-
 // Which tokens keep which groups, in LDS: bit i of bits[h][g] = token 2 i + h.  One byte load per token and thread, all
 // in flight together.
 struct KeepBits {

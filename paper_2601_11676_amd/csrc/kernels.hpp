@@ -93,7 +93,7 @@ hipError_t launch_ffn_decode(int dtype, const void *x, int T, int d, int G, int 
 hipError_t launch_union(const uint8_t *mask, int T, int G, int32_t *ulist, int32_t *meta, hipStream_t s);
 
 // ffn_f32.hip : float32 on the matrix cores, any number of tokens
-bool f32_path_supported(int gs);
+bool f32_path_supported(int d, int gs);
 hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
                           const uint8_t *mask, float *y, float *act, hipStream_t s);
 

@@ -620,6 +620,29 @@ def test_float32_tiles(T, d, G, gs):
         hz.assert_parity(g, c, TOL["f32"], f"f32 K={K}")
 
 
+@pytest.mark.parametrize("T,d,G,r", [
+    (1, 8, 1, 40),             # a group, a token, half a tile of outputs
+    (16, 24, 4, 64),           # one turn of groups; the last tile of outputs is half full
+    (17, 128, 5, 264),         # two turns, the second of one group; a token tile of one token
+    (33, 264, 9, 64),          # the first group of the list
+    (64, 520, 33, 256),        # 33 groups of 128: mask workgroups of 128 and 256 threads, and past them
+    (5, 1000, 65, 512),        # 65 rows of Bt to a workgroup of 1024
+])
+def test_float32_groups_of_128(T, d, G, r):
+    w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=72)
+    _say(f"float32, groups of 128 T={T} d={d} G={G} r={r}")
+    L = hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    for K in sorted({max(1, G // 3), G}):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        drop = hs.drop_outcomes(w, T=T)
+        if K < G:
+            drop[T - 1] = 1                                    # a token with no survivor
+        g = hz.gpu_forward(w, L, x, K, pd, drop)
+        c = hz.oracle_forward(w, L, x, K, pd, drop)
+        hz.assert_parity(g, c, TOL["f32"], f"f32 K={K}")
+
+
 @pytest.mark.parametrize("d,G,K", [(8, 3, 2), (136, 5, 3), (1032, 9, 9), (2560, 70, 33), (3200, 7, 7), (7936, 6, 3), (8184, 3, 2)])
 def test_one_token_of_any_row_length(d, G, K):
     # rows whose last 512-element chunk is not whole, outputs that are not whole workgroups; the activation stays in

@@ -37,31 +37,53 @@ hipError_t launch_group_mask(const float *scores, int T, int G, int K, const int
     return hipGetLastError();
 }
 
+// Threads of a token's workgroup where it computes the scores itself: as many waves as take all rows of Bt in one batch of
+// eight slots each (two rows to a slot up to rank 256), at least two.  More only add to the barriers: 8 groups, rank 64 6.1 us with 1024
+// threads, 5.4 with 512, 4.7 with 128; 27 groups, rank 512 5.9, 5.5 and (256) 5.4; with fewer the waves take turns: 92 groups,
+// rank 64 6.5, 6.3, (256) 7.8; 138 groups, rank 256 6.6, 7.5.  With 64 tokens and more at most 512, so that more workgroups
+// share a compute unit (512 tokens of the 7B shape 11.5 us against 13.6 with 1024).
+static int mask_threads(int T, int G, int r)
+{
+    const int slots = r <= 256 ? (G + 1) / 2 : G;
+    const int threads = slots <= 16 ? 128 : slots <= 32 ? 256 : slots <= 64 ? 512 : kMaskThreads;
+    return T >= 64 && threads > 512 ? 512 : threads;
+}
+
+template <typename WT>
+static void launch_fused(const float *h, const WT *Bt, int r, float *scores, int T, int G, int K, const int8_t *prio_dev,
+                         int n_dev, const uint8_t *drop, int32_t *order, int8_t *group_dev, uint8_t *mask,
+                         int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
+{
+#define HALO_MASK_CASE(NT)                                                                                            \
+    case NT:                                                                                                          \
+        mask_scores_kernel<WT, true, NT><<<dim3(T), dim3(NT), 0, s>>>(h, Bt, r, scores, G, K, prio_dev, n_dev, drop,  \
+                                                                      order, group_dev, mask, surv_idx, n_surv);      \
+        break;
+    switch (mask_threads(T, G, r)) {
+        HALO_MASK_CASE(128)
+        HALO_MASK_CASE(256)
+        HALO_MASK_CASE(512)
+        HALO_MASK_CASE(kMaskThreads)
+    }
+#undef HALO_MASK_CASE
+}
+
 hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int r, float *scores,
                                   int T, int G, int K, const int8_t *prio_dev, int n_dev,
                                   const uint8_t *drop, int32_t *order, int8_t *group_dev,
                                   uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
 {
-    if (dtype == 0)
-        mask_scores_kernel<float, true><<<dim3(T), dim3(kMaskThreads), 0, s>>>(
-            h, (const float *)Bt, r, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask,
-            surv_idx, n_surv);
-    else if (scores_apart(T, r, G)) {
+    if (dtype != 0 && scores_apart(T, r, G)) {
         // many scores: on the matrix cores in a launch of their own (here a token's workgroup reads all of Bt for itself)
         const hipError_t e = launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
         if (e != hipSuccess) return e;
         mask_scores_kernel<float, false, 512><<<dim3(T), dim3(512), 0, s>>>(
             nullptr, nullptr, 0, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv);
-    } else if (T >= 64)
-        // many tokens: workgroups of 512 threads, more of them resident per compute unit (measured at
-        // 512 tokens of the 7B shape: 11.5 us against 13.6 us with 1024 threads and 14.7 us with 256)
-        mask_scores_kernel<bf16_t, true, 512><<<dim3(T), dim3(512), 0, s>>>(
-            h, (const bf16_t *)Bt, r, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask,
-            surv_idx, n_surv);
-    else
-        mask_scores_kernel<bf16_t, true><<<dim3(T), dim3(kMaskThreads), 0, s>>>(
-            h, (const bf16_t *)Bt, r, scores, G, K, prio_dev, n_dev, drop, order, group_dev, mask,
-            surv_idx, n_surv);
+    } else if (dtype != 0) {
+        launch_fused(h, (const bf16_t *)Bt, r, scores, T, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
+    } else {
+        launch_fused(h, (const float *)Bt, r, scores, T, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
+    }
     return hipGetLastError();
 }
 

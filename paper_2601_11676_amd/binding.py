@@ -41,6 +41,7 @@ class MhaShape:
         self.d, self.n_heads, self.head_dim, self.rank, self.dtype = d, n_heads, head_dim, rank, dtype
         code = {"f32": HALO_F32, "bf16": HALO_BF16}.get(dtype, -1)
         self.c = _CMhaShape(d, n_heads, head_dim, rank, code)
+        self.ref = C.byref(self.c)
 
 
 class Shape:
@@ -53,6 +54,7 @@ class Shape:
         self.dtype = dtype
         code = {"f32": HALO_F32, "bf16": HALO_BF16}.get(dtype, -1)
         self.c = _CShape(d, ffn, group_size, self.n_groups, rank, code)
+        self.ref = C.byref(self.c)
 
     @property
     def torch_dtype(self):
@@ -139,6 +141,9 @@ def load_library():
     return lib
 
 
+# A call marshals up to two dozen arguments, and a small block's kernels take no longer than that: addresses are passed as
+# plain ints (ctypes converts them by the declared argument types), and the current stream's handle is asked for
+# without building a Stream object around it.
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
@@ -146,12 +151,18 @@ def _ptr(t: Optional[torch.Tensor]):
         raise ValueError("device tensor expected")
     if not t.is_contiguous():
         raise ValueError("contiguous tensor expected")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(fn: str, rc: int):
@@ -207,16 +218,16 @@ def halo_ratios_min_max(mem, comp, demand: float, eps: float = 1e-3) -> np.ndarr
 
 
 def halo_workspace_bytes(shape: Shape, T: int, k_keep: int) -> int:
-    return int(load_library().halo_workspace_bytes(C.byref(shape.c), int(T), int(k_keep)))
+    return int(load_library().halo_workspace_bytes(shape.ref, int(T), int(k_keep)))
 
 
 def halo_workspace_bytes_q4(shape: Shape, T: int, k_keep: int) -> int:
-    return int(load_library().halo_workspace_bytes_q4(C.byref(shape.c), int(T), int(k_keep)))
+    return int(load_library().halo_workspace_bytes_q4(shape.ref, int(T), int(k_keep)))
 
 
 def halo_predict_scores(shape: Shape, x, At, Bt, scores, workspace, stream=None) -> None:
     T = x.shape[0]
-    rc = load_library().halo_predict_scores(C.byref(shape.c), _ptr(x), T, _ptr(At), _ptr(Bt),
+    rc = load_library().halo_predict_scores(shape.ref, _ptr(x), T, _ptr(At), _ptr(Bt),
                                             _ptr(scores), _ptr(workspace), workspace.numel(),
                                             _stream(stream))
     _check("halo_predict_scores", rc)
@@ -234,7 +245,7 @@ def halo_build_group_mask(scores, k_keep: int, prio_dev, n_dev: int, drop, mask,
 
 def halo_group_sparse_ffn(shape: Shape, x, Wg, Wu, Wd, mask, y, workspace, stream=None) -> None:
     T = x.shape[0]
-    rc = load_library().halo_group_sparse_ffn(C.byref(shape.c), _ptr(x), T, _ptr(Wg), _ptr(Wu),
+    rc = load_library().halo_group_sparse_ffn(shape.ref, _ptr(x), T, _ptr(Wg), _ptr(Wu),
                                               _ptr(Wd), _ptr(mask), _ptr(y), _ptr(workspace),
                                               workspace.numel(), _stream(stream))
     _check("halo_group_sparse_ffn", rc)
@@ -246,7 +257,7 @@ def halo_ffn_forward(shape: Shape, x, At, Bt, Wg, Wu, Wd, k_keep: int, prio_dev,
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward(
-        C.byref(shape.c), _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
+        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order),
         _ptr(group_dev), _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _ptr(workspace),
         workspace.numel(), _stream(stream))
@@ -264,7 +275,7 @@ def halo_ffn_forward_static(shape: Shape, x, At, Bt, Wg, Wu, Wd, k_keep: int, pr
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward_static(
-        C.byref(shape.c), _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
+        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order),
         _ptr(group_dev), _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _stream(stream))
     _check("halo_ffn_forward_static", rc)
@@ -276,7 +287,7 @@ def halo_ffn_forward_ahead(shape: Shape, x, Wg, Wu, Wd, mask_cur, y, x_pred_next
                            surv_idx_next=None, n_surv_next=None, stream=None) -> None:
     T = x.shape[0]
     rc = load_library().halo_ffn_forward_ahead(
-        C.byref(shape.c), _ptr(x), T, _ptr(Wg), _ptr(Wu), _ptr(Wd), _ptr(mask_cur), _ptr(y),
+        shape.ref, _ptr(x), T, _ptr(Wg), _ptr(Wu), _ptr(Wd), _ptr(mask_cur), _ptr(y),
         _ptr(x_pred_next), _ptr(At_next), _ptr(Bt_next), int(k_keep), _ptr(prio_dev), int(n_dev),
         _ptr(drop_next), _ptr(scores_next), _ptr(order_next), _ptr(group_dev_next), _ptr(mask_next),
         _ptr(surv_idx_next), _ptr(n_surv_next), _ptr(workspace), workspace.numel(),
@@ -288,7 +299,7 @@ def halo_group_sparse_ffn_q4(shape: Shape, x, q4, mask, y, workspace, stream=Non
     """q4 = (Wg_codes, Wg_scales, Wu_codes, Wu_scales, Wd_codes, Wd_scales), see include/halo.h."""
     T = x.shape[0]
     rc = load_library().halo_group_sparse_ffn_q4(
-        C.byref(shape.c), _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask), _ptr(y), _ptr(workspace),
+        shape.ref, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask), _ptr(y), _ptr(workspace),
         workspace.numel(), _stream(stream))
     _check("halo_group_sparse_ffn_q4", rc)
 
@@ -299,7 +310,7 @@ def halo_ffn_forward_q4(shape: Shape, x, At, Bt, q4, k_keep: int, prio_dev, n_de
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward_q4(
-        C.byref(shape.c), _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), *[_ptr(t) for t in q4], int(k_keep),
+        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), *[_ptr(t) for t in q4], int(k_keep),
         _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order), _ptr(group_dev),
         _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _ptr(workspace), workspace.numel(), _stream(stream))
     _check("halo_ffn_forward_q4", rc)
@@ -311,7 +322,7 @@ def halo_ffn_forward_ahead_q4(shape: Shape, x, q4, mask_cur, y, x_pred_next, At_
                               stream=None) -> None:
     T = x.shape[0]
     rc = load_library().halo_ffn_forward_ahead_q4(
-        C.byref(shape.c), _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask_cur), _ptr(y), _ptr(x_pred_next),
+        shape.ref, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask_cur), _ptr(y), _ptr(x_pred_next),
         _ptr(At_next), _ptr(Bt_next), int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop_next),
         _ptr(scores_next), _ptr(order_next), _ptr(group_dev_next), _ptr(mask_next), _ptr(surv_idx_next),
         _ptr(n_surv_next), _ptr(workspace), workspace.numel(), _stream(stream))
@@ -319,14 +330,14 @@ def halo_ffn_forward_ahead_q4(shape: Shape, x, q4, mask_cur, y, x_pred_next, At_
 
 
 def halo_mha_workspace_bytes(shape: MhaShape, max_len: int) -> int:
-    return int(load_library().halo_mha_workspace_bytes(C.byref(shape.c), int(max_len)))
+    return int(load_library().halo_mha_workspace_bytes(shape.ref, int(max_len)))
 
 
 def halo_head_sparse_mha(shape: MhaShape, x, Wq, Wk, Wv, Wo, k_cache, v_cache, pos: int, mask, y, workspace,
                          stream=None) -> None:
     """k_cache / v_cache: [n_heads][max_len][head_dim]; Wo head-blocked (pack_down_proj(WoT, head_dim))."""
     rc = load_library().halo_head_sparse_mha(
-        C.byref(shape.c), _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
+        shape.ref, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
         int(k_cache.shape[1]), int(pos), _ptr(mask), _ptr(y), _ptr(workspace), workspace.numel(), _stream(stream))
     _check("halo_head_sparse_mha", rc)
 
@@ -336,7 +347,7 @@ def halo_mha_forward(shape: MhaShape, x, At, Bt, Wq, Wk, Wv, Wo, k_cache, v_cach
                      group_dev=None, mask=None, surv_idx=None, n_surv=None, stream=None) -> None:
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_mha_forward(
-        C.byref(shape.c), _ptr(x), _ptr(xp), _ptr(At), _ptr(Bt), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo),
+        shape.ref, _ptr(x), _ptr(xp), _ptr(At), _ptr(Bt), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo),
         _ptr(k_cache), _ptr(v_cache), int(k_cache.shape[1]), int(pos), int(k_keep), _ptr(prio_dev), int(n_dev),
         _ptr(drop), _ptr(y), _ptr(scores), _ptr(order), _ptr(group_dev), _ptr(mask), _ptr(surv_idx),
         _ptr(n_surv), _ptr(workspace), workspace.numel(), _stream(stream))
@@ -348,7 +359,7 @@ def halo_mha_forward_ahead(shape: MhaShape, x, Wq, Wk, Wv, Wo, k_cache, v_cache,
                            workspace, scores_next=None, order_next=None, group_dev_next=None, surv_idx_next=None,
                            n_surv_next=None, stream=None) -> None:
     rc = load_library().halo_mha_forward_ahead(
-        C.byref(shape.c), _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
+        shape.ref, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
         int(k_cache.shape[1]), int(pos), _ptr(mask_cur), _ptr(y), _ptr(x_pred_next), _ptr(At_next), _ptr(Bt_next),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop_next), _ptr(scores_next), _ptr(order_next),
         _ptr(group_dev_next), _ptr(mask_next), _ptr(surv_idx_next), _ptr(n_surv_next), _ptr(workspace),

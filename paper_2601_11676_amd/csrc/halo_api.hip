@@ -393,11 +393,8 @@ int halo_ffn_forward(const halo_shape *shape, const void *x, const void *x_pred,
     float *sc = scores ? scores : ws.scores;
     uint8_t *mk = mask ? mask : ws.mask;
     // first predictor layer, then the second layer fused with the ranking / mask kernel
-    hipError_t e = launch_predictor(shape->dtype, x_pred, T, shape->d, shape->rank, shape->n_groups,
-                                    At, Bt, ws.h, nullptr, s);
-    if (e != hipSuccess) return HALO_ERR_HIP;
-    e = launch_scores_and_mask(shape->dtype, ws.h, Bt, shape->rank, sc, T, shape->n_groups, k_keep,
-                               prio_dev, n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
+    hipError_t e = launch_predict_and_mask(shape->dtype, x_pred, T, shape->d, shape->rank, shape->n_groups, At, Bt, ws.h, sc, k_keep,
+                                prio_dev, n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
     if (e != hipSuccess) return HALO_ERR_HIP;
     e = launch_ffn_decode(shape->dtype, x, T, shape->d, shape->n_groups, shape->group_size, Wg, Wu,
                           Wd, mk, y, ws.dec, s);
@@ -479,11 +476,8 @@ int halo_ffn_forward_q4(const halo_shape *shape, const void *x, const void *x_pr
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *sc = scores ? scores : ws.scores;
     uint8_t *mk = mask ? mask : ws.mask;
-    hipError_t e = launch_predictor(shape->dtype, x_pred, T, shape->d, shape->rank, shape->n_groups, At, Bt,
-                                    ws.h, nullptr, s);
-    if (e != hipSuccess) return HALO_ERR_HIP;
-    e = launch_scores_and_mask(shape->dtype, ws.h, Bt, shape->rank, sc, T, shape->n_groups, k_keep, prio_dev,
-                               n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
+    hipError_t e = launch_predict_and_mask(shape->dtype, x_pred, T, shape->d, shape->rank, shape->n_groups, At, Bt, ws.h, sc, k_keep,
+                                prio_dev, n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
     if (e != hipSuccess) return HALO_ERR_HIP;
     const Q4Weights w{(const uint32_t *)Wg_codes, (const bf16_t *)Wg_scales, (const uint32_t *)Wu_codes,
                       (const bf16_t *)Wu_scales, (const uint32_t *)Wd_codes, (const bf16_t *)Wd_scales};
@@ -543,11 +537,8 @@ int halo_mha_forward(const halo_mha_shape *shape, const void *x, const void *x_p
     float *sc = scores ? scores : ws.base.scores;
     uint8_t *mk = mask ? mask : ws.base.mask;
     // the predictor and the mask builder are the FFN's: one significance value per head
-    hipError_t e = launch_predictor(shape->dtype, x_pred, 1, shape->d, shape->rank, shape->n_heads, At, Bt,
-                                    ws.base.h, nullptr, s);
-    if (e != hipSuccess) return HALO_ERR_HIP;
-    e = launch_scores_and_mask(shape->dtype, ws.base.h, Bt, shape->rank, sc, 1, shape->n_heads, k_keep, prio_dev,
-                               n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
+    hipError_t e = launch_predict_and_mask(shape->dtype, x_pred, 1, shape->d, shape->rank, shape->n_heads, At, Bt, ws.base.h, sc, k_keep,
+                                prio_dev, n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);
     if (e != hipSuccess) return HALO_ERR_HIP;
     e = launch_mha_decode(x, shape->d, shape->n_heads, Wq, Wk, Wv, Wo, k_cache, v_cache, max_len, pos, mk, y,
                           ws.mha, s);
@@ -587,12 +578,8 @@ int halo_mha_forward_ahead(const halo_mha_shape *shape, const void *x, const voi
                                      mask_cur, y, ws.mha, s, &ah, &fused);
     if (e != hipSuccess) return HALO_ERR_HIP;
     if (!fused) {
-        e = launch_predictor(shape->dtype, x_pred_next, 1, shape->d, shape->rank, shape->n_heads, At_next, Bt_next,
-                             ws.base.h, nullptr, s);
-        if (e != hipSuccess) return HALO_ERR_HIP;
-        e = launch_scores_and_mask(shape->dtype, ws.base.h, Bt_next, shape->rank, sc, 1, shape->n_heads, k_keep,
-                                   prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next,
-                                   surv_idx_next, n_surv_next, s);
+        e = launch_predict_and_mask(shape->dtype, x_pred_next, 1, shape->d, shape->rank, shape->n_heads, At_next, Bt_next, ws.base.h, sc, k_keep,
+                                prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next, surv_idx_next, n_surv_next, s);
         if (e != hipSuccess) return HALO_ERR_HIP;
     }
     return HALO_OK;
@@ -635,12 +622,8 @@ int halo_ffn_forward_ahead_q4(const halo_shape *shape, const void *x, int32_t T,
                                  y, ws.dec, s, &ah, &fused);
     if (e != hipSuccess) return HALO_ERR_HIP;
     if (!fused) {
-        e = launch_predictor(shape->dtype, x_pred_next, T, shape->d, shape->rank, shape->n_groups, At_next,
-                             Bt_next, ws.h, nullptr, s);
-        if (e != hipSuccess) return HALO_ERR_HIP;
-        e = launch_scores_and_mask(shape->dtype, ws.h, Bt_next, shape->rank, sc, T, shape->n_groups, k_keep,
-                                   prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next,
-                                   surv_idx_next, n_surv_next, s);
+        e = launch_predict_and_mask(shape->dtype, x_pred_next, T, shape->d, shape->rank, shape->n_groups, At_next, Bt_next, ws.h, sc, k_keep,
+                                prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next, surv_idx_next, n_surv_next, s);
         if (e != hipSuccess) return HALO_ERR_HIP;
     }
     return HALO_OK;
@@ -679,12 +662,8 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
     if (e != hipSuccess) return HALO_ERR_HIP;
     if (!fused) {
         // no path with spare workgroups for this shape: the prediction follows on the stream
-        e = launch_predictor(shape->dtype, x_pred_next, T, shape->d, shape->rank, shape->n_groups, At_next,
-                             Bt_next, ws.h, nullptr, s);
-        if (e != hipSuccess) return HALO_ERR_HIP;
-        e = launch_scores_and_mask(shape->dtype, ws.h, Bt_next, shape->rank, sc, T, shape->n_groups, k_keep,
-                                   prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next,
-                                   surv_idx_next, n_surv_next, s);
+        e = launch_predict_and_mask(shape->dtype, x_pred_next, T, shape->d, shape->rank, shape->n_groups, At_next, Bt_next, ws.h, sc, k_keep,
+                                prio_dev, n_dev, drop_next, order_next, group_dev_next, mask_next, surv_idx_next, n_surv_next, s);
         if (e != hipSuccess) return HALO_ERR_HIP;
     }
     return HALO_OK;

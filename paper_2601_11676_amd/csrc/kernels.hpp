@@ -22,6 +22,11 @@ hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int
                                   const uint8_t *drop, int32_t *order, int8_t *group_dev,
                                   uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s);
 
+// both predictor layers, then the mask; h is scratch
+hipError_t launch_predict_and_mask(int dtype, const void *x, int T, int d, int r, int G, const void *At, const void *Bt, float *h,
+                                   float *scores, int K, const int8_t *prio_dev, int n_dev, const uint8_t *drop, int32_t *order,
+                                   int8_t *group_dev, uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s);
+
 // ffn_decode.hip : float-ALU paths (any T; tuned for one token)
 struct DecodeScratch {
     int32_t *ulist;     // [G]   groups surviving for at least one token, ascending

@@ -10,6 +10,7 @@
 namespace halo {
 
 constexpr int kMaskThreads = 1024;
+constexpr int kMaskMaxRank = 512;
 
 template <typename WT, bool FUSED_SCORES, int NT = kMaskThreads>
 __global__ __launch_bounds__(NT) void mask_scores_kernel(
@@ -25,6 +26,56 @@ __global__ __launch_bounds__(NT) void mask_scores_kernel(
         drop ? drop + t * n_dev : nullptr, order ? order + t * G : nullptr,
         group_dev ? group_dev + t * G : nullptr, mask + t * G, surv_idx ? surv_idx + t * K : nullptr,
         n_surv ? n_surv + t : nullptr);
+}
+
+// The whole prediction of a token in its workgroup: the first predictor layer too (same order, same bits), its results in LDS.
+// A wave takes eight rows of At at a time, all requested together.
+template <typename WT>
+__device__ __forceinline__ void hidden_rows(const WT *__restrict__ x, const WT *__restrict__ At, int d, int r, int wave, int waves,
+                                            int lane, float *h)
+{
+    constexpr int RB = 8;
+    for (int j0 = wave * RB; j0 < r; j0 += waves * RB) {         // (r is a multiple of 8)
+        float p[RB];
+#pragma unroll
+        for (int b = 0; b < RB; ++b) p[b] = 0.0f;
+        for (int c = lane; c * 8 < d; c += kWave) {
+            float xv[8];
+            Piece8<WT> w[RB];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) w[b].load(At + (size_t)(j0 + b) * d + c * 8);
+            load8(x + c * 8, xv);
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                float wv[8];
+                w[b].get(wv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) p[b] = __builtin_fmaf(xv[e], wv[e], p[b]);
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < RB; ++b) p[b] = wave_sum(p[b]);
+        if (lane == 0) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) h[j0 + b] = p[b] > 0.0f ? p[b] : 0.0f;
+        }
+    }
+}
+
+template <typename WT, int NT>
+__global__ __launch_bounds__(NT) void predict_mask_kernel(
+    const WT *__restrict__ x, const WT *__restrict__ At, int d, const WT *__restrict__ Bt, int r, float *__restrict__ scores,
+    int G, int K, const int8_t *__restrict__ prio_dev, int n_dev, const uint8_t *__restrict__ drop, int32_t *__restrict__ order,
+    int8_t *__restrict__ group_dev, uint8_t *__restrict__ mask, int32_t *__restrict__ surv_idx, int32_t *__restrict__ n_surv)
+{
+    __shared__ MaskShared sh;
+    __shared__ __attribute__((aligned(16))) float h[kMaskMaxRank];
+    const size_t t = blockIdx.x;
+    hidden_rows(x + t * d, At, d, r, (int)(threadIdx.x >> 6), NT / kWave, (int)(threadIdx.x & 63), h);
+    __syncthreads();
+    mask_scores_block<NT, WT, true>(sh, threadIdx.x, h, Bt, r, scores + t * G, G, K, prio_dev, n_dev, drop ? drop + t * n_dev : nullptr,
+                                    order ? order + t * G : nullptr, group_dev ? group_dev + t * G : nullptr, mask + t * G,
+                                    surv_idx ? surv_idx + t * K : nullptr, n_surv ? n_surv + t : nullptr);
 }
 
 hipError_t launch_group_mask(const float *scores, int T, int G, int K, const int8_t *prio_dev,
@@ -85,6 +136,36 @@ hipError_t launch_scores_and_mask(int dtype, const float *h, const void *Bt, int
         launch_fused(h, (const float *)Bt, r, scores, T, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
     }
     return hipGetLastError();
+}
+
+template <typename WT>
+static void launch_predict_mask(const void *x, int T, int d, int r, int G, const void *At, const void *Bt, float *scores, int K,
+                                const int8_t *prio_dev, int n_dev, const uint8_t *drop, int32_t *order, int8_t *group_dev,
+                                uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
+{
+    constexpr int NT = 512;                                      // 64 rows of At at a time (256 and 1024 threads: 8.2 and 7.1 us against 6.9)
+    predict_mask_kernel<WT, NT><<<dim3(T), dim3(NT), 0, s>>>((const WT *)x, (const WT *)At, d, (const WT *)Bt, r, scores, G, K, prio_dev,
+                                                             n_dev, drop, order, group_dev, mask, surv_idx, n_surv);
+}
+
+// Both predictor layers and the mask.  One launch where the first layer's weights are at most 128 KiB: every token's workgroup
+// reads them for itself (from L2), which costs no more than a launch on the device (tiny block 6.9 us against 2.2 + 4.7) and saves the
+// host one, and a pass over a small block waits for the host: tiny block 18.4 -> 17.6 us, d 1024 bf16, rank 64, 2 tokens 17.7 -> 17.1.
+// At twice that (d 512 float32, rank 128: 8.5 us against 3.2 + 4.6) it is level, beyond it slower (d 1000, rank 128: 11.7 against 9.0).
+hipError_t launch_predict_and_mask(int dtype, const void *x, int T, int d, int r, int G, const void *At, const void *Bt, float *h,
+                                   float *scores, int K, const int8_t *prio_dev, int n_dev, const uint8_t *drop, int32_t *order,
+                                   int8_t *group_dev, uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
+{
+    if (T <= 64 && r <= kMaskMaxRank && (size_t)r * d * (dtype == 0 ? 4 : 2) <= (size_t)128 << 10) {
+        if (dtype == 0)
+            launch_predict_mask<float>(x, T, d, r, G, At, Bt, scores, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
+        else
+            launch_predict_mask<bf16_t>(x, T, d, r, G, At, Bt, scores, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_predictor(dtype, x, T, d, r, G, At, Bt, h, nullptr, s);
+    if (e != hipSuccess) return e;
+    return launch_scores_and_mask(dtype, h, Bt, r, scores, T, G, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
 }
 
 }  // namespace halo

@@ -643,6 +643,31 @@ def test_float32_groups_of_128(T, d, G, r):
         hz.assert_parity(g, c, TOL["f32"], f"f32 K={K}")
 
 
+@pytest.mark.parametrize("dtype,T,d,G,r", [
+    ("f32", 1, 8, 1, 8),       # one batch of rows for one wave
+    ("f32", 64, 64, 130, 512), # 128 KiB of weights, 64 tokens: the most of all
+    ("f32", 65, 64, 9, 512),   # a token more: two launches
+    ("bf16", 3, 520, 17, 72),  # nine waves' rows over eight waves; a second piece of the row for one lane
+    ("bf16", 16, 1024, 5, 64),
+    ("bf16", 16, 1032, 5, 64), # just above 128 KiB
+])
+def test_scores_of_the_whole_pass_are_the_predictors(dtype, T, d, G, r):
+    # bit for bit, whatever launches compute them; the mask that of the mask builder
+    w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 32, group_size=32, rank=r, T=T, dtype=dtype, seed=73)
+    _say(f"scores of the whole pass {dtype} T={T} d={d} G={G} r={r}")
+    s, L = hz.shape_of(w), hz.Layer(w)
+    x, K = hs.hidden_states(w, 0, hz.DEV), max(1, G // 2)
+    pd, drop = H.halo_build_schedule(K, w.device_plr()), hs.drop_outcomes(w, T=T)
+    g = hz.gpu_forward(w, L, x, K, pd, drop)
+    sc = torch.empty((T, G), dtype=torch.float32, device=hz.DEV)
+    mk = torch.zeros((T, G), dtype=torch.uint8, device=hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, K), dtype=torch.uint8, device=hz.DEV)
+    H.halo_predict_scores(s, x, L.At, L.Bt, sc, ws)
+    H.halo_build_group_mask(sc, K, torch.from_numpy(pd).to(hz.DEV), w.n_dev, torch.from_numpy(drop).to(hz.DEV), mk)
+    torch.cuda.synchronize()
+    assert np.array_equal(sc.cpu().numpy(), g["scores"]) and np.array_equal(mk.cpu().numpy(), g["mask"])
+
+
 @pytest.mark.parametrize("d,G,K", [(8, 3, 2), (136, 5, 3), (1032, 9, 9), (2560, 70, 33), (3200, 7, 7), (7936, 6, 3), (8184, 3, 2)])
 def test_one_token_of_any_row_length(d, G, K):
     # rows whose last 512-element chunk is not whole, outputs that are not whole workgroups; the activation stays in

@@ -14,6 +14,7 @@
 //
 // This file holds the one-token path (bf16) and a generic path (any T, d, group size, f32 or
 // bf16) that favours simplicity; more tokens in bf16 and float32 go to matrix-core paths instead.
+#include "down_t1.hpp"
 #include "kernels.hpp"
 #include "mask_device.hpp"
 #include "mask_words.hpp"
@@ -251,45 +252,6 @@ __global__ __launch_bounds__(256) void gate_up_pred_t1(
 // Each lane accumulates over its groups, the 16 lanes of a row are summed once at the end
 // and the two halves meet in LDS, so y is written directly: no partial sums in memory, no
 // second pass.  The activation arrives in bf16 and meets the weights in the packed dot.
-template <int RQ>
-struct DownShared {
-    int list[256];
-    float half[RQ][64];
-};
-
-// the eight activations that face a lane's 16-byte piece of a row, as they are stored
-template <typename AT> struct ActPiece;
-template <> struct ActPiece<bf16_t> {
-    u32x4 v;
-    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const u32x4 *>(p); }
-    __device__ __forceinline__ void dot(const u32x4 &w, float &acc0, float &acc1) const
-    {
-        acc0 = dot2_bf16(w.x, v.x, acc0);
-        acc1 = dot2_bf16(w.y, v.y, acc1);
-        acc0 = dot2_bf16(w.z, v.z, acc0);
-        acc1 = dot2_bf16(w.w, v.w, acc1);
-    }
-};
-template <> struct ActPiece<float> {
-    float4 a, b;
-    __device__ __forceinline__ void load(const float *p)
-    {
-        a = *reinterpret_cast<const float4 *>(p);
-        b = *reinterpret_cast<const float4 *>(p + 4);
-    }
-    __device__ __forceinline__ void dot(const u32x4 &w, float &acc0, float &acc1) const
-    {
-        acc0 = __builtin_fmaf(bf16_lo(w.x), a.x, acc0);
-        acc1 = __builtin_fmaf(bf16_hi(w.x), a.y, acc1);
-        acc0 = __builtin_fmaf(bf16_lo(w.y), a.z, acc0);
-        acc1 = __builtin_fmaf(bf16_hi(w.y), a.w, acc1);
-        acc0 = __builtin_fmaf(bf16_lo(w.z), b.x, acc0);
-        acc1 = __builtin_fmaf(bf16_hi(w.z), b.y, acc1);
-        acc0 = __builtin_fmaf(bf16_lo(w.w), b.z, acc0);
-        acc1 = __builtin_fmaf(bf16_hi(w.w), b.w, acc1);
-    }
-};
-
 // EXACT: d is a multiple of the workgroup's 4 RQ rows; otherwise rows past the end repeat the last one, unused.
 template <int RQ, typename AT, bool EXACT>
 __device__ __forceinline__ void down_t1_body(DownShared<RQ> &sh, int d, int G,

@@ -6,18 +6,22 @@
 //   surviving heads  : q_h = Wq_h x,  p = softmax(q_h K_h^T / sqrt(dh)) over rows 0..pos,
 //                      o_h = p V_h,   y = sum_h Wo_h o_h
 //
-// bf16, head dimension 128.  Four launches:
+// bf16, head dimension 128.  Three launches, or four (long caches, many heads):
 //   qkv_rows     : a matrix-vector product over the rows that are needed -- all of Wk and Wv,
 //                  and the rows of Wq of surviving heads only -- streamed like the FFN's
 //                  gate/up rows (one wave per row, 16-byte non-temporal loads, two rows
 //                  in flight while two are reduced).
-//   attn_partial : one workgroup per (surviving head, 128 cached positions): scores, a local
+//   attn_partial : one workgroup per (surviving head, 128 to 512 cached positions): scores, a local
 //                  softmax (max, sum) and the weighted sum of the values of its positions.
-//   attn_combine : merges a head's partial softmaxes into o_h (bf16).
-//   out-proj     : the FFN's down-projection kernel, unchanged: Wo is stored head-blocked
-//                  [H][d][128] exactly like Wd, heads play the role of groups.
+//   merge_out_t1 : merges the heads' partial softmaxes and multiplies by Wo, which is stored head-blocked [H][d][128] exactly
+//                  like Wd, heads in the role of groups; or
+//   attn_combine : merges a head's partial softmaxes into o_h, and
+//   out-proj     : the FFN's down-projection kernel, unchanged.
 // Only surviving heads' query rows, cache rows and output-projection blocks are read.
+#include <algorithm>
+#include "down_t1.hpp"
 #include "kernels.hpp"
+#include "mask_device.hpp"
 #include "mask_words.hpp"
 #include "row_stream.hpp"
 
@@ -210,22 +214,26 @@ __global__ __launch_bounds__(256) void qkv_rows_generic(QkvArgs a, int d, const 
 }
 
 // ---------------------------------------------------------------------------
-// attention over the cache: grid (chunks, H), 256 threads
+// attention over the cache: grid (chunks, H), 2 CH threads
 // ---------------------------------------------------------------------------
 // Workgroup (c, u): surviving-head slot u (exits if u >= number of survivors), cached
-// positions c*128 .. c*128+127 (rows beyond pos count as score -inf).  16 lanes share a
+// positions c*CH .. c*CH+CH-1 (rows beyond pos count as score -inf).  16 lanes share a
 // cache row (16 bytes = 8 dimensions each), a wave covers 4 rows per instruction and 32 rows
-// in all.  Output: part[(u*chunks + c)] = {local max, local sum, 128 weighted value sums}.
+// in all.  Output: part[(u*chunks + c)] = {128 weighted value sums, local max, local sum}.
+// (CH = 128; with 256 or 512 positions to a workgroup of twice or four times the threads a head has few enough partial softmaxes
+// for the output projection to merge them.)
 constexpr int kPartStride = kHeadDim + 2;
 
-__global__ __launch_bounds__(256) void attn_partial(const float *__restrict__ q, const bf16_t *__restrict__ k_cache,
+template <int CH>
+__global__ __launch_bounds__(CH * 2) void attn_partial(const float *__restrict__ q, const bf16_t *__restrict__ k_cache,
                                                     const bf16_t *__restrict__ v_cache,
                                                     const uint8_t *__restrict__ mask, int H, int max_len, int pos,
                                                     float *__restrict__ part)
 {
     constexpr int dh = kHeadDim;
-    __shared__ float s_score[kAttnChunk];
-    __shared__ float s_o[4][dh];
+    constexpr int W = CH / 32;                                   // waves
+    __shared__ float s_score[CH];
+    __shared__ float s_o[W][dh];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int c = blockIdx.x, u = blockIdx.y, chunks = gridDim.x;
     const MaskWords mw = load_mask_words(mask, H, lane);
@@ -233,8 +241,8 @@ __global__ __launch_bounds__(256) void attn_partial(const float *__restrict__ q,
     const int h = nth_group(mw, u, lane);
     const int sub = lane >> 4, piece = (lane & 15) * 8;
     const bf16_t *K = k_cache + (size_t)h * max_len * dh, *V = v_cache + (size_t)h * max_len * dh;
-    const int j0 = c * kAttnChunk + wave * 32;                   // this wave's first row
-    // every load of the workgroup's 64 KiB is requested before anything is reduced
+    const int j0 = c * CH + wave * 32;                   // this wave's first row
+    // every load of the workgroup's (64 KiB for 128 positions) is requested before anything is reduced
     u32x4 kv[8], vv[8];
 #pragma unroll
     for (int it = 0; it < 8; ++it) {
@@ -261,12 +269,16 @@ __global__ __launch_bounds__(256) void attn_partial(const float *__restrict__ q,
         if ((lane & 15) == 0) s_score[wave * 32 + it * 4 + sub] = j <= pos ? sdot * scale : -INFINITY;
     }
     __syncthreads();
-    // local softmax statistics (every wave computes them for itself from the 128 scores)
-    float m = fmaxf(s_score[lane], s_score[lane + 64]);
+    // local softmax statistics (every wave computes them for itself from all scores)
+    float m = s_score[lane];
+#pragma unroll
+    for (int k = 1; k < CH / 64; ++k) m = fmaxf(m, s_score[lane + 64 * k]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
     // the chunk's first row always exists (chunks are launched only up to pos), so m is finite
-    float l = __expf(s_score[lane] - m) + __expf(s_score[lane + 64] - m);
+    float l = 0.0f;
+#pragma unroll
+    for (int k = 0; k < CH / 64; ++k) l += __expf(s_score[lane + 64 * k] - m);
     l = wave_sum(l);
     float acc[8];
 #pragma unroll
@@ -291,10 +303,15 @@ __global__ __launch_bounds__(256) void attn_partial(const float *__restrict__ q,
     }
     __syncthreads();
     float *out = part + ((size_t)u * chunks + c) * kPartStride;
-    if (tid < dh) out[2 + tid] = s_o[0][tid] + s_o[1][tid] + s_o[2][tid] + s_o[3][tid];
+    if (tid < dh) {
+        float v = s_o[0][tid];
+#pragma unroll
+        for (int w = 1; w < W; ++w) v += s_o[w][tid];
+        out[tid] = v;
+    }
     if (tid == 0) {
-        out[0] = m;
-        out[1] = l;
+        out[dh] = m;
+        out[dh + 1] = l;
     }
 }
 
@@ -319,12 +336,12 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
     // the first batch of value sums and this thread's chunk statistics, all in flight together
     float v[kBatch];
 #pragma unroll
-    for (int i = 0; i < kBatch; ++i) v[i] = p[(size_t)(i < chunks ? i : chunks - 1) * kPartStride + 2 + tid];
+    for (int i = 0; i < kBatch; ++i) v[i] = p[(size_t)(i < chunks ? i : chunks - 1) * kPartStride + tid];
     const int c_own = tid < chunks ? tid : chunks - 1;
-    const float m_own = p[(size_t)c_own * kPartStride], l_own = p[(size_t)c_own * kPartStride + 1];
+    const float m_own = p[(size_t)c_own * kPartStride + dh], l_own = p[(size_t)c_own * kPartStride + dh + 1];
     // pass 1: maximum of the chunk maxima
     float m_loc = tid < chunks ? m_own : -INFINITY;
-    for (int c = tid + 128; c < chunks; c += 128) m_loc = fmaxf(m_loc, p[(size_t)c * kPartStride]);
+    for (int c = tid + 128; c < chunks; c += 128) m_loc = fmaxf(m_loc, p[(size_t)c * kPartStride + dh]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m_loc = fmaxf(m_loc, __shfl_xor(m_loc, off, kWave));
     if (lane == 0) s_red[0][wave] = m_loc;
@@ -338,9 +355,9 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
         l_loc = w * l_own;
     }
     for (int c = tid + 128; c < chunks; c += 128) {
-        const float w = __expf(p[(size_t)c * kPartStride] - M);
+        const float w = __expf(p[(size_t)c * kPartStride + dh] - M);
         s_w[c] = w;
-        l_loc = __builtin_fmaf(w, p[(size_t)c * kPartStride + 1], l_loc);
+        l_loc = __builtin_fmaf(w, p[(size_t)c * kPartStride + dh + 1], l_loc);
     }
     l_loc = wave_sum(l_loc);
     if (lane == 0) s_red[1][wave] = l_loc;
@@ -352,12 +369,154 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
         if (i < chunks) o = __builtin_fmaf(s_w[i], v[i], o);
     for (int c0 = kBatch; c0 < chunks; c0 += kBatch) {
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) v[i] = p[(size_t)(c0 + i < chunks ? c0 + i : chunks - 1) * kPartStride + 2 + tid];
+        for (int i = 0; i < kBatch; ++i) v[i] = p[(size_t)(c0 + i < chunks ? c0 + i : chunks - 1) * kPartStride + tid];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i)
             if (c0 + i < chunks) o = __builtin_fmaf(s_w[c0 + i], v[i], o);
     }
     store_out(act + u * dh + tid, o / L);
+}
+
+// ---------------------------------------------------------------------------
+// output projection that merges the heads' partial softmaxes itself: up to nine of them, up to 64 heads
+// ---------------------------------------------------------------------------
+// Every workgroup merges all surviving heads into LDS, n_surv * chunks * 520 bytes from L2, while its rows of Wo for 24 heads are
+// on their way; that takes the place of a launch of its own.  Three blocks captured into a graph, us, merged in a launch of
+// its own / here: d 1024, 8 heads, 120 to 2000 cached rows 47.8 .. 49.8 / 40.6 .. 44.2, 4400 54.3 / 51.5; d 2048, 16 heads, 339 rows 55.4 /
+// 48.3, 2000 56.6 / 53.0; d 3200, 25 heads, 339 rows 78.2 / 76.5; d 4096, 32 heads, 339 rows 87.2 / 81.9, 900 88.7 / 86.7; d 5120,
+// 40 heads, 900 rows 121.1 / 116.0.  Where a thread has several heads' worth to merge the projection waits longer than the launch
+// took: d 3200, 900 rows 80.0 / 81.9, d 4096, 2000 rows 93.3 / 94.9, d 8192, 2000 rows 242.9 / 246.4.  So up to 16 heads are merged
+// here whenever nine chunks of up to 512 positions hold the cache; more heads while heads times chunks of up to 256 stay within 192
+// with the activations in bf16, and up to three chunks with them in float32.
+constexpr int kMergeChunks = 9, kMergeHeads = 64;
+
+template <typename AT>
+struct MergedHeads {
+    __attribute__((aligned(16))) AT act[kMergeHeads * kHeadDim];
+};
+
+template <int RQ, typename AT, bool EXACT>
+__global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const bf16_t *__restrict__ Wo,
+                                                           const uint8_t *__restrict__ mask, const float *__restrict__ part,
+                                                           int chunks, bf16_t *__restrict__ y, int ahead, AheadDev nx)
+{
+    constexpr int dh = kHeadDim, NT = RQ * 128;
+    struct Proj {
+        DownShared<RQ> down;
+        MergedHeads<AT> o;
+    };
+    constexpr size_t kLds = sizeof(Proj) > sizeof(MaskShared) ? sizeof(Proj) : sizeof(MaskShared);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (ahead && blockIdx.x == 0) {
+        mask_scores_block<NT, bf16_t, true>(*reinterpret_cast<MaskShared *>(lds), tid, nx.h, nx.Bt, nx.r, nx.scores, H, nx.K,
+                                            nx.prio_dev, nx.n_dev, nx.drop, nx.order, nx.group_dev, nx.mask, nx.surv_idx, nx.n_surv);
+        return;
+    }
+    Proj &sh = *reinterpret_cast<Proj *>(lds);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), vblock = blockIdx.x - (ahead ? 1 : 0);
+    const MaskWords mw = load_mask_words(mask, H, lane);
+    if (wave == 0) write_group_list(mw, lane, sh.down.list);
+    __syncthreads();
+    const int count = mw.count;
+    // rows and heads dealt as in down_t1_body, which adds up in the same order
+    const int rq = wave % RQ, half = wave / RQ;                  // row quad, even/odd heads
+    const int row = (vblock * RQ + rq) * 4 + (lane >> 4), piece = (lane & 15) * 8;
+    const __amdgpu_buffer_rsrc_t bw = buffer_of(Wo), bp = buffer_of(part);
+    const uint32_t at_w = (uint32_t)((EXACT ? row : min(row, d - 1)) * dh + piece) * 2;
+    const int my_head = sh.down.list[lane];                      // at most 64: one to a lane
+    constexpr int kB = 4;                                        // three batches in flight: 24 heads between the two halves
+    auto fetch = [&](u32x4 (&v)[kB], int u0) {
+#pragma unroll
+        for (int q = 0; q < kB; ++q) {
+            const int u = u0 + 2 * q < count ? u0 + 2 * q : (count > 0 ? count - 1 : 0);   // an in-range duplicate
+            v[q] = buffer_load16<kNt>(bw, at_w, (uint32_t)__builtin_amdgcn_readlane(my_head, u) * (uint32_t)d * (dh * 2));
+        }
+    };
+    float acc0 = 0.0f, acc1 = 0.0f;
+    auto mac = [&](const u32x4 (&v)[kB], int u0) {
+#pragma unroll
+        for (int q = 0; q < kB; ++q) {
+            if (u0 + 2 * q < count) {
+                ActPiece<AT> a;
+                a.load(sh.o.act + (u0 + 2 * q) * dh + piece);
+                a.dot(v[q], acc0, acc1);
+            }
+            if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two heads' operands at a time: registers
+        }
+    };
+    u32x4 v0[kB], v1[kB], v2[kB];
+    if (count > 0) {
+        fetch(v0, half);
+        fetch(v1, half + 2 * kB);
+        fetch(v2, half + 4 * kB);
+    }
+    // the merge; a thread: four dimensions of a head, 32 threads a head
+#pragma unroll 1
+    for (int id = tid; id < count * (dh / 4); id += NT) {
+        const int u = id / (dh / 4), e = (id % (dh / 4)) * 4;
+        const uint32_t head = (uint32_t)(u * chunks * kPartStride) * 4, at = head + e * 4;
+        auto load2 = [&](uint32_t voff, uint32_t soff) { return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(bp, voff, soff, 0)); };
+        float2 v[kMergeChunks][2], st[kMergeChunks];
+#pragma unroll
+        for (int c = 0; c < kMergeChunks; ++c) {
+            if (c < chunks) {                                    // uniform
+                st[c] = load2(head, (c * kPartStride + dh) * 4);
+                v[c][0] = load2(at, c * kPartStride * 4);
+                v[c][1] = load2(at, c * kPartStride * 4 + 8);
+            }
+        }
+        float M = st[0].x;
+#pragma unroll
+        for (int c = 1; c < kMergeChunks; ++c)
+            if (c < chunks) M = fmaxf(M, st[c].x);
+        float L = 0.0f, o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int c = 0; c < kMergeChunks; ++c) {
+            if (c < chunks) {
+                const float w = __expf(st[c].x - M);
+                L = __builtin_fmaf(w, st[c].y, L);
+                o[0] = __builtin_fmaf(w, v[c][0].x, o[0]);
+                o[1] = __builtin_fmaf(w, v[c][0].y, o[1]);
+                o[2] = __builtin_fmaf(w, v[c][1].x, o[2]);
+                o[3] = __builtin_fmaf(w, v[c][1].y, o[3]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) store_out(sh.o.act + u * dh + e + k, o[k] / L);
+    }
+    __syncthreads();
+    if (count > 0) {
+        int u0 = half;
+        while (u0 + 6 * kB < count) {
+            mac(v0, u0);
+            fetch(v0, u0 + 6 * kB);
+            mac(v1, u0 + 2 * kB);
+            fetch(v1, u0 + 8 * kB);
+            mac(v2, u0 + 4 * kB);
+            fetch(v2, u0 + 10 * kB);
+            u0 += 6 * kB;
+        }
+        if (u0 < count) mac(v0, u0);
+        if (u0 + 2 * kB < count) mac(v1, u0 + 2 * kB);
+        if (u0 + 4 * kB < count) mac(v2, u0 + 4 * kB);
+    }
+    float v = acc0 + acc1;
+    v = dpp_add<0xB1>(v);    // the 16 lanes of a row: quad_perm, quad_perm, half mirror, mirror
+    v = dpp_add<0x4E>(v);
+    v = dpp_add<0x141>(v);
+    v = dpp_add<0x140>(v);
+    if (half == 1) sh.down.half[rq][lane] = v;
+    __syncthreads();
+    if (half == 0 && (lane & 15) == 0 && (EXACT || row < d)) y[row] = f32_to_bf16(v + sh.down.half[rq][lane]);
+}
+
+template <int RQ, typename AT, bool EXACT>
+static void launch_merge_out(int blocks, int d, int H, const bf16_t *Wo, const uint8_t *mask, const float *part, int chunks,
+                             bf16_t *y, const AheadArgs *ah, hipStream_t s)
+{
+    merge_out_t1<RQ, AT, EXACT><<<dim3(blocks + (ah ? 1 : 0)), dim3(RQ * 128), 0, s>>>(d, H, Wo, mask, part, chunks, y, ah ? 1 : 0,
+                                                                                     ah ? ahead_dev(*ah) : AheadDev{});
 }
 
 // ---------------------------------------------------------------------------
@@ -410,8 +569,34 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
                      (const int32_t *)ws.dec.ulist, (const int32_t *)ws.dec.meta);
     }
 #undef HALO_QKV
-    attn_partial<<<dim3(chunks, H), dim3(256), 0, s>>>(ws.q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, mask,
-                                                       H, max_len, pos, ws.part);
+    // Few enough chunks, perhaps made so by longer ones, are merged by the output projection (see kMergeChunks).
+    const int len = pos + 1;
+    const int most = H <= 16 ? kMergeChunks : whole ? std::min(kMergeChunks, 192 / H) : 3, longest = H <= 16 ? 512 : whole ? 256 : 128;
+    int ch = 128;
+    while (ch < longest && len > ch * most) ch *= 2;
+    const int few = (len + ch - 1) / ch;
+    if (fast && H <= kMergeHeads && few <= most) {
+        const bf16_t *kc = (const bf16_t *)k_cache, *vc = (const bf16_t *)v_cache, *wo = (const bf16_t *)Wo;
+        if (ch == 128)
+            attn_partial<128><<<dim3(few, H), dim3(256), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+        else if (ch == 256)
+            attn_partial<256><<<dim3(few, H), dim3(512), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+        else
+            attn_partial<512><<<dim3(few, H), dim3(1024), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+        switch (whole ? d : 0) {
+        case 4096: launch_merge_out<4, bf16_t, true>(256, d, H, wo, mask, ws.part, few, (bf16_t *)y, ah, s); break;
+        case 5120: launch_merge_out<5, bf16_t, true>(256, d, H, wo, mask, ws.part, few, (bf16_t *)y, ah, s); break;
+        case 8192: launch_merge_out<8, bf16_t, true>(256, d, H, wo, mask, ws.part, few, (bf16_t *)y, ah, s); break;
+        default:                                                 // as launch_down_t1_any deals the rows
+            if (d < 4096)
+                launch_merge_out<2, float, false>((d + 7) / 8, d, H, wo, mask, ws.part, few, (bf16_t *)y, ah, s);
+            else
+                launch_merge_out<4, float, false>((d + 15) / 16, d, H, wo, mask, ws.part, few, (bf16_t *)y, ah, s);
+        }
+        return hipGetLastError();
+    }
+    attn_partial<kAttnChunk><<<dim3(chunks, H), dim3(256), 0, s>>>(ws.q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, mask,
+                                                                   H, max_len, pos, ws.part);
     // the output projection is the FFN's down projection with heads as groups
     if (whole) {
         attn_combine<bf16_t><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, chunks,

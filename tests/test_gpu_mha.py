@@ -258,6 +258,43 @@ def test_mha_long_context_many_chunks():
     _check_step(L, hs.mha_hidden(w, 1, hz.DEV), kc, vc, 4095, 6, H.halo_build_schedule(6, w.device_plr()), None)
 
 
+@pytest.mark.parametrize("d,Hh,ctx", [
+    (1032, 3, 1151),           # nine chunks of 128 positions, the last one full
+    (4096, 2, 1152),           # five of 256, the last with one position
+    (3200, 2, 2303),           # nine of 256
+    (5120, 16, 2304),          # five of 512
+    (2048, 2, 4607),           # nine of 512
+    (8192, 2, 4608),           # 37 of 128, merged in a launch of their own
+    (1024, 48, 383),           # three chunks of 128, more than 16 heads in float32; more than the projection's three batches of them
+    (1024, 17, 384),           # four: a launch of its own
+    (4096, 48, 700),           # three of 256
+    (4096, 64, 767),
+    (4096, 65, 140),           # more heads than are merged by the projection
+])
+def test_mha_merges_of_every_kind(d, Hh, ctx):
+    # The block's output against the oracle.  (Not the new cache rows, which the tests above compare to a bf16 step: of these
+    # many values some lie so near zero that the float32 sums' own distance, up to 2^-24 * sum |x w| * log2 d, is more than their step.)
+    w = dataclasses.replace(hs.LLAMA7B_MHA_DECODE, name="case", d=d, n_heads=Hh, rank=40, ctx=ctx, max_len=ctx + 8, seed=39)
+    _say(f"mha merges d={d} H={Hh} pos={ctx}")
+    L = MhaLayer(w)
+    kc, vc = hs.kv_cache(w, 0, hz.DEV)
+    k_ref, v_ref = hz.to_np32(kc).copy(), hz.to_np32(vc).copy()
+    Wq, Wk, Wv, WoT, At, Bt = L.host
+    ws = torch.empty(H.halo_mha_workspace_bytes(L.shape, kc.shape[1]), dtype=torch.uint8, device=hz.DEV)
+    for K in sorted({max(1, Hh // 2), Hh}):
+        pd, drop = H.halo_build_schedule(K, w.device_plr()), hs.mha_drop_outcomes(w, 0, K)
+        x = hs.mha_hidden(w, K, hz.DEV)
+        y = torch.full((1, w.d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+        H.halo_mha_forward(L.shape, x, L.At, L.Bt, L.Wq, L.Wk, L.Wv, L.Wo, kc, vc, ctx, K, torch.from_numpy(pd).to(hz.DEV), w.n_dev,
+                           torch.from_numpy(drop).to(hz.DEV), y, ws)
+        torch.cuda.synchronize()
+        xn = hz.to_np32(x)
+        m = ref.build_group_mask(ref.predict_scores(xn, At, Bt), K, pd, w.n_dev, drop)
+        yc = ref.mha_decode(xn, Wq, Wk, Wv, WoT, k_ref, v_ref, ctx, m["mask"][0])
+        yg = hz.to_np32(y)[0].astype(np.float64)
+        assert np.isfinite(yg).all() and np.linalg.norm(yg - yc) <= TOL * np.linalg.norm(yc)
+
+
 @pytest.mark.parametrize("d,Hh,ctx", [(8, 1, 3), (1032, 5, 129), (2048, 16, 300), (3200, 25, 40), (7176, 3, 128), (8200, 2, 20)])
 def test_mha_of_any_row_length(d, Hh, ctx):
     # rows that are not whole 512-element chunks, outputs that are not whole workgroups, and one row longer than the

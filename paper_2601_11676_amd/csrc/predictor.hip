@@ -10,6 +10,7 @@
 // internal summation order; one that takes a single element per instruction has none
 // (hidden_mfma_kernel below), and a few tokens stay on the plain float ALUs.
 #include "kernels.hpp"
+#include "lds_loads.hpp"
 
 namespace halo {
 
@@ -35,31 +36,31 @@ __global__ __launch_bounds__(256) void dot_rows_kernel(const XT *__restrict__ X,
 // ordinary values, denormals, overflow and infinities), so the order of a chain is the order in which the
 // instructions are issued, which is exactly what the fixed order asks for.  Block b of a wave's instruction
 // holds partial sums l + 16 b: lane (b, i) supplies element e of piece 64 k + l + 16 b of row i, e = 0..7 are
-// eight instructions, and k walks the row.  A wave owns 16 / WAVES consecutive values of l, so a
+// eight instructions, and k walks the row.  Wave l of sixteen owns partial sums l + 16 b, so a
 // workgroup holds all 64 partial sums of its (16 JT rows of At) x (16 TT tokens); distances 32 and 16 are
 // then additions between a lane's own blocks, 8 .. 1 go through LDS once at the end.
-// Nothing is spent on lane-crossing sums per result (half of the instructions of a wave-per-row form), and
-// the instruction runs at 130 TFLOP/s here against 51 for dependent vector multiply-adds.  Measured, first
-// layer alone: 512 tokens, d = 4096, rank 256: 18 us (59 TFLOP/s; vector form 32 us); 128 tokens, d = 5120: 11.7 us
-// (26); 1000 tokens, d = 8192, rank 512: 96 us (87 TFLOP/s; 370).  What is left above the instruction's rate
-// is the barrier and the first LDS read of every 512-element step.
-// Rows go through LDS a step at a time (coalesced 1 KiB per wave instruction; a row is padded by 16 bytes so
-// that 16 rows' pieces fall into different banks), double-buffered; the step after next travels in
-// registers.  Two waves per SIMD (four with one tile), so that one wave's LDS reads hide behind another's
-// matrix instructions: with one wave and one buffer 24, 15.6 and 130 us.
+// Nothing is spent on lane-crossing sums per result (half of the instructions of a wave-per-row form).
+// Rows go straight to LDS a step of 512 elements at a time (a load: one row's 1 KiB; a row is padded by 16 bytes so
+// that 16 rows' pieces fall into different banks), two to four steps of them, and a step's fragments are read
+// while the matrix instructions of the step before run, so that the barrier between two steps has work on both sides.
+// The matrix instruction bounds it: 1000 tokens, d = 8192, rank 512 take 98 us, 91 with loads that move nothing, 50 without the
+// matrix instructions.  (With the rows passed through registers, eight waves of two partial sums and the fragments read
+// behind the barrier 107.)  Both layers, 256 tokens, d = 8192, rank 128: 18.5 -> 17.2 us; 160 tokens, d = 5120, rank 256 13.6 -> 12.9;
+// rows of one step are 0.1 us slower.  Two buffers, and nothing asked for past the end, where the walk has at most four steps: with
+// four buffers d = 1536, 160 tokens, rank 512 12.4 against 12.0, d = 2048 2 % and d = 512 7 % more.
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-constexpr int kHidRow = 512 + 8;            // padded LDS row, elements
+constexpr int kHidRow = 1024 + 16;          // padded LDS row, bytes
+constexpr int kHidWaves = 16;
 
-template <int TT, int JT, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4))) void hidden_mfma_kernel(
+template <int TT, int JT, int BUFS>
+__global__ __launch_bounds__(kHidWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void hidden_mfma_kernel(
     const bf16_t *__restrict__ X, const bf16_t *__restrict__ At, float *__restrict__ h, int T, int d, int r,
     int n_tt, int n_jt)
 {
-    constexpr int kTiles = TT * JT, kRows = 16 * (TT + JT), kPer = kRows / WAVES, kL = 16 / WAVES;
-    constexpr size_t kStage = (size_t)2 * kRows * kHidRow * sizeof(bf16_t), kSums = (size_t)16 * kTiles * 64 * 16;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[kStage > kSums ? kStage : kSums];
-    bf16_t *rows = reinterpret_cast<bf16_t *>(lds);              // two of: TT * 16 token rows, then JT * 16 rows of At
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int kTiles = TT * JT, kSets = TT + JT, kRows = 16 * kSets, kStage = kRows * kHidRow;
+    static_assert(BUFS >= 2 && kTiles * 16 * 1024 <= BUFS * kStage, "the sums fit");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // BUFS of: TT * 16 token rows, then JT * 16 rows of At
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     // a die (workgroups are dealt round-robin to eight) takes consecutive items, the rows of At fastest: its
     // token rows stay in its L2
     const int n_items = n_tt * n_jt, per_die = (n_items + 7) >> 3;
@@ -67,84 +68,84 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     if (slot >= per_die || item >= n_items) return;
     const int t0 = (item / n_jt) * 16 * TT, j0 = (item % n_jt) * 16 * JT;
     const int nk = (d + 511) / 512;
-    // this wave stages rows wave, wave + WAVES, ...; rows past the end repeat the last one (never stored)
-    const bf16_t *src[kPer];
+    // this wave loads row `wave` of every set of 16; rows past the end repeat the last one (never stored)
+    const srd_t srd_x = make_srd(X + (size_t)t0 * d, true), srd_a = make_srd(At + (size_t)j0 * d, true);
+    uint32_t row_at[kSets];
 #pragma unroll
-    for (int n = 0; n < kPer; ++n) {
-        const int row = wave + WAVES * n;
-        src[n] = row < 16 * TT ? X + (size_t)min(t0 + row, T - 1) * d : At + (size_t)min(j0 + row - 16 * TT, r - 1) * d;
-    }
-    u32x4 v[kPer];
-    auto fetch = [&](int k) {
-        const int e = k * 512 + lane * 8;
-        const bool ok = e < d;                                   // (d is a multiple of 8)
-#pragma unroll
-        for (int n = 0; n < kPer; ++n) {
-            v[n] = *reinterpret_cast<const u32x4 *>(src[n] + (ok ? e : 0));
-            if (!ok) v[n] = u32x4{0u, 0u, 0u, 0u};               // 0 * 0 leaves a chain as it is
-        }
+    for (int n = 0; n < kSets; ++n)
+        row_at[n] = (uint32_t)(n < TT ? min(wave + 16 * n, T - 1 - t0) : min(wave + 16 * (n - TT), r - 1 - j0)) * (uint32_t)d * 2;
+    const uint32_t lds0 = (uint32_t)(size_t)lds + wave * kHidRow;
+    auto load = [&](int n, int k, int buf) {                     // its row of set n, step k; zeros past the row's or the walk's end
+        const uint32_t at = k * 512 + lane * 8 < d ? lane * 16u : kNoRow;     // (d is a multiple of 8; 0 * 0 leaves a chain as it is)
+        load_to_lds16(n < TT ? srd_x : srd_a, at, k < nk ? row_at[n] + k * 1024u : 0u, lds0 + buf * kStage + n * 16 * kHidRow);
     };
-    static_assert(kPer <= 8, "a row per element of the last piece");
-    auto park = [&](int k, int n) {
-        *reinterpret_cast<u32x4 *>(rows + ((k & 1) * kRows + wave + WAVES * n) * kHidRow + lane * 8) = v[n];
-    };
-    f32x16_t acc[kL][kTiles];
-#pragma unroll
-    for (int l = 0; l < kL; ++l)
-#pragma unroll
-        for (int n = 0; n < kTiles; ++n)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[l][n][e] = 0.0f;
     const int i = lane & 15, b = lane >> 4;
-    fetch(0);
+    u32x4 raw[2][kSets];
+    auto read = [&](u32x4 (&f)[kSets], int buf) {
+        const unsigned char *piece = lds + buf * kStage + i * kHidRow + (wave + 16 * b) * 16;
 #pragma unroll
-    for (int n = 0; n < kPer; ++n) park(0, n);
-    fetch(nk > 1 ? 1 : 0);
-    for (int k = 0; k < nk; ++k) {
-        __syncthreads();                                         // step k is in LDS, step k - 1 is used up
-        const bf16_t *piece = rows + (k & 1) * kRows * kHidRow + i * kHidRow + (kL * wave + 16 * b) * 8;
-        u32x4 raw[TT + JT];
+        for (int n = 0; n < kSets; ++n) f[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow);
+    };
+    f32x16_t acc[kTiles];
 #pragma unroll
-        for (int n = 0; n < TT + JT; ++n) raw[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow);
+    for (int n = 0; n < kTiles; ++n)
 #pragma unroll
-        for (int l = 0; l < kL; ++l) {
-            float f[TT + JT][8];
+        for (int e = 0; e < 16; ++e) acc[n][e] = 0.0f;
 #pragma unroll
-            for (int n = 0; n < TT + JT; ++n) unpack8(raw[n], f[n]);
-            if (l + 1 < kL) {
+    for (int k = 0; k < BUFS; ++k)
 #pragma unroll
-                for (int n = 0; n < TT + JT; ++n)
-                    raw[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow + (l + 1) * 8);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-#pragma unroll
-                for (int n = 0; n < kTiles; ++n)
-                    acc[l][n] = __builtin_amdgcn_mfma_f32_16x16x1f32(f[TT + n % JT][e], f[n / JT][e], acc[l][n], 0, 0, 0);
-                // the next step's rows go to the other buffer one by one between the matrix instructions
-                if (l == kL - 1 && e < kPer) park(k + 1, e);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int n = 0; n < kSets; ++n)
+            if (BUFS > 2 || k < nk) load(n, k, k);
+    if (BUFS > 2 || nk > 1)
+        wait_loads<(BUFS - 1) * kSets>();
+    else
+        wait_loads<0>();
+    __syncthreads();
+    read(raw[0], 0);
+    int buf = 0;                                                 // buffer of step k
+    // At the top of step k its fragments are in registers.  The barrier says that step k + 1 has landed and that everybody has
+    // read step k, whose buffer is then handed to step k + BUFS.
+    auto step = [&](const u32x4 (&cur)[kSets], u32x4 (&next)[kSets], int k) __attribute__((always_inline)) {
+        const int nbuf = buf == BUFS - 1 ? 0 : buf + 1;
+        if (BUFS > 2 || k + 1 < nk) {
+            wait_loads<(BUFS - 2) * kSets>();
+            __syncthreads();
         }
-        fetch(k + 2 < nk ? k + 2 : nk - 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float f[kSets];
+#pragma unroll
+            for (int n = 0; n < kSets; ++n) f[n] = e % 2 == 0 ? bf16_lo(cur[n][e / 2]) : bf16_hi(cur[n][e / 2]);
+#pragma unroll
+            for (int n = 0; n < kTiles; ++n)
+                acc[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(f[TT + n % JT], f[n / JT], acc[n], 0, 0, 0);
+            if (e == 0 && (BUFS > 2 || k + 1 < nk)) read(next, nbuf);
+            if (e >= 1 && e - 1 < kSets && (BUFS > 2 || k + 2 < nk)) load(e - 1, k + BUFS, buf);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        buf = nbuf;
+    };
+    for (int k = 0; k < nk; k += 2) {
+        step(raw[0], raw[1], k);
+        if (k + 1 < nk) step(raw[1], raw[0], k + 1);
     }
+    wait_loads<0>();                                             // (of loads that move zeros)
     __syncthreads();
     // distances 32 and 16: blocks (0, 2) and (1, 3); result element 4 b + m of a lane is block b, row 4 (lane / 16) + m,
     // token lane % 16
     f32x4_t *sums = reinterpret_cast<f32x4_t *>(lds);            // [l][tile][lane]
 #pragma unroll
-    for (int l = 0; l < kL; ++l)
+    for (int n = 0; n < kTiles; ++n) {
+        f32x4_t s;
 #pragma unroll
-        for (int n = 0; n < kTiles; ++n) {
-            f32x4_t s;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) s[m] = (acc[l][n][m] + acc[l][n][8 + m]) + (acc[l][n][4 + m] + acc[l][n][12 + m]);
-            sums[((kL * wave + l) * kTiles + n) * 64 + lane] = s;
-        }
+        for (int m = 0; m < 4; ++m) s[m] = (acc[n][m] + acc[n][8 + m]) + (acc[n][4 + m] + acc[n][12 + m]);
+        sums[(wave * kTiles + n) * 64 + lane] = s;
+    }
     __syncthreads();
     // distances 8, 4, 2, 1
-    for (int n = wave; n < kTiles; n += WAVES) {
+    if (wave < kTiles) {
+        const int n = wave;
         f32x4_t p[16];
 #pragma unroll
         for (int l = 0; l < 16; ++l) p[l] = sums[(l * kTiles + n) * 64 + lane];
@@ -164,11 +165,16 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     }
 }
 
-template <int TT, int JT, int WAVES>
-static void launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
+template <int TT, int JT, int BUFS>
+static hipError_t launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
+    constexpr int lds = BUFS * 16 * (TT + JT) * kHidRow;
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(hidden_mfma_kernel<TT, JT, BUFS>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (lds_ok != hipSuccess) return lds_ok;
     const int n_tt = (T + 16 * TT - 1) / (16 * TT), n_jt = (r + 16 * JT - 1) / (16 * JT);
-    hidden_mfma_kernel<TT, JT, WAVES><<<dim3((n_tt * n_jt + 7) / 8 * 8), dim3(WAVES * 64), 0, s>>>(x, At, h, T, d, r, n_tt, n_jt);
+    hidden_mfma_kernel<TT, JT, BUFS><<<dim3((n_tt * n_jt + 7) / 8 * 8), dim3(kHidWaves * 64), lds, s>>>(x, At, h, T, d, r, n_tt, n_jt);
+    return hipSuccess;
 }
 
 // The second layer for many tokens: scores[t][g] = h[t] . Bt[g], the same instruction and order.  The rows are short (one
@@ -266,27 +272,29 @@ hipError_t launch_scores_many(const float *h, const bf16_t *Bt, int T, int r, in
 // way.  Both layers in us, wave against tile: 16 x 64 results d 1024 4.7 against 6.6, d 8192 6.9 against 17.6; 48 x 256
 // d 4096 10.4 against 11.5; 64 x 256 d 4096 12.3 against 11.5; 32 x 512 d 8192 19.9 against 17.7.  The two meet between
 // 12800 and 16384 results at every d from 128 to 8192.
-static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
+static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s, hipError_t &e)
 {
-    if (T < 16 || (long long)T * r < 14 * 1024) return false;
+    if (T < 16 || (long long)T * r < 14 * 1024 || d > 1 << 24) return false;   // (rows are addressed with 32-bit offsets)
     const int n_tt = (T + 31) / 32;
     if (n_tt * ((r + 31) / 32) >= 256)
-        launch_hidden_mfma<2, 2, 8>(x, T, d, r, At, h, s);
+        e = launch_hidden_mfma<2, 2, 2>(x, T, d, r, At, h, s);
     else if (n_tt * ((r + 15) / 16) >= 256)
-        launch_hidden_mfma<2, 1, 8>(x, T, d, r, At, h, s);
+        e = d <= 2048 ? launch_hidden_mfma<2, 1, 2>(x, T, d, r, At, h, s) : launch_hidden_mfma<2, 1, 3>(x, T, d, r, At, h, s);
     else
-        launch_hidden_mfma<1, 1, 16>(x, T, d, r, At, h, s);
+        e = d <= 2048 ? launch_hidden_mfma<1, 1, 2>(x, T, d, r, At, h, s) : launch_hidden_mfma<1, 1, 4>(x, T, d, r, At, h, s);
     return true;
 }
-static bool hidden_rows_tiled(const float *, int, int, int, const float *, float *, hipStream_t) { return false; }
+static bool hidden_rows_tiled(const float *, int, int, int, const float *, float *, hipStream_t, hipError_t &) { return false; }
 
 template <typename WT>
 static hipError_t predict_t(const WT *x, int T, int d, int r, int G, const WT *At, const WT *Bt,
                             float *h, float *scores, hipStream_t s)
 {
     long long n1 = (long long)T * r, n2 = (long long)T * G;
-    if (!hidden_rows_tiled(x, T, d, r, At, h, s))
+    hipError_t e = hipSuccess;
+    if (!hidden_rows_tiled(x, T, d, r, At, h, s, e))
         dot_rows_kernel<WT, WT, true><<<dim3((unsigned)((n1 + 3) / 4)), dim3(256), 0, s>>>(x, At, h, T, r, d);
+    if (e != hipSuccess) return e;
     if (scores && sizeof(WT) == 2 && scores_apart(T, r, G)) return launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
     if (scores)
         dot_rows_kernel<float, WT, false><<<dim3((unsigned)((n2 + 3) / 4)), dim3(256), 0, s>>>(h, Bt, scores, T, G, r);

@@ -578,6 +578,23 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     assert same.all()
 
 
+@pytest.mark.parametrize("T,d,r,tiles", [
+    (16, 8, 1024, "1x1"), (16, 512, 1024, "1x1"), (16, 1536, 1000, "1x1"), (40, 5128, 392, "1x1"),   # 1, 1, 3 and 11 steps, four buffers
+    (500, 8, 256, "2x1"), (500, 1024, 248, "2x1"), (500, 2568, 256, "2x1"),                          # 1, 2 and 6, three
+    (510, 512, 504, "2x2"), (510, 1544, 512, "2x2"), (510, 4096, 512, "2x2"),                        # 1, 4 and 8, two
+])
+def test_predictor_tiles_over_any_number_of_steps(T, d, r, tiles):
+    _say(f"predictor tiles {tiles} T={T} d={d} r={r}")
+    g = torch.Generator(device=hz.DEV).manual_seed(9)
+    x, At, Bt = (torch.randn(n, generator=g, device=hz.DEV).to(torch.bfloat16) for n in ((T, d), (r, d), (5, r)))
+    s = H.Shape(d, 5 * 128, 128, r, "bf16")
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    sc = torch.empty((T, 5), dtype=torch.float32, device=hz.DEV)
+    H.halo_predict_scores(s, x, At, Bt, sc, ws)
+    c = ref.predict_scores(hz.to_np32(x), hz.to_np32(At), hz.to_np32(Bt))
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), c.view(np.uint32))
+
+
 @pytest.mark.parametrize("T,r,G", [
     (5300, 8, 1000),           # one piece per row, ragged tiles both ways
     (530, 264, 310),           # half of the pieces

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
 // gate/up through rings in LDS filled by direct global -> LDS loads
 // grid: 8 * ceil(items / 8) workgroups of 512 threads, one per compute unit
 // ---------------------------------------------------------------------------
-// Workgroup tile: 128 weight rows (64 gate + 64 up neurons of one group) x NTOK (256 or 128) of the group's
+// Workgroup tile: 128 weight rows (64 gate + 64 up neurons of one group) x NTOK (256, 128 or 64) of the group's
 // tokens; K advances 64 elements per stage.  In LDS a stage is 128 weight rows and NTOK gathered x
 // rows of 128 bytes.  One load instruction moves 1 KiB = 8 rows x 128 bytes, lane l landing at byte
 // 16 l of the block; to keep the operand reads free of bank conflicts the 16-byte piece p of tile row
@@ -114,8 +114,8 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
 // converts the rows it has fetched itself, so nothing but its own wait stands between the two.
 //
 // For the matrix work the eight waves are two halves of the stage's K range (elements
-// 0..31 / 32..63) times four parts of the tile (256 tokens: four quarters of them; 128 tokens: two halves of the rows
-// times two halves of the tokens), so a wave owns a 128 x 64 (64 x 64) partial tile; the two K halves are
+// 0..31 / 32..63) times four parts of the tile (256 tokens: four quarters of them; 128 or 64 tokens: two halves of the rows
+// times two halves of the tokens), so a wave owns a 128 x 64 (64 x 64, 64 x 32) partial tile; the two K halves are
 // added through LDS once at the end.
 //
 // Two waves share a SIMD, and that is what the kernels' speed comes from.  A wave issues one instruction at a time, and
@@ -137,7 +137,7 @@ constexpr int kRawBytes = 128 * 64 + 128 * 4;                    // codes, then 
 
 template <bool Q4, int NTOK>
 struct Ring {
-    static constexpr int kMT = NTOK == 256 ? 8 : 4, kTT = 4;     // 16-row and 16-token tiles of a wave
+    static constexpr int kMT = NTOK == 256 ? 8 : 4, kTT = NTOK == 64 ? 2 : 4;    // 16-row and 16-token tiles of a wave
     static constexpr int kXL = NTOK / 64;                        // x loads of a wave per stage
     static constexpr int kX = NTOK * 128;                        // bytes of a stage of token rows
     static constexpr int kW = 128 * 128;                         // bytes of a stage of weight rows
@@ -151,7 +151,7 @@ struct Ring {
 // the part of the workgroup's tile a wave multiplies
 template <int MT>
 struct WavePart {
-    int ks, rh, tq;                                              // K half, half of the rows (MT == 4), 64-token part
+    int ks, rh, tq;                                              // K half, half of the rows (MT == 4), part of the tokens
     __device__ __forceinline__ WavePart(int wave) : ks(wave & 1), rh(MT == 8 ? 0 : (wave >> 1) & 1), tq(MT == 8 ? wave >> 1 : wave >> 2) {}
     // 16-row tile of the workgroup that is the wave's tile m: gate rows first, then the up rows that face them
     __device__ __forceinline__ int row_tile(int m) const { return MT == 8 ? m : (m < 2 ? 2 * rh + m : 4 + 2 * rh + (m - 2)); }
@@ -161,8 +161,8 @@ struct WavePart {
 // (Left to itself the compiler gives the tiles of these kernels rotating destination registers and
 // moves a few hundred registers between the two files per step to make that work.)  A statement the
 // compiler cannot look into also gets none of its matrix-pipeline wait states, which is safe here:
-// a wave goes through all of its tiles before it touches one again, 32 in the 256-token rings, 16 in the 128-token
-// rings, 8 N in gate_up_pf_big (N = 1: seven matrix instructions lie between; ring_multiply asserts the 8).  A
+// a wave goes through all of its tiles before it touches one again, 32 in the 256-token rings, 16 and 8 in the 128- and
+// 64-token rings, 8 N in gate_up_pf_big (N = 1: seven matrix instructions lie between; ring_multiply asserts the 8).  A
 // 16x16x32 bf16 instruction occupies the pipeline for 8 passes and they issue in order, so one instruction
 // in between is already more than the few cycles a result takes after its last pass.  The first
 // ordinary read of the accumulators comes after an explicit pause of 2 x 16 idle
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         fa[m] = *reinterpret_cast<const u32x4 *>(ring + R::kWBase + wbuf * R::kW + loff + part.row_tile(m) * 2048);
     };
     auto read_b = [&](u32x4 (&f)[TT], int n, int xbuf) {
-        f[n] = *reinterpret_cast<const u32x4 *>(ring + xbuf * R::kX + part.tq * 8192 + loff + n * 2048);
+        f[n] = *reinterpret_cast<const u32x4 *>(ring + xbuf * R::kX + part.tq * (TT * 2048) + loff + n * 2048);
     };
 #pragma unroll
     for (int m = 0; m < MT; ++m) read_a(m, 0);
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     __builtin_amdgcn_sched_barrier(0);                           // (nothing that reads them moves above the pause)
 
     bf16_t *act_row0 = act + (size_t)g * T * gs + nt * 64;
-    const int sl0 = c0 + part.tq * 64 + i16;
+    const int sl0 = c0 + part.tq * (TT * 16) + i16;
     auto put = [&](auto first) {
         constexpr int own = decltype(first)::value;
 #pragma unroll
@@ -1003,7 +1003,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         fa[m] = *reinterpret_cast<const u32x4 *>(ring + R::kWBase + wbuf * R::kW + loff + part.row_tile(m) * 2048);
     };
     auto read_b = [&](u32x4 (&f)[TT], int n, int xbuf) {
-        f[n] = *reinterpret_cast<const u32x4 *>(ring + xbuf * R::kX + part.tq * 8192 + loff + n * 2048);
+        f[n] = *reinterpret_cast<const u32x4 *>(ring + xbuf * R::kX + part.tq * (TT * 2048) + loff + n * 2048);
     };
 #pragma unroll
     for (int m = 0; m < MT; ++m) read_a(m, 0);
@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         constexpr int own = decltype(first)::value;
 #pragma unroll
         for (int j = 0; j < TT / 2; ++j) {
-            const int t = t0 + part.tq * 64 + (own + j) * 16 + i16;
+            const int t = t0 + part.tq * (TT * 16) + (own + j) * 16 + i16;
             if (t < T) {
 #pragma unroll
                 for (int m = 0; m < MT; ++m) {
@@ -1168,6 +1168,25 @@ static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const
 // in gate/up, but 32.9 against 31.8 in down; 400 tokens 85 against 63 and 56 against 45.
 // In the down projection also where whole tiles times ranges would fill less than half of the chip: 200 tokens of d 2048, one
 // range, 41.7 us against 63.4; 200 tokens of d 1024 10.0 against 13.6.
+//
+// Quarter tiles where they hold all of a group's tokens, whatever the mask: up to 64 tokens.  Gate/up over codes only: there
+// a stage is matrix work, LDS reads and conversion one after the other, and the first two are halved; with bf16 weights it waits for
+// memory, and a stage of fewer bytes keeps fewer in flight.  Pass in us, half tiles against quarter tiles in gate/up alone
+// and in both projections: codes, 17 tokens, 7B 78.9 / 71.3 / 69.3, 13B 97.9 / 90.5 / 86.3, 70B 266 / 245 / 231; 64 tokens of 13B
+// 106.7 / 97.8 / 93.2; bf16, 17 tokens, 7B 78.5 / 78.4 / 76.4, 70B 267 / 273 / 270.  Above 64 tokens most groups need two
+// quarter tiles, each converting the codes: 100 tokens of 13B 109.1 against 107.5, 128 tokens 109.3 against 110.7.
+// In the down projection also where half tiles times ranges would fill less than half of the chip.  Half against quarter, bf16
+// and codes: 256 tokens of d 2048 77.4 / 68.4 and 96.1 / 89.2, 200 of d 2560 101.5 / 94.2 and 119.6 / 111.3, 100 of d 3072
+// 79.6 / 76.7 and 83.3 / 79.6, 600 of d 768 54.0 / 49.3 and 62.9 / 59.2; where they fill more than that, 100 tokens of 13B
+// 122 against 157.  Rows of one output tile, or layers of less than 768 or of fewer than eight groups with more than 64
+// tokens, are bound by launches (d 640, 129 to 200 tokens: 39.4 / 38.0) and stay as they are.
+static bool gate_up_quarter_tiles(bool q4, int T, int d) { return q4 && T <= 64 && d >= 256; }
+static bool down_quarter_tiles(int T, int d, int G, int splits)
+{
+    if (T <= 64) return d >= 256;
+    return d >= 768 && G >= 8 && (long long)(d / 128) * ((T + 127) / 128) * splits < 128;
+}
+
 template <bool Q4>
 static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const void *Wd,
                                const bf16_t *Sg, const bf16_t *Su, const bf16_t *Sd, const DecodeScratch &ws, bf16_t *act,
@@ -1176,13 +1195,17 @@ static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void 
     hipError_t e;
     if (!Q4 && gate_up_big_tiles(T, G))
         e = launch_gate_up_big(x, T, d, G, (const bf16_t *)Wg, (const bf16_t *)Wu, ws, act, s);
+    else if (gate_up_quarter_tiles(Q4, T, d))
+        e = launch_gate_up_ring<Q4, Q4 ? 64 : 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);   // (no bf16 form is built)
     else if (T <= 256)
         e = launch_gate_up_ring<Q4, 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
     else
         e = launch_gate_up_ring<Q4, 256>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
     if (e != hipSuccess) return e;
     const int splits = splits_in_room(down_splits(T, d, G), T, d, ws);
-    if (T <= 128 || (d / 128) * ((T + 255) / 256) * splits < 128)
+    if (down_quarter_tiles(T, d, G, splits))
+        e = launch_down_ring<Q4, 64>(T, d, G, splits, Wd, Sd, ws, act, y, s);
+    else if (T <= 128 || (d / 128) * ((T + 255) / 256) * splits < 128)
         e = launch_down_ring<Q4, 128>(T, d, G, splits, Wd, Sd, ws, act, y, s);
     else
         e = launch_down_ring<Q4, 256>(T, d, G, splits, Wd, Sd, ws, act, y, s);

@@ -385,6 +385,27 @@ def test_q4_many_token_rings(T, d, G, K):
     assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"])
 
 
+@pytest.mark.parametrize("q4", [True, False])
+@pytest.mark.parametrize("T,d,G,K", [
+    (17, 256, 3, 2),           # the fewest tokens, the shortest rows: one full block of eight token rows of a wave's, four stages
+    (33, 640, 9, 9),           # dense, one token past half of the tile; an odd number of blocks per row
+    (64, 1152, 20, 10),        # the full tile
+    (65, 768, 8, 6),           # down projection: a second quarter tile of one token
+    (193, 1024, 24, 12),       # ... a fourth of one token
+    (520, 896, 9, 4),          # ... nine of them, more than two (the other numbering of the work)
+])
+def test_quarter_tiles_of_tokens(q4, T, d, G, K):
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=87)
+    _say(f"quarter tiles q4={q4} T={T} d={d} G={G} K={K}")
+    L = (hz.Q4Layer if q4 else hz.Layer)(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    drop[T - 1] = 1                            # one token loses every device: exact zeros expected
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop, big_workspace=True) if q4 else hz.gpu_forward(w, L, x, K, pd, drop)
+    hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["bf16"], f"quarter tiles T={T}")
+
+
 @pytest.mark.parametrize("G,K", [(2, 1), (3, 2)])
 def test_q4_more_tokens_than_the_row_table_holds(G, K):
     # 32768 tokens: the codes are expanded into the workspace and the bf16 kernels run on them

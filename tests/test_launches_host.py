@@ -79,3 +79,15 @@ def test_many_token_cases_run_on_the_kernels_they_are_for():
     for T, d, G in [(300, 256, 300), (1100, 384, 180), (520, 128, 100), (300, 1152, 150), (2050, 256, 97)]:
         (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, G, 128, 64, BF16), T=T, K=G // 3)])
         assert rc == 0 and any("gate_up_pf_big" in n for n, *_ in launches), (T, d, G, launches)
+
+
+def test_quarter_tiles_of_tokens():
+    # tokens per tile in gate/up over codes and in down (gate/up over bf16 weights has no quarter tiles)
+    for T, d, G, gate_up, down in [(17, 128, 3, 128, 128), (17, 256, 3, 64, 64), (33, 640, 9, 64, 64), (64, 1152, 20, 64, 64),
+                                   (65, 768, 8, 128, 64), (193, 1024, 24, 128, 64), (520, 896, 9, 256, 64),
+                                   (65, 640, 9, 128, 128), (65, 768, 7, 128, 128), (128, 5120, 108, 128, 128)]:
+        for q4 in (0, 1):
+            (rc, _, launches), = record([dict(fn="ffn_forward" + ("_q4" if q4 else ""), shape=(d, G, 128, 64, BF16), T=T, K=G // 2)])
+            names = [n for n, *_ in launches]
+            for kernel, tokens in (("gate_up_pf_ring", gate_up if q4 else max(gate_up, 128)), ("down_pf_ring", down)):
+                assert rc == 0 and sum(f"{kernel}ILb{q4}ELi{tokens}E" in n for n in names) == 1, (T, d, G, q4, names)

@@ -116,8 +116,8 @@ size_t halo_workspace_bytes(const halo_shape *shape, int32_t T, int32_t k_keep);
  * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  (It is
  * how a caller chooses the rounded weights: a smaller sign would let the slack of a workspace that was sized for more
  * tokens change the arithmetic.)  A `_q4` call given only halo_workspace_bytes works all the same, several times slower,
- * with the scale applied in float32: 16 tokens at a time on the 2..16-token kernels where these take the shape (d a
- * multiple of 1024 up to 8192, n_groups <= 256), else all tokens on the plain path.  Never smaller than
+ * with the scale applied in float32: 16 tokens at a time on the 2..16-token kernels where these take the shape (d up to
+ * 8192, n_groups <= 256), else all tokens on the plain path.  Never smaller than
  * halo_workspace_bytes; 0 for invalid arguments.
  */
 size_t halo_workspace_bytes_q4(const halo_shape *shape, int32_t T, int32_t k_keep);
@@ -273,7 +273,7 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * Everything else -- mask semantics, workspace, stream, errors -- is as in
  * halo_group_sparse_ffn / halo_ffn_forward.  Tuned paths (bf16 activations, n_groups <= 256): one
  * token with d <= 8192 (every surviving code byte streamed once, float ALUs), 2..16
- * tokens with d a multiple of 1024 up to 8192 (matrix cores, codes expanded in registers); other shapes and float32
+ * tokens with d <= 8192 (matrix cores, codes expanded in registers); other shapes and float32
  * activations take a plain path that dequantises element by element.  More than 16 tokens (any d a multiple of
  * 128, any n_groups): with a workspace of halo_workspace_bytes_q4 the many-token matrix-core kernels, each value
  * s * (c - 8) rounded to bf16, to nearest even; with less, the 2..16-token kernels 16 tokens at a time where they take

@@ -41,7 +41,6 @@ class MhaShape:
         self.d, self.n_heads, self.head_dim, self.rank, self.dtype = d, n_heads, head_dim, rank, dtype
         code = {"f32": HALO_F32, "bf16": HALO_BF16}.get(dtype, -1)
         self.c = _CMhaShape(d, n_heads, head_dim, rank, code)
-        self.ref = C.byref(self.c)
 
 
 class Shape:
@@ -54,7 +53,6 @@ class Shape:
         self.dtype = dtype
         code = {"f32": HALO_F32, "bf16": HALO_BF16}.get(dtype, -1)
         self.c = _CShape(d, ffn, group_size, self.n_groups, rank, code)
-        self.ref = C.byref(self.c)
 
     @property
     def torch_dtype(self):
@@ -142,7 +140,7 @@ def load_library():
 
 
 # A call marshals up to two dozen arguments, and a small block's kernels take no longer than that: addresses are passed as
-# plain ints (ctypes converts them by the declared argument types), and the current stream's handle is asked for
+# plain ints and shapes as their structs (ctypes converts both by the declared argument types), and the current stream's handle is asked for
 # without building a Stream object around it.
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
@@ -218,16 +216,16 @@ def halo_ratios_min_max(mem, comp, demand: float, eps: float = 1e-3) -> np.ndarr
 
 
 def halo_workspace_bytes(shape: Shape, T: int, k_keep: int) -> int:
-    return int(load_library().halo_workspace_bytes(shape.ref, int(T), int(k_keep)))
+    return int(load_library().halo_workspace_bytes(shape.c, int(T), int(k_keep)))
 
 
 def halo_workspace_bytes_q4(shape: Shape, T: int, k_keep: int) -> int:
-    return int(load_library().halo_workspace_bytes_q4(shape.ref, int(T), int(k_keep)))
+    return int(load_library().halo_workspace_bytes_q4(shape.c, int(T), int(k_keep)))
 
 
 def halo_predict_scores(shape: Shape, x, At, Bt, scores, workspace, stream=None) -> None:
     T = x.shape[0]
-    rc = load_library().halo_predict_scores(shape.ref, _ptr(x), T, _ptr(At), _ptr(Bt),
+    rc = load_library().halo_predict_scores(shape.c, _ptr(x), T, _ptr(At), _ptr(Bt),
                                             _ptr(scores), _ptr(workspace), workspace.numel(),
                                             _stream(stream))
     _check("halo_predict_scores", rc)
@@ -245,7 +243,7 @@ def halo_build_group_mask(scores, k_keep: int, prio_dev, n_dev: int, drop, mask,
 
 def halo_group_sparse_ffn(shape: Shape, x, Wg, Wu, Wd, mask, y, workspace, stream=None) -> None:
     T = x.shape[0]
-    rc = load_library().halo_group_sparse_ffn(shape.ref, _ptr(x), T, _ptr(Wg), _ptr(Wu),
+    rc = load_library().halo_group_sparse_ffn(shape.c, _ptr(x), T, _ptr(Wg), _ptr(Wu),
                                               _ptr(Wd), _ptr(mask), _ptr(y), _ptr(workspace),
                                               workspace.numel(), _stream(stream))
     _check("halo_group_sparse_ffn", rc)
@@ -257,7 +255,7 @@ def halo_ffn_forward(shape: Shape, x, At, Bt, Wg, Wu, Wd, k_keep: int, prio_dev,
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward(
-        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
+        shape.c, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order),
         _ptr(group_dev), _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _ptr(workspace),
         workspace.numel(), _stream(stream))
@@ -275,7 +273,7 @@ def halo_ffn_forward_static(shape: Shape, x, At, Bt, Wg, Wu, Wd, k_keep: int, pr
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward_static(
-        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
+        shape.c, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), _ptr(Wg), _ptr(Wu), _ptr(Wd),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order),
         _ptr(group_dev), _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _stream(stream))
     _check("halo_ffn_forward_static", rc)
@@ -287,7 +285,7 @@ def halo_ffn_forward_ahead(shape: Shape, x, Wg, Wu, Wd, mask_cur, y, x_pred_next
                            surv_idx_next=None, n_surv_next=None, stream=None) -> None:
     T = x.shape[0]
     rc = load_library().halo_ffn_forward_ahead(
-        shape.ref, _ptr(x), T, _ptr(Wg), _ptr(Wu), _ptr(Wd), _ptr(mask_cur), _ptr(y),
+        shape.c, _ptr(x), T, _ptr(Wg), _ptr(Wu), _ptr(Wd), _ptr(mask_cur), _ptr(y),
         _ptr(x_pred_next), _ptr(At_next), _ptr(Bt_next), int(k_keep), _ptr(prio_dev), int(n_dev),
         _ptr(drop_next), _ptr(scores_next), _ptr(order_next), _ptr(group_dev_next), _ptr(mask_next),
         _ptr(surv_idx_next), _ptr(n_surv_next), _ptr(workspace), workspace.numel(),
@@ -299,7 +297,7 @@ def halo_group_sparse_ffn_q4(shape: Shape, x, q4, mask, y, workspace, stream=Non
     """q4 = (Wg_codes, Wg_scales, Wu_codes, Wu_scales, Wd_codes, Wd_scales), see include/halo.h."""
     T = x.shape[0]
     rc = load_library().halo_group_sparse_ffn_q4(
-        shape.ref, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask), _ptr(y), _ptr(workspace),
+        shape.c, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask), _ptr(y), _ptr(workspace),
         workspace.numel(), _stream(stream))
     _check("halo_group_sparse_ffn_q4", rc)
 
@@ -310,7 +308,7 @@ def halo_ffn_forward_q4(shape: Shape, x, At, Bt, q4, k_keep: int, prio_dev, n_de
     T = x.shape[0]
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_ffn_forward_q4(
-        shape.ref, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), *[_ptr(t) for t in q4], int(k_keep),
+        shape.c, _ptr(x), _ptr(xp), T, _ptr(At), _ptr(Bt), *[_ptr(t) for t in q4], int(k_keep),
         _ptr(prio_dev), int(n_dev), _ptr(drop), _ptr(y), _ptr(scores), _ptr(order), _ptr(group_dev),
         _ptr(mask), _ptr(surv_idx), _ptr(n_surv), _ptr(workspace), workspace.numel(), _stream(stream))
     _check("halo_ffn_forward_q4", rc)
@@ -322,7 +320,7 @@ def halo_ffn_forward_ahead_q4(shape: Shape, x, q4, mask_cur, y, x_pred_next, At_
                               stream=None) -> None:
     T = x.shape[0]
     rc = load_library().halo_ffn_forward_ahead_q4(
-        shape.ref, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask_cur), _ptr(y), _ptr(x_pred_next),
+        shape.c, _ptr(x), T, *[_ptr(t) for t in q4], _ptr(mask_cur), _ptr(y), _ptr(x_pred_next),
         _ptr(At_next), _ptr(Bt_next), int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop_next),
         _ptr(scores_next), _ptr(order_next), _ptr(group_dev_next), _ptr(mask_next), _ptr(surv_idx_next),
         _ptr(n_surv_next), _ptr(workspace), workspace.numel(), _stream(stream))
@@ -330,14 +328,14 @@ def halo_ffn_forward_ahead_q4(shape: Shape, x, q4, mask_cur, y, x_pred_next, At_
 
 
 def halo_mha_workspace_bytes(shape: MhaShape, max_len: int) -> int:
-    return int(load_library().halo_mha_workspace_bytes(shape.ref, int(max_len)))
+    return int(load_library().halo_mha_workspace_bytes(shape.c, int(max_len)))
 
 
 def halo_head_sparse_mha(shape: MhaShape, x, Wq, Wk, Wv, Wo, k_cache, v_cache, pos: int, mask, y, workspace,
                          stream=None) -> None:
     """k_cache / v_cache: [n_heads][max_len][head_dim]; Wo head-blocked (pack_down_proj(WoT, head_dim))."""
     rc = load_library().halo_head_sparse_mha(
-        shape.ref, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
+        shape.c, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
         int(k_cache.shape[1]), int(pos), _ptr(mask), _ptr(y), _ptr(workspace), workspace.numel(), _stream(stream))
     _check("halo_head_sparse_mha", rc)
 
@@ -347,7 +345,7 @@ def halo_mha_forward(shape: MhaShape, x, At, Bt, Wq, Wk, Wv, Wo, k_cache, v_cach
                      group_dev=None, mask=None, surv_idx=None, n_surv=None, stream=None) -> None:
     xp = x if x_pred is None else x_pred
     rc = load_library().halo_mha_forward(
-        shape.ref, _ptr(x), _ptr(xp), _ptr(At), _ptr(Bt), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo),
+        shape.c, _ptr(x), _ptr(xp), _ptr(At), _ptr(Bt), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo),
         _ptr(k_cache), _ptr(v_cache), int(k_cache.shape[1]), int(pos), int(k_keep), _ptr(prio_dev), int(n_dev),
         _ptr(drop), _ptr(y), _ptr(scores), _ptr(order), _ptr(group_dev), _ptr(mask), _ptr(surv_idx),
         _ptr(n_surv), _ptr(workspace), workspace.numel(), _stream(stream))
@@ -359,7 +357,7 @@ def halo_mha_forward_ahead(shape: MhaShape, x, Wq, Wk, Wv, Wo, k_cache, v_cache,
                            workspace, scores_next=None, order_next=None, group_dev_next=None, surv_idx_next=None,
                            n_surv_next=None, stream=None) -> None:
     rc = load_library().halo_mha_forward_ahead(
-        shape.ref, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
+        shape.c, _ptr(x), _ptr(Wq), _ptr(Wk), _ptr(Wv), _ptr(Wo), _ptr(k_cache), _ptr(v_cache),
         int(k_cache.shape[1]), int(pos), _ptr(mask_cur), _ptr(y), _ptr(x_pred_next), _ptr(At_next), _ptr(Bt_next),
         int(k_keep), _ptr(prio_dev), int(n_dev), _ptr(drop_next), _ptr(scores_next), _ptr(order_next),
         _ptr(group_dev_next), _ptr(mask_next), _ptr(surv_idx_next), _ptr(n_surv_next), _ptr(workspace),

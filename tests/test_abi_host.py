@@ -1,8 +1,10 @@
 """Host-side checks of the C boundary that need no GPU: the library loads, exports every
 declared symbol, rejects bad arguments before touching the device, and its scheduler
 (host-only) agrees with the paper's example and with the oracle."""
+import copy
 import ctypes as C
 import os
+import pickle
 import re
 
 import numpy as np
@@ -33,6 +35,13 @@ def test_library_exports_every_declared_symbol():
             "halo_ffn_forward", "halo_build_schedule", "halo_workspace_bytes"} <= set(names)
     for n in names:
         assert getattr(lib, n) is not None
+
+
+@pytest.mark.parametrize("copied", [copy.copy, copy.deepcopy, lambda s: pickle.loads(pickle.dumps(s))])
+def test_shapes_can_be_copied_and_pickled(copied):
+    s, m = H.Shape(256, 1024, 128, 64, "f32"), H.MhaShape(1024, 8, 128, 64)
+    assert H.halo_workspace_bytes(copied(s), 4, 2) == H.halo_workspace_bytes(s, 4, 2) > 0
+    assert H.halo_mha_workspace_bytes(copied(m), 100) == H.halo_mha_workspace_bytes(m, 100) > 0
 
 
 def test_schedule_paper_example_and_oracle_agreement():

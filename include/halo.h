@@ -273,7 +273,8 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * Everything else -- mask semantics, workspace, stream, errors -- is as in
  * halo_group_sparse_ffn / halo_ffn_forward.  Tuned paths (bf16 activations, n_groups <= 256): one
  * token with d <= 8192 (every surviving code byte streamed once, float ALUs), 2..16
- * tokens with d <= 8192 (matrix cores, codes expanded in registers); other shapes and float32
+ * tokens with d <= 8192 (matrix cores, codes expanded in registers; the activation between the projections is rounded
+ * to bf16 where d is a multiple of 1024 and stays float32 at the other d); other shapes and float32
  * activations take a plain path that dequantises element by element.  More than 16 tokens (any d a multiple of
  * 128, any n_groups): with a workspace of halo_workspace_bytes_q4 the many-token matrix-core kernels, each value
  * s * (c - 8) rounded to bf16, to nearest even; with less, the 2..16-token kernels 16 tokens at a time where they take

@@ -1,6 +1,6 @@
 // Down projection over 4-bit block-quantised weights for a few tokens (2 <= T <= 16) on the matrix cores, activations in
 // bf16, and the launches of the whole FFN (paper Sec. V-A: the evaluated models are 4-bit; Sec. II-A neuron groups).  The
-// gate/up projection, and the down projection for activations of more than bf16, are in ffn_stream.hip.
+// gate/up projection, and the down projection for activations in float32, are in ffn_stream.hip.
 //
 // With four bits per weight the operand layout needs no re-shaping: v_mfma_f32_16x16x32_bf16 wants, in lane l, 8 elements
 // of row l%16 (A) and the same 8 elements of column l%16 (B), and WHICH 8 of a step's 32 elements lane group l/16 holds is
@@ -216,20 +216,21 @@ __global__ __launch_bounds__(WAVES * 64) void down_q4_mt(
     }
 }
 
-// Activations: bf16 where rows are whole multiples of 1024; for the other row lengths the sum of two bf16 values each, at most
-// 2^-17 of its value apart from the float32 that the plain path kept for them (the output's distance from 64 bits is the same,
-// 1.65e-3: its own rounding).  d 3200, 75 groups, 8 tokens 19 + 18 us; the plain path took 59 + 280 and a list of groups.
+// Rows that are whole multiples of 1024: activations in bf16.  The other row lengths: in float32 and with codes that need no
+// offset, as the plain path has them: activations are 0.79 .. 1.26e-7 from 64 bits over d 384 .. 8064 (theirs 0.81 .. 1.35e-7;
+// tokens' values of mean 0 or 1 alike).  Both projections, us: d 3200, 75 groups, 8 tokens 40, plain path 364; d 8064, 256 groups,
+// 16 tokens 161, plain 3084; d 1152, 27 groups, 2 tokens 19, plain 34.  (An offset and activations as the sum of two bf16 values:
+// 37, 140 and 17, but activations of 17 bits, and sums that cancel.)
 hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask,
                               bf16_t *y, const DecodeScratch &ws, hipStream_t s, const AheadArgs *ahead, bool *ahead_fused)
 {
     const int ffn = G * kQ4Block;
-    bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
     const AheadArgs *ah = (ahead && ahead_fused) ? ahead : nullptr;
     if (ahead_fused) *ahead_fused = ah != nullptr;
-    const size_t plane = d % 1024 == 0 ? 0 : (size_t)T * ffn;
-    const hipError_t e = launch_gate_up_q4_stream(x, T, d, G, w, mask, act, plane, s, ahead_pred_dev(ah));
+    const hipError_t e = launch_gate_up_q4_stream(x, T, d, G, w, mask, ws.act, s, ahead_pred_dev(ah));
     if (e != hipSuccess) return e;
-    if (plane) return launch_down_q4_planes(T, d, G, w, mask, act, plane, y, ah, s);
+    if (q4_few_tokens_exact(d)) return launch_down_q4_f32(T, d, G, w, mask, ws.act, y, ah, s);
+    const bf16_t *act = reinterpret_cast<const bf16_t *>(ws.act);
     const int n_mask = ah ? T : 0;
     const AheadDev nx = ah ? ahead_dev(*ah) : AheadDev{};
     // long rows: 32 rows to a workgroup of eight waves, so that the activations are read half as often

@@ -1,6 +1,6 @@
 // Few tokens (2 <= T <= 16) on the matrix cores, rows of any multiple of 128 up to 8192 (paper Sec. II-A neuron groups;
 // Sec. V-A 4-bit models): the gate/up projection over bf16 or 4-bit weights, and the down projection over 4-bit weights
-// with activations of more than bf16.
+// with activations in float32.
 //
 // The block is bound by streaming the union of the tokens' surviving groups from HBM, so everything else is kept out
 // of the way of that stream:
@@ -13,6 +13,8 @@
 // v_mfma_f32_16x16x32_bf16: A lane l = row l % 16 (a token), elements 8 (l / 16) .. + 7; B lane l = column l % 16, same
 // elements; D lane l = column l % 16, rows (tokens) 4 (l / 16) .. + 3.  Which 8 of the 32 elements a lane group holds is free
 // as long as A and B agree.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "mask_device.hpp"
 #include "mask_words.hpp"
@@ -67,17 +69,6 @@ __device__ __forceinline__ f32x4_t add_halves(const f32x4_t &v)
     return f32x4_t{xor_add<8>(v[0]), xor_add<8>(v[1]), xor_add<8>(v[2]), xor_add<8>(v[3])};
 }
 
-// activation v as one bf16 value, or (planes = 2) as the sum of two, 2^-18 of it apart from it at most
-__device__ __forceinline__ void store_act(bf16_t *__restrict__ act, size_t at, size_t plane, float v)
-{
-    const bf16_t hi = f32_to_bf16(v);
-    act[at] = hi;
-    if (plane) {
-        const float rest = v - to_float(hi);
-        act[plane + at] = rest - rest == 0.0f ? f32_to_bf16(rest) : (bf16_t)0;      // (infinities: all in the first)
-    }
-}
-
 // the fixed-order dot product of the predictor (dot_order64) for two rows of x against one of At, rows of up to NCH * 512
 // elements, eight chunks of all three requested at a time
 template <int NCH>
@@ -125,10 +116,15 @@ __device__ __forceinline__ void dot_order64_two(const bf16_t *__restrict__ x0, c
 // prediction on board, 59.3 -> 46 without; d 1152, 27 groups, 16 tokens 25.7 -> 11.7; bf16, d 2432, 66 groups, 8 tokens 26.1 ->
 // 18.2, 70B shape, 8 tokens 151.5 -> 142.4.  What bounds it: bf16, HBM (5.9 TB/s at the 70B shape); 4-bit, the stream (31 us of
 // it at the 70B shape) and the conversion of the codes side by side: with loads that move nothing it still takes 32.
-// 4-bit codes: c -> bf16 128 + c; a block's result, started at -136 * (sum of the tokens' values), is exact up to float
-// sums and meets the scale in float.
-template <bool Q4, int U>
+// 4-bit codes: a block's sum of products meets the scale in float.  Rows that are whole multiples of 1024 take a code as bf16
+// 128 + c and start a block at -136 * (sum of the tokens' values).  The others keep float32's precision (EXACT: such rows have
+// no other fast path): a code is c - 8, exactly, so that nothing has to cancel, and the activation is stored in float32.
+enum class Weights { Bf16, Codes, CodesExact };
+
+template <Weights W, int U>
 struct GateUpRing {
+    static constexpr bool Q4 = W != Weights::Bf16, EXACT = W == Weights::CodesExact;
+    typedef std::conditional_t<EXACT, float, bf16_t> Act;
     static constexpr int TR = Q4 ? 16 : 8;                       // rows of a tile
     static constexpr int L = Q4 ? 2 : 1;                         // load instructions per unit and matrix
     static constexpr int TB = Q4 ? (U == 1 ? 4 : U == 2 ? 2 : 1) : (U == 1 ? 8 : U == 2 ? 4 : U <= 4 ? 12 / U : U <= 6 ? 2 : 1);
@@ -151,19 +147,20 @@ __device__ __forceinline__ uint32_t cross8_lo(uint32_t keep, uint32_t take)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)keep, (int)take, 0x128, 0xf, 0x3, false);
 }
 
-template <bool Q4, int U>
+template <Weights W, int U>
 __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gate_up_stream(
     const bf16_t *__restrict__ x, int T, int d, int G, const void *__restrict__ Wg, const void *__restrict__ Wu,
-    const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const uint8_t *__restrict__ mask, bf16_t *__restrict__ act,
-    int act_stride, size_t plane, AheadPredDev ap)
+    const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const uint8_t *__restrict__ mask,
+    typename GateUpRing<W, U>::Act *__restrict__ act, int act_stride, AheadPredDev ap)
 {
-    using R = GateUpRing<Q4, U>;
+    using R = GateUpRing<W, U>;
+    constexpr bool Q4 = R::Q4, EXACT = R::EXACT, kOffset = Q4 && !EXACT;
     constexpr int TR = R::TR, L = R::L, TB = R::TB, NS = R::NS, kXF = R::kXF, kNCH = R::kNCH, kSums = R::kSums, gs = 128;
     constexpr int kElems = Q4 ? 256 : 64;                        // row elements of a unit
     static_assert((TB * U) % NS == 0, "a slot serves the same unit in every turn");
     extern __shared__ __attribute__((aligned(16))) float part[]; // [tile][wave][64 lanes][kSums]
     __shared__ KeepBits keep;
-    __shared__ __attribute__((aligned(16))) float s_off[Q4 ? kStreamWaves * U * 2 : 1][16];    // -136 * sum of x, [block][token]
+    __shared__ __attribute__((aligned(16))) float s_off[kOffset ? kStreamWaves * U * 2 : 1][16];    // -136 * sum of x, [block][token]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, q = lane >> 4, r = lane & 7, c = (lane >> 3) & 1;
@@ -272,7 +269,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
                                             u * (kElems * 2) + (Q4 ? (f >> 2) * 256 + (f & 3) * 16 : f * 64));
     }
     const Q4Consts qk = q4_consts();
-    if (Q4) {
+    if (kOffset) {
         // -136 * the sum of a token's values in a block: a matrix product with -136 everywhere (every column is the sum)
         const u32x4 m136 = {0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u};
 #pragma unroll
@@ -281,8 +278,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
             for (int b = 0; b < 2; ++b) {
                 f32x4_t s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int k = 0; k < 4; ++k) s = mfma16s(xf[u][(Q4 ? b * 4 + k : 0)], m136, s);
-                if (i16 == 0) *reinterpret_cast<f32x4_t *>(&s_off[(Q4 ? (wave * U + u) * 2 + b : 0)][4 * q]) = s;
+                for (int k = 0; k < 4; ++k) s = mfma16s(xf[u][(kOffset ? b * 4 + k : 0)], m136, s);
+                if (i16 == 0) *reinterpret_cast<f32x4_t *>(&s_off[(kOffset ? (wave * U + u) * 2 + b : 0)][4 * q]) = s;
             }
         // (a wave reads back its own entries only, and its LDS operations complete in order)
     }
@@ -306,15 +303,16 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
                     const uint32_t su = (uint32_t)__builtin_amdgcn_ds_bpermute((u * 16 + i16) * 4, (int)scale[tb].u);
                     f32x4_t tg[2], tu[2];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) tg[h] = tu[h] = *reinterpret_cast<const f32x4_t *>(&s_off[(wave * U + u) * 2 + h][4 * q]);
+                    for (int h = 0; h < 2; ++h)
+                        tg[h] = tu[h] = EXACT ? f32x4_t{0.f, 0.f, 0.f, 0.f} : *reinterpret_cast<const f32x4_t *>(&s_off[kOffset ? (wave * U + u) * 2 + h : 0][4 * q]);
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             const uint32_t vg = h ? cross8_lo(s.g[1][k], s.g[0][k]) : cross8_hi(s.g[0][k], s.g[1][k]);
                             const uint32_t vu = h ? cross8_lo(s.u[1][k], s.u[0][k]) : cross8_hi(s.u[0][k], s.u[1][k]);
-                            tg[h] = mfma16s(xf[u][h * 4 + k], q4_word_bf16(vg, qk), tg[h]);
-                            tu[h] = mfma16s(xf[u][h * 4 + k], q4_word_bf16(vu, qk), tu[h]);
+                            tg[h] = mfma16s(xf[u][h * 4 + k], EXACT ? q4_word_signed(vg) : q4_word_bf16(vg, qk), tg[h]);
+                            tu[h] = mfma16s(xf[u][h * 4 + k], EXACT ? q4_word_signed(vu) : q4_word_bf16(vu, qk), tu[h]);
                         }
                     }
 #pragma unroll
@@ -386,39 +384,53 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int t = 4 * tq + e;
-            if (t < T) store_act(act, (size_t)t * act_stride + n, plane, keep.keeps(t, g) ? silu_mul(gt[e], up[e]) : 0.0f);
+            const float f = EXACT ? kQ4Signed : 1.0f;
+            if (t < T) store_out(act + (size_t)t * act_stride + n, keep.keeps(t, g) ? silu_mul(f * gt[e], f * up[e]) : 0.0f);
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// down over 4-bit weights, activations in two planes: n_mask + up to 256 workgroups of eight waves
+// down over 4-bit weights, activations in float32: n_mask + up to 256 workgroups of eight waves
 // ---------------------------------------------------------------------------
 // The output rows are dealt over the workgroups in eights, at most RT tiles of sixteen to a workgroup; the waves take every
 // eighth of the union's groups and meet in LDS.  A tile's codes of a group are 1 KiB of consecutive bytes, one load, in operand
-// order.  The activations that face a group are fetched once for all of the workgroup's tiles, in operand order too.
-// FOLD (at most eight tokens): rows 8 .. 15 of the token operand are the second plane, one operand and one matrix instruction
-// for both; otherwise two of each.
-// Every workgroup reads all of the activations, T * 512 bytes per group: with eight tokens four times the bytes of the
-// codes that a tile brings, from L2, and that is what bounds the kernel (d 3200, 75 groups, 8 tokens 18 us; without the codes
-// 18, without the activations 10).
+// order, and so are the activations that face them: a lane's 32 floats of its token.  An activation is multiplied as the sum of three
+// bf16 values, its leading, middle and trailing eight bits -- all 24 of them -- with codes that are c - 8 exactly, so that float32 sums are
+// the only rounding.
 // The first n_mask workgroups do not project: each computes the next block's scores, ranking and mask for one token (paper
-// Sec. III-B.3, one layer ahead; dispatched first, it is the longest dependent chain).  DEPTH groups are in flight per wave, as
-// many as leave room for two workgroups on a compute unit: a mask workgroup that holds one for itself costs its length.
-template <int RT, bool FOLD>
+// Sec. III-B.3, one layer ahead; dispatched first, it is the longest dependent chain).  DEPTH groups are in flight per wave.
+template <int RT>
 struct DownStep {
-    static constexpr int PLANES = FOLD ? 1 : 2, DEPTH = FOLD ? (RT == 1 ? 4 : 3) : 2;
-    u32x4 w[RT], a[PLANES][4];
+    static constexpr int DEPTH = 2;
+    u32x4 w[RT];
+    f32x4_t a[8];
     uint32_t sc[RT];
 };
 
-template <int RT, bool FOLD>
-__global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_planes(
-    int T, int d, int G, const uint32_t *__restrict__ Dq, const bf16_t *__restrict__ Ds, const uint8_t *__restrict__ mask,
-    const bf16_t *__restrict__ act, int act_stride, size_t plane, bf16_t *__restrict__ y, int n_mask, AheadDev nx)
+// eight floats as the sum of three times eight bf16 values
+__device__ __forceinline__ void split3(const f32x4_t &lo, const f32x4_t &hi, u32x4 (&piece)[3])
 {
-    using Step = DownStep<RT, FOLD>;
-    constexpr int gs = 128, PLANES = Step::PLANES, DEPTH = Step::DEPTH;
+    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t top = __builtin_amdgcn_perm(__float_as_uint(v[2 * i + 1]), __float_as_uint(v[2 * i]), 0x07060302u);
+            piece[p][i] = top;
+            const float a = bf16_lo(top), b = bf16_hi(top);      // (of an infinity nothing is left)
+            v[2 * i] = p == 0 && v[2 * i] == a ? 0.0f : v[2 * i] - a;
+            v[2 * i + 1] = p == 0 && v[2 * i + 1] == b ? 0.0f : v[2 * i + 1] - b;
+        }
+}
+
+template <int RT>
+__global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
+    int T, int d, int G, const uint32_t *__restrict__ Dq, const bf16_t *__restrict__ Ds, const uint8_t *__restrict__ mask,
+    const float *__restrict__ act, int act_stride, bf16_t *__restrict__ y, int n_mask, AheadDev nx)
+{
+    using Step = DownStep<RT>;
+    constexpr int gs = 128, DEPTH = Step::DEPTH;
     struct Proj {
         KeepBits keep;
         int list[256];
@@ -448,10 +460,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_planes(
     if (wave == 0) write_group_list(uw, lane, sh.list);
     __syncthreads();
     const int n_u = uw.count;
-    const Q4Consts qk = q4_consts();
     const __amdgpu_buffer_rsrc_t bw = buffer_of(Dq), bs = buffer_of(Ds), ba = buffer_of(act), none = buffer_of(Dq, 0);
-    const int tok = FOLD ? i16 & 7 : i16;                        // rows past the last token repeat it, unused
-    const uint32_t at_act = ((uint32_t)(FOLD && i16 >= 8 ? plane : 0) + (tok < T ? tok : T - 1) * act_stride + q * 32) * 2;
+    const uint32_t at_act = (uint32_t)((i16 < T ? i16 : T - 1) * act_stride + q * 32) * 4;    // rows past the last token repeat it, unused
     uint32_t at_w[RT], at_s[RT];                                 // this lane's bytes of a group's block and of its scales
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -473,34 +483,32 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_planes(
             s.sc[rt] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, at_s[rt], g * (uint32_t)d * 2, 0);
         }
 #pragma unroll
-        for (int p = 0; p < PLANES; ++p)
-#pragma unroll
-            for (int f = 0; f < 4; ++f)                          // word f of the lane group's four
-                s.a[p][f] = buffer_load16<0>(ba, at_act, (uint32_t)(p * plane + (yes ? u : n_u - 1) * gs) * 2 + f * 16);
+        for (int f = 0; f < 8; ++f)                              // half word f of the lane's eight
+            s.a[f] = __builtin_bit_cast(f32x4_t, buffer_load16<0>(ba, at_act, (uint32_t)((yes ? u : n_u - 1) * gs) * 4 + f * 16));
     };
     f32x4_t acc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto consume = [&](const Step &s) {
-        // -136 * the sum of a token's activations of the group: a matrix product with -136 everywhere
-        const u32x4 m136 = {0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u};
-        f32x4_t off = {0.f, 0.f, 0.f, 0.f};
+        f32x4_t t[RT];
 #pragma unroll
-        for (int p = 0; p < PLANES; ++p)
+        for (int rt = 0; rt < RT; ++rt) t[rt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) off = mfma16s(s.a[p][k], m136, off);
+        for (int k = 0; k < 4; ++k) {                            // word k: eight elements
+            u32x4 piece[3];
+            split3(s.a[2 * k], s.a[2 * k + 1], piece);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const u32x4 v = q4_word_signed(s.w[rt][k]);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) t[rt] = mfma16s(piece[p], v, t[rt]);
+            }
+        }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            f32x4_t t = off;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32x4 v = q4_word_bf16(s.w[rt][k], qk);
-#pragma unroll
-                for (int p = 0; p < PLANES; ++p) t = mfma16s(s.a[p][k], v, t);
-            }
             const float f = bf16_lo(s.sc[rt]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[rt][e] = __builtin_fmaf(f, t[e], acc[rt][e]);
+            for (int e = 0; e < 4; ++e) acc[rt][e] = __builtin_fmaf(f, t[rt][e], acc[rt][e]);
         }
     };
     if (wave < n_u) {
@@ -525,11 +533,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_planes(
         if (t >= T || rt * 16 + rr >= nrows) continue;
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kStreamWaves; ++w) {
-            v += sh.part[w][rt][(t >> 2) * 16 + rr][t & 3];
-            if (FOLD) v += sh.part[w][rt][((t + 8) >> 2) * 16 + rr][t & 3];
-        }
-        y[(size_t)t * d + row0 + rt * 16 + rr] = f32_to_bf16(v);
+        for (int w = 0; w < kStreamWaves; ++w) v += sh.part[w][rt][(t >> 2) * 16 + rr][t & 3];
+        y[(size_t)t * d + row0 + rt * 16 + rr] = f32_to_bf16(kQ4Signed * v);
     }
 }
 
@@ -541,21 +546,20 @@ bool stream_path_supported(int T, int d, int G, int gs)
     return T >= 2 && T <= kStreamTokens && gs == 128 && d % 128 == 0 && d <= 8192 && G <= 256;
 }
 
-template <bool Q4, int U>
+template <Weights W, int U>
 static hipError_t launch_gate_up(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const bf16_t *Sg,
-                                 const bf16_t *Su, const uint8_t *mask, bf16_t *act, size_t plane, const AheadPredDev &ap,
-                                 hipStream_t s)
+                                 const bf16_t *Su, const uint8_t *mask, void *act, const AheadPredDev &ap, hipStream_t s)
 {
     // room for the sums of every tile that a workgroup can have
-    using R = GateUpRing<Q4, U>;
+    using R = GateUpRing<W, U>;
     const auto bytes = [](int groups) {
         return (size_t)((groups * 128 + kStreamBlocks - 1) / kStreamBlocks + R::TR - 1) / R::TR * kStreamWaves * 64 * R::kSums * sizeof(float);
     };
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(gate_up_stream<Q4, U>),
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(gate_up_stream<W, U>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes(256));
     if (lds_ok != hipSuccess) return lds_ok;
-    launch_timed_lds(Q4 ? "gate_up_q4_stream" : "gate_up_stream", gate_up_stream<Q4, U>, dim3(kStreamBlocks), dim3(kStreamWaves * 64),
-                     bytes(G), s, x, T, d, G, Wg, Wu, Sg, Su, mask, act, G * 128, plane, ap);
+    launch_timed_lds(R::Q4 ? "gate_up_q4_stream" : "gate_up_stream", gate_up_stream<W, U>, dim3(kStreamBlocks), dim3(kStreamWaves * 64),
+                     bytes(G), s, x, T, d, G, Wg, Wu, Sg, Su, mask, (typename R::Act *)act, G * 128, ap);
     return hipGetLastError();
 }
 
@@ -563,7 +567,7 @@ hipError_t launch_gate_up_stream(const bf16_t *x, int T, int d, int G, const bf1
                                  bf16_t *act, hipStream_t s, const AheadPredDev &ap)
 {
 #define HALO_CASE(U) \
-    case U: return launch_gate_up<false, U>(x, T, d, G, Wg, Wu, nullptr, nullptr, mask, act, 0, ap, s)
+    case U: return launch_gate_up<Weights::Bf16, U>(x, T, d, G, Wg, Wu, nullptr, nullptr, mask, act, ap, s)
     const int units = (d / 64 + kStreamWaves - 1) / kStreamWaves;
     switch (units > 12 ? (units + 1) / 2 * 2 : units) {
         HALO_CASE(1);
@@ -585,38 +589,48 @@ hipError_t launch_gate_up_stream(const bf16_t *x, int T, int d, int G, const bf1
 #undef HALO_CASE
 }
 
-hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *act,
-                                    size_t plane, hipStream_t s, const AheadPredDev &ap)
+bool q4_few_tokens_exact(int d) { return d % 1024 != 0; }
+
+hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, void *act,
+                                    hipStream_t s, const AheadPredDev &ap)
 {
-#define HALO_CASE(U) \
-    case U: return launch_gate_up<true, U>(x, T, d, G, w.gate_codes, w.up_codes, w.gate_scales, w.up_scales, mask, act, plane, ap, s)
-    switch ((d + 2047) / 2048) {
-        HALO_CASE(1);
-        HALO_CASE(2);
-        HALO_CASE(3);
-        HALO_CASE(4);
+#define HALO_CASE(W, U) \
+    case U: return launch_gate_up<W, U>(x, T, d, G, w.gate_codes, w.up_codes, w.gate_scales, w.up_scales, mask, act, ap, s)
+    const int units = (d + 2047) / 2048;
+    if (q4_few_tokens_exact(d)) {
+        switch (units) {
+            HALO_CASE(Weights::CodesExact, 1);
+            HALO_CASE(Weights::CodesExact, 2);
+            HALO_CASE(Weights::CodesExact, 3);
+            HALO_CASE(Weights::CodesExact, 4);
+        default: return hipErrorInvalidValue;
+        }
+    }
+    switch (units) {
+        HALO_CASE(Weights::Codes, 1);
+        HALO_CASE(Weights::Codes, 2);
+        HALO_CASE(Weights::Codes, 3);
+        HALO_CASE(Weights::Codes, 4);
     default: return hipErrorInvalidValue;
     }
 #undef HALO_CASE
 }
 
-template <int RT, bool FOLD>
-static hipError_t launch_planes(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const bf16_t *act, size_t plane,
-                                bf16_t *y, const AheadArgs *ah, hipStream_t s)
+template <int RT>
+static hipError_t launch_down_f32(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
+                                  const AheadArgs *ah, hipStream_t s)
 {
     const int n_mask = ah ? T : 0, blocks = d / 8 < kStreamBlocks ? d / 8 : kStreamBlocks;
-    down_q4_planes<RT, FOLD><<<dim3(blocks + n_mask), dim3(kStreamWaves * 64), 0, s>>>(
-        T, d, G, w.down_codes, w.down_scales, mask, act, G * 128, plane, y, n_mask, ah ? ahead_dev(*ah) : AheadDev{});
+    down_q4_f32<RT><<<dim3(blocks + n_mask), dim3(kStreamWaves * 64), 0, s>>>(
+        T, d, G, w.down_codes, w.down_scales, mask, act, G * 128, y, n_mask, ah ? ahead_dev(*ah) : AheadDev{});
     return hipGetLastError();
 }
 
-hipError_t launch_down_q4_planes(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const bf16_t *act, size_t plane,
-                                 bf16_t *y, const AheadArgs *ah, hipStream_t s)
+hipError_t launch_down_q4_f32(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
+                              const AheadArgs *ah, hipStream_t s)
 {
-    const bool one = (d / 8 + kStreamBlocks - 1) / kStreamBlocks <= 2, fold = T <= 8;       // at most 16 rows to a workgroup
-    if (one)
-        return fold ? launch_planes<1, true>(T, d, G, w, mask, act, plane, y, ah, s) : launch_planes<1, false>(T, d, G, w, mask, act, plane, y, ah, s);
-    return fold ? launch_planes<2, true>(T, d, G, w, mask, act, plane, y, ah, s) : launch_planes<2, false>(T, d, G, w, mask, act, plane, y, ah, s);
+    const bool one = (d / 8 + kStreamBlocks - 1) / kStreamBlocks <= 2;       // at most 16 rows to a workgroup
+    return one ? launch_down_f32<1>(T, d, G, w, mask, act, y, ah, s) : launch_down_f32<2>(T, d, G, w, mask, act, y, ah, s);
 }
 
 }  // namespace halo

@@ -155,11 +155,12 @@ hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weig
 bool stream_path_supported(int T, int d, int G, int gs);
 hipError_t launch_gate_up_stream(const bf16_t *x, int T, int d, int G, const bf16_t *Wg, const bf16_t *Wu, const uint8_t *mask,
                                  bf16_t *act, hipStream_t s, const AheadPredDev &ap);
-// plane: 0 = activations as one bf16 value each; otherwise as the sum of two, the second `plane` elements behind the first
-hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *act,
-                                    size_t plane, hipStream_t s, const AheadPredDev &ap);
-hipError_t launch_down_q4_planes(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const bf16_t *act, size_t plane,
-                                 bf16_t *y, const AheadArgs *ah, hipStream_t s);
+// 4-bit weights: act is float32 with codes that need no offset where q4_few_tokens_exact, else bf16
+bool q4_few_tokens_exact(int d);
+hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, void *act,
+                                    hipStream_t s, const AheadPredDev &ap);
+hipError_t launch_down_q4_f32(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
+                              const AheadArgs *ah, hipStream_t s);
 
 // mha_decode.hip : head-sparse attention for one new token (bf16, head dimension 128)
 struct MhaScratch {

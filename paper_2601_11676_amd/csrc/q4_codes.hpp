@@ -47,6 +47,24 @@ __device__ __forceinline__ u32x4 q4_word_bf16(uint32_t w, const Q4Consts &k)
                  ((w >> 12) & k.mask) | k.one28};
 }
 
+// the eight elements of a word as eight bf16 values (c - 8) / 16 in element order, exactly: v_cvt_off_f32_i4 takes a two's
+// complement nibble to sixteenths, and such a float's upper half is its bf16 value.  Twice the instructions of the offset form
+// above; nothing has to cancel in the sums.  (The word shifted by four first: the others are whole bytes of the two, which the
+// conversion selects by itself.)
+constexpr float kQ4Signed = 16.0f;
+__device__ __forceinline__ u32x4 q4_word_signed(uint32_t w)
+{
+    const uint32_t even = w ^ 0x88888888u, odd = even >> 4;
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t n = i % 2 ? odd : even;
+        const float lo = __builtin_amdgcn_cvt_off_f32_i4((n >> (i / 2 * 8)) & 0xffu), hi = __builtin_amdgcn_cvt_off_f32_i4((n >> (16 + i / 2 * 8)) & 0xffu);
+        v[i] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+    }
+    return v;
+}
+
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 }  // namespace halo

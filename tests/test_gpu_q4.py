@@ -209,6 +209,68 @@ def test_few_tokens_of_any_row_length(q4, T, d, G, r):
         assert np.array_equal(hz.to_np32(y).astype(np.float64), g["y"]) and np.array_equal(mn.cpu().numpy(), gn["mask"])
 
 
+def _pack_codes(k):
+    """integers -8 .. 7 [..., n] -> words [..., n / 8] of codes k + 8 in the storage order"""
+    c = (np.asarray(k, np.int64) + 8).reshape(*k.shape[:-1], -1, 8)
+    shift = [4 * (e // 2) + 16 * (e % 2) for e in range(8)]
+    return sum(c[..., e] << shift[e] for e in range(8)).astype(np.uint32).view(np.int32)
+
+
+@pytest.mark.parametrize("what", ["sums", "activations"])
+@pytest.mark.parametrize("T,d", [(2, 384), (8, 1152), (16, 5248), (37, 640)])
+def test_q4_few_tokens_of_any_row_length_keep_float32(what, T, d):
+    # Rows that are no multiple of 1024: sums over c - 8 in float32, the activation in float32.  y is bf16, so results are made
+    # small beside what they are summed from.  sums: the tokens' values have a mean of 1, and a row's products cancel (to a few
+    # hundredths of the largest); y is a neuron's activation.  activations: y is the difference of two that share 12 leading bits.
+    _say(f"q4 precision {what} T={T} d={d}")
+    rng = np.random.default_rng(17)
+    G = 2
+    kg, ku, kd = np.zeros((G * 128, d), np.int64), np.zeros((G * 128, d), np.int64), np.zeros((G, d, 128), np.int64)
+    m = np.arange(G * 128)
+    if what == "sums":
+        x = torch.from_numpy(rng.normal(1, 1, d).astype(np.float32)).to(torch.bfloat16).float().numpy().astype(np.float64)
+        kg[m, rng.choice(np.flatnonzero(np.abs(x) > 0.5), G * 128)] = 4
+        ku[:] = rng.integers(-1, 2, ku.shape)
+        for _ in range(40):                        # the code whose change by one brings each row's sum nearest to 0
+            u = ku @ x
+            step = np.abs(np.stack([np.where(ku < 1, u[:, None] + x, np.inf), np.where(ku > -1, u[:, None] - x, np.inf)]))
+            best = step.transpose(1, 0, 2).reshape(G * 128, -1)
+            at = best.argmin(1)
+            better = best.min(1) < np.abs(u)
+            ku[m[better], at[better] % d] += np.where(at[better] < d, 1, -1)
+        kd[m // 128, m, m % 128] = 1
+    else:
+        x = np.zeros(d)
+        x[[3, 130, 258]] = 1.0, 2.0 ** -10, 2.0 ** -13
+        kg[:, 3] = np.repeat(rng.integers(1, 8, G), 128)
+        ku[:, 3], ku[:, 130], ku[:, 258] = 7, rng.integers(-7, 8, G * 128), rng.integers(-7, 8, G * 128)
+        j = np.arange(G * 64)
+        kd[j // 64, j, j % 64], kd[j // 64, j, 64 + j % 64] = 1, -1
+    xs = np.stack([x * 2.0 ** -(t % 3) for t in range(T)])
+    ones = lambda *n: torch.ones(n, dtype=torch.bfloat16, device=hz.DEV)
+    q4 = tuple(w for k in (kg, ku) for w in (torch.from_numpy(_pack_codes(k)).to(hz.DEV), ones(G * 128, d // 128)))
+    q4 += (torch.from_numpy(_pack_codes(kd)).to(hz.DEV), ones(G, d))
+    s = H.Shape(d, G * 128, 128, 64, "bf16")
+    ws = torch.empty(H.halo_workspace_bytes(s, T, G), dtype=torch.uint8, device=hz.DEV)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+    H.halo_group_sparse_ffn_q4(s, torch.from_numpy(xs).to(torch.bfloat16).to(hz.DEV), q4,
+                               torch.ones((T, G), dtype=torch.uint8, device=hz.DEV), y, ws)
+    torch.cuda.synchronize()
+    yg = hz.to_np32(y).astype(np.float64)
+    yc = ref.group_sparse_ffn(xs, *ref.dequant_ffn_q4([q.float().cpu().numpy() if q.dtype == torch.bfloat16 else q.cpu().numpy() for q in q4]),
+                              128, np.ones((T, G), np.uint8))
+    # y's own rounding, 2^-8; the activation function's, well below 2^-18; and 2^-24 of what a sum is made of at each of its
+    # roundings: in gate/up at most 20 (four steps of a block, eight blocks of a wave, eight waves), of an activation two and its sums
+    gate = xs @ kg.T
+    silu = np.abs(gate / (1 + np.exp(-gate)))
+    part = 20 * silu * (np.abs(xs) @ np.abs(ku).T) if what == "sums" else 6 * silu * np.abs(xs @ ku.T)
+    bound = (2.0 ** -8 + 2.0 ** -18) * np.abs(yc)
+    for g in range(G):
+        bound += 2.0 ** -24 * part[:, g * 128:(g + 1) * 128] @ np.abs(kd[g]).T
+    worst = (np.abs(yg - yc)[bound > 0] / bound[bound > 0]).max()
+    assert worst <= 1 and not yg[bound == 0].any(), f"worst error {worst:.3f} of the bound"
+
+
 @pytest.mark.parametrize("d,T,r,G,K", [
     (4096, 1, 256, 20, 10), (8192, 1, 256, 20, 10), (512, 3, 256, 20, 10), (5120, 4, 256, 20, 10),
     (8192, 8, 256, 20, 10), (384, 3, 256, 20, 10),

@@ -73,16 +73,18 @@ struct PairSum {
 
 // NT: token tiles of 16 per workgroup.  grid (ffn / 16, ceil(T / (16 NT)))
 // A wave takes every eighth pair of pieces, 128 bytes of a row: with single pieces dealt out, two waves asked for the halves
-// of every cache line.  DEPTH pieces are in flight, the first ones requested beside the mask bytes that say whether anybody
-// wants them, and no load stands behind a condition.  (d 616, 13 groups, 36 tokens 13.2 -> 7.4 us, half of it because two token
-// tiles to a workgroup, not four, leave no compute unit idle; d 1000, 24 groups, 60 tokens 16.6 -> 16.2, either number of tiles.
+// of every cache line.  A pair is in flight (two: d 4096, 16 groups, 5 tokens 33.0 -> 38.0 us for both projections, 128 wide and 8
+// groups, 16 tokens 9.6 -> 10.0), and no load stands behind a condition.  (d 616, 13 groups, 36 tokens 13.2 -> 7.4 us, half of it because
+// two token tiles to a workgroup, not four, leave no compute unit idle; d 1000, 24 groups, 60 tokens 16.6 -> 16.2, either number of tiles.
 // Chunks of 128 elements through LDS, as in the down projection: 4.5 us at the tiny block, but 10 and 21 at these two.)
-template <int NT>
-__global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
+// ASK, for the few tokens that leave groups unwanted: the first loads wait for the mask bytes, and a compute unit takes one workgroup, so
+// that those that leave at once do not pair the others up.  Else the first pair is requested beside the mask bytes.
+template <int NT, bool ASK>
+__global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2, ASK ? 2 : 8))) void gate_up_f32(
     const float *__restrict__ x, int T, int d, int G, int gs, const float *__restrict__ Wg, const float *__restrict__ Wu,
     const uint8_t *__restrict__ mask, float *__restrict__ act, size_t group_stride, int token_stride)
 {
-    constexpr int W = kGateUpF32Waves, DEPTH = NT == 1 ? 4 : 2;
+    constexpr int W = kGateUpF32Waves;
     __shared__ f32x4_t part[W][2][NT][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 15, q = lane >> 4;
@@ -106,29 +108,27 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
 #pragma unroll
         for (int n = 0; n < NT; ++n) b.x[n] = load4(bx, ok ? at_x[n] : kOutOfRange, p * 64);
     };
-    Piece b[DEPTH];
+    const bool wanted_by_any = __ballot(mine != 0) != 0ull;      // uniform: the same bytes in every wave
+    if (ASK && !wanted_by_any) return;
+    Piece b[2];
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k) fetch(b[k], 2 * (wave + W * (k / 2)) + k % 2);
-    if (__ballot(mine != 0) == 0ull) return;                     // uniform: the same bytes in every wave
+    for (int k = 0; k < 2; ++k) fetch(b[k], 2 * wave + k);
+    if (!ASK && !wanted_by_any) return;
     f32x4_t cg[NT], cu[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) cg[n] = cu[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     PairSum<NT> sg, su;
-    for (int p = 2 * wave; p < np; p += W * DEPTH) {
+    for (int p = 2 * wave; p < np; p += 2 * W) {
+        sg.clear();
+        su.clear();
 #pragma unroll
-        for (int k = 0; k < DEPTH; ++k) {
-            if (k % 2 == 0) {
-                sg.clear();
-                su.clear();
-            }
+        for (int k = 0; k < 2; ++k) {
             sg.add(b[k].g, b[k].x);
             su.add(b[k].u, b[k].x);
-            fetch(b[k], p + W * (k / 2 * 2 + DEPTH) + k % 2);
-            if (k % 2 == 1) {
-                sg.fold(cg);
-                su.fold(cu);
-            }
+            fetch(b[k], p + 2 * W + k);
         }
+        sg.fold(cg);
+        su.fold(cu);
     }
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) void gate_up_f32(
 // 16-byte slot of one of the two per group, four groups go through LDS at a time and four more are on their way; wave w multiplies
 // pieces 2 w and 2 w + 1 of the 32.  (In operand order a load was 64 bytes of sixteen rows, and a compute unit's loads took
 // several times as long as their bytes: tiny block 7.2 -> 5.8 us, d 504, 20 groups, 25 tokens 18.8 -> 9.9, d 1000, 24 groups, 60
-// tokens 22.5 -> 13.2, one token 10.0 -> 7.6.)  The first eight groups are requested beside the mask bytes and used if the mask says so;
+// tokens 22.5 -> 13.2.)  The first eight groups are requested beside the mask bytes and used if the mask says so;
 // the rest comes from the list of the other groups that are kept.
 constexpr int kTurn = 4, kFirst = 2 * kTurn;
 
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32_128(
     }
 }
 
-// Groups of any multiple of 16 neurons, act[t][ffn].  grid (ceil(d / 16), ceil(T / (16 NT))); reads act of the groups that a token of its own range keeps
+// Groups of any multiple of 16 neurons, and of 128 where that is the better one (see launch_ffn_f32), act[t][ffn].  grid (ceil(d / 16), ceil(T / (16 NT))); reads act of the groups that a token of its own range keeps
 template <int NT>
 __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32(
     const float *__restrict__ act, int ffn, int T, int d, int G, int gs, const float *__restrict__ Wd,
@@ -366,13 +366,12 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32(
 // (offsets within a workgroup's rows have 32 bits)
 bool f32_path_supported(int d, int gs) { return gs % 16 == 0 && d <= 1 << 22; }
 
-template <int NT>
+template <int NT, bool ASK = false>
 static void launch_gate_up(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu,
-                           const uint8_t *mask, float *act, hipStream_t s)
+                           const uint8_t *mask, float *act, bool by_group, hipStream_t s)
 {
     const int ffn = G * gs;
-    const bool by_group = gs == 128;                             // how the down projection wants it
-    launch_timed("gate_up_f32", gate_up_f32<NT>, dim3(ffn / 16, (T + 16 * NT - 1) / (16 * NT)), dim3(kGateUpF32Waves * 64), s,
+    launch_timed("gate_up_f32", gate_up_f32<NT, ASK>, dim3(ffn / 16, (T + 16 * NT - 1) / (16 * NT)), dim3(kGateUpF32Waves * 64), s,
                  x, T, d, G, gs, Wg, Wu, mask, act, by_group ? (size_t)T * gs : (size_t)gs, by_group ? gs : ffn);
 }
 
@@ -387,15 +386,17 @@ static void launch_down(const float *act, int T, int d, int G, int gs, const flo
 // The weights are read once per range of tokens (from L2 after the first).  A range of down lies within one of gate/up, so the
 // groups it walks have been written.  nt: token tiles of a workgroup in gate/up.
 static hipError_t launch_blocks(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
-                                const uint8_t *mask, float *y, float *act, int nt, hipStream_t s)
+                                const uint8_t *mask, float *y, float *act, int nt, bool ask, bool by_group, hipStream_t s)
 {
-    if (nt == 1)
-        launch_gate_up<1>(x, T, d, G, gs, Wg, Wu, mask, act, s);
+    if (ask)
+        launch_gate_up<1, true>(x, T, d, G, gs, Wg, Wu, mask, act, by_group, s);
+    else if (nt == 1)
+        launch_gate_up<1>(x, T, d, G, gs, Wg, Wu, mask, act, by_group, s);
     else if (nt == 2)
-        launch_gate_up<2>(x, T, d, G, gs, Wg, Wu, mask, act, s);
+        launch_gate_up<2>(x, T, d, G, gs, Wg, Wu, mask, act, by_group, s);
     else
-        launch_gate_up<4>(x, T, d, G, gs, Wg, Wu, mask, act, s);
-    if (gs == 128)
+        launch_gate_up<4>(x, T, d, G, gs, Wg, Wu, mask, act, by_group, s);
+    if (by_group)
         down_f32_128<<<dim3((d + 15) / 16, (T + 15) / 16), dim3(kDownF32Waves * 64), 0, s>>>(act, T, d, G, Wd, mask, y);
     else if (nt == 1)
         launch_down<1>(act, T, d, G, gs, Wd, mask, y, s);
@@ -409,12 +410,21 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
 {
     // four token tiles to a workgroup read the weights least often, two where four would leave compute units without one
     const int nt = T <= 16 ? 1 : T <= 32 || (long long)((T + 63) / 64) * (G * gs / 16) < 256 ? 2 : 4;
-    const int run = gs == 128 ? 1 << 19 : 1 << 20;               // ranges of tokens are a grid's y, which ends at 65535
-    for (int t0 = 0;; t0 += run) {
+    // Up to five tokens leave groups unwanted, and what is asked for before the mask is known is wasted: both projections, groups of
+    // 128, half of them kept, us, asked for at once / after the mask: one token, d 256, 8 groups 10.3 / 8.4, d 1000, 24 groups 17.4 / 14.8,
+    // d 2048, 44 groups 37.9 / 25.3, d 8192, 64 groups 126 / 109; four tokens 10.8 / 10.2, 21.5 / 20.5, 46.4 / 43.5, 156 / 152.
+    const bool ask = T <= 5;
+    // down_f32_128 asks for its first eight groups at once (up to eight groups it pays from nine tokens on: 128 wide, three tenths kept,
+    // five tokens 9.6 against 8.8 us, eight 9.5 / 9.6), and reads Wd once per 16 tokens, down_f32 once per 32: of many tokens it takes those
+    // that give no compute unit more than one workgroup (d 1000, 24 groups, 64 tokens 34 against 43 us, 128 57 / 55, 512 176 / 168;
+    // d 256, 8 groups, 256 tokens 14.3 / 17.4, 512 25.0 / 24.2; d 4096, 86 groups, 512 tokens 2299 / 2181).
+    const bool by_group = gs == 128 && !ask && (G > 8 || T > 8) && (T <= 64 || (long long)((d + 15) / 16) * ((T + 15) / 16) <= 256);
+    constexpr int kRun = 1 << 20;                                // ranges of tokens are a grid's y, which ends at 65535
+    for (int t0 = 0;; t0 += kRun) {
         const size_t t = (size_t)t0;
-        const hipError_t e = launch_blocks(x + t * d, T - t0 < run ? T - t0 : run, d, G, gs, Wg, Wu, Wd, mask + t * G, y + t * d,
-                                           act + t * G * gs, nt, s);
-        if (e != hipSuccess || T - t0 <= run) return e;
+        const hipError_t e = launch_blocks(x + t * d, T - t0 < kRun ? T - t0 : kRun, d, G, gs, Wg, Wu, Wd, mask + t * G, y + t * d,
+                                           act + t * G * gs, nt, ask, by_group, s);
+        if (e != hipSuccess || T - t0 <= kRun) return e;
     }
 }
 

@@ -643,7 +643,11 @@ def test_float32_tiles(T, d, G, gs):
     (17, 128, 5, 264),         # two turns, the second of one group; a token tile of one token
     (33, 264, 9, 64),          # the first group of the list
     (64, 520, 33, 256),        # 33 groups of 128: mask workgroups of 128 and 256 threads, and past them
-    (5, 1000, 65, 512),        # 65 rows of Bt to a workgroup of 1024
+    (5, 1000, 65, 512),        # 65 rows of Bt to a workgroup of 1024; the most tokens that ask for nothing before the mask is known
+    (6, 24, 9, 64),            # a token more: eight groups at once
+    (9, 40, 3, 64),            # ... of no more groups than that
+    (70, 1000, 9, 64),         # more than one workgroup per compute unit: 32 tokens to a workgroup of the down projection
+    (130, 24, 12, 64),         # more than 64 tokens, and fewer
 ])
 def test_float32_groups_of_128(T, d, G, r):
     w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=72)

@@ -35,13 +35,24 @@ def test_grids_of_very_many_tokens_stay_within_the_limits():
     # the recorder refuses more than 65535 workgroups in y, as a device may
     scores, ffn = [1048560, 1048561, 1048576, 5000000], [2097121, 2100000, 4194304, 4200000]
     calls = [dict(fn="predict_scores", shape=(8, 8, 128, 8, BF16), T=T) for T in scores]
-    calls += [dict(fn="group_sparse_ffn", shape=(8, 2, 16, 8, F32), T=T) for T in ffn]
+    calls += [dict(fn="group_sparse_ffn", shape=(8, 2, gs, 8, F32), T=T) for T in ffn for gs in (16, 128)]
     for c, (rc, _, launches) in zip(calls, record(calls)):
         assert rc == 0, (c, launches)
         # every token is covered: rows per workgroup of the kernels
         for name, rows in [("scores_mfma", 16), ("gate_up_f32", 64), ("down_f32", 32)]:
             runs = [y for n, _, y, _, _ in launches if name in n]
             assert not runs or (sum(runs) - 1) * rows < c["T"] <= sum(runs) * rows, (c, launches)
+
+
+def test_float32_projections_by_the_number_of_tokens():
+    # groups of 128: what is asked for before the mask is known, and the form of the down projection
+    for T, d, G, ask, down in [(1, 1024, 24, True, "down_f32ILi1E"), (5, 256, 8, True, "down_f32ILi1E"), (6, 256, 9, False, "down_f32_128"),
+                               (8, 256, 8, False, "down_f32ILi1E"), (9, 256, 8, False, "down_f32_128"), (64, 8192, 64, False, "down_f32_128"),
+                               (65, 816, 24, False, "down_f32_128"), (65, 824, 24, False, "down_f32ILi2E"), (512, 128, 8, False, "down_f32_128"),
+                               (512, 256, 8, False, "down_f32ILi2E")]:
+        (rc, _, launches), = record([dict(fn="group_sparse_ffn", shape=(d, G, 128, 64, F32), T=T)])
+        assert rc == 0 and len(launches) == 2 and down in launches[1][0], (T, d, G, launches)
+        assert ("gate_up_f32ILi1ELb1E" in launches[0][0]) == ask, (T, d, G, launches)
 
 
 def test_first_predictor_layer_by_the_number_of_results():

@@ -291,6 +291,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
             if (Q4) scale_next[tb] = load_scales(t0 + TB + tb);
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
+            // The last turn's tiles that do not exist are left out: without this they were multiplied, all zeros (what they would
+            // ask for does not exist either).  Both projections, 4-bit, d 1024, 27 groups, 2 tokens 16.0 -> 13.9 us, d 2048, 44 groups
+            // 17.9 -> 16.2; bf16, d 1536, 20 groups, 5 tokens 15.7 -> 14.9.
+            if (TB > 1 && t0 + tb >= ntile) break;
             f32x4_t ag[2], au[2];                                // 4-bit: [0] only
 #pragma unroll
             for (int h = 0; h < 2; ++h) ag[h] = au[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
                     load(s, row_next[(jn - TB * U) / U], jn % U);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (t0 + tb < ntile) {
+            {
                 float *dst = part + (((t0 + tb) * kStreamWaves + wave) * 64 + lane) * kSums;
                 if (Q4) {
                     *reinterpret_cast<f32x4_t *>(dst) = ag[0];

@@ -162,8 +162,7 @@ static hipError_t launch_exact(const bf16_t *x, int G, int gs, const bf16_t *Wg,
                                const AheadPredDev &ap)
 {
     constexpr size_t lds = (size_t)T * (NCH * 512 + 8) * sizeof(bf16_t);
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(gate_up_ft<NCH, T>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t lds_ok = allow_lds<gate_up_ft<NCH, T>>(lds);
     if (lds_ok != hipSuccess) return lds_ok;
     launch_timed_lds("gate_up_ft", gate_up_ft<NCH, T>, dim3(256 + ap.n_pred), dim3(256), lds, s, x, G, gs, Wg, Wu,
                      mask, act, act_stride, ap);

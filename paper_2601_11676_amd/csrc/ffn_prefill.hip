@@ -1104,18 +1104,11 @@ bool prefill_path_supported(int T, int d, int gs)
     return T > 1 && d % 128 == 0 && gs == 128 && (size_t)T * d * sizeof(bf16_t) < (1ull << 31);
 }
 
-// LDS beyond 64 KiB has to be asked for once per kernel
-template <typename F>
-static hipError_t allow_lds(F kernel, int bytes)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
-
 template <bool Q4, int NTOK>
 static hipError_t launch_gate_up_ring(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const bf16_t *Sg,
                                       const bf16_t *Su, const DecodeScratch &ws, bf16_t *act, hipStream_t s)
 {
-    static const hipError_t lds_ok = allow_lds(gate_up_pf_ring<Q4, NTOK>, Ring<Q4, NTOK>::kBytes);
+    const hipError_t lds_ok = allow_lds<gate_up_pf_ring<Q4, NTOK>>(Ring<Q4, NTOK>::kBytes);
     if (lds_ok != hipSuccess) return lds_ok;
     const int items_max = 2 * G * ((T + NTOK - 1) / NTOK);                  // every group kept by every token
     launch_timed_lds("gate_up_pf_ring", gate_up_pf_ring<Q4, NTOK>, dim3((items_max + 7) / 8 * 8), dim3(kRingWaves * 64),
@@ -1135,7 +1128,7 @@ static hipError_t launch_down_ring(int T, int d, int G, int splits, const void *
                                    const bf16_t *act, bf16_t *y, hipStream_t s)
 {
     constexpr int bytes = down_ring_bytes<Q4, NTOK>();
-    static const hipError_t lds_ok = allow_lds(down_pf_ring<Q4, NTOK>, bytes);
+    const hipError_t lds_ok = allow_lds<down_pf_ring<Q4, NTOK>>(bytes);
     if (lds_ok != hipSuccess) return lds_ok;
     const int items = (d / 128) * ((T + NTOK - 1) / NTOK) * splits;
     down_pf_ring<Q4, NTOK><<<dim3((items + 7) / 8 * 8), dim3(kRingWaves * 64), bytes, s>>>(
@@ -1155,7 +1148,7 @@ static bool gate_up_big_tiles(int T, int G) { return (long long)G * (T + 256) > 
 static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const bf16_t *Wg, const bf16_t *Wu,
                                      const DecodeScratch &ws, bf16_t *act, hipStream_t s)
 {
-    static const hipError_t lds_ok = allow_lds(gate_up_pf_big, 5 * kBigStage);
+    const hipError_t lds_ok = allow_lds<gate_up_pf_big>(5 * kBigStage);
     if (lds_ok != hipSuccess) return lds_ok;
     launch_timed_lds("gate_up_pf_big", gate_up_pf_big, dim3((G * ((T + 255) / 256) + 7) / 8 * 8),
                      dim3(kRingWaves * 64), 5 * kBigStage, s, x, T, d, G, Wg, Wu, (const int32_t *)ws.tok_list, (const int32_t *)ws.tok_cnt, act);

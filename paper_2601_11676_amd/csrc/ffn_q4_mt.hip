@@ -237,9 +237,7 @@ hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weig
     const bool wide = d >= 8192 && d % 32 == 0;
 #define HALO_DOWN_Q4(TM, TILES, WAVES, GB)                                                                       \
     do {                                                                                                         \
-        static const hipError_t lds_ok = hipFuncSetAttribute(                                                    \
-            reinterpret_cast<const void *>(down_q4_mt<TM, TILES, WAVES, GB>), hipFuncAttributeMaxDynamicSharedMemorySize, \
-            (int)q_down_lds_bytes(16, WAVES, GB, TILES));                                                               \
+        const hipError_t lds_ok = allow_lds<down_q4_mt<TM, TILES, WAVES, GB>>((int)q_down_lds_bytes(16, WAVES, GB, TILES));   \
         if (lds_ok != hipSuccess) return lds_ok;                                                                 \
         down_q4_mt<TM, TILES, WAVES, GB><<<dim3(d / (16 * TILES) + n_mask), dim3(WAVES * 64), q_down_lds_bytes(T, WAVES, GB, TILES), s>>>( \
             T, d, G, w.down_codes, w.down_scales, mask, act, ffn, y, n_mask, nx);                                \

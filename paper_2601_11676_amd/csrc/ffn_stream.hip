@@ -559,8 +559,7 @@ static hipError_t launch_gate_up(const bf16_t *x, int T, int d, int G, const voi
     const auto bytes = [](int groups) {
         return (size_t)((groups * 128 + kStreamBlocks - 1) / kStreamBlocks + R::TR - 1) / R::TR * kStreamWaves * 64 * R::kSums * sizeof(float);
     };
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(gate_up_stream<W, U>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes(256));
+    const hipError_t lds_ok = allow_lds<gate_up_stream<W, U>>((int)bytes(256));
     if (lds_ok != hipSuccess) return lds_ok;
     launch_timed_lds(R::Q4 ? "gate_up_q4_stream" : "gate_up_stream", gate_up_stream<W, U>, dim3(kStreamBlocks), dim3(kStreamWaves * 64),
                      bytes(G), s, x, T, d, G, Wg, Wu, Sg, Su, mask, (typename R::Act *)act, G * 128, ap);

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_ext.h>
 
+#include <atomic>
+
 #include "common.hpp"
 
 namespace halo {
@@ -175,6 +177,22 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
                              const void *Wo, void *k_cache, void *v_cache, int max_len, int pos,
                              const uint8_t *mask, void *y, const MhaScratch &ws, hipStream_t s,
                              const AheadArgs *ahead = nullptr, bool *ahead_fused = nullptr);
+
+// A kernel's dynamic LDS beyond 64 KiB has to be allowed, on each GPU that is to run it: asked for by the first launch with that
+// device current.
+template <auto Kernel>
+inline hipError_t allow_lds(int bytes)
+{
+    static std::atomic<uint64_t> allowed{0};                     // a bit per device; past 63 every call asks
+    int dev = 0;
+    const hipError_t got = hipGetDevice(&dev);
+    if (got != hipSuccess) return got;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+    if (allowed.load(std::memory_order_acquire) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) allowed.fetch_or(bit, std::memory_order_release);
+    return e;
+}
 
 // profile.hip : optional HIP-event bracket around the dominant FFN kernel
 bool timer_acquire(hipEvent_t *start, hipEvent_t *stop);   // false: not profiling (or pool used up)

@@ -169,8 +169,7 @@ template <int TT, int JT, int BUFS>
 static hipError_t launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
     constexpr int lds = BUFS * 16 * (TT + JT) * kHidRow;
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(hidden_mfma_kernel<TT, JT, BUFS>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t lds_ok = allow_lds<hidden_mfma_kernel<TT, JT, BUFS>>(lds);
     if (lds_ok != hipSuccess) return lds_ok;
     const int n_tt = (T + 16 * TT - 1) / (16 * TT), n_jt = (r + 16 * JT - 1) / (16 * JT);
     hidden_mfma_kernel<TT, JT, BUFS><<<dim3((n_tt * n_jt + 7) / 8 * 8), dim3(kHidWaves * 64), lds, s>>>(x, At, h, T, d, r, n_tt, n_jt);

@@ -13,7 +13,7 @@ LIB = os.path.join(os.path.dirname(HERE), "paper_2601_11676_amd", "libhalo.so")
 
 def record(calls):
     """calls: dicts with fn (an entry point without its halo_ prefix), shape (d, n_groups, group_size, rank, dtype 0 | 1), T, K
-    and, where it is not the queried one, ws (bytes).  Returns per call (status, workspace bytes, [(kernel, grid x, y, z, threads)])."""
+    and, where it is not the queried one, ws (bytes), and where it is not 0, device (up to 7).  Returns per call (status, workspace bytes, [(kernel, grid x, y, z, threads)])."""
     with tempfile.TemporaryDirectory() as tmp:
         shim = os.path.join(tmp, "recorder.so")
         subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(HERE, "launch_recorder.c")], check=True)
@@ -35,6 +35,7 @@ def _child(shim):
     for c in json.load(sys.stdin):
         d, G, gs, rank, dtype = c["shape"]
         shape = C.byref((C.c_int32 * 6)(d, G * gs, gs, G, rank, dtype))
+        recorder.recorder_device(c.get("device", 0))
         T, K, fn = C.c_int32(c["T"]), C.c_int32(c.get("K", 0)), c["fn"]
         q4 = fn.endswith("_q4")
         size = lib.halo_workspace_bytes_q4 if q4 else lib.halo_workspace_bytes

@@ -44,6 +44,15 @@ def test_grids_of_very_many_tokens_stay_within_the_limits():
             assert not runs or (sum(runs) - 1) * rows < c["T"] <= sum(runs) * rows, (c, launches)
 
 
+def test_more_lds_is_allowed_on_each_device():
+    # kernels with more than 64 KiB of dynamic LDS, launched with one device current and then with another
+    calls = [dict(fn="predict_scores", shape=(4096, 8, 128, 512, BF16), T=40, device=dev) for dev in (0, 1, 0, 7)]
+    calls += [dict(fn=fn, shape=(d, 20, 128, 64, BF16), T=T, K=4, device=dev) for dev in (0, 1, 0, 7)
+              for fn in ("ffn_forward", "ffn_forward_q4") for d in (8192, 3200) for T in (4, 16, 40, 300)]
+    for c, (rc, _, launches) in zip(calls, record(calls)):
+        assert rc == 0 and launches, (c, rc, launches)
+
+
 def test_float32_projections_by_the_number_of_tokens():
     # groups of 128: what is asked for before the mask is known, and the form of the down projection
     for T, d, G, ask, down in [(1, 1024, 24, True, "down_f32ILi1E"), (5, 256, 8, True, "down_f32ILi1E"), (6, 256, 9, False, "down_f32_128"),

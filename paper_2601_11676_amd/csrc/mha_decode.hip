@@ -380,14 +380,14 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
 // ---------------------------------------------------------------------------
 // output projection that merges the heads' partial softmaxes itself: up to nine of them, up to 64 heads
 // ---------------------------------------------------------------------------
-// Every workgroup merges all surviving heads into LDS, n_surv * chunks * 520 bytes from L2, while its rows of Wo for 24 heads are
-// on their way; that takes the place of a launch of its own.  Three blocks captured into a graph, us, merged in a launch of
-// its own / here: d 1024, 8 heads, 120 to 2000 cached rows 47.8 .. 49.8 / 40.6 .. 44.2, 4400 54.3 / 51.5; d 2048, 16 heads, 339 rows 55.4 /
-// 48.3, 2000 56.6 / 53.0; d 3200, 25 heads, 339 rows 78.2 / 76.5; d 4096, 32 heads, 339 rows 87.2 / 81.9, 900 88.7 / 86.7; d 5120,
-// 40 heads, 900 rows 121.1 / 116.0.  Where a thread has several heads' worth to merge the projection waits longer than the launch
-// took: d 3200, 900 rows 80.0 / 81.9, d 4096, 2000 rows 93.3 / 94.9, d 8192, 2000 rows 242.9 / 246.4.  So up to 16 heads are merged
-// here whenever nine chunks of up to 512 positions hold the cache; more heads while heads times chunks of up to 256 stay within 192
-// with the activations in bf16, and up to three chunks with them in float32.
+// Every workgroup merges all surviving heads into LDS, n_surv * chunks * 520 bytes from L2, while its rows of Wo for the first heads are
+// on their way; that takes the place of a launch of its own.  A block without the next one's prediction, captured into a graph, us,
+// merged in a launch of its own / here: d 1024, 8 heads, 120 to 2000 cached rows 14.1 .. 14.9 / 11.6 .. 13.7, 16 heads, 4400 19.4 / 17.5;
+// d 2048, 16 heads, 339 rows 17.5 / 15.3, 2000 18.3 / 17.2; d 3200, 25 heads, 339 rows 23.9 / 22.0; d 4096, 32 heads, 339 rows
+// 28.3 / 27.0; d 7168, 56 heads, 300 rows 65.2 / 59.6.  Where a thread has several heads' worth to merge the projection waits longer than
+// the launch took (three blocks: d 3200, 900 rows 80.0 / 81.9, d 4096, 2000 rows 93.3 / 94.9, d 8192, 2000 rows 242.9 / 246.4).  So up to
+// 16 heads are merged here whenever nine chunks of up to 512 positions hold the cache; more heads while heads times chunks of up to 256
+// stay within 192 with the activations in bf16, and up to three chunks with them in float32.
 constexpr int kMergeChunks = 9, kMergeHeads = 64;
 
 template <typename AT>
@@ -425,7 +425,9 @@ __global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const 
     const __amdgpu_buffer_rsrc_t bw = buffer_of(Wo), bp = buffer_of(part);
     const uint32_t at_w = (uint32_t)((EXACT ? row : min(row, d - 1)) * dh + piece) * 2;
     const int my_head = sh.down.list[lane];                      // at most 64: one to a lane
-    constexpr int kB = 4;                                        // three batches in flight: 24 heads between the two halves
+    // three batches in flight: 24 heads between the two halves, 18 with activations in float32 (with 24 that form spilled 19 registers:
+    // d 1024, 8 heads, 339 rows 12.5 -> 11.9 us, d 7168, 56 heads, 300 rows 64.0 -> 59.6; d 3200, 40 heads, 300 rows 29.1 -> 29.5)
+    constexpr int kB = sizeof(AT) == 4 ? 3 : 4;
     auto fetch = [&](u32x4 (&v)[kB], int u0) {
 #pragma unroll
         for (int q = 0; q < kB; ++q) {

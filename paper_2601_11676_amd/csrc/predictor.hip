@@ -40,14 +40,13 @@ __global__ __launch_bounds__(256) void dot_rows_kernel(const XT *__restrict__ X,
 // workgroup holds all 64 partial sums of its (16 JT rows of At) x (16 TT tokens); distances 32 and 16 are
 // then additions between a lane's own blocks, 8 .. 1 go through LDS once at the end.
 // Nothing is spent on lane-crossing sums per result (half of the instructions of a wave-per-row form).
-// Rows go straight to LDS a step of 512 elements at a time (a load: one row's 1 KiB; a row is padded by 16 bytes so
-// that 16 rows' pieces fall into different banks), two to four steps of them, and a step's fragments are read
-// while the matrix instructions of the step before run, so that the barrier between two steps has work on both sides.
-// The matrix instruction bounds it: 1000 tokens, d = 8192, rank 512 take 98 us, 91 with loads that move nothing, 50 without the
-// matrix instructions.  (With the rows passed through registers, eight waves of two partial sums and the fragments read
-// behind the barrier 107.)  Both layers, 256 tokens, d = 8192, rank 128: 18.5 -> 17.2 us; 160 tokens, d = 5120, rank 256 13.6 -> 12.9;
-// rows of one step are 0.1 us slower.  Two buffers, and nothing asked for past the end, where the walk has at most four steps: with
-// four buffers d = 1536, 160 tokens, rank 512 12.4 against 12.0, d = 2048 2 % and d = 512 7 % more.
+// Rows go to LDS a step of 512 elements at a time (a load: one row's 1 KiB; a row is padded by 16 bytes so that 16 rows'
+// pieces fall into different banks).  BUFS >= 2: straight there, into that many buffers, and a step's fragments are read while the matrix
+// instructions of the step before run, so that the barrier between two steps has work on both sides.  BUFS = 1: through registers
+// into two buffers, a step's fragments read behind its barrier.  BUFS = 0, rows of up to two steps: fragments straight from memory.
+// launch_hidden_mfma's caller says which is the faster where.  The longest walk, 1000 tokens, d = 8192, rank 512, takes 87 us with
+// the second layer (107 through registers, eight waves of two partial sums): the matrix instruction needs 66 of them at the 130
+// TFLOP/s that it reaches alone; with loads that move nothing a few less, so the rest is the conversions and LDS reads beside it.
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kHidRow = 1024 + 16;          // padded LDS row, bytes
 constexpr int kHidWaves = 16;
@@ -58,8 +57,7 @@ __global__ __launch_bounds__(kHidWaves * 64) __attribute__((amdgpu_waves_per_eu(
     int n_tt, int n_jt)
 {
     constexpr int kTiles = TT * JT, kSets = TT + JT, kRows = 16 * kSets, kStage = kRows * kHidRow;
-    static_assert(BUFS >= 2 && kTiles * 16 * 1024 <= BUFS * kStage, "the sums fit");
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // BUFS of: TT * 16 token rows, then JT * 16 rows of At
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];   // BUFS of: TT * 16 token rows, then JT * 16 rows of At; at the end the sums
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     // a die (workgroups are dealt round-robin to eight) takes consecutive items, the rows of At fastest: its
     // token rows stay in its L2
@@ -68,70 +66,122 @@ __global__ __launch_bounds__(kHidWaves * 64) __attribute__((amdgpu_waves_per_eu(
     if (slot >= per_die || item >= n_items) return;
     const int t0 = (item / n_jt) * 16 * TT, j0 = (item % n_jt) * 16 * JT;
     const int nk = (d + 511) / 512;
-    // this wave loads row `wave` of every set of 16; rows past the end repeat the last one (never stored)
-    const srd_t srd_x = make_srd(X + (size_t)t0 * d, true), srd_a = make_srd(At + (size_t)j0 * d, true);
-    uint32_t row_at[kSets];
-#pragma unroll
-    for (int n = 0; n < kSets; ++n)
-        row_at[n] = (uint32_t)(n < TT ? min(wave + 16 * n, T - 1 - t0) : min(wave + 16 * (n - TT), r - 1 - j0)) * (uint32_t)d * 2;
-    const uint32_t lds0 = (uint32_t)(size_t)lds + wave * kHidRow;
-    auto load = [&](int n, int k, int buf) {                     // its row of set n, step k; zeros past the row's or the walk's end
-        const uint32_t at = k * 512 + lane * 8 < d ? lane * 16u : kNoRow;     // (d is a multiple of 8; 0 * 0 leaves a chain as it is)
-        load_to_lds16(n < TT ? srd_x : srd_a, at, k < nk ? row_at[n] + k * 1024u : 0u, lds0 + buf * kStage + n * 16 * kHidRow);
-    };
     const int i = lane & 15, b = lane >> 4;
     u32x4 raw[2][kSets];
-    auto read = [&](u32x4 (&f)[kSets], int buf) {
-        const unsigned char *piece = lds + buf * kStage + i * kHidRow + (wave + 16 * b) * 16;
-#pragma unroll
-        for (int n = 0; n < kSets; ++n) f[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow);
-    };
     f32x16_t acc[kTiles];
 #pragma unroll
     for (int n = 0; n < kTiles; ++n)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[n][e] = 0.0f;
+    auto multiply = [&](const u32x4 (&cur)[kSets], int e) {      // element e of the fragments
+        float f[kSets];
 #pragma unroll
-    for (int k = 0; k < BUFS; ++k)
+        for (int n = 0; n < kSets; ++n) f[n] = e % 2 == 0 ? bf16_lo(cur[n][e / 2]) : bf16_hi(cur[n][e / 2]);
+#pragma unroll
+        for (int n = 0; n < kTiles; ++n)
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(f[TT + n % JT], f[n / JT], acc[n], 0, 0, 0);
+    };
+    if constexpr (BUFS == 0) {
+        // rows of up to two steps: all of the wave's fragments straight from memory, requested together
+        const __amdgpu_buffer_rsrc_t rx = buffer_of(X + (size_t)t0 * d), ra = buffer_of(At + (size_t)j0 * d);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int n = 0; n < kSets; ++n) {
+                const uint32_t row = n < TT ? min(i + 16 * n, T - 1 - t0) : min(i + 16 * (n - TT), r - 1 - j0), at = k * 512 + (wave + 16 * b) * 8;
+                raw[k][n] = buffer_load16<0>(n < TT ? rx : ra, at < (uint32_t)d ? (row * d + at) * 2 : kOutOfRange, 0);
+            }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (k < nk) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) multiply(raw[k], e);
+            }
+    } else {
+        // this wave loads row `wave` of every set of 16; rows past the end repeat the last one (never stored)
+        uint32_t row_at[kSets];
 #pragma unroll
         for (int n = 0; n < kSets; ++n)
-            if (BUFS > 2 || k < nk) load(n, k, k);
-    if (BUFS > 2 || nk > 1)
-        wait_loads<(BUFS - 1) * kSets>();
-    else
-        wait_loads<0>();
-    __syncthreads();
-    read(raw[0], 0);
-    int buf = 0;                                                 // buffer of step k
-    // At the top of step k its fragments are in registers.  The barrier says that step k + 1 has landed and that everybody has
-    // read step k, whose buffer is then handed to step k + BUFS.
-    auto step = [&](const u32x4 (&cur)[kSets], u32x4 (&next)[kSets], int k) __attribute__((always_inline)) {
-        const int nbuf = buf == BUFS - 1 ? 0 : buf + 1;
-        if (BUFS > 2 || k + 1 < nk) {
-            wait_loads<(BUFS - 2) * kSets>();
+            row_at[n] = (uint32_t)(n < TT ? min(wave + 16 * n, T - 1 - t0) : min(wave + 16 * (n - TT), r - 1 - j0)) * (uint32_t)d * 2;
+        auto read = [&](u32x4 (&f)[kSets], int buf) {
+            const unsigned char *piece = lds + buf * kStage + i * kHidRow + (wave + 16 * b) * 16;
+#pragma unroll
+            for (int n = 0; n < kSets; ++n) f[n] = *reinterpret_cast<const u32x4 *>(piece + n * 16 * kHidRow);
+        };
+        if constexpr (BUFS == 1) {
+            // through registers, into two buffers: step k is multiplied, step k + 1 goes to LDS beside it, step k + 2 is asked for behind it
+            const __amdgpu_buffer_rsrc_t rx = buffer_of(X + (size_t)t0 * d), ra = buffer_of(At + (size_t)j0 * d);
+            u32x4 v[kSets];
+            auto fetch = [&](int k) {
+                const uint32_t at = k * 512 + lane * 8;          // (d is a multiple of 8; 0 * 0 leaves a chain as it is)
+#pragma unroll
+                for (int n = 0; n < kSets; ++n) v[n] = buffer_load16<0>(n < TT ? rx : ra, at < (uint32_t)d ? row_at[n] + at * 2 : kOutOfRange, 0);
+            };
+            auto park = [&](int k, int n) {
+                *reinterpret_cast<u32x4 *>(lds + (k & 1) * kStage + (n * 16 + wave) * kHidRow + lane * 16) = v[n];
+            };
+            fetch(0);
+#pragma unroll
+            for (int n = 0; n < kSets; ++n) park(0, n);
+            fetch(1);
+            for (int k = 0; k < nk; ++k) {
+                __syncthreads();                                 // step k is in LDS, step k - 1 is used up
+                read(raw[0], k & 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    multiply(raw[0], e);
+                    if (e < kSets) park(k + 1, e);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                fetch(k + 2);
+            }
+            __syncthreads();
+        } else {
+            const srd_t srd_x = make_srd(X + (size_t)t0 * d, true), srd_a = make_srd(At + (size_t)j0 * d, true);
+            const uint32_t lds0 = (uint32_t)(size_t)lds + wave * kHidRow;
+            auto load = [&](int n, int k, int buf) {                     // its row of set n, step k; zeros past the row's or the walk's end
+                const uint32_t at = k * 512 + lane * 8 < d ? lane * 16u : kNoRow;
+                load_to_lds16(n < TT ? srd_x : srd_a, at, k < nk ? row_at[n] + k * 1024u : 0u, lds0 + buf * kStage + n * 16 * kHidRow);
+            };
+#pragma unroll
+            for (int k = 0; k < BUFS; ++k)
+#pragma unroll
+                for (int n = 0; n < kSets; ++n)
+                    if (BUFS > 2 || k < nk) load(n, k, k);
+            if (BUFS > 2 || nk > 1)
+                wait_loads<(BUFS - 1) * kSets>();
+            else
+                wait_loads<0>();
+            __syncthreads();
+            read(raw[0], 0);
+            int buf = 0;                                                 // buffer of step k
+            // At the top of step k its fragments are in registers.  The barrier says that step k + 1 has landed and that everybody has
+            // read step k, whose buffer is then handed to step k + BUFS.
+            auto step = [&](const u32x4 (&cur)[kSets], u32x4 (&next)[kSets], int k) __attribute__((always_inline)) {
+                const int nbuf = buf == BUFS - 1 ? 0 : buf + 1;
+                if (BUFS > 2 || k + 1 < nk) {
+                    wait_loads<(BUFS - 2) * kSets>();
+                    __syncthreads();
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    multiply(cur, e);
+                    if (e == 0 && (BUFS > 2 || k + 1 < nk)) read(next, nbuf);
+                    if (e >= 1 && e - 1 < kSets && (BUFS > 2 || k + 2 < nk)) load(e - 1, k + BUFS, buf);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                buf = nbuf;
+            };
+            for (int k = 0; k < nk; k += 2) {
+                step(raw[0], raw[1], k);
+                if (k + 1 < nk) step(raw[1], raw[0], k + 1);
+            }
+            wait_loads<0>();                                             // (of loads that move zeros)
             __syncthreads();
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float f[kSets];
-#pragma unroll
-            for (int n = 0; n < kSets; ++n) f[n] = e % 2 == 0 ? bf16_lo(cur[n][e / 2]) : bf16_hi(cur[n][e / 2]);
-#pragma unroll
-            for (int n = 0; n < kTiles; ++n)
-                acc[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(f[TT + n % JT], f[n / JT], acc[n], 0, 0, 0);
-            if (e == 0 && (BUFS > 2 || k + 1 < nk)) read(next, nbuf);
-            if (e >= 1 && e - 1 < kSets && (BUFS > 2 || k + 2 < nk)) load(e - 1, k + BUFS, buf);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        buf = nbuf;
-    };
-    for (int k = 0; k < nk; k += 2) {
-        step(raw[0], raw[1], k);
-        if (k + 1 < nk) step(raw[1], raw[0], k + 1);
     }
-    wait_loads<0>();                                             // (of loads that move zeros)
-    __syncthreads();
     // distances 32 and 16: blocks (0, 2) and (1, 3); result element 4 b + m of a lane is block b, row 4 (lane / 16) + m,
     // token lane % 16
     f32x4_t *sums = reinterpret_cast<f32x4_t *>(lds);            // [l][tile][lane]
@@ -168,7 +218,7 @@ __global__ __launch_bounds__(kHidWaves * 64) __attribute__((amdgpu_waves_per_eu(
 template <int TT, int JT, int BUFS>
 static hipError_t launch_hidden_mfma(const bf16_t *x, int T, int d, int r, const bf16_t *At, float *h, hipStream_t s)
 {
-    constexpr int lds = BUFS * 16 * (TT + JT) * kHidRow;
+    constexpr int kStages = (BUFS == 1 ? 2 : BUFS) * 16 * (TT + JT) * kHidRow, kSums = TT * JT * 16 * 1024, lds = kStages > kSums ? kStages : kSums;
     const hipError_t lds_ok = allow_lds<hidden_mfma_kernel<TT, JT, BUFS>>(lds);
     if (lds_ok != hipSuccess) return lds_ok;
     const int n_tt = (T + 16 * TT - 1) / (16 * TT), n_jt = (r + 16 * JT - 1) / (16 * JT);
@@ -275,12 +325,21 @@ static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t
 {
     if (T < 16 || (long long)T * r < 14 * 1024 || d > 1 << 24) return false;   // (rows are addressed with 32-bit offsets)
     const int n_tt = (T + 31) / 32;
+    // How the rows come (both layers, us): up to 768 elements straight to registers, 32 tokens, rank 512, d 512 5.5 against 5.6 and 5.7, d 768
+    // 6.1 against 6.4 and 6.7, but d 1024 6.5 against 6.4; tiles of one by one through registers up to 3072, 128 tokens, rank 256, d 1024
+    // 6.8 against 7.1 (loads to two buffers) to 7.5 (four), d 2048 8.4 against 8.7 and 8.9, d 3072 10.0 against 10.3, d 4096 11.6
+    // against 11.7, but 32 tokens, rank 512, d 8192 17.5 against 16.4; loads to LDS in the larger tiles, 1000 tokens, rank 512, d 1024 25.2
+    // against 23.9, d 8192 94 against 87.
     if (n_tt * ((r + 31) / 32) >= 256)
-        e = launch_hidden_mfma<2, 2, 2>(x, T, d, r, At, h, s);
+        e = d <= 768 ? launch_hidden_mfma<2, 2, 0>(x, T, d, r, At, h, s) : launch_hidden_mfma<2, 2, 2>(x, T, d, r, At, h, s);
     else if (n_tt * ((r + 15) / 16) >= 256)
-        e = d <= 2048 ? launch_hidden_mfma<2, 1, 2>(x, T, d, r, At, h, s) : launch_hidden_mfma<2, 1, 3>(x, T, d, r, At, h, s);
+        e = d <= 768    ? launch_hidden_mfma<2, 1, 0>(x, T, d, r, At, h, s)
+            : d <= 2048 ? launch_hidden_mfma<2, 1, 2>(x, T, d, r, At, h, s)
+                        : launch_hidden_mfma<2, 1, 3>(x, T, d, r, At, h, s);
     else
-        e = d <= 2048 ? launch_hidden_mfma<1, 1, 2>(x, T, d, r, At, h, s) : launch_hidden_mfma<1, 1, 4>(x, T, d, r, At, h, s);
+        e = d <= 768    ? launch_hidden_mfma<1, 1, 0>(x, T, d, r, At, h, s)
+            : d <= 3072 ? launch_hidden_mfma<1, 1, 1>(x, T, d, r, At, h, s)
+                        : launch_hidden_mfma<1, 1, 4>(x, T, d, r, At, h, s);
     return true;
 }
 static bool hidden_rows_tiled(const float *, int, int, int, const float *, float *, hipStream_t, hipError_t &) { return false; }

@@ -582,6 +582,8 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     (16, 8, 1024, "1x1"), (16, 512, 1024, "1x1"), (16, 1536, 1000, "1x1"), (40, 5128, 392, "1x1"),   # 1, 1, 3 and 11 steps, four buffers
     (500, 8, 256, "2x1"), (500, 1024, 248, "2x1"), (500, 2568, 256, "2x1"),                          # 1, 2 and 6, three
     (510, 512, 504, "2x2"), (510, 1544, 512, "2x2"), (510, 4096, 512, "2x2"),                        # 1, 4 and 8, two
+    (16, 520, 1024, "1x1"), (500, 768, 256, "2x1"), (510, 640, 512, "2x2"),                          # 2 steps straight from memory
+    (17, 776, 1000, "1x1"), (16, 1024, 1024, "1x1"), (40, 3072, 392, "1x1"),                         # 2, 2 and 6 through registers
 ])
 def test_predictor_tiles_over_any_number_of_steps(T, d, r, tiles):
     _say(f"predictor tiles {tiles} T={T} d={d} r={r}")

@@ -1171,13 +1171,14 @@ static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const
 // In the down projection also where half tiles times ranges would fill less than half of the chip.  Half against quarter, bf16
 // and codes: 256 tokens of d 2048 77.4 / 68.4 and 96.1 / 89.2, 200 of d 2560 101.5 / 94.2 and 119.6 / 111.3, 100 of d 3072
 // 79.6 / 76.7 and 83.3 / 79.6, 600 of d 768 54.0 / 49.3 and 62.9 / 59.2; where they fill more than that, 100 tokens of 13B
-// 122 against 157.  Rows of one output tile, or layers of less than 768 or of fewer than eight groups with more than 64
-// tokens, are bound by launches (d 640, 129 to 200 tokens: 39.4 / 38.0) and stay as they are.
+// 122 against 157.  So it is down to the shortest rows and the fewest groups.  The FFN on its own, bf16 and codes: d 256, 2 groups, 65 tokens
+// 16.3 / 15.1 and 19.4 / 18.1, 256 tokens 17.6 / 16.0 and 20.6 / 18.9; d 640, 40 groups, 128 tokens 28.3 / 25.9 and 32.4 / 30.5; d 1024,
+// 6 groups, 256 tokens 28.7 / 26.4 and 32.8 / 30.6; over d 256 .. 1024, 2 .. 40 groups, 65 .. 400 tokens 1.00 to 1.12 times as fast, never
+// slower.  Rows of one output tile stay as they are.
 static bool gate_up_quarter_tiles(bool q4, int T, int d) { return q4 && T <= 64 && d >= 256; }
-static bool down_quarter_tiles(int T, int d, int G, int splits)
+static bool down_quarter_tiles(int T, int d, int splits)
 {
-    if (T <= 64) return d >= 256;
-    return d >= 768 && G >= 8 && (long long)(d / 128) * ((T + 127) / 128) * splits < 128;
+    return d >= 256 && (T <= 64 || (long long)(d / 128) * ((T + 127) / 128) * splits < 128);
 }
 
 template <bool Q4>
@@ -1196,7 +1197,7 @@ static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void 
         e = launch_gate_up_ring<Q4, 256>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
     if (e != hipSuccess) return e;
     const int splits = splits_in_room(down_splits(T, d, G), T, d, ws);
-    if (down_quarter_tiles(T, d, G, splits))
+    if (down_quarter_tiles(T, d, splits))
         e = launch_down_ring<Q4, 64>(T, d, G, splits, Wd, Sd, ws, act, y, s);
     else if (T <= 128 || (d / 128) * ((T + 255) / 256) * splits < 128)
         e = launch_down_ring<Q4, 128>(T, d, G, splits, Wd, Sd, ws, act, y, s);

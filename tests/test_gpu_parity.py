@@ -719,10 +719,12 @@ def test_one_token_of_any_row_length(d, G, K):
 @pytest.mark.parametrize("T,d,G,K", [
     (17, 128, 3, 2),           # rows of two stages, a range per group
     (128, 256, 5, 2),          # a full half tile of tokens in the down projection
-    (129, 640, 40, 20),        # two half tiles, one token in the second
+    (129, 640, 40, 20),        # two half tiles in gate/up, one token in the second; in down three quarter tiles
+    (129, 1152, 24, 12),       # two half tiles in both
     (129, 4096, 40, 20),       # half tiles in gate/up, a whole tile with half of it empty in down
     (256, 384, 70, 60),        # two half tiles for the groups that most tokens keep
     (257, 1024, 6, 6),         # dense: no token needs a row of zeros
+    (257, 1152, 9, 5),         # three half tiles in down, one token in the last
     (300, 256, 300, 30),       # more than 256 groups
     (515, 4224, 9, 4),         # whole tiles in gate/up, five half tiles in down, one range
     (515, 4224, 40, 10),       # three whole tiles in down, the last with three tokens

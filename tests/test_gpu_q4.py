@@ -417,9 +417,11 @@ def test_q4_one_token_of_any_row_length(d, G, K, r):
 @pytest.mark.parametrize("T,d,G,K", [
     (17, 128, 3, 2),           # one block of codes per row
     (128, 640, 5, 2),          # an odd number of blocks per row: the scales' words straddle rows
-    (200, 384, 70, 60),        # half tiles, many groups of three blocks
+    (200, 384, 70, 60),        # half tiles in gate/up, many groups of three blocks
+    (129, 1152, 24, 12),       # two half tiles in both, one token in the second
     (129, 4096, 40, 20),       # half tiles in gate/up, a whole tile with half of it empty in down
     (257, 1024, 6, 6),         # dense: no token needs a row of zeros
+    (257, 1152, 9, 5),         # three half tiles in down, one token in the last
     (300, 256, 300, 30),       # more groups than the few-token kernels take
     (515, 4224, 9, 4),         # whole tiles in gate/up, five half tiles in down, one range
     (515, 4224, 40, 10),       # three whole tiles in down, the last with three tokens

@@ -89,8 +89,8 @@ def test_kernels_past_the_row_table():
 
 def test_many_token_cases_run_on_the_kernels_they_are_for():
     # the forms of the ring kernels that the parity cases are chosen to reach: tokens per tile, in gate/up and down
-    for T, d, G, gate_up, down in [(17, 128, 3, 128, 128), (129, 640, 40, 128, 128), (129, 4096, 40, 128, 256),
-                                   (257, 1024, 6, 256, 128), (515, 4224, 9, 256, 128), (515, 4224, 40, 256, 256)]:
+    for T, d, G, gate_up, down in [(17, 128, 3, 128, 128), (129, 640, 40, 128, 64), (129, 1152, 24, 128, 128), (129, 4096, 40, 128, 256),
+                                   (257, 1024, 6, 256, 64), (257, 1152, 9, 256, 128), (515, 4224, 9, 256, 128), (515, 4224, 40, 256, 256)]:
         for q4 in (0, 1):
             (rc, _, launches), = record([dict(fn="ffn_forward" + ("_q4" if q4 else ""), shape=(d, G, 128, 64, BF16), T=T, K=G // 2)])
             names = [n for n, *_ in launches]
@@ -105,7 +105,8 @@ def test_quarter_tiles_of_tokens():
     # tokens per tile in gate/up over codes and in down (gate/up over bf16 weights has no quarter tiles)
     for T, d, G, gate_up, down in [(17, 128, 3, 128, 128), (17, 256, 3, 64, 64), (33, 640, 9, 64, 64), (64, 1152, 20, 64, 64),
                                    (65, 768, 8, 128, 64), (193, 1024, 24, 128, 64), (520, 896, 9, 256, 64),
-                                   (65, 640, 9, 128, 128), (65, 768, 7, 128, 128), (128, 5120, 108, 128, 128)]:
+                                   (65, 640, 9, 128, 64), (65, 768, 7, 128, 64), (400, 256, 2, 256, 64), (65, 128, 9, 128, 128),
+                                   (65, 2048, 24, 128, 128), (128, 5120, 108, 128, 128)]:
         for q4 in (0, 1):
             (rc, _, launches), = record([dict(fn="ffn_forward" + ("_q4" if q4 else ""), shape=(d, G, 128, 64, BF16), T=T, K=G // 2)])
             names = [n for n, *_ in launches]

@@ -172,13 +172,17 @@ def test_q4_few_tokens_with_handmade_masks(T, d, G):
 @pytest.mark.parametrize("q4", [True, False])
 @pytest.mark.parametrize("T,d,G,r", [
     (2, 128, 3, 40),           # 4-bit: half a unit, seven of eight waves without one; bf16: two units
-    (8, 1152, 27, 264),        # the most tokens of a folded operand; an odd number of blocks
-    (9, 2176, 5, 64),          # one more: two operands; the last wave's second unit is half a unit
+    (8, 1152, 27, 264),        # an odd number of blocks
+    (9, 2176, 5, 64),          # the last wave's second unit is half a unit
     (16, 3200, 40, 512),       # four passes of two predictor rows
     (3, 5248, 200, 256),       # three rows of eight outputs to a workgroup
     (13, 6784, 6, 64),         # bf16: thirteen or fourteen units to a wave
     (5, 7936, 9, 256),         # ... fifteen or sixteen
     (16, 8064, 256, 64),       # the most groups: every neuron of a workgroup's run in one group
+    (2, 8320, 3, 40),          # rows longer than the streaming kernels take: the other gate/up, and the plain path over codes
+    (16, 8320, 5, 72),
+    (7, 256, 260, 64),         # more groups than they take: a list of groups in memory
+    (16, 640, 257, 40),
 ])
 def test_few_tokens_of_any_row_length(q4, T, d, G, r):
     # against the oracle, and the overlapped form equal to the serial one bit for bit

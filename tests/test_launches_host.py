@@ -53,6 +53,16 @@ def test_more_lds_is_allowed_on_each_device():
         assert rc == 0 and launches, (c, rc, launches)
 
 
+def test_few_token_gate_up_by_shape():
+    # the streaming kernel up to rows of 8192 and 256 groups, past either the one that walks its rows in chunks
+    for T, d, G, name in [(2, 8192, 256, "gate_up_ft"), (5, 8192, 256, "gate_up_streamILNS_7WeightsE0E"), (16, 128, 3, "gate_up_streamILNS_7WeightsE0E"),
+                          (2, 8320, 3, "gate_up_mtILb1E"), (16, 8320, 256, "gate_up_mtILb1E"), (7, 256, 260, "gate_up_mtILb0E"),
+                          (16, 640, 257, "gate_up_mtILb0E")]:
+        serial, ahead = record([dict(fn=fn, shape=(d, G, 128, 64, BF16), T=T, K=G // 2) for fn in ("group_sparse_ffn", "ffn_forward_ahead")])
+        for rc, _, launches in (serial, ahead):
+            assert rc == 0 and sum(name in n for n, *_ in launches) == 1, (T, d, G, launches)
+
+
 def test_float32_projections_by_the_number_of_tokens():
     # groups of 128: what is asked for before the mask is known, and the form of the down projection
     for T, d, G, ask, down in [(1, 1024, 24, True, "down_f32ILi1E"), (5, 256, 8, True, "down_f32ILi1E"), (6, 256, 9, False, "down_f32_128"),

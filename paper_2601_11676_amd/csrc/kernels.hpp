@@ -68,8 +68,8 @@ struct AheadDev {
     int32_t *surv_idx;
     int32_t *n_surv;
 };
-// The first predictor layer of the next block for T tokens, riding in the first n_pred workgroups of
-// a gate/up launch (four rows of At per workgroup): h[t][j] = ReLU(x_next[t] . At[j]).
+// The first predictor layer of the next block for T tokens, h[t][j] = ReLU(x_next[t] . At[j]), riding in a gate/up launch: in its
+// first n_pred workgroups, four rows of At each, or (gate_up_stream) dealt over all of them.
 struct AheadPredDev {
     const bf16_t *x_next, *At;
     float *h;
@@ -112,7 +112,7 @@ hipError_t launch_ffn_mfma(const bf16_t *x, int T, int d, int G, int gs, const b
                            const DecodeScratch &ws, hipStream_t s, const AheadArgs *ahead = nullptr,
                            bool *ahead_fused = nullptr);
 
-// ffn_few.hip : gate/up for 2..8 tokens on the float ALUs (rows streamed as in the one-token path)
+// ffn_few.hip : gate/up for 2..4 tokens on the float ALUs (rows streamed as in the one-token path)
 bool few_path_supported(int T, int d, int G, int gs);
 hipError_t launch_gate_up_few(const bf16_t *x, int T, int d, int G, int gs, const bf16_t *Wg, const bf16_t *Wu,
                               const uint8_t *mask, bf16_t *act, int act_stride, hipStream_t s,
@@ -148,7 +148,7 @@ bool prefill_q4_supported(int T, int d, int G, int gs);
 hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask, bf16_t *y,
                                  const DecodeScratch &ws, hipStream_t s);
 
-// ffn_q4_mt.hip : 4-bit weights, 2..16 tokens, matrix cores
+// ffn_q4_mt.hip : 4-bit weights, 2..16 tokens, matrix cores: d up to 8192, up to 256 groups
 hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask,
                               bf16_t *y, const DecodeScratch &ws, hipStream_t s, const AheadArgs *ahead = nullptr,
                               bool *ahead_fused = nullptr);

@@ -152,11 +152,16 @@ static void launch_predict_mask(const void *x, int T, int d, int r, int G, const
 // reads them for itself (from L2), which costs no more than a launch on the device (tiny block 6.9 us against 2.2 + 4.7) and saves the
 // host one, and a pass over a small block waits for the host: tiny block 18.4 -> 17.6 us, d 1024 bf16, rank 64, 2 tokens 17.7 -> 17.1.
 // At twice that (d 512 float32, rank 128: 8.5 us against 3.2 + 4.6) it is level, beyond it slower (d 1000, rank 128: 11.7 against 9.0).
+// Up to 64 tokens, the passes that wait for the host; with more the kernels that follow cover the launch (on the device one stays
+// ahead: d 256 float32, 128 tokens 6.8 us against 3.3 + 4.6, 512 tokens 9.2 against 6.9 + 5.1).  Rows of bf16 that are no multiple of
+// 128, up to 4 tokens: their FFN runs on the plain kernels, which gain from x in every die's L2, where the first layer's own launch
+// leaves it (d 1000, 8 groups, rank 64, 64 tokens: their gate/up 50 us after two launches, 61 after one; 8 tokens 51.3 / 52.2 the pass).
 hipError_t launch_predict_and_mask(int dtype, const void *x, int T, int d, int r, int G, const void *At, const void *Bt, float *h,
                                    float *scores, int K, const int8_t *prio_dev, int n_dev, const uint8_t *drop, int32_t *order,
                                    int8_t *group_dev, uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
 {
-    if (T <= 64 && r <= kMaskMaxRank && (size_t)r * d * (dtype == 0 ? 4 : 2) <= (size_t)128 << 10) {
+    const int most = dtype != 0 && d % 128 != 0 ? 4 : 64;
+    if (T <= most && r <= kMaskMaxRank && (size_t)r * d * (dtype == 0 ? 4 : 2) <= (size_t)128 << 10) {
         if (dtype == 0)
             launch_predict_mask<float>(x, T, d, r, G, At, Bt, scores, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
         else

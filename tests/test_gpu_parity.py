@@ -671,6 +671,7 @@ def test_float32_groups_of_128(T, d, G, r):
     ("f32", 64, 64, 130, 512), # 128 KiB of weights, 64 tokens: the most of all
     ("f32", 65, 64, 9, 512),   # a token more: two launches
     ("bf16", 3, 520, 17, 72),  # nine waves' rows over eight waves; a second piece of the row for one lane
+    ("bf16", 5, 520, 17, 72),  # more than four tokens of a row that is no multiple of 128: two launches
     ("bf16", 16, 1024, 5, 64),
     ("bf16", 16, 1032, 5, 64), # just above 128 KiB
 ])

@@ -53,6 +53,13 @@ def test_more_lds_is_allowed_on_each_device():
         assert rc == 0 and launches, (c, rc, launches)
 
 
+def test_prediction_in_one_launch_by_shape():
+    for T, d, r, dtype, one in [(64, 1024, 64, BF16, True), (65, 1024, 64, BF16, False), (16, 1032, 64, BF16, False), (4, 1000, 64, BF16, True),
+                                (5, 1000, 64, BF16, False), (64, 504, 64, F32, True), (64, 512, 64, F32, True), (64, 520, 64, F32, False)]:
+        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, 8, 128, r, dtype), T=T, K=4)])
+        assert rc == 0 and ("predict_mask_kernel" in launches[0][0]) == one, (T, d, r, launches)
+
+
 def test_few_token_gate_up_by_shape():
     # the streaming kernel up to rows of 8192 and 256 groups, past either the one that walks its rows in chunks
     for T, d, G, name in [(2, 8192, 256, "gate_up_ft"), (5, 8192, 256, "gate_up_streamILNS_7WeightsE0E"), (16, 128, 3, "gate_up_streamILNS_7WeightsE0E"),

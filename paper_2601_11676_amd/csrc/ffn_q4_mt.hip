@@ -218,9 +218,9 @@ __global__ __launch_bounds__(WAVES * 64) void down_q4_mt(
 
 // Rows that are whole multiples of 1024: activations in bf16.  The other row lengths: in float32 and with codes that need no
 // offset, as the plain path has them: activations are 0.79 .. 1.26e-7 from 64 bits over d 384 .. 8064 (theirs 0.81 .. 1.35e-7;
-// tokens' values of mean 0 or 1 alike).  Both projections, us: d 3200, 75 groups, 8 tokens 40, plain path 364; d 8064, 256 groups,
-// 16 tokens 161, plain 3084; d 1152, 27 groups, 2 tokens 19, plain 34.  (An offset and activations as the sum of two bf16 values:
-// 37, 140 and 17, but activations of 17 bits, and sums that cancel.)
+// tokens' values of mean 0 or 1 alike).  Both projections, us: d 3200, 75 groups, 8 tokens 34, plain path 364; d 8064, 256 groups,
+// 16 tokens 161, plain 3084; d 1152, 27 groups, 2 tokens 13, plain 34.  (An offset and activations as the sum of two bf16 values gave
+// activations of 17 bits, and sums that cancel; d 8064, 256 groups, 16 tokens took 140 us that way.)
 hipError_t launch_ffn_q4_mfma(const bf16_t *x, int T, int d, int G, const Q4Weights &w, const uint8_t *mask,
                               bf16_t *y, const DecodeScratch &ws, hipStream_t s, const AheadArgs *ahead, bool *ahead_fused)
 {

@@ -112,10 +112,11 @@ __device__ __forceinline__ void dot_order64_two(const bf16_t *__restrict__ x0, c
 // Wave v multiplies units nu v / 8 .. of every row (a unit = 128 bytes of a row: 64 bf16 values, or two quantisation
 // blocks of 128 codes), at most U of them, and leaves its sums of a tile in LDS; they meet there once, at the end.
 // A ring of NS units of gate and up is in flight per wave, over TB tiles where a tile has few units.
-// Measured (T tokens; us per launch, the kernels before -> this one): 4-bit, 70B shape, 8 tokens 62.8 -> 53 with the next block's
-// prediction on board, 59.3 -> 46 without; d 1152, 27 groups, 16 tokens 25.7 -> 11.7; bf16, d 2432, 66 groups, 8 tokens 26.1 ->
-// 18.2, 70B shape, 8 tokens 151.5 -> 142.4.  What bounds it: bf16, HBM (5.9 TB/s at the 70B shape); 4-bit, the stream (31 us of
-// it at the 70B shape) and the conversion of the codes side by side: with loads that move nothing it still takes 32.
+// Measured (us per launch): 4-bit, 70B shape, 8 tokens 58 with the next block's prediction on board, 50.5 without (a plain read 34; the
+// former kernel 62 with it); bf16, 70B shape, 8 tokens 140 (a plain read 126; the former 150), d 2432, 66 groups, 8 tokens 18.2 (26.1).
+// What bounds it: bf16, HBM (6.1 TB/s at the 70B shape); 4-bit, the stream (31 us of it at the 70B shape) and the conversion of the codes
+// side by side: with loads that move nothing it still takes 32; by the counters a SIMD's two waves spend 0.44 of the time in vector
+// and 0.13 in matrix instructions.
 // 4-bit codes: a block's sum of products meets the scale in float.  Rows that are whole multiples of 1024 take a code as bf16
 // 128 + c and start a block at -136 * (sum of the tokens' values).  The others keep float32's precision (EXACT: such rows have
 // no other fast path): a code is c - 8, exactly, so that nothing has to cancel, and the activation is stored in float32.
@@ -399,27 +400,30 @@ __global__ __launch_bounds__(kStreamWaves * 64) __attribute__((amdgpu_waves_per_
 // ---------------------------------------------------------------------------
 // The output rows are dealt over the workgroups in eights, at most RT tiles of sixteen to a workgroup; the waves take every
 // eighth of the union's groups and meet in LDS.  A tile's codes of a group are 1 KiB of consecutive bytes, one load, in operand
-// order, and so are the activations that face them: a lane's 32 floats of its token.  An activation is multiplied as the sum of three
-// bf16 values, its leading, middle and trailing eight bits -- all 24 of them -- with codes that are c - 8 exactly, so that float32 sums are
-// the only rounding.
+// order.  An activation is multiplied as the sum of three bf16 values, its leading, middle and trailing eight bits -- all 24 of them --
+// with codes that are c - 8 exactly, so that float32 sums are the only rounding.
+// TL > 0, up to 2 TL tokens: a wave's lanes share the split: a load brings two tokens' 512 bytes, a lane splits its four values, and the pieces
+// go through the wave's own LDS region into operand order.  TL = 0: operand order from memory, a lane splits the 32 values of its token's
+// that it multiplies; sixteen tokens have nothing to share.  (With that for every number of tokens two of them paid for sixteen: both
+// projections, us, d 3200, 75 groups, 2 tokens 27.1 -> 22.3, 8 tokens 37.3 -> 33.8; d 8064, 256 groups, 2 tokens 100 -> 87.)
 // The first n_mask workgroups do not project: each computes the next block's scores, ranking and mask for one token (paper
 // Sec. III-B.3, one layer ahead; dispatched first, it is the longest dependent chain).  DEPTH groups are in flight per wave.
-template <int RT>
+template <int RT, int TL>
 struct DownStep {
-    static constexpr int DEPTH = 2;
+    static constexpr int DEPTH = TL == 0 ? 2 : RT * TL == 8 ? 3 : 4, kLoads = TL == 0 ? 8 : TL;
     u32x4 w[RT];
-    f32x4_t a[8];
+    f32x4_t a[kLoads];
     uint32_t sc[RT];
 };
 
-// eight floats as the sum of three times eight bf16 values
-__device__ __forceinline__ void split3(const f32x4_t &lo, const f32x4_t &hi, u32x4 (&piece)[3])
+// four floats as the sum of three times four bf16 values
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split3(f32x4_t v, u32x2 (&piece)[3])
 {
-    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 #pragma unroll
     for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 2; ++i) {
             const uint32_t top = __builtin_amdgcn_perm(__float_as_uint(v[2 * i + 1]), __float_as_uint(v[2 * i]), 0x07060302u);
             piece[p][i] = top;
             const float a = bf16_lo(top), b = bf16_hi(top);      // (of an infinity nothing is left)
@@ -428,17 +432,21 @@ __device__ __forceinline__ void split3(const f32x4_t &lo, const f32x4_t &hi, u32
         }
 }
 
-template <int RT>
+template <int RT, int TL>
 __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
     int T, int d, int G, const uint32_t *__restrict__ Dq, const bf16_t *__restrict__ Ds, const uint8_t *__restrict__ mask,
     const float *__restrict__ act, int act_stride, bf16_t *__restrict__ y, int n_mask, AheadDev nx)
 {
-    using Step = DownStep<RT>;
+    using Step = DownStep<RT, TL>;
     constexpr int gs = 128, DEPTH = Step::DEPTH;
+    constexpr int kPitch = gs * 2 + 16, kPlane = 2 * TL * kPitch;           // bytes of a token's row of pieces, of all rows
+    constexpr int kRegion = 3 * kPlane > RT * 1024 ? 3 * kPlane : RT * 1024;
     struct Proj {
         KeepBits keep;
         int list[256];
-        __attribute__((aligned(16))) float part[kStreamWaves][RT][64][4];           // [16 token quad + row][token in quad]
+        __attribute__((aligned(16))) unsigned char region[kStreamWaves][kRegion];   // a wave's pieces; at the end its sums
+        // [16 token quad + row][token in quad]
+        __device__ __forceinline__ float (*sums(int wave))[64][4] { return reinterpret_cast<float(*)[64][4]>(region[wave]); }
     };
     constexpr size_t kLds = sizeof(Proj) > sizeof(MaskShared) ? sizeof(Proj) : sizeof(MaskShared);
     __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
@@ -465,7 +473,13 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
     __syncthreads();
     const int n_u = uw.count;
     const __amdgpu_buffer_rsrc_t bw = buffer_of(Dq), bs = buffer_of(Ds), ba = buffer_of(act), none = buffer_of(Dq, 0);
-    const uint32_t at_act = (uint32_t)((i16 < T ? i16 : T - 1) * act_stride + q * 32) * 4;    // rows past the last token repeat it, unused
+    // rows past the last token repeat it, unused
+    uint32_t at_act[TL == 0 ? 1 : TL];
+#pragma unroll
+    for (int n = 0; n < (TL == 0 ? 1 : TL); ++n)
+        at_act[n] = TL == 0 ? (uint32_t)((i16 < T ? i16 : T - 1) * act_stride + q * 32) * 4
+                            : (uint32_t)(min(2 * n + (lane >> 5), T - 1) * act_stride + (lane & 31) * 4) * 4;
+    unsigned char *mine = sh.region[wave];
     uint32_t at_w[RT], at_s[RT];                                 // this lane's bytes of a group's block and of its scales
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -487,8 +501,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
             s.sc[rt] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, at_s[rt], g * (uint32_t)d * 2, 0);
         }
 #pragma unroll
-        for (int f = 0; f < 8; ++f)                              // half word f of the lane's eight
-            s.a[f] = __builtin_bit_cast(f32x4_t, buffer_load16<0>(ba, at_act, (uint32_t)((yes ? u : n_u - 1) * gs) * 4 + f * 16));
+        for (int n = 0; n < Step::kLoads; ++n)
+            s.a[n] = __builtin_bit_cast(f32x4_t, buffer_load16<0>(ba, at_act[TL == 0 ? 0 : n], (uint32_t)((yes ? u : n_u - 1) * gs) * 4 + (TL == 0 ? n * 16 : 0)));
     };
     f32x4_t acc[RT];
 #pragma unroll
@@ -497,10 +511,31 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
         f32x4_t t[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) t[rt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if constexpr (TL > 0) {
+            // (the region is the wave's own and its LDS operations complete in order, so no barrier is needed)
+#pragma unroll
+            for (int n = 0; n < TL; ++n) {
+                u32x2 piece[3];
+                split3(s.a[n], piece);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<u32x2 *>(mine + p * kPlane + (2 * n + (lane >> 5)) * kPitch + (lane & 31) * 8) = piece[p];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {                            // word k: eight elements
             u32x4 piece[3];
-            split3(s.a[2 * k], s.a[2 * k + 1], piece);
+            if constexpr (TL > 0) {
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    piece[p] = *reinterpret_cast<const u32x4 *>(mine + p * kPlane + (i16 & (2 * TL - 1)) * kPitch + (q * 32 + k * 8) * 2);
+            } else {
+                u32x2 lo[3], hi[3];
+                split3(s.a[TL == 0 ? 2 * k : 0], lo);
+                split3(s.a[TL == 0 ? 2 * k + 1 : 0], hi);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) piece[p] = u32x4{lo[p][0], lo[p][1], hi[p][0], hi[p][1]};
+            }
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 const u32x4 v = q4_word_signed(s.w[rt][k]);
@@ -529,7 +564,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
         }
     }
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) *reinterpret_cast<f32x4_t *>(sh.part[wave][rt][lane]) = acc[rt];
+    for (int rt = 0; rt < RT; ++rt) *reinterpret_cast<f32x4_t *>(sh.sums(wave)[rt][lane]) = acc[rt];
     __syncthreads();
     // a thread finishes one row for one token
     for (int id = tid; id < RT * 256; id += kStreamWaves * 64) {
@@ -537,7 +572,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 4) void down_q4_f32(
         if (t >= T || rt * 16 + rr >= nrows) continue;
         float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kStreamWaves; ++w) v += sh.part[w][rt][(t >> 2) * 16 + rr][t & 3];
+        for (int w = 0; w < kStreamWaves; ++w) v += sh.sums(w)[rt][(t >> 2) * 16 + rr][t & 3];
         y[(size_t)t * d + row0 + rt * 16 + rr] = f32_to_bf16(kQ4Signed * v);
     }
 }
@@ -619,21 +654,31 @@ hipError_t launch_gate_up_q4_stream(const bf16_t *x, int T, int d, int G, const 
 #undef HALO_CASE
 }
 
-template <int RT>
+template <int RT, int TL>
 static hipError_t launch_down_f32(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
                                   const AheadArgs *ah, hipStream_t s)
 {
     const int n_mask = ah ? T : 0, blocks = d / 8 < kStreamBlocks ? d / 8 : kStreamBlocks;
-    down_q4_f32<RT><<<dim3(blocks + n_mask), dim3(kStreamWaves * 64), 0, s>>>(
+    down_q4_f32<RT, TL><<<dim3(blocks + n_mask), dim3(kStreamWaves * 64), 0, s>>>(
         T, d, G, w.down_codes, w.down_scales, mask, act, G * 128, y, n_mask, ah ? ahead_dev(*ah) : AheadDev{});
     return hipGetLastError();
+}
+
+template <int RT>
+static hipError_t launch_down_f32_by_tokens(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
+                                            const AheadArgs *ah, hipStream_t s)
+{
+    if (T <= 2) return launch_down_f32<RT, 1>(T, d, G, w, mask, act, y, ah, s);
+    if (T <= 4) return launch_down_f32<RT, 2>(T, d, G, w, mask, act, y, ah, s);
+    if (T <= 8) return launch_down_f32<RT, 4>(T, d, G, w, mask, act, y, ah, s);
+    return launch_down_f32<RT, 0>(T, d, G, w, mask, act, y, ah, s);
 }
 
 hipError_t launch_down_q4_f32(int T, int d, int G, const Q4Weights &w, const uint8_t *mask, const float *act, bf16_t *y,
                               const AheadArgs *ah, hipStream_t s)
 {
     const bool one = (d / 8 + kStreamBlocks - 1) / kStreamBlocks <= 2;       // at most 16 rows to a workgroup
-    return one ? launch_down_f32<1>(T, d, G, w, mask, act, y, ah, s) : launch_down_f32<2>(T, d, G, w, mask, act, y, ah, s);
+    return one ? launch_down_f32_by_tokens<1>(T, d, G, w, mask, act, y, ah, s) : launch_down_f32_by_tokens<2>(T, d, G, w, mask, act, y, ah, s);
 }
 
 }  // namespace halo

@@ -7,11 +7,11 @@
 // workgroup until a wave's share is a handful of loads that are all requested together, and meet in LDS once.
 //   gate/up : workgroup = 16 neurons of one group x up to 64 tokens; leaves at once when none of its tokens
 //             keeps the group, so no list of groups is needed.  act = mask ? SiLU(gate) * up : 0.
-//   down    : workgroup = 16 outputs x up to 16 tokens, its waves share the pieces of the union's groups.
+//   down    : workgroup = 16 outputs x up to 16 or 32 tokens, its waves share the pieces of the union's groups.
 // WHICH 4 of a 16-element piece an instruction's lane group multiplies is free as long as both operands agree:
 // lane (i, q) = (l % 16, l / 16) holds elements 4 q .. 4 q + 3 of row i in one 16-byte load, and instruction e
 // multiplies element 4 q + e of every lane group.  D: lane l holds column (token) l % 16, rows 4 (l / 16) .. + 3.
-// Tiny block: gate/up 4.7 us and down 5.8 us per launch, the pass called from Python 19 us; a wave per neuron / per output
+// Tiny block: gate/up 4.6 us and down 5.8 us per launch, the pass called from Python 16 us; a wave per neuron / per output
 // row that walked its groups one 4-byte load at a time took 10, 68 and 89.  Error against 64 bits over d 128..1024, 4..24 groups,
 // 1..64 tokens: 0.89..1.01 times theirs.
 #include "kernels.hpp"

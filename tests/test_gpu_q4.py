@@ -221,7 +221,7 @@ def _pack_codes(k):
 
 
 @pytest.mark.parametrize("what", ["sums", "activations"])
-@pytest.mark.parametrize("T,d", [(2, 384), (8, 1152), (16, 5248), (37, 640)])
+@pytest.mark.parametrize("T,d", [(2, 384), (8, 1152), (16, 5248), (37, 640), (4, 1152), (2, 5248), (7, 5248)])
 def test_q4_few_tokens_of_any_row_length_keep_float32(what, T, d):
     # Rows that are no multiple of 1024: sums over c - 8 in float32, the activation in float32.  y is bf16, so results are made
     # small beside what they are summed from.  sums: the tokens' values have a mean of 1, and a row's products cancel (to a few

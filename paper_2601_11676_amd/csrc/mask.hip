@@ -10,7 +10,7 @@
 namespace halo {
 
 constexpr int kMaskThreads = 1024;
-constexpr int kMaskMaxRank = 512;
+constexpr int kOneLaunchRank = 128, kOneLaunchGroups = 128;
 
 template <typename WT, bool FUSED_SCORES, int NT = kMaskThreads>
 __global__ __launch_bounds__(NT) void mask_scores_kernel(
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(NT) void predict_mask_kernel(
     int8_t *__restrict__ group_dev, uint8_t *__restrict__ mask, int32_t *__restrict__ surv_idx, int32_t *__restrict__ n_surv)
 {
     __shared__ MaskShared sh;
-    __shared__ __attribute__((aligned(16))) float h[kMaskMaxRank];
+    __shared__ __attribute__((aligned(16))) float h[kOneLaunchRank];
     const size_t t = blockIdx.x;
     hidden_rows(x + t * d, At, d, r, (int)(threadIdx.x >> 6), NT / kWave, (int)(threadIdx.x & 63), h);
     __syncthreads();
@@ -91,13 +91,15 @@ hipError_t launch_group_mask(const float *scores, int T, int G, int K, const int
 // Threads of a token's workgroup where it computes the scores itself: as many waves as take all rows of Bt in one batch of
 // eight slots each (two rows to a slot up to rank 256), at least two.  More only add to the barriers: 8 groups, rank 64 6.1 us with 1024
 // threads, 5.4 with 512, 4.7 with 128; 27 groups, rank 512 5.9, 5.5 and (256) 5.4; with fewer the waves take turns: 92 groups,
-// rank 64 6.5, 6.3, (256) 7.8; 138 groups, rank 256 6.6, 7.5.  With 64 tokens and more at most 512, so that more workgroups
-// share a compute unit (512 tokens of the 7B shape 11.5 us against 13.6 with 1024).
+// rank 64 6.5, 6.3, (256) 7.8; 138 groups, rank 256 6.6, 7.5.  With 64 tokens and more at most 512 for bf16, so that more workgroups
+// share a compute unit (512 tokens of the 7B shape 11.5 us against 13.6 with 1024); float32 rows are twice the work of a wave (64 tokens,
+// 200 groups, rank 512 19.8 us against 17.9 with 1024, both layers).
+template <typename WT>
 static int mask_threads(int T, int G, int r)
 {
     const int slots = r <= 256 ? (G + 1) / 2 : G;
     const int threads = slots <= 16 ? 128 : slots <= 32 ? 256 : slots <= 64 ? 512 : kMaskThreads;
-    return T >= 64 && threads > 512 ? 512 : threads;
+    return sizeof(WT) == 2 && T >= 64 && threads > 512 ? 512 : threads;
 }
 
 template <typename WT>
@@ -110,7 +112,7 @@ static void launch_fused(const float *h, const WT *Bt, int r, float *scores, int
         mask_scores_kernel<WT, true, NT><<<dim3(T), dim3(NT), 0, s>>>(h, Bt, r, scores, G, K, prio_dev, n_dev, drop,  \
                                                                       order, group_dev, mask, surv_idx, n_surv);      \
         break;
-    switch (mask_threads(T, G, r)) {
+    switch (mask_threads<WT>(T, G, r)) {
         HALO_MASK_CASE(128)
         HALO_MASK_CASE(256)
         HALO_MASK_CASE(512)
@@ -151,7 +153,10 @@ static void launch_predict_mask(const void *x, int T, int d, int r, int G, const
 // Both predictor layers and the mask.  One launch where the first layer's weights are at most 128 KiB: every token's workgroup
 // reads them for itself (from L2), which costs no more than a launch on the device (tiny block 6.9 us against 2.2 + 4.7) and saves the
 // host one, and a pass over a small block waits for the host: tiny block 18.4 -> 17.6 us, d 1024 bf16, rank 64, 2 tokens 17.7 -> 17.1.
-// At twice that (d 512 float32, rank 128: 8.5 us against 3.2 + 4.6) it is level, beyond it slower (d 1000, rank 128: 11.7 against 9.0).
+// Up to rank 128, two rounds of rows, and 128 groups, one round of eight waves over Bt: a block of d 256 in bf16, one token, in a
+// graph, rank 64 / 128 / 256, two launches against one: 8 groups 12.0 / 12.3 / 12.3 us against 11.1 / 12.2 / 14.3, 128 groups 25.0 / 25.0 / 24.7
+// against 23.8 / 24.7 / 26.7, 200 groups 32.1 / 32.3 / 32.0 against 32.6 / 33.8 / 35.6; float32, 16 tokens, 200 groups 27.7 against 29.2.
+// At twice 128 KiB (d 512 float32, rank 128: 8.5 us against 3.2 + 4.6) it is level, beyond it slower (d 1000, rank 128: 11.7 against 9.0).
 // Up to 64 tokens, the passes that wait for the host; with more the kernels that follow cover the launch (on the device one stays
 // ahead: d 256 float32, 128 tokens 6.8 us against 3.3 + 4.6, 512 tokens 9.2 against 6.9 + 5.1).  Rows of bf16 that are no multiple of
 // 128, up to 4 tokens: their FFN runs on the plain kernels, which gain from x in every die's L2, where the first layer's own launch
@@ -161,7 +166,7 @@ hipError_t launch_predict_and_mask(int dtype, const void *x, int T, int d, int r
                                    int8_t *group_dev, uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
 {
     const int most = dtype != 0 && d % 128 != 0 ? 4 : 64;
-    if (T <= most && r <= kMaskMaxRank && (size_t)r * d * (dtype == 0 ? 4 : 2) <= (size_t)128 << 10) {
+    if (T <= most && r <= kOneLaunchRank && G <= kOneLaunchGroups && (size_t)r * d * (dtype == 0 ? 4 : 2) <= (size_t)128 << 10) {
         if (dtype == 0)
             launch_predict_mask<float>(x, T, d, r, G, At, Bt, scores, K, prio_dev, n_dev, drop, order, group_dev, mask, surv_idx, n_surv, s);
         else

@@ -668,7 +668,8 @@ def test_float32_groups_of_128(T, d, G, r):
 
 @pytest.mark.parametrize("dtype,T,d,G,r", [
     ("f32", 1, 8, 1, 8),       # one batch of rows for one wave
-    ("f32", 64, 64, 130, 512), # 128 KiB of weights, 64 tokens: the most of all
+    ("f32", 64, 64, 130, 512), # 128 KiB of weights, 64 tokens, but more groups and a larger rank than one launch takes
+    ("f32", 64, 256, 128, 128), # 128 KiB of weights, 64 tokens: the most of all
     ("f32", 65, 64, 9, 512),   # a token more: two launches
     ("bf16", 3, 520, 17, 72),  # nine waves' rows over eight waves; a second piece of the row for one lane
     ("bf16", 5, 520, 17, 72),  # more than four tokens of a row that is no multiple of 128: two launches

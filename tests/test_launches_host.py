@@ -54,6 +54,9 @@ def test_more_lds_is_allowed_on_each_device():
 
 
 def test_prediction_in_one_launch_by_shape():
+    for T, G, d, r, one in [(64, 128, 256, 128, True), (64, 129, 256, 128, False), (64, 128, 240, 136, False)]:
+        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, G, 128, r, F32), T=T, K=4)])
+        assert rc == 0 and ("predict_mask_kernel" in launches[0][0]) == one, (T, G, d, r, launches)
     for T, d, r, dtype, one in [(64, 1024, 64, BF16, True), (65, 1024, 64, BF16, False), (16, 1032, 64, BF16, False), (4, 1000, 64, BF16, True),
                                 (5, 1000, 64, BF16, False), (64, 504, 64, F32, True), (64, 512, 64, F32, True), (64, 520, 64, F32, False)]:
         (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, 8, 128, r, dtype), T=T, K=4)])

@@ -114,9 +114,10 @@ __device__ __forceinline__ void dot_order64_two(const bf16_t *__restrict__ x0, c
 // A ring of NS units of gate and up is in flight per wave, over TB tiles where a tile has few units.
 // Measured (us per launch): 4-bit, 70B shape, 8 tokens 58 with the next block's prediction on board, 50.5 without (a plain read 34; the
 // former kernel 62 with it); bf16, 70B shape, 8 tokens 140 (a plain read 126; the former 150), d 2432, 66 groups, 8 tokens 18.2 (26.1).
-// What bounds it: bf16, HBM (6.1 TB/s at the 70B shape); 4-bit, the stream (31 us of it at the 70B shape) and the conversion of the codes
-// side by side: with loads that move nothing it still takes 32; by the counters a SIMD's two waves spend 0.44 of the time in vector
-// and 0.13 in matrix instructions.
+// What bounds it: bf16, HBM (6.1 TB/s at the 70B shape); 4-bit, the loads that a compute unit has in flight (64 KiB: two units of four
+// load instructions a wave): 54 us without the prediction under the tracer, 58 with the codes not converted, 47 with every row from
+// cache, 36 with both, 24 with loads that move nothing (timing-only builds).  By the counters a SIMD's two waves spend 0.44 of the time in
+// vector and 0.13 in matrix instructions.
 // 4-bit codes: a block's sum of products meets the scale in float.  Rows that are whole multiples of 1024 take a code as bf16
 // 128 + c and start a block at -136 * (sum of the tokens' values).  The others keep float32's precision (EXACT: such rows have
 // no other fast path): a code is c - 8, exactly, so that nothing has to cancel, and the activation is stored in float32.

@@ -34,10 +34,12 @@ def test_q4_generator_bits_identical_on_cpu_and_gpu():
 @pytest.mark.parametrize("dtype,T,d,G,r", [
     ("f32", 16, 256, 8, 64),       # the tiny shape
     ("f32", 5, 640, 7, 72),
-    ("bf16", 3, 384, 9, 40),
-    ("bf16", 1, 1024, 5, 264),     # one token, but not a row length of the streaming path
+    ("bf16", 3, 384, 9, 40),       # (these four run on the tuned kernels)
+    ("bf16", 1, 1024, 5, 264),
     ("bf16", 7, 4096, 6, 256),
-    ("bf16", 40, 512, 70, 64),     # more groups than a wave, many tokens
+    ("bf16", 40, 512, 70, 64),
+    ("bf16", 20, 8320, 3, 40),     # rows longer than they take
+    ("bf16", 40, 128, 260, 64),    # more groups
 ])
 def test_q4_plain_path_whole_pass(dtype, T, d, G, r):
     w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, rank=r, T=T, dtype=dtype, seed=12)

@@ -71,6 +71,13 @@ def test_few_token_gate_up_by_shape():
         serial, ahead = record([dict(fn=fn, shape=(d, G, 128, 64, BF16), T=T, K=G // 2) for fn in ("group_sparse_ffn", "ffn_forward_ahead")])
         for rc, _, launches in (serial, ahead):
             assert rc == 0 and sum(name in n for n, *_ in launches) == 1, (T, d, G, launches)
+    # over 4-bit weights: codes with an offset, codes as they are, and past the streaming kernels the plain path
+    for T, d, G, names in [(2, 8192, 256, ["gate_up_streamILNS_7WeightsE1E", "down_q4_mt"]), (16, 1024, 3, ["gate_up_streamILNS_7WeightsE1E", "down_q4_mt"]),
+                           (2, 8064, 256, ["gate_up_streamILNS_7WeightsE2E", "down_q4_f32ILi2ELi1E"]), (4, 128, 3, ["gate_up_streamILNS_7WeightsE2E", "down_q4_f32ILi1ELi2E"]),
+                           (8, 4224, 9, ["gate_up_streamILNS_7WeightsE2E", "down_q4_f32ILi2ELi4E"]), (9, 3968, 9, ["gate_up_streamILNS_7WeightsE2E", "down_q4_f32ILi1ELi0E"]),
+                           (2, 8320, 3, ["union_kernel", "gate_up_q4_generic", "down_q4_generic"]), (16, 640, 257, ["union_kernel", "gate_up_q4_generic", "down_q4_generic"])]:
+        (rc, _, launches), = record([dict(fn="group_sparse_ffn_q4", shape=(d, G, 128, 64, BF16), T=T)])
+        assert rc == 0 and len(launches) == len(names) and all(a in b[0] for a, b in zip(names, launches)), (T, d, G, launches)
 
 
 def test_float32_projections_by_the_number_of_tokens():

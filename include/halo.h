@@ -113,7 +113,8 @@ size_t halo_workspace_bytes(const halo_shape *shape, int32_t T, int32_t k_keep);
  * The same, for callers of the `_q4` entry points further down: for more than 16 tokens (bf16) the bound
  * also holds one block's FFN weights as bf16 (3 * ffn * d * 2 bytes).  With that room a many-token call runs on
  * the many-token matrix-core kernels over the weights rounded to bf16: up to 32767 tokens the codes are expanded
- * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  (It is
+ * on their way into LDS and the room itself stays unused, above that they are expanded once into it.  (17..64 tokens with d of at least
+ * 256 are an exception: there the many-token kernels apply the scale in float32 and nothing is rounded.)  (It is
  * how a caller chooses the rounded weights: a smaller sign would let the slack of a workspace that was sized for more
  * tokens change the arithmetic.)  A `_q4` call given only halo_workspace_bytes works all the same, several times slower,
  * with the scale applied in float32: 16 tokens at a time on the 2..16-token kernels where these take the shape (d up to
@@ -277,7 +278,7 @@ int halo_ffn_forward_ahead(const halo_shape *shape, const void *x, int32_t T, co
  * to bf16 where d is a multiple of 1024 and stays float32 at the other d); other shapes and float32
  * activations take a plain path that dequantises element by element.  More than 16 tokens (any d a multiple of
  * 128, any n_groups): with a workspace of halo_workspace_bytes_q4 the many-token matrix-core kernels, each value
- * s * (c - 8) rounded to bf16, to nearest even; with less, the 2..16-token kernels 16 tokens at a time where they take
+ * s * (c - 8) rounded to bf16, to nearest even (up to 64 tokens with d >= 256 unrounded, the scale applied in float32); with less, the 2..16-token kernels 16 tokens at a time where they take
  * the shape, else the plain path.
  */
 int halo_group_sparse_ffn_q4(const halo_shape *shape, const void *x, int32_t T, const void *Wg_codes,

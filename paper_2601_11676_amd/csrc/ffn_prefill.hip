@@ -20,7 +20,8 @@
 //                  walking all groups), kept for more tokens than the row table's 16 bits hold.
 //
 // Both ring kernels take bf16 weights or 4-bit codes (Q4); the codes become the bf16 values s * (c - 8), rounded
-// to nearest even, on their way into LDS, between the matrix instructions of the stage before.
+// to nearest even, on their way into LDS, between the matrix instructions of the stage before.  Up to 64 tokens over codes have
+// kernels of their own (prefill_codes.hpp).
 //
 // v_mfma_f32_16x16x32_bf16 operand layout as in ffn_mfma.hip: A lane l = row l%16, elements
 // 8*(l/16)..+7; B lane l = column l%16, same elements; D lane l = column l%16, rows 4*(l/16)..+3.
@@ -29,32 +30,56 @@
 #include <type_traits>
 
 #include "kernels.hpp"
-#include "lds_loads.hpp"
-#include "q4_codes.hpp"
+#include "prefill_codes.hpp"
 
 namespace halo {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f32x4_t mfma16p(const u32x4 &a, const u32x4 &b, const f32x4_t &c)
+// the sums of x over the blocks of 128 elements, 16 lanes to a block, four blocks of a lane requested together
+__device__ __forceinline__ void block_sums(const bf16_t *__restrict__ x, int T, int d, float *__restrict__ xsum, int wg, int n_wg)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                   __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    constexpr int U = 4;
+    const int nb = d / kQ4Block, i16 = threadIdx.x & 15;
+    const size_t n = (size_t)T * nb, stride = (size_t)n_wg * 16;
+    for (size_t i0 = (size_t)wg * 16 + (threadIdx.x >> 4); i0 < n; i0 += stride * U) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t i = i0 + u * stride < n ? i0 + u * stride : i0;
+            v[u] = reinterpret_cast<const u32x4 *>(x)[i * 16 + i16];             // (blocks follow each other token after token)
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t i = i0 + u * stride;
+            float e[8];
+            unpack8(v[u], e);
+            float sum = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+            sum = xor_add<8>(sum);
+            sum = xor_add<4>(sum);
+            sum = xor_add<2>(sum);
+            sum = xor_add<1>(sum);
+            if (i16 == 0 && i < n) xsum[(i % nb) * T + i / nb] = sum;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
-// token lists: grid = G workgroups of 256 threads
+// token lists: grid = G workgroups of 256 threads (and those that add up x)
 // ---------------------------------------------------------------------------
 // rows != nullptr: row table [G][row_pitch] (row_pitch = T rounded up to 8; the entries past T are 0).
 // slot != nullptr instead (more than 32767 tokens): [T][G] positions in the list, -1 = not kept.
-__host__ __device__ inline int prefill_row_pitch(int T) { return (T + 7) & ~7; }
-
+// For gate_up_codes (xsum != nullptr) workgroups past the groups' add up x over the 128 elements of every quantisation block, xsum [d/128][T],
+// and the row of zeros has a sum too, asum [2][G][T].
 __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__restrict__ mask, int T, int G,
                                                            int32_t *__restrict__ tok_list,
                                                            int32_t *__restrict__ tok_cnt, int16_t *__restrict__ rows,
-                                                           int32_t *__restrict__ slot, bf16_t *__restrict__ act)
+                                                           int32_t *__restrict__ slot, bf16_t *__restrict__ act,
+                                                           const bf16_t *__restrict__ x, int d, float *__restrict__ xsum,
+                                                           float *__restrict__ asum)
 {
+    if ((int)blockIdx.x >= G) {
+        block_sums(x, T, d, xsum, blockIdx.x - G, gridDim.x - G);
+        return;
+    }
     __shared__ int s_wave[4];
     __shared__ int s_base;
     const int g = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -92,13 +117,14 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
     // the row after the group's last activation row is kept zero (group size 128): the down
     // projection points the tokens that do not keep the group at it
     if (cnt < T && tid < 64) reinterpret_cast<uint32_t *>(act + ((size_t)g * T + cnt) * 128)[tid] = 0u;
+    if (asum && cnt < T && tid < 2) asum[((size_t)tid * G + g) * T + cnt] = 0.0f;
 }
 
 // ---------------------------------------------------------------------------
 // gate/up through rings in LDS filled by direct global -> LDS loads
 // grid: 8 * ceil(items / 8) workgroups of 512 threads, one per compute unit
 // ---------------------------------------------------------------------------
-// Workgroup tile: 128 weight rows (64 gate + 64 up neurons of one group) x NTOK (256, 128 or 64) of the group's
+// Workgroup tile: 128 weight rows (64 gate + 64 up neurons of one group) x NTOK (256 or 128) of the group's
 // tokens; K advances 64 elements per stage.  In LDS a stage is 128 weight rows and NTOK gathered x
 // rows of 128 bytes.  One load instruction moves 1 KiB = 8 rows x 128 bytes, lane l landing at byte
 // 16 l of the block; to keep the operand reads free of bank conflicts the 16-byte piece p of tile row
@@ -131,7 +157,6 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
 // the 48 KiB come from memory, which is what a compute unit can have in flight; a stage of codes 0.9 us, the conversion
 // being added to the matrix work (59 -> 46 us without it).
 constexpr int kRingStages = 3;
-constexpr int kRingWaves = 8;
 constexpr int kRawBlocks = 3;                                    // blocks of codes in LDS
 constexpr int kRawBytes = 128 * 64 + 128 * 4;                    // codes, then a word with the scale of every row
 
@@ -182,53 +207,6 @@ __device__ __forceinline__ void clear_accumulators(f32x4_t (&acc)[MT][TT])
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int n = 0; n < TT; ++n) acc[m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-}
-
-// Token tiles are numbered group by group (group g has ceil(cnt[g] / tile_tokens) of them), and only
-// tiles that exist get a number, so the working workgroups are consecutive.  Called by whole waves;
-// results are the same in every lane.
-__device__ __forceinline__ int wave_inclusive_sum(int n, int lane)
-{
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(n, off);
-        if (lane >= off) n += v;
-    }
-    return n;
-}
-
-// tiles(n): the tiles of a group that n tokens keep
-template <typename Tiles>
-__device__ __forceinline__ int count_tiles(const int32_t *__restrict__ tok_cnt, int G, int lane, Tiles tiles)
-{
-    int total = 0;
-    for (int g0 = 0; g0 < G; g0 += 64) {
-        const int g = g0 + lane;
-        const int n = g < G ? tiles(tok_cnt[g]) : 0;
-        total += __shfl(wave_inclusive_sum(n, lane), 63);
-    }
-    return total;
-}
-
-// group and tile within the group of tile number `target` (< count_tiles)
-template <typename Tiles>
-__device__ __forceinline__ int2 find_tile(const int32_t *__restrict__ tok_cnt, int G, int target, int lane, Tiles tiles)
-{
-    int base = 0;
-    for (int g0 = 0; g0 < G; g0 += 64) {
-        const int g = g0 + lane;
-        const int n = g < G ? tiles(tok_cnt[g]) : 0;
-        const int incl = wave_inclusive_sum(n, lane);
-        const int total = __shfl(incl, 63);
-        if (target < base + total) {
-            const unsigned long long m = __ballot(target < base + incl);
-            const int l = __ffsll((long long)m) - 1;
-            const int excl = __shfl(incl - n, l);
-            return make_int2(g0 + l, target - base - excl);
-        }
-        base += total;
-    }
-    return make_int2(-1, 0);
 }
 
 // The 4-bit side of a ring: this thread's row of the tile is 16 wave + lane / 4, and it converts elements
@@ -345,7 +323,7 @@ template <bool Q4, int NTOK>
 __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gate_up_pf_ring(
     const bf16_t *__restrict__ x, int T, int d, int G, const void *__restrict__ Wg, const void *__restrict__ Wu,
     const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const int32_t *__restrict__ tok_list,
-    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act)
+    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act, const float *, float *)
 {
     using R = Ring<Q4, NTOK>;
     constexpr int MT = R::kMT, TT = R::kTT, EV = Q4 ? 2 : 0;     // EV: loads of a wave per block of codes
@@ -523,6 +501,16 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         exchange_halves<0, MT, TT>(acc, ring, wave, lane, put);
     else
         exchange_halves<1, MT, TT>(acc, ring, wave, lane, put);
+}
+
+// codes of up to 64 tokens
+template <>
+__global__ __launch_bounds__(kRingWaves * 64, 2) void gate_up_pf_ring<true, 64>(
+    const bf16_t *__restrict__ x, int T, int d, int G, const void *__restrict__ Wg, const void *__restrict__ Wu,
+    const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const int32_t *__restrict__ tok_list,
+    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act, const float *__restrict__ xsum, float *__restrict__ asum)
+{
+    gate_up_codes(x, T, d, G, (const unsigned char *)Wg, (const unsigned char *)Wu, Sg, Su, tok_list, tok_cnt, xsum, act, asum);
 }
 
 // ---------------------------------------------------------------------------
@@ -825,7 +813,6 @@ __global__ __launch_bounds__(256) void down_pf(
 // their partial sums, 1000 tokens 509 + 43 us; one range takes 370).
 // A token that does not keep the group is pointed at the group's row of zeros (written by group_tokens), so
 // it contributes exactly nothing.  Everything else is as in gate_up_pf_ring.
-constexpr int kTabGroups = 4, kTabBytes = 512;                   // groups of the table in LDS; 256 tokens x 2 bytes
 constexpr int kDownMaxSplits = 8;
 
 template <bool Q4, int NTOK>
@@ -877,11 +864,12 @@ static int splits_in_room(int splits, int T, int d, const DecodeScratch &ws)
     return room >= (size_t)splits ? splits : room < 1 ? 1 : (int)room;
 }
 
-// Wd: bf16 [G][d][128], or (Q4) code words [G][d][16] with scales Sd [G][d]; rows: the row table
-template <bool Q4, int NTOK>
+// Wd: bf16 [G][d][128], or (Q4) code words [G][d][16] with scales Sd [G][d]; rows: the row table.  SCALED: codes of up to 64 tokens
+// (down_codes), with the sums of the activations
+template <bool Q4, int NTOK, bool SCALED>
 __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void down_pf_ring(
     int T, int d, int G, int splits, const void *__restrict__ Wd, const bf16_t *__restrict__ Sd,
-    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y)
+    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y, const float *)
 {
     using R = Ring<Q4, NTOK>;
     constexpr int MT = R::kMT, TT = R::kTT, EV = Q4 ? 3 : 1;     // EV: loads of a wave per group besides the stages'
@@ -890,33 +878,10 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const WavePart<MT> part(wave);
     const int i16 = lane & 15, q = lane >> 4;
-    // work items: (token tile, group range, output tile) triples; a die gets a consecutive run of them
-    const int n_ot = d / 128;
-    const int n_tt = (T + NTOK - 1) / NTOK;
-    const int n_items = n_ot * n_tt * splits;
-    const int per_die = (n_items + 7) >> 3;
-    const int die = blockIdx.x & 7, dslot = blockIdx.x >> 3;
-    const int item = die * per_die + dslot;
-    if (dslot >= per_die || item >= n_items) return;             // uniform for the workgroup
-    // Two numberings.  With one or two token tiles the items of a die are the token tiles of consecutive
-    // output tiles of one range: a tile of Wd is fetched from memory by the first and found in the die's
-    // L2 by the second, and the act rows of both token tiles fit beside it.  With more token tiles the
-    // items of a die share one token tile's act rows instead (they would not all fit).
-    int ttile, split, j0;
-    if (n_tt <= 2) {
-        ttile = item % n_tt;
-        const int rest = item / n_tt;
-        split = rest / n_ot;
-        j0 = (rest - split * n_ot) * 128;
-    } else {
-        const int pair = item / n_ot;
-        j0 = (item - pair * n_ot) * 128;
-        ttile = pair / splits;
-        split = pair - ttile * splits;
-    }
-    const int t0 = ttile * NTOK;
-    const int g_lo = (int)((long long)split * G / splits), g_hi = (int)((long long)(split + 1) * G / splits);
-    const int ng = g_hi - g_lo;                                  // >= 1
+    DownItem it;
+    if (!down_item<NTOK>(T, d, G, splits, it)) return;
+    const int t0 = it.t0, j0 = it.j0, g_lo = it.g_lo, split = it.split;
+    const int ng = it.g_hi - g_lo;                               // >= 1
     const int ns = 2 * ng;
 
     // loading role: the stage's blocks of 8 rows are dealt round-robin, wave w takes the act blocks w + 8 j and (bf16)
@@ -1078,6 +1043,14 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         exchange_halves<1, MT, TT>(acc, ring, wave, lane, put);
 }
 
+template <>
+__global__ __launch_bounds__(kRingWaves * 64, 2) void down_pf_ring<true, 64, true>(
+    int T, int d, int G, int splits, const void *__restrict__ Wd, const bf16_t *__restrict__ Sd,
+    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y, const float *__restrict__ asum)
+{
+    down_codes(T, d, G, splits, (const unsigned char *)Wd, Sd, rows, act, asum, partial, y);
+}
+
 // y = sum of the ranges' partial sums, added in the order of the ranges; n = T * d, a multiple of 8
 __global__ __launch_bounds__(256) void reduce_partials(const float *__restrict__ partial, int splits, size_t n,
                                                        bf16_t *__restrict__ y)
@@ -1104,16 +1077,26 @@ bool prefill_path_supported(int T, int d, int gs)
     return T > 1 && d % 128 == 0 && gs == 128 && (size_t)T * d * sizeof(bf16_t) < (1ull << 31);
 }
 
+// Up to 64 tokens over codes (rows of at least 256: pairs of blocks): prefill_codes.hpp, the scale applied in float as for fewer tokens.  Above
+// that the values are rounded to bf16 and the results are those of the bf16 kernels on the expanded weights, bit for bit, which callers may
+// count on (the same kernel in a 128-token tile would run 13B, 100 tokens of d 3200 and 128 in 70 us instead of 85 and 98 instead of 109).
+static bool codes_path(int T, int d) { return T <= 64 && d >= 256; }
+// ... and its sums: of x where the expanded weights would go, of the activations, [2][G][T], behind these (which are halves of the words
+// that the workspace has for them)
+static float *codes_x_sums(const DecodeScratch &ws) { return reinterpret_cast<float *>(ws.q4_w); }
+static float *codes_act_sums(const DecodeScratch &ws, int T, int G) { return ws.act + (size_t)T * G * 64; }
+
 template <bool Q4, int NTOK>
 static hipError_t launch_gate_up_ring(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const bf16_t *Sg,
                                       const bf16_t *Su, const DecodeScratch &ws, bf16_t *act, hipStream_t s)
 {
-    const hipError_t lds_ok = allow_lds<gate_up_pf_ring<Q4, NTOK>>(Ring<Q4, NTOK>::kBytes);
+    constexpr int bytes = Q4 && NTOK == 64 ? kCodesBytes : Ring<Q4, NTOK>::kBytes;
+    const hipError_t lds_ok = allow_lds<gate_up_pf_ring<Q4, NTOK>>(bytes);
     if (lds_ok != hipSuccess) return lds_ok;
     const int items_max = 2 * G * ((T + NTOK - 1) / NTOK);                  // every group kept by every token
     launch_timed_lds("gate_up_pf_ring", gate_up_pf_ring<Q4, NTOK>, dim3((items_max + 7) / 8 * 8), dim3(kRingWaves * 64),
-                     Ring<Q4, NTOK>::kBytes, s, x, T, d, G, Wg, Wu, Sg, Su, (const int32_t *)ws.tok_list,
-                     (const int32_t *)ws.tok_cnt, act);
+                     bytes, s, x, T, d, G, Wg, Wu, Sg, Su, (const int32_t *)ws.tok_list, (const int32_t *)ws.tok_cnt, act,
+                     (const float *)codes_x_sums(ws), codes_act_sums(ws, T, G));
     return hipSuccess;
 }
 
@@ -1123,16 +1106,17 @@ static void launch_reduce(const float *partial, int splits, int T, int d, bf16_t
     reduce_partials<<<dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s>>>(partial, splits, n, y);
 }
 
-template <bool Q4, int NTOK>
+template <bool Q4, int NTOK, bool SCALED = false>
 static hipError_t launch_down_ring(int T, int d, int G, int splits, const void *Wd, const bf16_t *Sd, const DecodeScratch &ws,
                                    const bf16_t *act, bf16_t *y, hipStream_t s)
 {
-    constexpr int bytes = down_ring_bytes<Q4, NTOK>();
-    const hipError_t lds_ok = allow_lds<down_pf_ring<Q4, NTOK>>(bytes);
+    constexpr int bytes = SCALED ? kCodesBytes + kTabGroups * kTabBytes / 2 : down_ring_bytes<Q4, NTOK>();
+    const hipError_t lds_ok = allow_lds<down_pf_ring<Q4, NTOK, SCALED>>(bytes);
     if (lds_ok != hipSuccess) return lds_ok;
     const int items = (d / 128) * ((T + NTOK - 1) / NTOK) * splits;
-    down_pf_ring<Q4, NTOK><<<dim3((items + 7) / 8 * 8), dim3(kRingWaves * 64), bytes, s>>>(
-        T, d, G, splits, Wd, Sd, reinterpret_cast<const int16_t *>(ws.slot), act, splits > 1 ? ws.partial : (float *)nullptr, y);
+    down_pf_ring<Q4, NTOK, SCALED><<<dim3((items + 7) / 8 * 8), dim3(kRingWaves * 64), bytes, s>>>(
+        T, d, G, splits, Wd, Sd, reinterpret_cast<const int16_t *>(ws.slot), act, splits > 1 ? ws.partial : (float *)nullptr, y,
+        SCALED ? (const float *)codes_act_sums(ws, T, G) : (const float *)nullptr);
     if (splits > 1) launch_reduce(ws.partial, splits, T, d, y, s);
     return hipSuccess;
 }
@@ -1162,12 +1146,9 @@ static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const
 // In the down projection also where whole tiles times ranges would fill less than half of the chip: 200 tokens of d 2048, one
 // range, 41.7 us against 63.4; 200 tokens of d 1024 10.0 against 13.6.
 //
-// Quarter tiles where they hold all of a group's tokens, whatever the mask: up to 64 tokens.  Gate/up over codes only: there
-// a stage is matrix work, LDS reads and conversion one after the other, and the first two are halved; with bf16 weights it waits for
-// memory, and a stage of fewer bytes keeps fewer in flight.  Pass in us, half tiles against quarter tiles in gate/up alone
-// and in both projections: codes, 17 tokens, 7B 78.9 / 71.3 / 69.3, 13B 97.9 / 90.5 / 86.3, 70B 266 / 245 / 231; 64 tokens of 13B
-// 106.7 / 97.8 / 93.2; bf16, 17 tokens, 7B 78.5 / 78.4 / 76.4, 70B 267 / 273 / 270.  Above 64 tokens most groups need two
-// quarter tiles, each converting the codes: 100 tokens of 13B 109.1 against 107.5, 128 tokens 109.3 against 110.7.
+// Quarter tiles where they hold all of a group's tokens, whatever the mask: up to 64 tokens, in the down projection (and over codes, see
+// codes_path).  Not in gate/up: it waits for memory, and a stage of fewer bytes keeps fewer in flight.  Pass in us, half tiles against quarter
+// tiles in gate/up alone and in both projections: 17 tokens, 7B 78.5 / 78.4 / 76.4, 70B 267 / 273 / 270.
 // In the down projection also where half tiles times ranges would fill less than half of the chip.  Half against quarter, bf16
 // and codes: 256 tokens of d 2048 77.4 / 68.4 and 96.1 / 89.2, 200 of d 2560 101.5 / 94.2 and 119.6 / 111.3, 100 of d 3072
 // 79.6 / 76.7 and 83.3 / 79.6, 600 of d 768 54.0 / 49.3 and 62.9 / 59.2; where they fill more than that, 100 tokens of 13B
@@ -1175,7 +1156,6 @@ static hipError_t launch_gate_up_big(const bf16_t *x, int T, int d, int G, const
 // 16.3 / 15.1 and 19.4 / 18.1, 256 tokens 17.6 / 16.0 and 20.6 / 18.9; d 640, 40 groups, 128 tokens 28.3 / 25.9 and 32.4 / 30.5; d 1024,
 // 6 groups, 256 tokens 28.7 / 26.4 and 32.8 / 30.6; over d 256 .. 1024, 2 .. 40 groups, 65 .. 400 tokens 1.00 to 1.12 times as fast, never
 // slower.  Rows of one output tile stay as they are.
-static bool gate_up_quarter_tiles(bool q4, int T, int d) { return q4 && T <= 64 && d >= 256; }
 static bool down_quarter_tiles(int T, int d, int splits)
 {
     return d >= 256 && (T <= 64 || (long long)(d / 128) * ((T + 127) / 128) * splits < 128);
@@ -1189,7 +1169,7 @@ static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void 
     hipError_t e;
     if (!Q4 && gate_up_big_tiles(T, G))
         e = launch_gate_up_big(x, T, d, G, (const bf16_t *)Wg, (const bf16_t *)Wu, ws, act, s);
-    else if (gate_up_quarter_tiles(Q4, T, d))
+    else if (Q4 && codes_path(T, d))
         e = launch_gate_up_ring<Q4, Q4 ? 64 : 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);   // (no bf16 form is built)
     else if (T <= 256)
         e = launch_gate_up_ring<Q4, 128>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
@@ -1197,7 +1177,9 @@ static hipError_t launch_rings(const bf16_t *x, int T, int d, int G, const void 
         e = launch_gate_up_ring<Q4, 256>(x, T, d, G, Wg, Wu, Sg, Su, ws, act, s);
     if (e != hipSuccess) return e;
     const int splits = splits_in_room(down_splits(T, d, G), T, d, ws);
-    if (down_quarter_tiles(T, d, splits))
+    if (Q4 && codes_path(T, d))
+        e = launch_down_ring<Q4, 64, Q4>(T, d, G, splits, Wd, Sd, ws, act, y, s);
+    else if (down_quarter_tiles(T, d, splits))
         e = launch_down_ring<Q4, 64>(T, d, G, splits, Wd, Sd, ws, act, y, s);
     else if (T <= 128 || (d / 128) * ((T + 255) / 256) * splits < 128)
         e = launch_down_ring<Q4, 128>(T, d, G, splits, Wd, Sd, ws, act, y, s);
@@ -1216,7 +1198,8 @@ hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, cons
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
     const bool ring = prefill_down_splits(T, d, G) > 0 && row_table_fits(T);
     group_tokens_kernel<<<dim3(G), dim3(256), 0, s>>>(mask, T, G, ws.tok_list, ws.tok_cnt,
-                                                     ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act);
+                                                     ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act, x, d,
+                                                     nullptr, nullptr);
     if (ring) return launch_rings<false>(x, T, d, G, Wg, Wu, Wd, nullptr, nullptr, nullptr, ws, act, y, s);
     const hipError_t e = launch_gate_up_ring<false, 256>(x, T, d, G, Wg, Wu, nullptr, nullptr, ws, act, s);
     if (e != hipSuccess) return e;
@@ -1234,8 +1217,10 @@ hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4W
                                  const DecodeScratch &ws, hipStream_t s)
 {
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
-    group_tokens_kernel<<<dim3(G), dim3(256), 0, s>>>(mask, T, G, ws.tok_list, ws.tok_cnt,
-                                                     reinterpret_cast<int16_t *>(ws.slot), ws.slot, act);
+    const bool codes = codes_path(T, d);
+    group_tokens_kernel<<<dim3(G + (codes ? (T * (d / kQ4Block) + 63) / 64 : 0)), dim3(256), 0, s>>>(
+        mask, T, G, ws.tok_list, ws.tok_cnt, reinterpret_cast<int16_t *>(ws.slot), ws.slot, act, x, d, codes ? codes_x_sums(ws) : nullptr,
+        codes ? codes_act_sums(ws, T, G) : nullptr);
     return launch_rings<true>(x, T, d, G, w.gate_codes, w.up_codes, w.down_codes, w.gate_scales, w.up_scales, w.down_scales,
                               ws, act, y, s);
 }

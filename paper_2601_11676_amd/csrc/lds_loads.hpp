@@ -36,7 +36,20 @@ __device__ __forceinline__ void load_to_lds16(const srd_t &srd, uint32_t voff, u
                      "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(__builtin_amdgcn_readfirstlane(lds_addr))
                      : "memory");
 }
-// the same for the lanes of `lanes` only: a lane out of range still writes zeros to its place in LDS, a lane that is
+// the same with the LDS address lds_addr + AT: one scalar instruction
+template <int AT, bool STREAM = false>
+__device__ __forceinline__ void load_to_lds16_at(const srd_t &srd, uint32_t voff, uint32_t soff, uint32_t lds_addr)
+{
+    if (STREAM)
+        asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen nt lds" ::"v"(voff), "s"(srd),
+                     "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "n"(AT)
+                     : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(srd),
+                     "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "n"(AT)
+                     : "memory", "scc");
+}
+// the same as load_to_lds16 for the lanes of `lanes` only: a lane out of range still writes zeros to its place in LDS, a lane that is
 // switched off writes nothing.  BYTES: 16 or 4.
 template <int BYTES>
 __device__ __forceinline__ void load_to_lds_lanes(unsigned long long lanes, const srd_t &srd, uint32_t voff, uint32_t soff,

@@ -491,3 +491,29 @@ def test_q4_more_tokens_than_the_row_table_holds(G, K):
     c = hz.oracle_forward(w, L, x[torch.from_numpy(rows).to(hz.DEV)], K, pd, drop[rows])
     hz.assert_parity({k: v[rows] for k, v in g.items()}, c, TOL["bf16"], "q4 past the row table")
     assert np.isfinite(g["y"]).all()
+
+
+@pytest.mark.parametrize("mean", [0, 1])
+@pytest.mark.parametrize("T,d,G,K", [
+    (17, 256, 1, 1),           # one group: half a pair of groups in down, one pair of blocks in gate/up
+    (18, 384, 5, 3),           # three blocks: some dies start their walk at half a pair
+    (32, 256, 7, 7),           # dense, two full 16-token tiles
+    (33, 640, 9, 4),           # an odd number of blocks per row: the scales' words straddle rows; three tiles in down
+    (49, 1024, 12, 6),         # four tiles
+    (64, 768, 33, 20),         # the full tile, ranges of an odd number of groups
+    (64, 2176, 9, 9),          # dense, 17 blocks
+])
+def test_q4_17_to_64_tokens_scale_in_float(T, d, G, K, mean):
+    # nothing is rounded but the activation and y, 2^-9 of a value at most each (relative L2 2.8e-3 together, 3.3e-3 with rounded
+    # weights); the offset that the codes carry cancels also where the tokens' values do not sum to about nothing
+    w = dataclasses.replace(hs.LLAMA7B_PREFILL, name="case", d=d, ffn=G * 128, rank=64, T=T, seed=91)
+    _say(f"q4 17 to 64 tokens T={T} d={d} G={G} K={K} mean={mean}")
+    L = hz.Q4Layer(w)
+    x = (hs.hidden_states(w, 0, hz.DEV).float() + mean).to(torch.bfloat16)
+    pd = H.halo_build_schedule(K, w.device_plr())
+    drop = hs.drop_outcomes(w, T=T)
+    drop[T - 1] = 1                            # a token that loses every device: exact zeros expected
+    g = hz.gpu_forward_q4(w, L, x, K, pd, drop, big_workspace=True)
+    c = hz.oracle_forward(w, L, x, K, pd, drop)
+    hz.assert_parity(g, c, TOL["bf16"], f"q4 17 to 64 tokens T={T}")
+    assert np.linalg.norm(g["y"] - c["y"]) <= 2 ** 0.5 * 2.0 ** -9 * np.linalg.norm(c["y"])

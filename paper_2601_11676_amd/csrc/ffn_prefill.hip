@@ -154,8 +154,8 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
 // What bounds them now, from builds with one thing taken out at a time (7B shape, 512 tokens): a launch, the tile
 // lookup, the first stage and the exchange at the end 12 us; a stage 0.53 us of matrix work at what the chip sustains (46
 // and 38 us with nothing else), 0.57 with the LDS reads, the barrier and loads that move nothing, 0.80 in gate/up when
-// the 48 KiB come from memory, which is what a compute unit can have in flight; a stage of codes 0.9 us, the conversion
-// being added to the matrix work (59 -> 46 us without it).
+// the 48 KiB come from memory, which is what a compute unit can have in flight; a stage of codes 0.8 us, the conversion
+// being added to the matrix work.
 constexpr int kRingStages = 3;
 constexpr int kRawBlocks = 3;                                    // blocks of codes in LDS
 constexpr int kRawBytes = 128 * 64 + 128 * 4;                    // codes, then a word with the scale of every row
@@ -210,14 +210,14 @@ __device__ __forceinline__ void clear_accumulators(f32x4_t (&acc)[MT][TT])
 }
 
 // The 4-bit side of a ring: this thread's row of the tile is 16 wave + lane / 4, and it converts elements
-// 16 (lane & 3) .. + 15 of every stage: eight pairs, each in three parts of two or three vector instructions.
+// 16 (lane & 3) .. + 15 of every stage: eight pairs, each in three parts of one or two vector instructions.
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 struct Q4Stage {
     uint2 codes;
     u32x4 out;
-    float scale, off, lo, hi;
-    uint32_t word, pair;
-    Q4Consts k;
+    float scale[2], off, lo, hi;
+    uint32_t word, pair, shifted;
     // block slot `raw` (LDS bytes), second or first stage of the block
     __device__ __forceinline__ void read(const unsigned char *raw, int wave, int lane, bool second)
     {
@@ -228,20 +228,28 @@ struct Q4Stage {
     // upper: the scale is the upper half of the word
     __device__ __forceinline__ void set_scale(bool upper)
     {
-        scale = __uint_as_float(upper ? word & 0xffff0000u : word << 16);
-        off = -136.0f * scale;
+        const float s = __uint_as_float(upper ? word & 0xffff0000u : word << 16);
+        scale[0] = 0x1p24f * s;
+        scale[1] = 0x1p20f * s;
+        off = -8.0f * s;
     }
-    // part 0, 1, 2 of pair p (0..7): s * (128 + c) - 136 s = s * (c - 8), exact in float; one instruction rounds both
+    // part 0, 1, 2 of pair p (0..7).  A code in the lowest bits of a half float is c 2^-24, four bits further up c 2^-20, and
+    // the mixed multiply-add takes half floats as they lie in the pair: s 2^24 * c 2^-24 - 8 s = s * (c - 8), exact in float (scales
+    // below 2^104); one instruction rounds both.  4.25 instructions per pair; as 128 + c in bf16, which has to be widened first, 6.75: a
+    // pass of 128 tokens at the 13B shape 109 -> 106 us, of 600 at 70B 760 -> 732, 97 tokens of d 3200, 75 groups 85.1 -> 81.3
     __device__ __forceinline__ void part(int p, int which)
     {
         const int i = p & 3;
         if (which == 0) {
-            pair = (((p >> 2 ? codes.y : codes.x) >> (4 * i)) & k.mask) | k.one28;
+            const uint32_t w = p >> 2 ? codes.y : codes.x;
+            if (i == 2) shifted = w >> 8;
+            pair = (i < 2 ? w : shifted) & (i & 1 ? 0x00F000F0u : 0x000F000Fu);
         } else if (which == 1) {
-            lo = bf16_lo(pair);
-            hi = bf16_hi(pair);
+            const f16x2_t h = __builtin_bit_cast(f16x2_t, pair);
+            lo = __builtin_fmaf((float)h[0], scale[i & 1], off);
+            hi = __builtin_fmaf((float)h[1], scale[i & 1], off);
         } else {
-            const f32x2_t v = {__builtin_fmaf(lo, scale, off), __builtin_fmaf(hi, scale, off)};
+            const f32x2_t v = {lo, hi};
             out[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
         }
     }
@@ -418,7 +426,6 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     // compute is stored.)
     Q4Stage qs;
     if (Q4) {
-        qs.k = q4_consts();
 #pragma unroll
         for (int e = 0; e < kRawBlocks; ++e) request_codes(e, e < nd);
     }
@@ -952,7 +959,6 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     }
     Q4Stage qs;
     if (Q4) {
-        qs.k = q4_consts();
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             qs.read(raw_of(0), wave, lane, k == 1);

@@ -11,10 +11,11 @@
 // WHICH 4 of a 16-element piece an instruction's lane group multiplies is free as long as both operands agree:
 // lane (i, q) = (l % 16, l / 16) holds elements 4 q .. 4 q + 3 of row i in one 16-byte load, and instruction e
 // multiplies element 4 q + e of every lane group.  D: lane l holds column (token) l % 16, rows 4 (l / 16) .. + 3.
-// Tiny block: gate/up 4.6 us and down 5.8 us per launch, the pass called from Python 16 us; a wave per neuron / per output
+// Tiny block: gate/up 4.6 us and down 5.8 us per launch; a wave per neuron / per output
 // row that walked its groups one 4-byte load at a time took 10, 68 and 89.  Error against 64 bits over d 128..1024, 4..24 groups,
 // 1..64 tokens: 0.89..1.01 times theirs.
 #include "kernels.hpp"
+#include "mask_device.hpp"
 
 namespace halo {
 
@@ -79,17 +80,20 @@ struct PairSum {
 // Chunks of 128 elements through LDS, as in the down projection: 4.5 us at the tiny block, but 10 and 21 at these two.)
 // ASK, for the few tokens that leave groups unwanted: the first loads wait for the mask bytes, and a compute unit takes one workgroup, so
 // that those that leave at once do not pair the others up.  Else the first pair is requested beside the mask bytes.
-template <int NT, bool ASK>
-__global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2, ASK ? 2 : 8))) void gate_up_f32(
-    const float *__restrict__ x, int T, int d, int G, int gs, const float *__restrict__ Wg, const float *__restrict__ Wu,
-    const uint8_t *__restrict__ mask, float *__restrict__ act, size_t group_stride, int token_stride)
+enum class F32Asks { kAfterMask, kBeside, kAll };                // kAll: no mask, act of every group and token
+
+template <int NT, F32Asks ASKS>
+__device__ __forceinline__ void gate_up_f32_block(int tile_x, int tile_y, const float *__restrict__ x, int T, int d, int G, int gs,
+                                                  const float *__restrict__ Wg, const float *__restrict__ Wu,
+                                                  const uint8_t *__restrict__ mask, float *__restrict__ act, size_t group_stride, int token_stride)
 {
     constexpr int W = kGateUpF32Waves;
     __shared__ f32x4_t part[W][2][NT][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * 16, g = n0 / gs, t0 = blockIdx.y * 16 * NT;
-    const uint8_t mine = mask[(size_t)min(t0 + min(lane, 16 * NT - 1), T - 1) * G + g];
+    constexpr bool kAll = ASKS == F32Asks::kAll;
+    const int n0 = tile_x * 16, g = n0 / gs, t0 = tile_y * 16 * NT;
+    const uint8_t mine = kAll ? 1 : mask[(size_t)min(t0 + min(lane, 16 * NT - 1), T - 1) * G + g];
     // (descriptors of the workgroup's own rows: the offsets stay small whatever the matrices' sizes)
     const __amdgpu_buffer_rsrc_t bg = buffer_of(Wg + (size_t)n0 * d), bu = buffer_of(Wu + (size_t)n0 * d),
                                  bx = buffer_of(x + (size_t)t0 * d);
@@ -109,11 +113,11 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_p
         for (int n = 0; n < NT; ++n) b.x[n] = load4(bx, ok ? at_x[n] : kOutOfRange, p * 64);
     };
     const bool wanted_by_any = __ballot(mine != 0) != 0ull;      // uniform: the same bytes in every wave
-    if (ASK && !wanted_by_any) return;
+    if (ASKS == F32Asks::kAfterMask && !wanted_by_any) return;
     Piece b[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) fetch(b[k], 2 * wave + k);
-    if (!ASK && !wanted_by_any) return;
+    if (ASKS == F32Asks::kBeside && !wanted_by_any) return;
     f32x4_t cg[NT], cu[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) cg[n] = cu[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_p
         }
         const f32x4_t g_ = pairwise_sum(pg), u_ = pairwise_sum(pu);
         const int t = t0 + 16 * wave + i;
-        const bool wanted = __shfl(mine, 16 * wave + i) != 0;
+        const bool wanted = kAll || __shfl(mine, 16 * wave + i) != 0;
         if (t < T) {
             f32x4_t v;
 #pragma unroll
@@ -153,6 +157,37 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_p
             *reinterpret_cast<f32x4_t *>(act + g * group_stride + (size_t)t * token_stride + (n0 - g * gs) + 4 * q) = v;
         }
     }
+}
+
+template <int NT, bool ASK>
+__global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2, ASK ? 2 : 8))) void gate_up_f32(
+    const float *__restrict__ x, int T, int d, int G, int gs, const float *__restrict__ Wg, const float *__restrict__ Wu,
+    const uint8_t *__restrict__ mask, float *__restrict__ act, size_t group_stride, int token_stride)
+{
+    gate_up_f32_block<NT, ASK ? F32Asks::kAfterMask : F32Asks::kBeside>(blockIdx.x, blockIdx.y, x, T, d, G, gs, Wg, Wu, mask, act,
+                                                                        group_stride, token_stride);
+}
+
+// The whole pass of a small block in two launches: gate/up of EVERY group beside the first predictor layer, then the down projection,
+// whose workgroups work out the masks of their tokens.  Such a pass is a chain of launches that each wait for the one before: prediction,
+// gate/up and down of the tiny block take 6.6 + 4.5 + 5.7 us, these two 4.7 + 7.8, a pass 16.4 -> 12.4 us.  Reading the groups that nobody
+// keeps costs less than the launches while the weights are few (forward_f32_supported has the line).
+// This one: n_gu workgroups of gate/up, 8 G to a range of tokens, then a wave per result of the first layer.  Groups of 128, act [g][t][128].
+template <int NT>
+__global__ __launch_bounds__(kGateUpF32Waves * 64) void hidden_gate_up_f32(
+    const float *__restrict__ x, int T, int d, int G, const float *__restrict__ Wg, const float *__restrict__ Wu, float *__restrict__ act,
+    const float *__restrict__ x_pred, const float *__restrict__ At, int r, float *__restrict__ h, int n_gu)
+{
+    if ((int)blockIdx.x < n_gu) {
+        const int n_x = G * 8;                                   // tiles of 16 neurons
+        gate_up_f32_block<NT, F32Asks::kAll>(blockIdx.x % n_x, blockIdx.x / n_x, x, T, d, G, 128, Wg, Wu, nullptr, act, (size_t)T * 128, 128);
+        return;
+    }
+    const int lane = threadIdx.x & 63, idx = (blockIdx.x - n_gu) * kGateUpF32Waves + (threadIdx.x >> 6);
+    if (idx >= T * r) return;                                    // uniform per wave
+    const int t = idx / r, j = idx - t * r;
+    const float p = dot_order64(x_pred + (size_t)t * d, At + (size_t)j * d, d, lane);
+    if (lane == 0) h[idx] = p > 0.0f ? p : 0.0f;
 }
 
 // Groups of 128 neurons, act[g][t][128].  grid (ceil(d / 16), ceil(T / 16)); uses act and Wd of the groups that a token of its own
@@ -253,6 +288,232 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32_128(
         const f32x4_t s = pairwise_sum(p);
         const int t = t0 + i, j = j0 + 4 * q;
         if (t < T && j < d) *reinterpret_cast<f32x4_t *>(y + (size_t)t * d + j) = s;     // (d is a multiple of 8)
+    }
+}
+
+// ... and this one: down_f32_128 with the mask of its 16 tokens worked out by its 16 waves, up to 32 groups: the second predictor
+// layer in the fixed order (same bits as mask_scores_block), a group's rank by comparing its key with all others, a lane per group.  act holds every token's activations
+// of every group here, so what a token does not keep is dropped as it is loaded.  The workgroups of the first 16 outputs write the
+// prediction's results.
+struct PredictF32 {
+    const float *h, *Bt;
+    int r, K, n_dev, share;                                      // share: waves to a row (pair of rows) of Bt
+    unsigned long long parts;                                    // four bits a wave: which of them it is
+    const int8_t *prio_dev;
+    const uint8_t *drop;
+    float *scores;
+    int32_t *order;
+    int8_t *group_dev;
+    uint8_t *mask;
+    int32_t *surv_idx, *n_surv;
+};
+// rows, or pairs of them, that a wave of the 16 can take
+static int f32_score_slots(int G, int r) { return r <= 256 ? (G + 1) / 2 : G; }
+
+// What the prediction of 16 tokens holds in LDS, in the place of the projection's stages: h padded with zeros to 256 or 512 elements,
+// scores and rank keys of up to 32 groups.
+struct PredictF32Lds {
+    __attribute__((aligned(16))) float h[16 * 512];
+    __attribute__((aligned(16))) unsigned long long key[16][32];
+    float score[16][32];
+};
+
+// Scores and keys of tokens t0 .. + n_tok - 1 (at most 16); called by the whole workgroup of 16 waves.  A row of Bt (up to rank 256: a pair
+// of rows, one to each half of the wave, as in mask_scores_block) and four tokens at a time are a wave's share (with a token to every wave,
+// from memory, the rows went through the unit's cache 16 times: 3.3 to 6 us more than without a mask to make).  The four tokens' butterflies
+// share their first two steps: what two tokens send across a distance is swapped in one exchange, and the partial sums meet as they
+// do in xor_add, so the bits are the same (four butterflies of their own: d 816, 20 groups, rank 128, 20 tokens 14.1 us).
+// beside(): what else is to be asked for behind the requests here.
+template <typename Beside>
+__device__ __forceinline__ void scores_f32_block(const PredictF32 &p, int t0, int n_tok, int G, int tid, PredictF32Lds &sh, Beside beside)
+{
+    constexpr int W = kDownF32Waves, TB = 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = p.r;
+    const bool paired = r <= 256;
+    const int pl = paired ? (lane & 31) : lane, half = paired ? (lane >> 5) : 0, n_slots = paired ? (G + 1) / 2 : G;
+    // as many waves to a slot as there are, each some of the tokens
+    const int part = (int)(p.parts >> (4 * wave)) & 15, slot = wave - part * n_slots, row = paired ? 2 * slot + half : slot;
+    const int shift = paired ? 6 : 7, pitch = paired ? 256 : 512;                    // 16-byte pieces of a token's h: 64 or 128
+    const __amdgpu_buffer_rsrc_t bh = buffer_of(p.h + (size_t)t0 * r), bb = buffer_of(p.Bt);
+    f32x4_t hv[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int idx = tid + k * W * 64, t = idx >> shift, c = (idx - (t << shift)) * 4;
+        hv[k] = load4(bh, t < n_tok && c < r ? (uint32_t)(t * r + c) * 4 : kOutOfRange, 0);
+    }
+    const uint32_t at_row = pl * 8 < r && row < G ? (uint32_t)(row * r + pl * 8) * 4 : kOutOfRange;
+    const f32x4_t w0 = load4(bb, at_row, 0), w1 = load4(bb, at_row, 16);
+    beside();
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 512) (&sh.key[0][0])[tid] = 0ull;                  // (the pad of an odd number of groups)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (k == 0 || !paired) reinterpret_cast<f32x4_t *>(sh.h)[tid + k * W * 64] = hv[k];
+    __syncthreads();
+    for (int t = part * TB; part < p.share && t < n_tok; t += p.share * TB) {        // uniform
+        float q[TB];
+#pragma unroll
+        for (int k = 0; k < TB; ++k) {
+            const f32x4_t *hp = reinterpret_cast<const f32x4_t *>(sh.h + (t + k) * pitch + pl * 8);
+            const f32x4_t h0 = hp[0], h1 = hp[1];
+            q[k] = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[k] = __builtin_fmaf(h0[e], w0[e], q[k]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[k] = __builtin_fmaf(h1[e], w1[e], q[k]);
+        }
+        auto as_u = [](float v) { return __builtin_bit_cast(unsigned, v); };
+        auto as_f = [](unsigned v) { return __builtin_bit_cast(float, v); };
+        float v;
+        int k;                                                   // whose sum this lane ends with
+        bool writes;
+        if (paired) {
+            // distance 32: the upper half's partial sums are +0
+#pragma unroll
+            for (int n = 0; n < TB; ++n) q[n] = q[n] + 0.0f;
+            const auto ab = __builtin_amdgcn_permlane16_swap(as_u(q[0]), as_u(q[1]), false, false), cd = __builtin_amdgcn_permlane16_swap(as_u(q[2]), as_u(q[3]), false, false);
+            const float s01 = xor_add<8>(as_f(ab[0]) + as_f(ab[1])), s23 = xor_add<8>(as_f(cd[0]) + as_f(cd[1]));
+            v = lane & 8 ? s23 : s01;
+            k = (lane >> 4 & 1) + (lane & 8 ? 2 : 0);
+            writes = (lane & 7) == 0;
+        } else {
+            const auto ab = __builtin_amdgcn_permlane32_swap(as_u(q[0]), as_u(q[1]), false, false), cd = __builtin_amdgcn_permlane32_swap(as_u(q[2]), as_u(q[3]), false, false);
+            const auto m = __builtin_amdgcn_permlane16_swap(as_u(as_f(ab[0]) + as_f(ab[1])), as_u(as_f(cd[0]) + as_f(cd[1])), false, false);
+            v = xor_add<8>(as_f(m[0]) + as_f(m[1]));
+            k = (lane >> 5) + (lane & 16 ? 2 : 0);
+            writes = (lane & 15) == 0;
+        }
+        v = xor_add<4>(v);
+        v = xor_add<2>(v);
+        v = xor_add<1>(v);
+        if (writes && row < G && t + k < n_tok) {
+            sh.score[t + k][row] = v;
+            sh.key[t + k][row] = rank_key(v, row);
+        }
+    }
+    __syncthreads();
+}
+
+// The groups that token t keeps, from the keys in LDS; called by a whole wave, whose halves share the comparisons: lane g and lane g + 32 are
+// group g's.
+__device__ __forceinline__ uint32_t token_mask_32(const PredictF32 &p, int t, int G, int lane, const unsigned long long *keys, float score, int8_t prio,
+                                                  uint8_t lost, bool write)
+{
+    const int g = lane & 31, n2 = (G + 1) / 2;
+    const unsigned long long key = keys[g];
+    const ulonglong2 *k2 = reinterpret_cast<const ulonglong2 *>(keys);
+    int pos = 0;                                                 // groups that come before this lane's
+    for (int o = 0; o < n2; o += 4) {                            // (keys past the groups are 0 and come before none)
+        const ulonglong2 a = k2[o + (lane >> 5)], b = k2[o + 2 + (lane >> 5)];
+        pos += (a.x > key ? 1 : 0) + (a.y > key ? 1 : 0) + (b.x > key ? 1 : 0) + (b.y > key ? 1 : 0);
+    }
+    pos += __shfl_xor(pos, 32);
+    const int planned = __shfl((int)prio, min(pos, 63));         // (all lanes take part: the bytes lie in each of them)
+    const int dev = lane < G && pos < p.K && planned >= 0 && planned < p.n_dev ? planned : -1;      // malformed entry: not executed
+    const int gone = __shfl((int)lost, max(dev, 0));
+    const bool keep = dev >= 0 && gone == 0;
+    const uint32_t kept = (uint32_t)__ballot(keep);              // (G <= 32)
+    if (write && lane < G) {
+        const size_t at = (size_t)t * G + lane;
+        p.scores[at] = score;
+        if (p.order) p.order[(size_t)t * G + pos] = lane;
+        if (p.group_dev) p.group_dev[at] = (int8_t)dev;
+        p.mask[at] = keep ? 1 : 0;
+        const int total = __popc(kept);
+        if (p.surv_idx) {
+            if (keep) p.surv_idx[(size_t)t * p.K + __popc(kept & ((1u << lane) - 1u))] = lane;
+            if (lane >= total && lane < p.K) p.surv_idx[(size_t)t * p.K + lane] = -1;
+        }
+        if (p.n_surv && lane == 0) p.n_surv[t] = total;
+    }
+    return kept;
+}
+
+__global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const float *__restrict__ act, int T, int d, int G,
+                                                                       const float *__restrict__ Wd, float *__restrict__ y, PredictF32 pr)
+{
+    constexpr int W = kDownF32Waves, gs = 128;
+    __shared__ __attribute__((aligned(16))) float stage[kTurn * 2 * 16 * kRowF32];
+    static_assert(sizeof(PredictF32Lds) <= sizeof(stage), "the prediction comes before the stages");
+    __shared__ uint32_t s_kept[W];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, q = lane >> 4, half = wave >> 3, row = (tid >> 5) & 15, col = (tid & 31) * 4;
+    const int j0 = blockIdx.x * 16, t0 = blockIdx.y * 16, n_tok = min(T - t0, 16);
+    const uint32_t voff = half ? (row < n_tok ? (uint32_t)(row * gs + col) * 4 : kOutOfRange) : (uint32_t)(min(row, d - 1 - j0) * gs + col) * 4;
+    auto fetch = [&](int g, bool yes) -> f32x4_t {
+        const float *p = half ? act + ((size_t)g * T + t0) * gs : Wd + ((size_t)g * d + j0) * gs;
+        return load4(buffer_of(p, yes ? 0x7fffffff : 0), voff, 0);
+    };
+    // schedule and loss outcomes, a byte per lane
+    const int t = t0 + min(wave, n_tok - 1);
+    const int8_t prio = pr.K > 0 ? pr.prio_dev[min(lane, pr.K - 1)] : (int8_t)-1;
+    const uint8_t lost = pr.drop ? pr.drop[(size_t)t * pr.n_dev + min(lane, pr.n_dev - 1)] : (uint8_t)0;
+    PredictF32Lds &sh = *reinterpret_cast<PredictF32Lds *>(stage);
+    f32x4_t A[kTurn], B[kTurn];
+    scores_f32_block(pr, t0, n_tok, G, tid, sh, [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) A[k] = fetch(min(k, G - 1), k < G);
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) B[k] = fetch(min(k + kTurn, G - 1), k + kTurn < G);
+    });
+    const uint32_t own = wave < n_tok ? token_mask_32(pr, t, G, lane, sh.key[wave], sh.score[wave][lane & 31], prio, lost, blockIdx.x == 0) : 0u;
+    if (lane == 0) s_kept[wave] = own;
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) any |= s_kept[w];
+    any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
+    const uint32_t mine = half ? s_kept[row] : any;              // the groups whose values this thread may use
+    uint32_t rest = any & ~((1u << kFirst) - 1u);                // not asked for yet
+    f32x4_t c[1] = {f32x4_t{0.f, 0.f, 0.f, 0.f}};
+    int ga[kTurn], gb[kTurn];                                    // the groups that A and B hold, -1: none
+#pragma unroll
+    for (int k = 0; k < kTurn; ++k) {
+        ga[k] = k < G ? k : -1;
+        gb[k] = k + kTurn < G ? k + kTurn : -1;
+    }
+    auto turn = [&](f32x4_t (&b)[kTurn], int (&gk)[kTurn]) {
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k)
+            *reinterpret_cast<f32x4_t *>(stage + ((k * 2 + half) * 16 + row) * kRowF32 + col) =
+                gk[k] >= 0 && ((mine >> gk[k]) & 1u) ? b[k] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) {
+            const bool yes = rest != 0u;                         // uniform
+            gk[k] = yes ? __builtin_ctz(rest) : -1;
+            rest &= rest - 1u;                                   // (0 stays 0)
+            b[k] = fetch(yes ? gk[k] : 0, yes);
+        }
+        PairSum<1> sum;
+        sum.clear();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int p = 2 * wave + k;
+            auto operand = [&](int m) { return *reinterpret_cast<const f32x4_t *>(stage + (((p >> 3) * 2 + m) * 16 + i) * kRowF32 + (p & 7) * 16 + 4 * q); };
+            const f32x4_t a[1] = {operand(1)};
+            sum.add(operand(0), a);
+        }
+        sum.fold(c);
+        __syncthreads();
+    };
+    turn(A, ga);
+    if (G > kTurn) turn(B, gb);
+    while (ga[0] >= 0) {
+        turn(A, ga);
+        if (gb[0] >= 0) turn(B, gb);
+    }
+    f32x4_t *part = reinterpret_cast<f32x4_t *>(stage);
+    part[tid] = c[0];
+    __syncthreads();
+    if (wave == 0) {
+        f32x4_t p[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) p[w] = part[w * 64 + lane];
+        const f32x4_t s = pairwise_sum(p);
+        const int ty = t0 + i, j = j0 + 4 * q;
+        if (ty < T && j < d) *reinterpret_cast<f32x4_t *>(y + (size_t)ty * d + j) = s;     // (d is a multiple of 8)
     }
 }
 
@@ -426,6 +687,44 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
                                            act + t * G * gs, nt, ask, by_group, s);
         if (e != hipSuccess || T - t0 <= kRun) return e;
     }
+}
+
+// Whole pass in two launches, see hidden_gate_up_f32, against three or four, us, three tenths of the groups kept: d 1024, 24 groups, 1, 2, 4, 16,
+// 32 tokens 18.4 / 17.2, 19.7 / 18.9, 22.4 / 19.0, 26.7 / 23.7, 29.0 / 25.9; d 1024, 32 groups 19.5 / 19.2, 21.4 / 21.4, 25.0 / 23.3,
+// 30.4 / 27.2, 33.2 / 30.7, half kept, rank 256, one token 20.8 / 21.0; d 2048, 32 groups 24.0 / 29.2, 26.6 / 31.2, 33.2 / 31.7, 41.3 / 39.4, 47.0 / 44.8;
+// d 4096, 16 groups 31.7 / 35.5, 34.3 / 36.5, 39.1 / 37.3, 47.2 / 40.4, 63.9 / 64.5; d 256, 12 groups 14.4 / 11.9 ... 19.1 / 14.5.  So the weights of
+// all groups may be 24 Ki rows of 128 elements, 32 Ki from four tokens on.  From 64 tokens on the prediction keeps a launch of its own, which
+// callers and tests know it by (it would be ahead there too: d 256, 12 groups 19.2 / 14.7, d 1024, 24 groups 37.3 / 33.3; 128 tokens of
+// 32 groups of d 1024 not, 65.8 / 68.5).
+bool forward_f32_supported(int T, int d, int G, int gs, int r, int n_dev)
+{
+    return gs == 128 && r <= 512 && f32_score_slots(G, r) <= kDownF32Waves && n_dev <= 64 && T < 64 &&
+           (long long)G * d <= (T < 4 ? 24 : 32) * 1024;
+}
+
+template <int NT>
+static void launch_hidden_gate_up(const float *x, const float *x_pred, int T, int d, int r, int G, const float *At, const float *Wg,
+                                  const float *Wu, float *h, float *act, hipStream_t s)
+{
+    const int n_gu = G * 8 * ((T + 16 * NT - 1) / (16 * NT)), n_hid = (T * r + kGateUpF32Waves - 1) / kGateUpF32Waves;
+    launch_timed("hidden_gate_up_f32", hidden_gate_up_f32<NT>, dim3(n_gu + n_hid), dim3(kGateUpF32Waves * 64), s, x, T, d, G, Wg, Wu, act, x_pred, At, r, h, n_gu);
+}
+
+hipError_t launch_forward_f32(const float *x, const float *x_pred, int T, int d, int r, int G, const float *At, const float *Bt,
+                              const float *Wg, const float *Wu, const float *Wd, float *h, float *act, float *scores, int K,
+                              const int8_t *prio_dev, int n_dev, const uint8_t *drop, float *y, int32_t *order, int8_t *group_dev,
+                              uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s)
+{
+    if (T <= 16)
+        launch_hidden_gate_up<1>(x, x_pred, T, d, r, G, At, Wg, Wu, h, act, s);
+    else
+        launch_hidden_gate_up<2>(x, x_pred, T, d, r, G, At, Wg, Wu, h, act, s);
+    const int slots = f32_score_slots(G, r), share = kDownF32Waves / slots;
+    unsigned long long parts = 0;
+    for (int w = 0; w < kDownF32Waves; ++w) parts |= (unsigned long long)(w / slots) << (4 * w);
+    const PredictF32 pr{h, Bt, r, K, n_dev, share, parts, prio_dev, drop, scores, order, group_dev, mask, surv_idx, n_surv};
+    predict_down_f32<<<dim3((d + 15) / 16, (T + 15) / 16), dim3(kDownF32Waves * 64), 0, s>>>(act, T, d, G, Wd, y, pr);
+    return hipGetLastError();
 }
 
 }  // namespace halo

@@ -392,6 +392,12 @@ int halo_ffn_forward(const halo_shape *shape, const void *x, const void *x_pred,
     hipStream_t s = static_cast<hipStream_t>(stream);
     float *sc = scores ? scores : ws.scores;
     uint8_t *mk = mask ? mask : ws.mask;
+    if (shape->dtype == HALO_F32 && forward_f32_supported(T, shape->d, shape->n_groups, shape->group_size, shape->rank, n_dev)) {
+        const hipError_t e = launch_forward_f32((const float *)x, (const float *)x_pred, T, shape->d, shape->rank, shape->n_groups, (const float *)At,
+                                                (const float *)Bt, (const float *)Wg, (const float *)Wu, (const float *)Wd, ws.h, ws.dec.act, sc,
+                                                k_keep, prio_dev, n_dev, drop, (float *)y, order, group_dev, mk, surv_idx, n_surv, s);
+        return e == hipSuccess ? HALO_OK : HALO_ERR_HIP;
+    }
     // first predictor layer, then the second layer fused with the ranking / mask kernel
     hipError_t e = launch_predict_and_mask(shape->dtype, x_pred, T, shape->d, shape->rank, shape->n_groups, At, Bt, ws.h, sc, k_keep,
                                 prio_dev, n_dev, drop, order, group_dev, mk, surv_idx, n_surv, s);

@@ -103,6 +103,12 @@ hipError_t launch_union(const uint8_t *mask, int T, int G, int32_t *ulist, int32
 bool f32_path_supported(int d, int gs);
 hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
                           const uint8_t *mask, float *y, float *act, hipStream_t s);
+// ... and the whole pass of a small block, prediction and FFN, in two launches
+bool forward_f32_supported(int T, int d, int G, int gs, int r, int n_dev);
+hipError_t launch_forward_f32(const float *x, const float *x_pred, int T, int d, int r, int G, const float *At, const float *Bt,
+                              const float *Wg, const float *Wu, const float *Wd, float *h, float *act, float *scores, int K,
+                              const int8_t *prio_dev, int n_dev, const uint8_t *drop, float *y, int32_t *order, int8_t *group_dev,
+                              uint8_t *mask, int32_t *surv_idx, int32_t *n_surv, hipStream_t s);
 
 // ffn_mfma.hip : bf16 matrix-core path for a few tokens (2 <= T <= 16)
 constexpr int kFewTokens = 16;

@@ -832,3 +832,48 @@ def test_more_tokens_than_the_row_table_holds(G, K):
     c = hz.oracle_forward(w, L, x[torch.from_numpy(rows).to(hz.DEV)], K, pd, drop[rows])
     hz.assert_parity({k: v[rows] for k, v in g.items()}, c, TOL["bf16"], "past the row table")
     assert np.isfinite(g["y"]).all()
+
+
+@pytest.mark.parametrize("T,d,G,r", [
+    (1, 8, 1, 8),              # sixteen waves to the only row of Bt
+    (2, 24, 3, 40),            # an odd number of groups, pairs of rows
+    (5, 264, 8, 64),           # eight groups: nothing comes behind the first turns; two batches of tokens
+    (17, 512, 9, 128),         # one group behind them, a token tile of one token
+    (33, 1000, 16, 512),       # a row of Bt to each of sixteen waves
+    (63, 256, 31, 256),        # pairs of rows to each of sixteen waves, the last of one
+    (3, 1024, 24, 72),         # the most weights of few tokens
+    (4, 1024, 32, 256),        # the most of all
+    (4, 1032, 32, 256),        # past it: the launches of larger blocks
+])
+def test_small_float32_blocks_in_two_launches(T, d, G, r):
+    w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=92)
+    _say(f"small float32 blocks T={T} d={d} G={G} r={r}")
+    s, L = hz.shape_of(w), hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    for K in sorted({1, max(1, G // 3), G}):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        drop = hs.drop_outcomes(w, T=T)
+        if K < G:
+            drop[T - 1] = 1                                    # a token with no survivor
+        g = hz.gpu_forward(w, L, x, K, pd, drop)
+        hz.assert_parity(g, hz.oracle_forward(w, L, x, K, pd, drop), TOL["f32"], f"f32 K={K}")
+    # ties, NaN scores and malformed schedule entries: as the mask builder has them; groups that nobody keeps may hold anything
+    K = max(1, G // 3)
+    pd = np.array([(0, -1, 1, 100, 2, 3)[i % 6] for i in range(K)], dtype=np.int8)
+    drop = hs.drop_outcomes(w, T=T)
+    if G > 2:
+        L.Bt[1] = L.Bt[0]
+        L.Bt[2] = float("nan")
+    g = hz.gpu_forward(w, L, x, K, pd, drop)
+    sc = torch.from_numpy(g["scores"]).to(hz.DEV)
+    ref_out = {k: torch.full(v.shape, 77, dtype=torch.from_numpy(v).dtype, device=hz.DEV) for k, v in g.items() if k not in ("y", "scores")}
+    H.halo_build_group_mask(sc, K, torch.from_numpy(pd).to(hz.DEV), w.n_dev, torch.from_numpy(drop).to(hz.DEV), **ref_out)
+    torch.cuda.synchronize()
+    for k, v in ref_out.items():
+        assert np.array_equal(v.cpu().numpy(), g[k]), k
+    idle = torch.from_numpy(~g["mask"].astype(bool).any(axis=0)).to(hz.DEV)
+    for m in (L.Wg, L.Wu):
+        m.view(G, 128, d)[idle] = float("nan")
+    L.Wd[idle] = float("nan")
+    again = hz.gpu_forward(w, L, x, K, pd, drop)
+    assert np.isfinite(g["y"]).all() and np.array_equal(g["y"], again["y"])

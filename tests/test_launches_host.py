@@ -139,3 +139,13 @@ def test_quarter_tiles_of_tokens():
             names = [n for n, *_ in launches]
             for kernel, tokens in (("gate_up_pf_ring", gate_up if q4 else max(gate_up, 128)), ("down_pf_ring", down)):
                 assert rc == 0 and sum(f"{kernel}ILb{q4}ELi{tokens}E" in n for n in names) == 1, (T, d, G, q4, names)
+
+
+def test_small_float32_blocks_by_shape():
+    # the whole pass in two launches: fewer than 64 tokens, groups of 128, a wave of sixteen to a row (pair of rows) of Bt, few weights
+    for T, d, G, gs, r, two in [(1, 1024, 24, 128, 64, True), (3, 1032, 24, 128, 64, False), (4, 1024, 32, 128, 256, True), (4, 1032, 32, 128, 256, False),
+                                (63, 256, 8, 128, 64, True), (64, 256, 8, 128, 64, False), (8, 64, 33, 128, 256, False), (8, 64, 16, 128, 512, True),
+                                (8, 64, 17, 128, 264, False), (8, 64, 4, 128, 520, False), (8, 64, 8, 64, 64, False)]:
+        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, G, gs, r, F32), T=T, K=G // 2)])
+        names = [n for n, *_ in launches]
+        assert rc == 0 and (len(names) == 2 and "hidden_gate_up_f32" in names[0] and "predict_down_f32" in names[1]) == two, (T, d, G, gs, r, names)

@@ -530,7 +530,9 @@ __global__ __launch_bounds__(kRingWaves * 64, 2) void gate_up_pf_ring<true, 64>(
 // Groups end in a tile of any length (their token counts differ widely), so a wave's tiles are every fourth one and a tile
 // of one, two or three quarters runs with as many per wave: 1000 tokens of the 70B shape 523 -> 495.  (Taking all whole
 // tiles first and the short ones behind them evened out the last round, but then no two tiles of a group share their
-// weight rows in a die's L2: 13B shape 138 -> 192.)
+// weight rows in a die's L2: 13B shape 138 -> 192.)  So the weight rows carry no hint here: with the non-temporal one, which keeps
+// gate_up_pf_ring's from pushing x out, they were gone when the next tile of the group came (pass of 800 tokens of 13B 305 -> 294, of 1000 at 70B
+// 917 -> 897).
 // Two stages of 64 KiB fit, so a step is cut in two: half kk of the 64 elements of stage s is multiplied while the
 // fragments of the next half are read.  The barrier sits in front of the second half, when everybody has read all of
 // stage s: its buffers go to the stages that follow, token rows one step ahead, weight rows (three buffers: they come from
@@ -586,7 +588,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     };
     auto load_w = [&](int j, int s, int b) {                     // b = s % 3
         const bool yes = s < ns;
-        load_to_lds16<true>(if_exists(j < 2 ? srd_g : srd_u, yes), off_w[j & 1], byte_of(yes ? s : 0),
+        load_to_lds16(if_exists(j < 2 ? srd_g : srd_u, yes), off_w[j & 1], byte_of(yes ? s : 0),
                             ring0 + kWBase + b * kBigStage + j * 8192);
     };
     // the wave's row tiles: four of the gate rows and the four of the up rows that face them; its 16-token tiles: tq + 4 n

@@ -86,22 +86,13 @@ __device__ __forceinline__ bool down_item(int T, int d, int G, int splits, DownI
     const int die = blockIdx.x & 7, dslot = blockIdx.x >> 3;
     const int item = die * per_die + dslot;
     if (dslot >= per_die || item >= n_items) return false;       // uniform for the workgroup
-    // Two numberings.  With one or two token tiles the items of a die are the token tiles of consecutive
-    // output tiles of one range: a tile of Wd is fetched from memory by the first and found in the die's
-    // L2 by the second, and the act rows of both token tiles fit beside it.  With more token tiles the
-    // items of a die share one token tile's act rows instead (they would not all fit).
-    int ttile;
-    if (n_tt <= 2) {
-        ttile = item % n_tt;
-        const int rest = item / n_tt;
-        it.split = rest / n_ot;
-        it.j0 = (rest - it.split * n_ot) * 128;
-    } else {
-        const int pair = item / n_ot;
-        it.j0 = (item - pair * n_ot) * 128;
-        ttile = pair / splits;
-        it.split = pair - ttile * splits;
-    }
+    // The items of a die are the token tiles of consecutive output tiles of one range: a tile of Wd is fetched from memory by the first
+    // and found in the die's L2 by the others, which walk the groups beside it, and so are the act rows of a step, whatever the
+    // number of token tiles.  (Where a die's items shared one token tile's act rows instead, above two token tiles, every die fetched Wd for
+    // itself.  Pass in us: 600 tokens of the 70B shape 765 -> 705, 1000 910 -> 887, 1500 1297 -> 1260, 800 of 13B 296 -> 291, 900 of 7B 215 -> 209.)
+    const int ttile = item % n_tt, rest = item / n_tt;
+    it.split = rest / n_ot;
+    it.j0 = (rest - it.split * n_ot) * 128;
     it.t0 = ttile * NTOK;
     it.g_lo = (int)((long long)it.split * G / splits);
     it.g_hi = (int)((long long)(it.split + 1) * G / splits);

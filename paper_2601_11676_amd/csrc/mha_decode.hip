@@ -380,14 +380,18 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
 // ---------------------------------------------------------------------------
 // output projection that merges the heads' partial softmaxes itself: up to nine of them, up to 64 heads
 // ---------------------------------------------------------------------------
-// Every workgroup merges all surviving heads into LDS, n_surv * chunks * 520 bytes from L2, while its rows of Wo for the first heads are
-// on their way; that takes the place of a launch of its own.  A block without the next one's prediction, captured into a graph, us,
-// merged in a launch of its own / here: d 1024, 8 heads, 120 to 2000 cached rows 14.1 .. 14.9 / 11.6 .. 13.7, 16 heads, 4400 19.4 / 17.5;
-// d 2048, 16 heads, 339 rows 17.5 / 15.3, 2000 18.3 / 17.2; d 3200, 25 heads, 339 rows 23.9 / 22.0; d 4096, 32 heads, 339 rows
-// 28.3 / 27.0; d 7168, 56 heads, 300 rows 65.2 / 59.6.  Where a thread has several heads' worth to merge the projection waits longer than
-// the launch took (three blocks: d 3200, 900 rows 80.0 / 81.9, d 4096, 2000 rows 93.3 / 94.9, d 8192, 2000 rows 242.9 / 246.4).  So up to
-// 16 heads are merged here whenever nine chunks of up to 512 positions hold the cache; more heads while heads times chunks of up to 256
-// stay within 192 with the activations in bf16, and up to three chunks with them in float32.
+// Every workgroup merges all surviving heads into LDS, n_surv * chunks * 520 bytes from L2, before it multiplies; that takes the place
+// of a launch of its own.  A wave's loads return in order, so a thread asks for its first head's partials before the rows of Wo for the
+// first heads, 48 loads of 16 bytes from HBM: behind them the merge began when the last of them had come.  A block with the next one's
+// prediction, half the heads, us, us merged behind Wo's rows or in a launch of its own / merged in front of them: d 4096, 32 heads,
+// 339 rows 27.9 / 27.5, 2048 rows 31.2 / 30.4, d 3200, 25 heads, 700 rows 24.8 / 23.5, d 7168, 56 heads, 700 rows 63.8 / 61.5.
+// Up to 16 heads are merged here whenever nine chunks of up to 512 positions hold the cache (d 1024, 8 heads, 120 to 2000 rows
+// 14.1 .. 14.9 in a launch of its own, 11.6 .. 13.7 here; d 2048, 16 heads, 2000 rows 18.3 / 17.2).  With more heads a thread has
+// several heads' worth to merge one after the other, and there is a point from where the launch is the faster (own launch / here: d 3200,
+// 25 heads, 8 chunks of 256 25.9 / 26.2; d 8192, 64 heads, 8 chunks of 128 77.4 / 77.9, 4 of 256 77.4 / 76.6; d 5120, 40 heads,
+// 7 chunks of 256 40.4 / 39.6, 8 of 256 level; 32 heads, 9 chunks of 256 31.7 / 31.1; with chunks of 512 26.4 / 27.6 at 25 heads,
+// 3000 rows).  So more than 16 heads are merged here while heads times chunks of up to 256 stay within 288 with the activations in
+// bf16, and up to six chunks with them in float32.
 constexpr int kMergeChunks = 9, kMergeHeads = 64;
 
 template <typename AT>
@@ -447,27 +451,24 @@ __global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const 
             if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two heads' operands at a time: registers
         }
     };
-    u32x4 v0[kB], v1[kB], v2[kB];
-    if (count > 0) {
-        fetch(v0, half);
-        fetch(v1, half + 2 * kB);
-        fetch(v2, half + 4 * kB);
-    }
-    // the merge; a thread: four dimensions of a head, 32 threads a head
-#pragma unroll 1
-    for (int id = tid; id < count * (dh / 4); id += NT) {
-        const int u = id / (dh / 4), e = (id % (dh / 4)) * 4;
+    // the merge; a thread: four dimensions of a head, 32 threads a head.  Its first loads go in front of Wo's, which are many bytes more, and
+    // loads return in order
+    const int n_ids = count * (dh / 4);
+    float2 pv[kMergeChunks][2], st[kMergeChunks];
+    auto ask = [&](int id) __attribute__((always_inline)) {
+        const int u = min(id, n_ids - 1) / (dh / 4), e = (id % (dh / 4)) * 4;
         const uint32_t head = (uint32_t)(u * chunks * kPartStride) * 4, at = head + e * 4;
         auto load2 = [&](uint32_t voff, uint32_t soff) { return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(bp, voff, soff, 0)); };
-        float2 v[kMergeChunks][2], st[kMergeChunks];
 #pragma unroll
         for (int c = 0; c < kMergeChunks; ++c) {
             if (c < chunks) {                                    // uniform
                 st[c] = load2(head, (c * kPartStride + dh) * 4);
-                v[c][0] = load2(at, c * kPartStride * 4);
-                v[c][1] = load2(at, c * kPartStride * 4 + 8);
+                pv[c][0] = load2(at, c * kPartStride * 4);
+                pv[c][1] = load2(at, c * kPartStride * 4 + 8);
             }
         }
+    };
+    auto merge = [&](int id) __attribute__((always_inline)) {
         float M = st[0].x;
 #pragma unroll
         for (int c = 1; c < kMergeChunks; ++c)
@@ -478,14 +479,31 @@ __global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const 
             if (c < chunks) {
                 const float w = __expf(st[c].x - M);
                 L = __builtin_fmaf(w, st[c].y, L);
-                o[0] = __builtin_fmaf(w, v[c][0].x, o[0]);
-                o[1] = __builtin_fmaf(w, v[c][0].y, o[1]);
-                o[2] = __builtin_fmaf(w, v[c][1].x, o[2]);
-                o[3] = __builtin_fmaf(w, v[c][1].y, o[3]);
+                o[0] = __builtin_fmaf(w, pv[c][0].x, o[0]);
+                o[1] = __builtin_fmaf(w, pv[c][0].y, o[1]);
+                o[2] = __builtin_fmaf(w, pv[c][1].x, o[2]);
+                o[3] = __builtin_fmaf(w, pv[c][1].y, o[3]);
             }
         }
+        if (id < n_ids) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) store_out(sh.o.act + u * dh + e + k, o[k] / L);
+            for (int k = 0; k < 4; ++k) store_out(sh.o.act + id / (dh / 4) * dh + (id % (dh / 4)) * 4 + k, o[k] / L);
+        }
+    };
+    u32x4 v0[kB], v1[kB], v2[kB];
+    if (count > 0) {
+        ask(tid);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(v0, half);
+        fetch(v1, half + 2 * kB);
+        fetch(v2, half + 4 * kB);
+        __builtin_amdgcn_sched_barrier(0);
+        merge(tid);
+#pragma unroll 1
+        for (int id = tid + NT; id < n_ids; id += NT) {
+            ask(id);
+            merge(id);
+        }
     }
     __syncthreads();
     if (count > 0) {
@@ -573,7 +591,7 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
 #undef HALO_QKV
     // Few enough chunks, perhaps made so by longer ones, are merged by the output projection (see kMergeChunks).
     const int len = pos + 1;
-    const int most = H <= 16 ? kMergeChunks : whole ? std::min(kMergeChunks, 192 / H) : 3, longest = H <= 16 ? 512 : whole ? 256 : 128;
+    const int most = H <= 16 ? kMergeChunks : whole ? std::min(kMergeChunks, 288 / H) : 6, longest = H <= 16 ? 512 : 256;
     int ch = 128;
     while (ch < longest && len > ch * most) ch *= 2;
     const int few = (len + ch - 1) / ch;

@@ -266,9 +266,9 @@ def test_mha_long_context_many_chunks():
     (2048, 2, 4607),           # nine of 512
     (8192, 2, 4608),           # 37 of 128, merged in a launch of their own
     (1024, 48, 383),           # three chunks of 128, more than 16 heads in float32; more than the projection's three batches of them
-    (1024, 17, 384),           # four: a launch of its own
-    (4096, 48, 700),           # three of 256
-    (4096, 64, 767),
+    (1024, 17, 384),           # four
+    (4096, 48, 700),           # six of 128
+    (4096, 64, 767),           # three of 256
     (4096, 65, 140),           # more heads than are merged by the projection
 ])
 def test_mha_merges_of_every_kind(d, Hh, ctx):
@@ -293,6 +293,19 @@ def test_mha_merges_of_every_kind(d, Hh, ctx):
         yc = ref.mha_decode(xn, Wq, Wk, Wv, WoT, k_ref, v_ref, ctx, m["mask"][0])
         yg = hz.to_np32(y)[0].astype(np.float64)
         assert np.isfinite(yg).all() and np.linalg.norm(yg - yc) <= TOL * np.linalg.norm(yc)
+
+
+@pytest.mark.parametrize("d,Hh,ctx", [
+    (4096, 32, 2303),          # heads times chunks 288: nine chunks of 256, the last one full
+    (4096, 32, 2304),          # ten: a launch of its own
+    (5120, 40, 896),           # four of 256, one position past seven of 128
+    (5120, 40, 1792),          # eight of 256: a launch of its own
+    (8192, 64, 1023),          # four of 256
+    (1024, 17, 1535),          # six of 256, heads in float32
+    (1024, 17, 1536),          # a launch of its own
+])
+def test_mha_merges_of_more_than_16_heads(d, Hh, ctx):
+    test_mha_merges_of_every_kind(d, Hh, ctx)
 
 
 @pytest.mark.parametrize("d,Hh,ctx", [(8, 1, 3), (1032, 5, 129), (2048, 16, 300), (3200, 25, 40), (7176, 3, 128), (8200, 2, 20)])

@@ -34,8 +34,12 @@ constexpr int kAttnChunk = 128;      // cached positions per workgroup of attn_p
 // q / k / v rows: grid = 256 workgroups of 256 threads
 // ---------------------------------------------------------------------------
 // Row v of the job list: v < H*dh -> Wk row v, < 2*H*dh -> Wv row, else a Wq row of the
-// (v - 2*H*dh) / dh -th surviving head.  K/V rows do not depend on the mask, so every wave
-// starts on its share of them at once and meets the mask only for its query rows.
+// (v - 2*H*dh) / dh -th surviving head.  K/V rows do not depend on the mask, so every wave starts on its share of them at once and meets
+// the mask only for its query rows.  They follow in the same sequence of loads and sums: with a sequence of its own for each, nothing was
+// on its way while the last key or value row was summed up, and shares of both that were not whole numbers left some waves two pairs of
+// rows more than others.  A block with half its heads and the next one's prediction, us, two sequences / one: d 1024, 8 heads 13.7 / 13.2;
+// d 2048, 16 heads 16.8 / 15.8; d 3200, 25 heads 23.6 / 22.8; d 4096, 32 heads 29.8 / 29.3 (84 MB, this launch alone 16.1 / 15.6: 5.4 TB/s);
+// d 5120, 40 heads 42.6 / 41.9; d 7168, 8192 level.
 template <int NCH>
 struct RowRegs {
     u32x4 a[NCH], b[NCH];            // two independent rows
@@ -86,38 +90,6 @@ struct QkvArgs {
     int r, n_pred;
 };
 
-// pairs of rows [p0, p1) of a job list whose row v comes from src(v) and goes to put(v, value)
-template <int NCH, bool TAIL, typename Src, typename Put>
-__device__ __forceinline__ void sweep_pairs(int p0, int p1, const u32x4 (&xr)[NCH], const RowLanes<NCH, TAIL> &rl, int lane,
-                                            Src src, Put put)
-{
-    if (p0 >= p1) return;
-    RowRegs<NCH> A, B;
-    auto load = [&](RowRegs<NCH> &r, int p) { load_two<NCH, TAIL>(r, src(2 * p), src(2 * p + 1), rl, lane); };
-    auto finish = [&](const RowRegs<NCH> &r, int p) {
-        float va, vb;
-        dot_two<NCH, TAIL>(r, xr, rl, va, vb);
-        put(2 * p, va);
-        put(2 * p + 1, vb);
-    };
-    load(A, p0);
-    int p = p0;
-    while (p + 2 < p1) {
-        load(B, p + 1);
-        finish(A, p);
-        load(A, p + 2);
-        finish(B, p + 1);
-        p += 2;
-    }
-    if (p + 1 < p1) {
-        load(B, p + 1);
-        finish(A, p);
-        finish(B, p + 1);
-    } else {
-        finish(A, p);
-    }
-}
-
 template <int NCH, bool TAIL>
 __global__ __launch_bounds__(256) void qkv_rows(QkvArgs a, int len)
 {
@@ -135,45 +107,80 @@ __global__ __launch_bounds__(256) void qkv_rows(QkvArgs a, int len)
         return;
     }
     const int nw = (gridDim.x - a.n_pred) * 4, w = (blockIdx.x - a.n_pred) * 4 + wave;
-    const MaskWords mw = load_mask_words(a.mask, a.H, lane);     // needed only further down
+    const MaskWords mw = load_mask_words(a.mask, a.H, lane);     // needed behind the first rows' loads
     u32x4 xr[NCH];
 #pragma unroll
     for (int k = 0; k < NCH; ++k) xr[k] = rl.keep(reinterpret_cast<const u32x4 *>(a.x)[rl.piece(k, lane)], k);
-    // keys and values of every head: 2*H*dh rows, taken in pairs
-    {
-        const int hd = a.H * dh;
-        const long long pairs = hd;                              // 2*hd rows
-        const int p0 = (int)(pairs * w / nw), p1 = (int)(pairs * (w + 1) / nw);
-        auto src = [&](int v) -> const bf16_t * {
-            return v < hd ? a.Wk + (size_t)v * d : a.Wv + (size_t)(v - hd) * d;
-        };
-        auto put = [&](int v, float val) {
-            if (lane == 0) {
-                const int r = v < hd ? v : v - hd;
-                const int h = r / dh, e = r - h * dh;
-                bf16_t *dst = (v < hd ? a.k_cache : a.v_cache) + ((size_t)h * a.max_len + a.pos) * dh + e;
-                *dst = f32_to_bf16(val);
-            }
-        };
-        sweep_pairs<NCH, TAIL>(p0, p1, xr, rl, lane, src, put);
-    }
-    // queries of the surviving heads: count*dh rows (an even number), compact by slot
-    {
-        const long long pairs = (long long)mw.count * (dh / 2);
-        const int p0 = (int)(pairs * w / nw), p1 = (int)(pairs * (w + 1) / nw);
-        int cur_u = -1, cur_g = 0;
-        auto src = [&](int v) -> const bf16_t * {
-            const int u = v / dh;
+    // this wave's pairs of rows in one sequence: n_kv of the 2*H*dh key and value rows, then those of the surviving heads' query rows
+    // (count*dh rows, compact by slot)
+    const int hd = a.H * dh, p0 = (int)((long long)hd * w / nw), n_kv = (int)((long long)hd * (w + 1) / nw) - p0;
+    int q0 = 0, cur_u = -1, cur_g = 0;
+    auto load = [&](RowRegs<NCH> &r, int i) __attribute__((always_inline)) {
+        const bf16_t *src;
+        if (i < n_kv) {
+            const int v = 2 * (p0 + i);                          // hd is even: both rows on one side
+            src = v < hd ? a.Wk + (size_t)v * d : a.Wv + (size_t)(v - hd) * d;
+        } else {
+            const int v = 2 * (q0 + i - n_kv), u = v / dh;
             if (u != cur_u) {
                 cur_u = u;
                 cur_g = nth_group(mw, u, lane);
             }
-            return a.Wq + ((size_t)cur_g * dh + (v - u * dh)) * d;
-        };
-        auto put = [&](int v, float val) {
-            if (lane == 0) a.q[v] = val;
-        };
-        sweep_pairs<NCH, TAIL>(p0, p1, xr, rl, lane, src, put);
+            src = a.Wq + ((size_t)cur_g * dh + (v - u * dh)) * d;
+        }
+        load_two<NCH, TAIL>(r, src, src + d, rl, lane);
+    };
+    auto finish = [&](const RowRegs<NCH> &r, int i) __attribute__((always_inline)) {
+        float va, vb;
+        dot_two<NCH, TAIL>(r, xr, rl, va, vb);
+        if (lane != 0) return;
+        if (i < n_kv) {
+            const int v = 2 * (p0 + i), row = v < hd ? v : v - hd, h = row / dh;
+            bf16_t *dst = (v < hd ? a.k_cache : a.v_cache) + ((size_t)h * a.max_len + a.pos) * dh + (row - h * dh);
+            dst[0] = f32_to_bf16(va);
+            dst[1] = f32_to_bf16(vb);
+        } else {
+            float *dst = a.q + 2 * (q0 + i - n_kv);
+            dst[0] = va;
+            dst[1] = vb;
+        }
+    };
+    RowRegs<NCH> A, B;
+    {
+        // keys and values don't depend on the mask: their first rows are on their way while it arrives (a row that exists where this
+        // wave has none)
+        const int v = 2 * min(p0, hd - 1);
+        const bf16_t *src = v < hd ? a.Wk + (size_t)v * d : a.Wv + (size_t)(v - hd) * d;
+        load_two<NCH, TAIL>(A, src, src + d, rl, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the queries' share: as many as bring this wave's sum to its share of all pairs, where that takes none away from anyone
+    const int qp = mw.count * (dh / 2);
+    int q1;
+    if (qp >= nw) {
+        q0 = (int)((long long)(hd + qp) * w / nw) - p0;
+        q1 = (int)((long long)(hd + qp) * (w + 1) / nw) - (p0 + n_kv);
+    } else {
+        q0 = (int)((long long)qp * w / nw);
+        q1 = (int)((long long)qp * (w + 1) / nw);
+    }
+    const int n = n_kv + q1 - q0;
+    if (n == 0) return;
+    if (n_kv == 0) load(A, 0);
+    int i = 0;
+    while (i + 2 < n) {
+        load(B, i + 1);
+        finish(A, i);
+        load(A, i + 2);
+        finish(B, i + 1);
+        i += 2;
+    }
+    if (i + 1 < n) {
+        load(B, i + 1);
+        finish(A, i);
+        finish(B, i + 1);
+    } else {
+        finish(A, i);
     }
 }
 

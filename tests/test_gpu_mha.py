@@ -308,6 +308,23 @@ def test_mha_merges_of_more_than_16_heads(d, Hh, ctx):
     test_mha_merges_of_every_kind(d, Hh, ctx)
 
 
+@pytest.mark.parametrize("d,Hh", [
+    (1024, 1),                 # 128 pairs of key and value rows for 1024 waves, 64 of query rows
+    (1032, 7),                 # 896: waves without one
+    (2048, 9),                 # 1152, and fewer than 1024 pairs of query rows whatever the mask
+    (1024, 17),                # both sides of 1024 pairs of query rows
+    (4096, 33),
+])
+def test_mha_shares_of_the_projections_rows(d, Hh):
+    # a wave's key, value and query rows are one sequence; every count of pairs a wave can have, whole numbers and not
+    w = dataclasses.replace(hs.LLAMA7B_MHA_DECODE, name="case", d=d, n_heads=Hh, rank=24, ctx=9, max_len=16, seed=40)
+    _say(f"mha projections' rows d={d} H={Hh}")
+    L = MhaLayer(w)
+    for K in sorted({1, max(1, Hh // 2), Hh}):
+        kc, vc = hs.kv_cache(w, 0, hz.DEV)
+        _check_step(L, hs.mha_hidden(w, K, hz.DEV), kc, vc, w.ctx, K, H.halo_build_schedule(K, w.device_plr()), None)
+
+
 @pytest.mark.parametrize("d,Hh,ctx", [(8, 1, 3), (1032, 5, 129), (2048, 16, 300), (3200, 25, 40), (7176, 3, 128), (8200, 2, 20)])
 def test_mha_of_any_row_length(d, Hh, ctx):
     # rows that are not whole 512-element chunks, outputs that are not whole workgroups, and one row longer than the

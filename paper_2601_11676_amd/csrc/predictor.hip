@@ -29,6 +29,70 @@ __global__ __launch_bounds__(256) void dot_rows_kernel(const XT *__restrict__ X,
     if (lane == 0) out[idx] = RELU ? (p > 0.0f ? p : 0.0f) : p;
 }
 
+// The first layer for a tile's worth of tokens and more, bf16, where there are too few results for the matrix cores (hidden_mfma_kernel).
+// A wave: four tokens against one row of At, so a row is loaded and unpacked once for four of them, and four butterflies are one from distance
+// 16 down.  The loads of four steps of 512 elements are under way, without which the walk waits on each.  17 tokens, d 8192, rank 512: 17 us
+// with a wave per result, now 12; its multiply-adds and conversions alone are 5, and 2.5 waves a SIMD don't hide the rest.
+constexpr int kRowTokens = 4, kRowAhead = 4;
+
+__global__ __launch_bounds__(256) void dot_rows_tokens_kernel(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W,
+                                                              float *__restrict__ out, int T, int R, int n)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row_blocks = (R + 3) / 4;                          // a die keeps its rows for every token where this is a multiple of eight
+    const int t0 = blockIdx.x / row_blocks * kRowTokens, j = blockIdx.x % row_blocks * 4 + wave;
+    if (j >= R) return;
+    const __amdgpu_buffer_rsrc_t bw = buffer_of(W + (size_t)j * n, 2 * n);
+    __amdgpu_buffer_rsrc_t bx[kRowTokens];
+#pragma unroll
+    for (int t = 0; t < kRowTokens; ++t) {
+        const bool any = t0 + t < T;
+        bx[t] = buffer_of(X + (size_t)(any ? t0 + t : 0) * n, any ? 2 * n : 0);
+    }
+    // a piece past the end is zeros on both sides and leaves the chains as they are
+    u32x4 wv[kRowAhead], xv[kRowAhead][kRowTokens];
+    auto request = [&](int s, int k) __attribute__((always_inline)) {
+        const uint32_t at = (uint32_t)k * 1024u + lane * 16;
+        wv[s] = buffer_load16<0>(bw, at, 0);
+#pragma unroll
+        for (int t = 0; t < kRowTokens; ++t) xv[s][t] = buffer_load16<0>(bx[t], at, 0);
+    };
+    float p[kRowTokens] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const int nk = (n + 511) / 512;
+#pragma unroll
+    for (int s = 0; s < kRowAhead; ++s) request(s, s);
+    for (int k = 0; k < nk; k += kRowAhead) {
+#pragma unroll
+        for (int s = 0; s < kRowAhead; ++s) {
+            if (k + s < nk) {                                    // uniform
+                float w[8];
+                unpack8(wv[s], w);
+#pragma unroll
+                for (int t = 0; t < kRowTokens; ++t) {
+                    float x[8];
+                    unpack8(xv[s][t], x);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) p[t] = __builtin_fmaf(x[e], w[e], p[t]);
+                }
+            }
+            request(s, k + kRowAhead + s);
+        }
+    }
+    // the four butterflies as one from distance 16 down: half a wave, then a quarter, holds a token's
+    auto meet = [](float a, float b, auto swap) {
+        const auto v = swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b));
+        return __builtin_bit_cast(float, (unsigned)v[0]) + __builtin_bit_cast(float, (unsigned)v[1]);
+    };
+    auto swap32 = [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); };
+    auto swap16 = [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); };
+    float v = meet(meet(p[0], p[1], swap32), meet(p[2], p[3], swap32), swap16);
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
+    // quarters of the wave: tokens 0, 2, 1, 3
+    const int quarter = lane >> 4, t = t0 + ((quarter & 1) << 1 | quarter >> 1);
+    if ((lane & 15) == 0 && t < T) out[(size_t)t * R + j] = v > 0.0f ? v : 0.0f;
+}
+
 // The first layer for many tokens, bf16, on the matrix cores in the fixed order.
 //
 // v_mfma_f32_16x16x1_4b_f32 multiplies four independent blocks of 16 x 16 results by ONE element of the
@@ -344,14 +408,30 @@ static bool hidden_rows_tiled(const bf16_t *x, int T, int d, int r, const bf16_t
 }
 static bool hidden_rows_tiled(const float *, int, int, int, const float *, float *, hipStream_t, hipError_t &) { return false; }
 
+// A wave per four results instead of one where that leaves each SIMD more than two waves and a wave a walk of eight steps and more.
+// A pass, us, one / four: 17 tokens, d 8192, rank 512, 4-bit weights 147.9 / 143.1, 26 155.0 / 152.7; 34 x 256 of d 4096 56.7 / 55.7, 40 x 256
+// in bf16 80.7 / 79.7; 48 x 256 of d 5120 71.6 / 70.6.  With 8192 results and fewer the waves are too few to hide their loads (17 x 256 of
+// d 4096 level, 32 x 256 of d 5120 64.4 / 64.8, 100 x 64 of d 2048 47.4 / 48.1), and short walks do better in many waves (40 x 256 of
+// d 2048 level, 25 x 512 of d 1024 34.7 / 36.9).
+template <typename WT>
+static bool hidden_rows_shared(int T, int d, long long results)
+{
+    return sizeof(WT) == 2 && T >= 16 && results > 8192 && d >= 4096 && d <= 1 << 24;
+}
+
 template <typename WT>
 static hipError_t predict_t(const WT *x, int T, int d, int r, int G, const WT *At, const WT *Bt,
                             float *h, float *scores, hipStream_t s)
 {
     long long n1 = (long long)T * r, n2 = (long long)T * G;
     hipError_t e = hipSuccess;
-    if (!hidden_rows_tiled(x, T, d, r, At, h, s, e))
+    if (hidden_rows_tiled(x, T, d, r, At, h, s, e)) {
+    } else if (hidden_rows_shared<WT>(T, d, n1)) {
+        dot_rows_tokens_kernel<<<dim3((unsigned)((r + 3) / 4 * ((T + kRowTokens - 1) / kRowTokens))), dim3(256), 0, s>>>(
+            (const bf16_t *)x, (const bf16_t *)At, h, T, r, d);
+    } else {
         dot_rows_kernel<WT, WT, true><<<dim3((unsigned)((n1 + 3) / 4)), dim3(256), 0, s>>>(x, At, h, T, r, d);
+    }
     if (e != hipSuccess) return e;
     if (scores && sizeof(WT) == 2 && scores_apart(T, r, G)) return launch_scores_many(h, (const bf16_t *)Bt, T, r, G, scores, s);
     if (scores)

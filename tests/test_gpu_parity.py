@@ -578,6 +578,16 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     assert same.all()
 
 
+@pytest.mark.parametrize("T,d,r", [
+    (17, 4096, 512),           # a group of four tokens with one in it
+    (16, 4104, 520),           # a ninth step of one piece
+    (35, 8192, 256),
+    (27, 6152, 304),           # thirteen steps, just more than 8192 results
+])
+def test_predictor_four_tokens_to_a_wave_keeps_the_fixed_order(T, d, r):
+    test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, 9)
+
+
 @pytest.mark.parametrize("T,d,r,tiles", [
     (16, 8, 1024, "1x1"), (16, 512, 1024, "1x1"), (16, 1536, 1000, "1x1"), (40, 5128, 392, "1x1"),   # 1, 1, 3 and 11 steps, four buffers
     (500, 8, 256, "2x1"), (500, 1024, 248, "2x1"), (500, 2568, 256, "2x1"),                          # 1, 2 and 6, three

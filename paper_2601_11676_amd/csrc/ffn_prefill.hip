@@ -120,6 +120,88 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
     if (asum && cnt < T && tid < 2) asum[((size_t)tid * G + g) * T + cnt] = 0.0f;
 }
 
+// The same lists for more than 256 tokens: a workgroup asks for the mask bytes of RUNS runs of 256 tokens at once and places them behind one
+// barrier; where that is all of them the list's length comes from the same bytes.  (A run at a time, three barriers and a trip to memory
+// each, after a pass over the bytes for the length: 1000 tokens, 224 groups 7.0 us, now 5.2; a pass of 5000 tokens, d 1024, 24 groups
+// 120.9 / 115.2, of 2000 tokens of the 7B shape 376.9 / 372.6, of 300 tokens, d 2048 71.8 / 71.0.  Up to 256 tokens it is level.)
+constexpr int kGroupRuns = 8;
+
+template <int RUNS>
+__global__ __launch_bounds__(256) void group_tokens_runs_kernel(const uint8_t *__restrict__ mask, int T, int G,
+                                                                int32_t *__restrict__ tok_list,
+                                                                int32_t *__restrict__ tok_cnt, int16_t *__restrict__ rows,
+                                                                int32_t *__restrict__ slot, bf16_t *__restrict__ act)
+{
+    __shared__ __attribute__((aligned(16))) int s_cnt[RUNS][4];
+    __shared__ int s_wave[4];
+    const int g = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int pitch = prefill_row_pitch(T);
+    // the list's length is the zero row of the tokens that do not keep the group, so it is needed first
+    int cnt = 0, base = 0;
+    if (RUNS == kGroupRuns && T > RUNS * 256) {
+        int mine = 0;
+        for (int t = tid; t < T; t += 256) mine += mask[(size_t)t * G + g] != 0 ? 1 : 0;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, kWave);
+        if (lane == 0) s_wave[wave] = mine;
+        __syncthreads();
+        cnt = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+    }
+    for (int t0 = 0; t0 < pitch; t0 += RUNS * 256) {
+        uint8_t kept[RUNS];
+#pragma unroll
+        for (int i = 0; i < RUNS; ++i) {
+            const int t = t0 + i * 256 + tid;
+            kept[i] = mask[(size_t)min(t, T - 1) * G + g];
+        }
+        unsigned long long b[RUNS];
+#pragma unroll
+        for (int i = 0; i < RUNS; ++i) {
+            b[i] = __ballot(t0 + i * 256 + tid < T && kept[i] != 0);
+            if (lane == 0) s_cnt[i][wave] = __popcll(b[i]);
+        }
+        __syncthreads();
+        int before[RUNS];
+#pragma unroll
+        for (int i = 0; i < RUNS; ++i) {
+            const int c0 = s_cnt[i][0], c1 = s_cnt[i][1], c2 = s_cnt[i][2], c3 = s_cnt[i][3];
+            before[i] = base + (wave > 0 ? c0 : 0) + (wave > 1 ? c1 : 0) + (wave > 2 ? c2 : 0);
+            base += c0 + c1 + c2 + c3;
+        }
+        if (T <= RUNS * 256) cnt = base;
+#pragma unroll
+        for (int i = 0; i < RUNS; ++i) {
+            const int t = t0 + i * 256 + tid;
+            const bool keep = (b[i] >> lane & 1) != 0;
+            const int pos = before[i] + __popcll(b[i] & ((1ull << lane) - 1ull));
+            if (keep) tok_list[(size_t)g * T + pos] = t;
+            if (rows) {
+                if (t < pitch) rows[(size_t)g * pitch + t] = (int16_t)(t < T ? (keep ? pos : cnt) : 0);
+            } else if (t < T) {
+                slot[(size_t)t * G + g] = keep ? pos : -1;
+            }
+        }
+        if (t0 + RUNS * 256 < pitch) __syncthreads();           // before s_cnt is written again
+    }
+    if (tid == 0) tok_cnt[g] = cnt;
+    // the row after the group's last activation row is kept zero (group size 128): the down
+    // projection points the tokens that do not keep the group at it
+    if (cnt < T && tid < 64) reinterpret_cast<uint32_t *>(act + ((size_t)g * T + cnt) * 128)[tid] = 0u;
+}
+
+static void launch_group_tokens(const uint8_t *mask, int T, int G, int32_t *tok_list, int32_t *tok_cnt, int16_t *rows, int32_t *slot, bf16_t *act,
+                                const bf16_t *x, int d, float *xsum, float *asum, hipStream_t s)
+{
+    // x's sums are there up to 64 tokens only
+    if (T <= 256)
+        group_tokens_kernel<<<dim3(G + (xsum ? (T * (d / kQ4Block) + 63) / 64 : 0)), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot,
+                                                                                                       act, x, d, xsum, asum);
+    else if (T <= 512)
+        group_tokens_runs_kernel<2><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
+    else
+        group_tokens_runs_kernel<kGroupRuns><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
+}
+
 // ---------------------------------------------------------------------------
 // gate/up through rings in LDS filled by direct global -> LDS loads
 // grid: 8 * ceil(items / 8) workgroups of 512 threads, one per compute unit
@@ -1205,9 +1287,8 @@ hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, cons
 {
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
     const bool ring = prefill_down_splits(T, d, G) > 0 && row_table_fits(T);
-    group_tokens_kernel<<<dim3(G), dim3(256), 0, s>>>(mask, T, G, ws.tok_list, ws.tok_cnt,
-                                                     ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act, x, d,
-                                                     nullptr, nullptr);
+    launch_group_tokens(mask, T, G, ws.tok_list, ws.tok_cnt, ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act, x, d,
+                        nullptr, nullptr, s);
     if (ring) return launch_rings<false>(x, T, d, G, Wg, Wu, Wd, nullptr, nullptr, nullptr, ws, act, y, s);
     const hipError_t e = launch_gate_up_ring<false, 256>(x, T, d, G, Wg, Wu, nullptr, nullptr, ws, act, s);
     if (e != hipSuccess) return e;
@@ -1226,9 +1307,9 @@ hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4W
 {
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
     const bool codes = codes_path(T, d);
-    group_tokens_kernel<<<dim3(G + (codes ? (T * (d / kQ4Block) + 63) / 64 : 0)), dim3(256), 0, s>>>(
-        mask, T, G, ws.tok_list, ws.tok_cnt, reinterpret_cast<int16_t *>(ws.slot), ws.slot, act, x, d, codes ? codes_x_sums(ws) : nullptr,
-        codes ? codes_act_sums(ws, T, G) : nullptr);
+    launch_group_tokens(mask, T, G, ws.tok_list, ws.tok_cnt,
+                        reinterpret_cast<int16_t *>(ws.slot), ws.slot, act, x, d, codes ? codes_x_sums(ws) : nullptr,
+                        codes ? codes_act_sums(ws, T, G) : nullptr, s);
     return launch_rings<true>(x, T, d, G, w.gate_codes, w.up_codes, w.down_codes, w.gate_scales, w.up_scales, w.down_scales,
                               ws, act, y, s);
 }

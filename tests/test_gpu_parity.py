@@ -578,6 +578,25 @@ def test_predictor_of_many_tokens_keeps_the_fixed_order(T, d, r, G):
     assert same.all()
 
 
+@pytest.mark.parametrize("T", [256, 257, 512, 513, 2040, 2048, 2049, 4103])
+def test_token_lists_over_runs_of_256_tokens(T):
+    # one run, two, eight at once, and more than eight; groups that all, none, the first, the last and some of the tokens keep
+    w = dataclasses.replace(hs.LLAMA7B_DECODE, name="case", d=512, ffn=6 * 128, rank=16, T=T, seed=77)
+    _say(f"token lists T={T}")
+    s, L = hz.shape_of(w), hz.Layer(w)
+    x = hs.hidden_states(w, 0, hz.DEV)
+    m = np.zeros((T, 6), np.uint8)
+    m[:, 0] = 1
+    m[0, 2] = m[T - 1, 3] = 1
+    m[:, 4:] = np.random.default_rng(T).random((T, 2)) < 0.4
+    y = torch.full((T, w.d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+    ws = torch.empty(H.halo_workspace_bytes(s, T, 0), dtype=torch.uint8, device=hz.DEV)
+    H.halo_group_sparse_ffn(s, x, L.Wg, L.Wu, L.Wd, torch.from_numpy(m).to(hz.DEV), y, ws)
+    torch.cuda.synchronize()
+    yc = ref.group_sparse_ffn(hz.to_np32(x), *(hz.to_np32(t) for t in (L.Wg, L.Wu, L.WdT)), 128, m)
+    hz.check_y(hz.to_np32(y), yc, m.sum(axis=1), TOL["bf16"], f"token lists T={T}")
+
+
 @pytest.mark.parametrize("T,d,r", [
     (17, 4096, 512),           # a group of four tokens with one in it
     (16, 4104, 520),           # a ninth step of one piece

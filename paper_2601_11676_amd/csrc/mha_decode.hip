@@ -366,17 +366,18 @@ __global__ __launch_bounds__(128) void attn_combine(const float *__restrict__ pa
     const MaskWords mw = load_mask_words(mask, H, lane);
     if (u >= mw.count) return;
     const float *p = part + (size_t)u * chunks * kPartStride;
-    // the first batch of value sums and this thread's chunk statistics, all in flight together
+    // this thread's chunk statistics and the first batch of value sums, all in flight together, the statistics in front: loads return in
+    // order, and the weights are computed from them while the values arrive
+    const int c_own = tid < chunks ? tid : chunks - 1;
+    const float m_own = p[(size_t)c_own * kPartStride + dh], l_own = p[(size_t)c_own * kPartStride + dh + 1];
+    __builtin_amdgcn_sched_barrier(0);
     float v[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) v[i] = p[(size_t)(i < chunks ? i : chunks - 1) * kPartStride + tid];
-    const int c_own = tid < chunks ? tid : chunks - 1;
-    const float m_own = p[(size_t)c_own * kPartStride + dh], l_own = p[(size_t)c_own * kPartStride + dh + 1];
     // pass 1: maximum of the chunk maxima
     float m_loc = tid < chunks ? m_own : -INFINITY;
     for (int c = tid + 128; c < chunks; c += 128) m_loc = fmaxf(m_loc, p[(size_t)c * kPartStride + dh]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m_loc = fmaxf(m_loc, __shfl_xor(m_loc, off, kWave));
+    m_loc = wave_max(m_loc);
     if (lane == 0) s_red[0][wave] = m_loc;
     __syncthreads();
     const float M = fmaxf(s_red[0][0], s_red[0][1]);
@@ -648,16 +649,30 @@ hipError_t launch_mha_decode(const void *x, int d, int H, const void *Wq, const 
         }
         return hipGetLastError();
     }
-    attn_partial<kAttnChunk><<<dim3(chunks, H), dim3(256), 0, s>>>(ws.q, (const bf16_t *)k_cache, (const bf16_t *)v_cache, mask,
-                                                                   H, max_len, pos, ws.part);
+    // The merge kernel asks for 32 chunks at a time, one round trip after the other; up to 32 heads a chunk is longer where there would be
+    // more than 36.  A block, us, chunks of 128 / of 256 or 512: 32 heads, 6000 rows 36.4 / 36.1, 15 000 51.1 / 49.3; 16 heads, 15 000 31.1 / 27.6;
+    // 8 heads, 8000 19.0 / 18.3; 25 heads, 5000 28.1 / 27.7; but 32 heads, 4200 34.4 / 34.6,
+    // and 40 heads, 10 000 57.7 / 58.3.
+    ch = kAttnChunk;
+    while (H <= 32 && ch < 512 && len > ch * 36) ch *= 2;
+    const int n_chunks = (len + ch - 1) / ch;
+    {
+        const bf16_t *kc = (const bf16_t *)k_cache, *vc = (const bf16_t *)v_cache;
+        if (ch == 128)
+            attn_partial<128><<<dim3(n_chunks, H), dim3(256), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+        else if (ch == 256)
+            attn_partial<256><<<dim3(n_chunks, H), dim3(512), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+        else
+            attn_partial<512><<<dim3(n_chunks, H), dim3(1024), 0, s>>>(ws.q, kc, vc, mask, H, max_len, pos, ws.part);
+    }
     // the output projection is the FFN's down projection with heads as groups
     if (whole) {
-        attn_combine<bf16_t><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, chunks,
+        attn_combine<bf16_t><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, n_chunks,
                                                            reinterpret_cast<bf16_t *>(ws.dec.act));
         return launch_down_t1((const bf16_t *)Wo, d, H, mask, reinterpret_cast<const bf16_t *>(ws.dec.act),
                               (bf16_t *)y, s, ah);
     }
-    attn_combine<float><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, chunks, ws.dec.act);
+    attn_combine<float><<<dim3(H), dim3(128), 0, s>>>(ws.part, mask, H, n_chunks, ws.dec.act);
     return launch_down_t1_any((const bf16_t *)Wo, d, H, mask, (const float *)ws.dec.act, (bf16_t *)y, s, ah);
 }
 

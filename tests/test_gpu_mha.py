@@ -264,7 +264,7 @@ def test_mha_long_context_many_chunks():
     (3200, 2, 2303),           # nine of 256
     (5120, 16, 2304),          # five of 512
     (2048, 2, 4607),           # nine of 512
-    (8192, 2, 4608),           # 37 of 128, merged in a launch of their own
+    (8192, 2, 4608),           # 19 of 256, merged in a launch of their own
     (1024, 48, 383),           # three chunks of 128, more than 16 heads in float32; more than the projection's three batches of them
     (1024, 17, 384),           # four
     (4096, 48, 700),           # six of 128
@@ -305,6 +305,17 @@ def test_mha_merges_of_every_kind(d, Hh, ctx):
     (1024, 17, 1536),          # a launch of its own
 ])
 def test_mha_merges_of_more_than_16_heads(d, Hh, ctx):
+    test_mha_merges_of_every_kind(d, Hh, ctx)
+
+
+@pytest.mark.parametrize("d,Hh,ctx", [
+    (4096, 17, 4607),          # 36 chunks of 128
+    (4096, 17, 4608),          # 19 of 256, the last with one position
+    (1024, 17, 9216),          # 19 of 512
+    (1024, 2, 16500),          # 33 of 512
+    (1024, 33, 4700),          # more than 32 heads: 37 of 128
+])
+def test_mha_chunks_of_long_caches(d, Hh, ctx):
     test_mha_merges_of_every_kind(d, Hh, ctx)
 
 

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kGateUpF32Waves * 64) __attribute__((amdgpu_waves_p
 
 // The whole pass of a small block in two launches: gate/up of EVERY group beside the first predictor layer, then the down projection,
 // whose workgroups work out the masks of their tokens.  Such a pass is a chain of launches that each wait for the one before: prediction,
-// gate/up and down of the tiny block take 6.6 + 4.5 + 5.7 us, these two 4.7 + 7.8, a pass 16.4 -> 12.4 us.  Reading the groups that nobody
+// gate/up and down of the tiny block take 6.6 + 4.5 + 5.7 us, these two 4.5 + 7.6, a pass 16.1 -> 11.6 us.  Reading the groups that nobody
 // keeps costs less than the launches while the weights are few (forward_f32_supported has the line).
 // This one: n_gu workgroups of gate/up, 8 G to a range of tokens, then a wave per result of the first layer.  Groups of 128, act [g][t][128].
 template <int NT>
@@ -291,10 +291,13 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void down_f32_128(
     }
 }
 
-// ... and this one: down_f32_128 with the mask of its 16 tokens worked out by its 16 waves, up to 32 groups: the second predictor
+// ... and this one: the down projection with the mask of its 16 tokens worked out by its 16 waves, up to 32 groups: the second predictor
 // layer in the fixed order (same bits as mask_scores_block), a group's rank by comparing its key with all others, a lane per group.  act holds every token's activations
 // of every group here, so what a token does not keep is dropped as it is loaded.  The workgroups of the first 16 outputs write the
 // prediction's results.
+// It adds up as the kernel does that launch_ffn_f32 takes for the shape, so that the pass has the bits of its parts: BY_GROUP as down_f32_128
+// (the first eight groups asked for beside the prediction and taken by position), else as down_f32<1> (the groups that are kept, four to a turn,
+// a wave's two pieces 16 apart).
 struct PredictF32 {
     const float *h, *Bt;
     int r, K, n_dev, share;                                      // share: waves to a row (pair of rows) of Bt
@@ -429,6 +432,7 @@ __device__ __forceinline__ uint32_t token_mask_32(const PredictF32 &p, int t, in
     return kept;
 }
 
+template <bool BY_GROUP>
 __global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const float *__restrict__ act, int T, int d, int G,
                                                                        const float *__restrict__ Wd, float *__restrict__ y, PredictF32 pr)
 {
@@ -452,6 +456,7 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const flo
     PredictF32Lds &sh = *reinterpret_cast<PredictF32Lds *>(stage);
     f32x4_t A[kTurn], B[kTurn];
     scores_f32_block(pr, t0, n_tok, G, tid, sh, [&]() __attribute__((always_inline)) {
+        if (!BY_GROUP) return;
 #pragma unroll
         for (int k = 0; k < kTurn; ++k) A[k] = fetch(min(k, G - 1), k < G);
 #pragma unroll
@@ -465,20 +470,10 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const flo
     for (int w = 0; w < W; ++w) any |= s_kept[w];
     any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
     const uint32_t mine = half ? s_kept[row] : any;              // the groups whose values this thread may use
-    uint32_t rest = any & ~((1u << kFirst) - 1u);                // not asked for yet
+    uint32_t rest = BY_GROUP ? any & ~((1u << kFirst) - 1u) : any;                   // not asked for yet
     f32x4_t c[1] = {f32x4_t{0.f, 0.f, 0.f, 0.f}};
     int ga[kTurn], gb[kTurn];                                    // the groups that A and B hold, -1: none
-#pragma unroll
-    for (int k = 0; k < kTurn; ++k) {
-        ga[k] = k < G ? k : -1;
-        gb[k] = k + kTurn < G ? k + kTurn : -1;
-    }
-    auto turn = [&](f32x4_t (&b)[kTurn], int (&gk)[kTurn]) {
-#pragma unroll
-        for (int k = 0; k < kTurn; ++k)
-            *reinterpret_cast<f32x4_t *>(stage + ((k * 2 + half) * 16 + row) * kRowF32 + col) =
-                gk[k] >= 0 && ((mine >> gk[k]) & 1u) ? b[k] : f32x4_t{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
+    auto ask = [&](f32x4_t (&b)[kTurn], int (&gk)[kTurn]) {
 #pragma unroll
         for (int k = 0; k < kTurn; ++k) {
             const bool yes = rest != 0u;                         // uniform
@@ -486,11 +481,29 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const flo
             rest &= rest - 1u;                                   // (0 stays 0)
             b[k] = fetch(yes ? gk[k] : 0, yes);
         }
+    };
+    if (BY_GROUP) {
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k) {
+            ga[k] = k < G ? k : -1;
+            gb[k] = k + kTurn < G ? k + kTurn : -1;
+        }
+    } else {
+        ask(A, ga);
+        ask(B, gb);
+    }
+    auto turn = [&](f32x4_t (&b)[kTurn], int (&gk)[kTurn]) {
+#pragma unroll
+        for (int k = 0; k < kTurn; ++k)
+            *reinterpret_cast<f32x4_t *>(stage + ((k * 2 + half) * 16 + row) * kRowF32 + col) =
+                gk[k] >= 0 && ((mine >> gk[k]) & 1u) ? b[k] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        ask(b, gk);
         PairSum<1> sum;
         sum.clear();
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const int p = 2 * wave + k;
+            const int p = BY_GROUP ? 2 * wave + k : wave + W * k;
             auto operand = [&](int m) { return *reinterpret_cast<const f32x4_t *>(stage + (((p >> 3) * 2 + m) * 16 + i) * kRowF32 + (p & 7) * 16 + 4 * q); };
             const f32x4_t a[1] = {operand(1)};
             sum.add(operand(0), a);
@@ -498,8 +511,10 @@ __global__ __launch_bounds__(kDownF32Waves * 64) void predict_down_f32(const flo
         sum.fold(c);
         __syncthreads();
     };
-    turn(A, ga);
-    if (G > kTurn) turn(B, gb);
+    if (BY_GROUP) {
+        turn(A, ga);
+        if (G > kTurn) turn(B, gb);
+    }
     while (ga[0] >= 0) {
         turn(A, ga);
         if (gb[0] >= 0) turn(B, gb);
@@ -666,20 +681,26 @@ static hipError_t launch_blocks(const float *x, int T, int d, int G, int gs, con
     return hipGetLastError();
 }
 
+// Up to five tokens leave groups unwanted, and what is asked for before the mask is known is wasted: both projections, groups of
+// 128, half of them kept, us, asked for at once / after the mask: one token, d 256, 8 groups 10.3 / 8.4, d 1000, 24 groups 17.4 / 14.8,
+// d 2048, 44 groups 37.9 / 25.3, d 8192, 64 groups 126 / 109; four tokens 10.8 / 10.2, 21.5 / 20.5, 46.4 / 43.5, 156 / 152.
+static bool ask_after_mask(int T) { return T <= 5; }
+
+// down_f32_128 asks for its first eight groups at once (up to eight groups it pays from nine tokens on: 128 wide, three tenths kept,
+// five tokens 9.6 against 8.8 us, eight 9.5 / 9.6), and reads Wd once per 16 tokens, down_f32 once per 32: of many tokens it takes those
+// that give no compute unit more than one workgroup (d 1000, 24 groups, 64 tokens 34 against 43 us, 128 57 / 55, 512 176 / 168;
+// d 256, 8 groups, 256 tokens 14.3 / 17.4, 512 25.0 / 24.2; d 4096, 86 groups, 512 tokens 2299 / 2181).
+static bool down_by_group(int T, int d, int G, int gs)
+{
+    return gs == 128 && !ask_after_mask(T) && (G > 8 || T > 8) && (T <= 64 || (long long)((d + 15) / 16) * ((T + 15) / 16) <= 256);
+}
+
 hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const float *Wg, const float *Wu, const float *Wd,
                           const uint8_t *mask, float *y, float *act, hipStream_t s)
 {
     // four token tiles to a workgroup read the weights least often, two where four would leave compute units without one
     const int nt = T <= 16 ? 1 : T <= 32 || (long long)((T + 63) / 64) * (G * gs / 16) < 256 ? 2 : 4;
-    // Up to five tokens leave groups unwanted, and what is asked for before the mask is known is wasted: both projections, groups of
-    // 128, half of them kept, us, asked for at once / after the mask: one token, d 256, 8 groups 10.3 / 8.4, d 1000, 24 groups 17.4 / 14.8,
-    // d 2048, 44 groups 37.9 / 25.3, d 8192, 64 groups 126 / 109; four tokens 10.8 / 10.2, 21.5 / 20.5, 46.4 / 43.5, 156 / 152.
-    const bool ask = T <= 5;
-    // down_f32_128 asks for its first eight groups at once (up to eight groups it pays from nine tokens on: 128 wide, three tenths kept,
-    // five tokens 9.6 against 8.8 us, eight 9.5 / 9.6), and reads Wd once per 16 tokens, down_f32 once per 32: of many tokens it takes those
-    // that give no compute unit more than one workgroup (d 1000, 24 groups, 64 tokens 34 against 43 us, 128 57 / 55, 512 176 / 168;
-    // d 256, 8 groups, 256 tokens 14.3 / 17.4, 512 25.0 / 24.2; d 4096, 86 groups, 512 tokens 2299 / 2181).
-    const bool by_group = gs == 128 && !ask && (G > 8 || T > 8) && (T <= 64 || (long long)((d + 15) / 16) * ((T + 15) / 16) <= 256);
+    const bool ask = ask_after_mask(T), by_group = down_by_group(T, d, G, gs);
     constexpr int kRun = 1 << 20;                                // ranges of tokens are a grid's y, which ends at 65535
     for (int t0 = 0;; t0 += kRun) {
         const size_t t = (size_t)t0;
@@ -689,13 +710,15 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
     }
 }
 
-// Whole pass in two launches, see hidden_gate_up_f32, against three or four, us, three tenths of the groups kept: d 1024, 24 groups, 1, 2, 4, 16,
-// 32 tokens 18.4 / 17.2, 19.7 / 18.9, 22.4 / 19.0, 26.7 / 23.7, 29.0 / 25.9; d 1024, 32 groups 19.5 / 19.2, 21.4 / 21.4, 25.0 / 23.3,
-// 30.4 / 27.2, 33.2 / 30.7, half kept, rank 256, one token 20.8 / 21.0; d 2048, 32 groups 24.0 / 29.2, 26.6 / 31.2, 33.2 / 31.7, 41.3 / 39.4, 47.0 / 44.8;
-// d 4096, 16 groups 31.7 / 35.5, 34.3 / 36.5, 39.1 / 37.3, 47.2 / 40.4, 63.9 / 64.5; d 256, 12 groups 14.4 / 11.9 ... 19.1 / 14.5.  So the weights of
-// all groups may be 24 Ki rows of 128 elements, 32 Ki from four tokens on.  From 64 tokens on the prediction keeps a launch of its own, which
-// callers and tests know it by (it would be ahead there too: d 256, 12 groups 19.2 / 14.7, d 1024, 24 groups 37.3 / 33.3; 128 tokens of
-// 32 groups of d 1024 not, 65.8 / 68.5).
+// Whole pass in two launches, see hidden_gate_up_f32, against three or four, us in a graph of blocks, one block over and over, and (in
+// brackets) blocks of 1.2 GB in all, whose weights come from HBM.  One group kept, the least there is to read, rank 256: d 1024, 24 groups, 1, 3, 4,
+// 16 tokens 15.9 / 12.5 (16.6 / 15.6), 17.0 / 13.5 (17.8 / 16.5), 16.9 / 13.6 (18.6 / 16.7), 22.7 / 20.3 (25.9 / 24.3); d 1024, 32 groups 15.9 / 13.9
+// (16.8 / 17.9), 16.8 / 14.4 (17.8 / 17.9), 17.5 / 15.0 (18.4 / 18.0), 23.0 / 20.9 (26.7 / 26.0).  Half of the groups kept: d 1024, 24 groups 18.2 / 15.4
+// (21.9 / 18.7), 21.7 / 18.8 (25.2 / 22.6), 23.4 / 19.1 (26.3 / 23.1), 26.2 / 22.7 (29.4 / 27.1); d 256, 8 groups, 1 and 16 tokens 13.6 / 9.3 (15.2 / 10.9),
+// 15.7 / 11.0 (18.1 / 13.0).  Above the line d 2048, 32 groups, one group kept, 1, 4, 16 tokens 19.8 / 21.0 (21.6 / 24.8), 21.3 / 20.4 (23.6 / 25.3),
+// 29.0 / 27.3 (32.5 / 32.4).  So the weights of all groups may be 24 Ki rows of 128 elements, 32 Ki from four tokens on, whatever share of the groups
+// is kept.  From 64 tokens on the prediction keeps a launch of its own, which callers and tests know it by (it would be ahead there too: d 256,
+// 12 groups 18.4 / 14.0, d 1024, 24 groups 38.9 / 32.6; 128 tokens of 32 groups of d 1024 not, 70.3 / 76.2).
 bool forward_f32_supported(int T, int d, int G, int gs, int r, int n_dev)
 {
     return gs == 128 && r <= 512 && f32_score_slots(G, r) <= kDownF32Waves && n_dev <= 64 && T < 64 &&
@@ -723,7 +746,11 @@ hipError_t launch_forward_f32(const float *x, const float *x_pred, int T, int d,
     unsigned long long parts = 0;
     for (int w = 0; w < kDownF32Waves; ++w) parts |= (unsigned long long)(w / slots) << (4 * w);
     const PredictF32 pr{h, Bt, r, K, n_dev, share, parts, prio_dev, drop, scores, order, group_dev, mask, surv_idx, n_surv};
-    predict_down_f32<<<dim3((d + 15) / 16, (T + 15) / 16), dim3(kDownF32Waves * 64), 0, s>>>(act, T, d, G, Wd, y, pr);
+    const dim3 grid((d + 15) / 16, (T + 15) / 16), block(kDownF32Waves * 64);
+    if (down_by_group(T, d, G, 128))
+        predict_down_f32<true><<<grid, block, 0, s>>>(act, T, d, G, Wd, y, pr);
+    else                                                         // (at most eight tokens)
+        predict_down_f32<false><<<grid, block, 0, s>>>(act, T, d, G, Wd, y, pr);
     return hipGetLastError();
 }
 

@@ -906,3 +906,37 @@ def test_small_float32_blocks_in_two_launches(T, d, G, r):
     L.Wd[idle] = float("nan")
     again = hz.gpu_forward(w, L, x, K, pd, drop)
     assert np.isfinite(g["y"]).all() and np.array_equal(g["y"], again["y"])
+
+
+@pytest.mark.parametrize("T,d,G,r", [
+    (1, 256, 8, 64),           # one token: the FFN on its own walks the groups that are kept
+    (5, 1000, 12, 72),
+    (6, 264, 9, 40),           # the first eight groups by position
+    (8, 512, 8, 64),           # up to eight tokens and eight groups: as one token
+    (8, 1024, 24, 256),
+    (9, 512, 8, 264),
+    (63, 256, 31, 128),
+])
+def test_float32_pass_has_the_bits_of_its_parts(T, d, G, r):
+    w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=93)
+    _say(f"float32 pass against its parts T={T} d={d} G={G} r={r}")
+    s, L = hz.shape_of(w), hz.Layer(w)
+    x, drop = hs.hidden_states(w, 0, hz.DEV), hs.drop_outcomes(w, T=T)
+    on = lambda a: torch.from_numpy(a).to(hz.DEV)              # noqa: E731
+    for K in sorted({0, 1, G // 2, G}):
+        pd = H.halo_build_schedule(K, w.device_plr())
+        g = hz.gpu_forward(w, L, x, K, pd, drop)
+        ws = torch.empty(H.halo_workspace_bytes(s, T, K), dtype=torch.uint8, device=hz.DEV)
+        sc = torch.empty((T, G), dtype=torch.float32, device=hz.DEV)
+        mask = torch.empty((T, G), dtype=torch.uint8, device=hz.DEV)
+        y, y_ahead = (torch.full((T, d), float("nan"), device=hz.DEV) for _ in range(2))
+        H.halo_predict_scores(s, x, L.At, L.Bt, sc, ws)
+        H.halo_build_group_mask(sc, K, on(pd), w.n_dev, on(drop), mask)
+        H.halo_group_sparse_ffn(s, x, L.Wg, L.Wu, L.Wd, mask, y, ws)
+        H.halo_ffn_forward_ahead(s, x, L.Wg, L.Wu, L.Wd, mask, y_ahead, x, L.At, L.Bt, K, on(pd), w.n_dev, on(drop),
+                                 torch.empty_like(mask), ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(sc.cpu().numpy().view(np.uint32), g["scores"].view(np.uint32)), K
+        assert np.array_equal(mask.cpu().numpy(), g["mask"]), K
+        for v in (y, y_ahead):
+            assert np.array_equal(hz.to_np32(v).astype(np.float64), g["y"]), K

@@ -34,52 +34,16 @@
 
 namespace halo {
 
-// the sums of x over the blocks of 128 elements, 16 lanes to a block, four blocks of a lane requested together
-__device__ __forceinline__ void block_sums(const bf16_t *__restrict__ x, int T, int d, float *__restrict__ xsum, int wg, int n_wg)
-{
-    constexpr int U = 4;
-    const int nb = d / kQ4Block, i16 = threadIdx.x & 15;
-    const size_t n = (size_t)T * nb, stride = (size_t)n_wg * 16;
-    for (size_t i0 = (size_t)wg * 16 + (threadIdx.x >> 4); i0 < n; i0 += stride * U) {
-        u32x4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t i = i0 + u * stride < n ? i0 + u * stride : i0;
-            v[u] = reinterpret_cast<const u32x4 *>(x)[i * 16 + i16];             // (blocks follow each other token after token)
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const size_t i = i0 + u * stride;
-            float e[8];
-            unpack8(v[u], e);
-            float sum = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-            sum = xor_add<8>(sum);
-            sum = xor_add<4>(sum);
-            sum = xor_add<2>(sum);
-            sum = xor_add<1>(sum);
-            if (i16 == 0 && i < n) xsum[(i % nb) * T + i / nb] = sum;
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
-// token lists: grid = G workgroups of 256 threads (and those that add up x)
+// token lists: grid = G workgroups of 256 threads
 // ---------------------------------------------------------------------------
 // rows != nullptr: row table [G][row_pitch] (row_pitch = T rounded up to 8; the entries past T are 0).
 // slot != nullptr instead (more than 32767 tokens): [T][G] positions in the list, -1 = not kept.
-// For gate_up_codes (xsum != nullptr) workgroups past the groups' add up x over the 128 elements of every quantisation block, xsum [d/128][T],
-// and the row of zeros has a sum too, asum [2][G][T].
 __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__restrict__ mask, int T, int G,
                                                            int32_t *__restrict__ tok_list,
                                                            int32_t *__restrict__ tok_cnt, int16_t *__restrict__ rows,
-                                                           int32_t *__restrict__ slot, bf16_t *__restrict__ act,
-                                                           const bf16_t *__restrict__ x, int d, float *__restrict__ xsum,
-                                                           float *__restrict__ asum)
+                                                           int32_t *__restrict__ slot, bf16_t *__restrict__ act)
 {
-    if ((int)blockIdx.x >= G) {
-        block_sums(x, T, d, xsum, blockIdx.x - G, gridDim.x - G);
-        return;
-    }
     __shared__ int s_wave[4];
     __shared__ int s_base;
     const int g = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -117,7 +81,6 @@ __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__rest
     // the row after the group's last activation row is kept zero (group size 128): the down
     // projection points the tokens that do not keep the group at it
     if (cnt < T && tid < 64) reinterpret_cast<uint32_t *>(act + ((size_t)g * T + cnt) * 128)[tid] = 0u;
-    if (asum && cnt < T && tid < 2) asum[((size_t)tid * G + g) * T + cnt] = 0.0f;
 }
 
 // The same lists for more than 256 tokens: a workgroup asks for the mask bytes of RUNS runs of 256 tokens at once and places them behind one
@@ -190,12 +153,10 @@ __global__ __launch_bounds__(256) void group_tokens_runs_kernel(const uint8_t *_
 }
 
 static void launch_group_tokens(const uint8_t *mask, int T, int G, int32_t *tok_list, int32_t *tok_cnt, int16_t *rows, int32_t *slot, bf16_t *act,
-                                const bf16_t *x, int d, float *xsum, float *asum, hipStream_t s)
+                                hipStream_t s)
 {
-    // x's sums are there up to 64 tokens only
     if (T <= 256)
-        group_tokens_kernel<<<dim3(G + (xsum ? (T * (d / kQ4Block) + 63) / 64 : 0)), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot,
-                                                                                                       act, x, d, xsum, asum);
+        group_tokens_kernel<<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
     else if (T <= 512)
         group_tokens_runs_kernel<2><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
     else
@@ -413,7 +374,7 @@ template <bool Q4, int NTOK>
 __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gate_up_pf_ring(
     const bf16_t *__restrict__ x, int T, int d, int G, const void *__restrict__ Wg, const void *__restrict__ Wu,
     const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const int32_t *__restrict__ tok_list,
-    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act, const float *, float *)
+    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act)
 {
     using R = Ring<Q4, NTOK>;
     constexpr int MT = R::kMT, TT = R::kTT, EV = Q4 ? 2 : 0;     // EV: loads of a wave per block of codes
@@ -597,9 +558,9 @@ template <>
 __global__ __launch_bounds__(kRingWaves * 64, 2) void gate_up_pf_ring<true, 64>(
     const bf16_t *__restrict__ x, int T, int d, int G, const void *__restrict__ Wg, const void *__restrict__ Wu,
     const bf16_t *__restrict__ Sg, const bf16_t *__restrict__ Su, const int32_t *__restrict__ tok_list,
-    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act, const float *__restrict__ xsum, float *__restrict__ asum)
+    const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act)
 {
-    gate_up_codes(x, T, d, G, (const unsigned char *)Wg, (const unsigned char *)Wu, Sg, Su, tok_list, tok_cnt, xsum, act, asum);
+    gate_up_codes(x, T, d, G, (const unsigned char *)Wg, (const unsigned char *)Wu, Sg, Su, tok_list, tok_cnt, act);
 }
 
 // ---------------------------------------------------------------------------
@@ -960,7 +921,7 @@ static int splits_in_room(int splits, int T, int d, const DecodeScratch &ws)
 template <bool Q4, int NTOK, bool SCALED>
 __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void down_pf_ring(
     int T, int d, int G, int splits, const void *__restrict__ Wd, const bf16_t *__restrict__ Sd,
-    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y, const float *)
+    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y)
 {
     using R = Ring<Q4, NTOK>;
     constexpr int MT = R::kMT, TT = R::kTT, EV = Q4 ? 3 : 1;     // EV: loads of a wave per group besides the stages'
@@ -1136,9 +1097,9 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
 template <>
 __global__ __launch_bounds__(kRingWaves * 64, 2) void down_pf_ring<true, 64, true>(
     int T, int d, int G, int splits, const void *__restrict__ Wd, const bf16_t *__restrict__ Sd,
-    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y, const float *__restrict__ asum)
+    const int16_t *__restrict__ rows, const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y)
 {
-    down_codes(T, d, G, splits, (const unsigned char *)Wd, Sd, rows, act, asum, partial, y);
+    down_codes(T, d, G, splits, (const unsigned char *)Wd, Sd, rows, act, partial, y);
 }
 
 // y = sum of the ranges' partial sums, added in the order of the ranges; n = T * d, a multiple of 8
@@ -1171,10 +1132,6 @@ bool prefill_path_supported(int T, int d, int gs)
 // that the values are rounded to bf16 and the results are those of the bf16 kernels on the expanded weights, bit for bit, which callers may
 // count on (the same kernel in a 128-token tile would run 13B, 100 tokens of d 3200 and 128 in 70 us instead of 85 and 98 instead of 109).
 static bool codes_path(int T, int d) { return T <= 64 && d >= 256; }
-// ... and its sums: of x where the expanded weights would go, of the activations, [2][G][T], behind these (which are halves of the words
-// that the workspace has for them)
-static float *codes_x_sums(const DecodeScratch &ws) { return reinterpret_cast<float *>(ws.q4_w); }
-static float *codes_act_sums(const DecodeScratch &ws, int T, int G) { return ws.act + (size_t)T * G * 64; }
 
 template <bool Q4, int NTOK>
 static hipError_t launch_gate_up_ring(const bf16_t *x, int T, int d, int G, const void *Wg, const void *Wu, const bf16_t *Sg,
@@ -1185,8 +1142,7 @@ static hipError_t launch_gate_up_ring(const bf16_t *x, int T, int d, int G, cons
     if (lds_ok != hipSuccess) return lds_ok;
     const int items_max = 2 * G * ((T + NTOK - 1) / NTOK);                  // every group kept by every token
     launch_timed_lds("gate_up_pf_ring", gate_up_pf_ring<Q4, NTOK>, dim3((items_max + 7) / 8 * 8), dim3(kRingWaves * 64),
-                     bytes, s, x, T, d, G, Wg, Wu, Sg, Su, (const int32_t *)ws.tok_list, (const int32_t *)ws.tok_cnt, act,
-                     (const float *)codes_x_sums(ws), codes_act_sums(ws, T, G));
+                     bytes, s, x, T, d, G, Wg, Wu, Sg, Su, (const int32_t *)ws.tok_list, (const int32_t *)ws.tok_cnt, act);
     return hipSuccess;
 }
 
@@ -1205,8 +1161,7 @@ static hipError_t launch_down_ring(int T, int d, int G, int splits, const void *
     if (lds_ok != hipSuccess) return lds_ok;
     const int items = (d / 128) * ((T + NTOK - 1) / NTOK) * splits;
     down_pf_ring<Q4, NTOK, SCALED><<<dim3((items + 7) / 8 * 8), dim3(kRingWaves * 64), bytes, s>>>(
-        T, d, G, splits, Wd, Sd, reinterpret_cast<const int16_t *>(ws.slot), act, splits > 1 ? ws.partial : (float *)nullptr, y,
-        SCALED ? (const float *)codes_act_sums(ws, T, G) : (const float *)nullptr);
+        T, d, G, splits, Wd, Sd, reinterpret_cast<const int16_t *>(ws.slot), act, splits > 1 ? ws.partial : (float *)nullptr, y);
     if (splits > 1) launch_reduce(ws.partial, splits, T, d, y, s);
     return hipSuccess;
 }
@@ -1287,8 +1242,7 @@ hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, cons
 {
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
     const bool ring = prefill_down_splits(T, d, G) > 0 && row_table_fits(T);
-    launch_group_tokens(mask, T, G, ws.tok_list, ws.tok_cnt, ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act, x, d,
-                        nullptr, nullptr, s);
+    launch_group_tokens(mask, T, G, ws.tok_list, ws.tok_cnt, ring ? reinterpret_cast<int16_t *>(ws.slot) : nullptr, ws.slot, act, s);
     if (ring) return launch_rings<false>(x, T, d, G, Wg, Wu, Wd, nullptr, nullptr, nullptr, ws, act, y, s);
     const hipError_t e = launch_gate_up_ring<false, 256>(x, T, d, G, Wg, Wu, nullptr, nullptr, ws, act, s);
     if (e != hipSuccess) return e;
@@ -1306,10 +1260,8 @@ hipError_t launch_ffn_prefill_q4(const bf16_t *x, int T, int d, int G, const Q4W
                                  const DecodeScratch &ws, hipStream_t s)
 {
     bf16_t *act = reinterpret_cast<bf16_t *>(ws.act);
-    const bool codes = codes_path(T, d);
     launch_group_tokens(mask, T, G, ws.tok_list, ws.tok_cnt,
-                        reinterpret_cast<int16_t *>(ws.slot), ws.slot, act, x, d, codes ? codes_x_sums(ws) : nullptr,
-                        codes ? codes_act_sums(ws, T, G) : nullptr, s);
+                        reinterpret_cast<int16_t *>(ws.slot), ws.slot, act, s);
     return launch_rings<true>(x, T, d, G, w.gate_codes, w.up_codes, w.down_codes, w.gate_scales, w.up_scales, w.down_scales,
                               ws, act, y, s);
 }

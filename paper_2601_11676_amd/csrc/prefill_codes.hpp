@@ -1,32 +1,33 @@
 // 17 to 64 tokens over 4-bit weights: the codes become matrix operands in registers.
 //
-// A code is c in 0..15, its value s * (c - 8) with one scale s per row and block of 128 elements.  An and-or makes the pair of
-// bf16 values 128 + c that a matrix instruction multiplies; a block's sum starts at -136 * (the sum of the token's elements), and the
-// finished block is scaled in float on its way into the running sum: two vector instructions per pair, where a value that is
-// scaled, rounded to bf16 and parked in LDS for all waves takes seven, an LDS write and reads of twice the bytes.
+// A code is c in 0..15, its value s * (c - 8) with one scale s per row and block of 128 elements.  A matrix instruction multiplies (c - 8) / 16,
+// exact in bf16 (q4_word_signed), and the finished block is scaled in float on its way into the running sum: three and a half vector instructions
+// per pair of codes, where a value that is scaled, rounded to bf16 and parked in LDS for all waves takes seven, an LDS write and reads of twice the
+// bytes.  (128 + c, less 136 times the sum of the token's elements, is half the conversion and gained 1 to 4 %, but its sums carry 17 times what
+// the block is made of: rows that cancel were up to 400 times further from 64 bits than here, blocks over codes of 8 alone were not 0,
+// and sums of a block's elements from 2^121 on overflowed.)
 //
 // Workgroup tile: 128 weight rows x 64 tokens, eight waves: two halves of the blocks (a wave takes every other block) times four quarters
 // of the rows, gate (or lower) and up (upper) rows alike; a wave owns 32 x 64, N of its four 16-token tiles existing.  A step is 64
 // elements of each of two blocks, a unit the two steps of a pair of blocks.  In LDS: three steps of token rows (128 bytes each) and three
-// units of codes (64 bytes a row, 16-byte piece p of row r at p ^ ((r >> 2) & 3)), scales and sums.
+// units of codes (64 bytes a row, 16-byte piece p of row r at p ^ ((r >> 2) & 3)) and scales.
 //
-// What bounds it: the instructions of a wave, one per four cycles, half of them the conversion and the scaling, and the barrier of
-// a step; with loads that move nothing gate/up of 17 tokens at the 70B shape takes 61 us of its 80, without the conversion and the matrix
-// instructions besides 51.  Pass in us, codes rounded to bf16 on their way into LDS (as for more tokens) against this: 17 tokens 7B 68.7 / 49.7,
-// 13B 85.4 / 61.7, 70B 231 / 150 (gate/up 140 -> 80, down 70 -> 37); 33 tokens 13B 90.3 / 69.0, 64 tokens 92.4 / 75.2; d 2048, 44 groups, 40 tokens
-// 46.3 / 37.7.  Two such workgroups to a compute unit (rings of two steps and two units, 128 registers) took 189 us at 70B, 17 tokens, four
-// units of codes instead of three 151.  The scalar address work is kept to an addition per load (17 tokens of 70B 157 -> 150), and the
-// barrier stands in the middle of a step, where the fragments of its second half have long been read.
+// What bounds it: the instructions of a wave, one per four cycles, more than half of them the conversion and the scaling, and the barrier of
+// a step.  Pass in us, codes rounded to bf16 on their way into LDS (as for more tokens) against this: 17 tokens 7B 68.2 / 50.1,
+// 13B 84.0 / 62.0, 70B 224.5 / 144.2; 33 tokens 13B 89.1 / 67.3, 48 of 70B 226.8 / 158.7, 64 of 13B 91.4 / 74.6; d 2048, 44 groups, 40 tokens
+// 46.6 / 38.3; d 256, 4 groups, 17 tokens 23.0 / 18.8.  With 128 + c: two such workgroups to a compute unit (rings of two steps and two units, 128 registers)
+// took 189 us at 70B, 17 tokens, where one took 150, four units of codes instead of three 151.  The scalar address work is kept to an addition per load
+// (157 -> 150 there), and the barrier stands in the middle of a step, where the fragments of its second half have long been read.
 #pragma once
 #include "prefill_tiles.hpp"
 
 namespace halo {
 
 constexpr int kCodesTokens = 64;
-constexpr int kCodesX = 2 * kCodesTokens * 128, kCodesRaw = 2 * 8192, kCodesScale = 2 * 512, kCodesSum = 8 * 32 * 4;
+constexpr int kCodesX = 2 * kCodesTokens * 128, kCodesRaw = 2 * 8192, kCodesScale = 2 * 512;
 constexpr int kCodesSteps = 3, kCodesUnits = 3;                  // ring buffers
 constexpr int kCodesRawBase = kCodesSteps * kCodesX, kCodesScaleBase = kCodesRawBase + kCodesUnits * kCodesRaw;
-constexpr int kCodesSumBase = kCodesScaleBase + kCodesUnits * kCodesScale, kCodesBytes = kCodesSumBase + kCodesUnits * kCodesSum;
+constexpr int kCodesBytes = kCodesScaleBase + kCodesUnits * kCodesScale;
 static_assert(kCodesBytes + kTabGroups * kTabBytes / 2 <= 160 * 1024, "fits a compute unit");
 
 // The 16-byte piece of a token row's 128 bytes that is parked at position v ^ (row & 7): a lane group q multiplies pieces 2 q and
@@ -40,17 +41,16 @@ struct CodesPart {
     __device__ __forceinline__ int row_tile(int m) const { return 4 * m + rw; }
 };
 
-// The steps of a tile over n_units units: total[m][n] = sum over the wave's blocks.
+// The steps of a tile over n_units units: total[m][n] = sum over the wave's blocks, over kQ4Signed.
 // load_x(half, buf): token rows of three steps on, that half of its unit, into ring buffer buf (two loads of every wave).  load_unit(): end of
 // the first step of a unit; requests the next but one (EV loads of every wave), and load_x turns to it.
-// upper(j): the scale of rows 4 q + j is the upper half of its word.  P: partial sums of a token and block that the sums come in.
-template <int N, int P, int EV, typename LoadX, typename LoadUnit, typename Upper>
+// upper(j): the scale of rows 4 q + j is the upper half of its word.
+template <int N, int EV, typename LoadX, typename LoadUnit, typename Upper>
 __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned char *ring, int n_units, int wave, int lane,
                                                LoadX load_x, LoadUnit load_unit, Upper upper)
 {
     const CodesPart part(wave);
     const int i16 = lane & 15, q = lane >> 4;
-    const Q4Consts k = q4_consts();
     const unsigned char *xbase = ring + part.ks * (kCodesTokens * 128) + i16 * 128;
     const int xoff[2] = {(q ^ (i16 & 7)) * 16, ((4 + q) ^ (i16 & 7)) * 16};
     auto read_b = [&](u32x4 &f, int n, int t, int buf) __attribute__((always_inline)) {
@@ -61,19 +61,9 @@ __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned 
     auto read_c = [&](uint2 &c, int m, int half, int ub) __attribute__((always_inline)) {
         c = *reinterpret_cast<const uint2 *>(cbase + ub * kCodesRaw + part.row_tile(m) * 1024 + coff[half]);
     };
-    // token tk is lane (ks P + p) 8 + tk % 8 of the load of wave tk / 8
-    auto read_sum = [&](int n, int ub) __attribute__((always_inline)) {
-        const int tk = n * 16 + i16;
-        float v = 0.0f;
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-            v += *reinterpret_cast<const float *>(ring + kCodesSumBase + ub * kCodesSum + (tk >> 3) * 128 + ((part.ks * P + p) * 8 + (tk & 7)) * 4);
-        return -136.0f * v;
-    };
     f32x4_t blk[2][N];
     u32x4 b0[N], b1[N], a, sc[2];
     uint2 c[2];
-    float sum[N];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         read_c(c[m], m, 0, 0);
@@ -82,11 +72,8 @@ __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned 
         for (int n = 0; n < N; ++n) total[m][n] = blk[m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int n = 0; n < N; ++n) {
-        read_b(b0[n], n, 0, 0);
-        sum[n] = read_sum(n, 0);
-    }
-    a = q4_word_bf16(c[0].x, k);
+    for (int n = 0; n < N; ++n) read_b(b0[n], n, 0, 0);
+    a = q4_word_signed(c[0].x);
     uint32_t sel[2] = {0u, 0u};                                  // which half of a word of scales, rows 4 q + j with even and odd j
     auto fold = [&](int m) __attribute__((always_inline)) {
 #pragma unroll
@@ -109,10 +96,10 @@ __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned 
 #pragma unroll
             for (int n = m * N; n < (m + 1) * N && n < N; ++n) read_b(b1[n], n, 1, buf);
             const u32x4 w = a;
-            a = q4_word_bf16(m == 0 ? c[1].x : c[0].y, k);
+            a = q4_word_signed(m == 0 ? c[1].x : c[0].y);
             if (m == 0 && !second) fold(1);                      // (of the unit before; at first: nothing to scale)
 #pragma unroll
-            for (int n = 0; n < N; ++n) blk[m][n] = mfma16p(w, b0[n], second ? blk[m][n] : f32x4_t{sum[n], sum[n], sum[n], sum[n]});
+            for (int n = 0; n < N; ++n) blk[m][n] = mfma16p(w, b0[n], second ? blk[m][n] : f32x4_t{0.f, 0.f, 0.f, 0.f});
             __builtin_amdgcn_sched_barrier(0);
         }
         // the rows of step s+2 may still be on their way, and the unit requested last (in step s-1 or s-2); everybody has read step s
@@ -125,7 +112,7 @@ __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned 
 #pragma unroll
             for (int n = m * N; n < (m + 1) * N && n < N; ++n) read_b(b0[n], n, 0, nbuf);
             const u32x4 w = a;
-            a = q4_word_bf16(m == 0 ? c[1].y : c[0].x, k);
+            a = q4_word_signed(m == 0 ? c[1].y : c[0].x);
             if (m == 0) load_x(!second, buf);
             if (m == 0 && second) {
                 sel[0] = upper(0) ? 0x07060c0cu : 0x05040c0cu;
@@ -139,13 +126,10 @@ __device__ __forceinline__ void multiply_codes(f32x4_t (&total)[2][N], unsigned 
             for (int n = 0; n < N; ++n) blk[m][n] = mfma16p(w, b1[n], blk[m][n]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (second) {
-#pragma unroll
-            for (int n = 0; n < N; ++n) sum[n] = read_sum(n, nub);
+        if (second)
             ub = nub;
-        } else {
+        else
             load_unit();
-        }
         buf = nbuf;
     };
     for (int e = 0; e < n_units; ++e) {
@@ -191,15 +175,13 @@ __device__ __forceinline__ void with_token_tiles(int tokens, Body body)
         body(std::integral_constant<int, 1>{});
 }
 
-// Wg, Wu: code words [ffn][d/8]; xsum [d/128][T]: sums of x over the blocks; asum [2][G][T]: sums of the activations over the two halves
-// of a group's neurons, by the token's slot in the group's list.  T <= 64.
+// Wg, Wu: code words [ffn][d/8].  T <= 64.
 __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int T, int d, int G, const unsigned char *__restrict__ Wg,
                                               const unsigned char *__restrict__ Wu, const bf16_t *__restrict__ Sg,
                                               const bf16_t *__restrict__ Su, const int32_t *__restrict__ tok_list,
-                                              const int32_t *__restrict__ tok_cnt, const float *__restrict__ xsum,
-                                              bf16_t *__restrict__ act, float *__restrict__ asum)
+                                              const int32_t *__restrict__ tok_cnt, bf16_t *__restrict__ act)
 {
-    constexpr int gs = 128, EV = 4;
+    constexpr int gs = 128, EV = 3;
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -221,10 +203,9 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
     const int nb = d / kQ4Block, nu = (nb + 1) / 2;              // blocks, units
     const int unit0 = (die * nu) >> 3;                           // the dies start at different places, as in gate_up_pf_ring
     const int br = lane >> 3, piece = codes_piece((lane & 7) ^ br);
-    // the wave loads rows 8 wave .. + 7 of the tile, and of the sums lanes 8 ks + r theirs
-    const int sl = wave * 8 + br, sum_ks = lane >> 3, sum_sl = wave * 8 + (lane & 7);
+    // the wave loads rows 8 wave .. + 7 of the tile
+    const int sl = wave * 8 + br;
     const uint32_t off_x = sl < cnt ? (uint32_t)(list[sl] * d + piece * 8) * 2u : kNoRow;
-    const uint32_t off_s = lane < 16 && sum_sl < cnt ? (uint32_t)(list[sum_sl] + sum_ks * T) * 4u : kNoRow;
     // its 16 rows are gate rows (waves 0..3) or up rows; one load covers 16 rows x 64 bytes
     const size_t q_row0 = (size_t)g * gs + nt * 64 + (wave & 3) * 16;
     const uint32_t off_c = (uint32_t)((lane >> 2) * (d / 2) + ((lane & 3) ^ ((lane >> 4) & 3)) * 16);
@@ -236,7 +217,7 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
         srd_x[ks] = make_srd(x, true);
         srd_c[ks] = make_srd((wave < 4 ? Wg : Wu) + q_row0 * (d / 2), true);
     }
-    srd_t srd_s = make_srd((wave < 4 ? Sg : Su) + q_row0 * nb, true), srd_sum = make_srd(xsum, true);
+    srd_t srd_s = make_srd((wave < 4 ? Sg : Su) + q_row0 * nb, true);
     const uint32_t ring0 = (uint32_t)(size_t)ring, xdst = ring0 + wave * 1024, cdst = ring0 + kCodesRawBase + wave * 1024;
     const uint32_t end = (uint32_t)nu * 512u;
     uint32_t at = (uint32_t)unit0 * 512u;                        // the unit's place in a row of x, bytes
@@ -247,14 +228,12 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
     };
     auto request = [&]() __attribute__((always_inline)) {
         const bool half_unit = at + 256u >= (uint32_t)nb * 256u;
-        srd_x[0].z = srd_c[0].z = srd_s.z = srd_sum.z = (uint32_t)__builtin_amdgcn_readfirstlane(left > 0 ? kAnySize : 0u);
+        srd_x[0].z = srd_c[0].z = srd_s.z = (uint32_t)__builtin_amdgcn_readfirstlane(left > 0 ? kAnySize : 0u);
         srd_x[1].z = srd_c[1].z = (uint32_t)__builtin_amdgcn_readfirstlane(half_unit ? 0u : srd_x[0].z);
         load_to_lds16_at<0, true>(srd_c[0], off_c, at >> 2, cdst + rb * kCodesRaw);
         load_to_lds16_at<8192, true>(srd_c[1], off_c, (at >> 2) + 64u, cdst + rb * kCodesRaw);
         load_to_lds_lanes<4>(0xffffffffull, srd_s, half_unit && lane >= 16 ? kNoRow : off_p, (at >> 9) * 4u,
                              ring0 + kCodesScaleBase + rb * kCodesScale + wave * 128);
-        load_to_lds_lanes<4>(0xffffffffull, srd_sum, half_unit && sum_ks == 1 ? kNoRow : off_s, (at >> 8) * (uint32_t)T * 4u,
-                             ring0 + kCodesSumBase + rb * kCodesSum + wave * 128);
         rb = rb == kCodesUnits - 1 ? 0 : rb + 1;
     };
     auto load_unit = [&]() __attribute__((always_inline)) {
@@ -270,11 +249,10 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
     load_x(false, 2);
     wait_loads<4 + EV>();
     __syncthreads();
-    float *sums = reinterpret_cast<float *>(ring + 32 * 1024);   // [wave][64 tokens], behind what meet_codes uses
     with_token_tiles(cnt, [&](auto n_c) __attribute__((always_inline)) {
         constexpr int N = decltype(n_c)::value;
         f32x4_t total[2][N];
-        multiply_codes<N, 1, EV>(total, ring, nu, wave, lane, load_x, load_unit, upper);
+        multiply_codes<N, EV>(total, ring, nu, wave, lane, load_x, load_unit, upper);
         bf16_t *act_row0 = act + (size_t)g * T * gs + nt * 64;
         auto put = [&](auto half) __attribute__((always_inline)) {
             constexpr int KH = decltype(half)::value;
@@ -282,15 +260,10 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
 #pragma unroll
             for (int n = KH; n < N; n += 2) {
                 const int s = n * 16 + i16;
-                const f32x4_t gt = total[0][n], up = total[1][n];
+                const f32x4_t gt = kQ4Signed * total[0][n], up = kQ4Signed * total[1][n];
                 const uint32_t lo = (uint32_t)f32_to_bf16(silu_mul_fast(gt[0], up[0])) | ((uint32_t)f32_to_bf16(silu_mul_fast(gt[1], up[1])) << 16);
                 const uint32_t hi = (uint32_t)f32_to_bf16(silu_mul_fast(gt[2], up[2])) | ((uint32_t)f32_to_bf16(silu_mul_fast(gt[3], up[3])) << 16);
                 if (s < cnt) *reinterpret_cast<uint2 *>(act_row0 + (size_t)s * gs + part.rw * 16 + 4 * q) = make_uint2(lo, hi);
-                // the sum of what was stored, over the wave's rows
-                float v = (bf16_lo(lo) + bf16_hi(lo)) + (bf16_lo(hi) + bf16_hi(hi));
-                v = xor_add<32>(v);
-                v = xor_add<16>(v);
-                if (q == 0) sums[part.rw * kCodesTokens + s] = v;
             }
         };
         if (part.ks == 0)
@@ -298,20 +271,14 @@ __device__ __forceinline__ void gate_up_codes(const bf16_t *__restrict__ x, int 
         else
             put(std::integral_constant<int, 1>{});
     });
-    __syncthreads();
-    if (tid < cnt) {                                             // (cnt <= 64)
-        const float v = (sums[tid] + sums[kCodesTokens + tid]) + (sums[2 * kCodesTokens + tid] + sums[3 * kCodesTokens + tid]);
-        asum[((size_t)nt * G + g) * T + tid] = v;
-    }
 }
 
 // Wd: code words [G][d][16]; rows: the row table.  T <= 64: one token tile.
 __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, const unsigned char *__restrict__ Wd,
                                            const bf16_t *__restrict__ Sd, const int16_t *__restrict__ rows,
-                                           const bf16_t *__restrict__ act, const float *__restrict__ asum,
-                                           float *__restrict__ partial, bf16_t *__restrict__ y)
+                                           const bf16_t *__restrict__ act, float *__restrict__ partial, bf16_t *__restrict__ y)
 {
-    constexpr int EV = 5, kTab = kTabBytes / 2;                  // bytes of the table's entries of a unit
+    constexpr int EV = 4, kTab = kTabBytes / 2;                  // bytes of the table's entries of a unit
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -347,10 +314,8 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
     const unsigned long long a_step = (unsigned long long)T * 256u, c_step = (unsigned long long)d * 64u;
     const uint32_t off_c = (uint32_t)((lane >> 2) * 64 + ((lane & 3) ^ ((lane >> 4) & 3)) * 16);
     const uint32_t off_p = (uint32_t)((lane >> 4 & 1) * d + j0 + wave * 16 + (lane & 14)) * 2u;
-    const int sum_ks = lane >> 4 & 1;                            // sums: lane (ks 2 + p) 8 + r
-    const uint32_t off_s = (uint32_t)(((lane >> 3 & 1) * G + sum_ks) * T) * 4u;
-    srd_t srd_s = make_srd(Sd, true), srd_sum = make_srd(asum, true);
-    uint32_t s_at = (uint32_t)(g_lo * d) * 2u, sum_at = (uint32_t)(g_lo * T) * 4u;
+    srd_t srd_s = make_srd(Sd, true);
+    uint32_t s_at = (uint32_t)(g_lo * d) * 2u;
     int left = ng, rb = 0;                                       // groups from it on; buffer of the unit that is requested next
     const uint32_t xdst = ring0 + wave * 1024, cdst = ring0 + kCodesRawBase + wave * 1024;
     auto load_x = [&](bool half, int b) __attribute__((always_inline)) {
@@ -366,11 +331,9 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
         }
         load_to_lds16_at<0>(srd_c[0], off_c, 0, cdst + rb * kCodesRaw);
         load_to_lds16_at<8192>(srd_c[1], off_c, 0, cdst + rb * kCodesRaw);
-        srd_s.z = srd_sum.z = srd_c[0].z;
+        srd_s.z = srd_c[0].z;
         load_to_lds_lanes<4>(0xffffffffull, srd_s, left == 1 && lane >= 16 ? kNoRow : off_p, s_at,
                              ring0 + kCodesScaleBase + rb * kCodesScale + wave * 128);
-        load_to_lds_lanes<4>(0xffffffffull, srd_sum, left == 1 && sum_ks == 1 ? kNoRow : off_s + (uint32_t)entry(tab, sum_ks, lane & 7) * 4u, sum_at,
-                             ring0 + kCodesSumBase + rb * kCodesSum + wave * 128);
         rb = rb == kCodesUnits - 1 ? 0 : rb + 1;
     };
     int tb = 0;                                                  // the unit's table
@@ -379,7 +342,6 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
         a_at += 2 * a_step;
         c_at += 2 * c_step;
         s_at += (uint32_t)(2 * d) * 2u;
-        sum_at += (uint32_t)(2 * T) * 4u;
         request_table(tb);                                       // the unit four on takes the place of the one that was
         tb = (tb + 1) & 3;
         request(tb);
@@ -399,7 +361,7 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
     with_token_tiles(T, [&](auto n_c) __attribute__((always_inline)) {
         constexpr int N = decltype(n_c)::value;
         f32x4_t total[2][N];
-        multiply_codes<N, 2, EV>(total, ring, nu, wave, lane, load_x, load_unit, upper);
+        multiply_codes<N, EV>(total, ring, nu, wave, lane, load_x, load_unit, upper);
         auto put = [&](auto half) __attribute__((always_inline)) {
             constexpr int KH = decltype(half)::value;
             meet_codes<N, KH>(total, ring, wave, lane);
@@ -409,7 +371,7 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
                 if (t < T) {
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
-                        const f32x4_t v = total[m][n];
+                        const f32x4_t v = kQ4Signed * total[m][n];
                         const size_t at = (size_t)t * d + j0 + part.row_tile(m) * 16 + 4 * q;
                         if (out) {
                             *reinterpret_cast<f32x4_t *>(out + at) = v;

@@ -517,3 +517,40 @@ def test_q4_17_to_64_tokens_scale_in_float(T, d, G, K, mean):
     c = hz.oracle_forward(w, L, x, K, pd, drop)
     hz.assert_parity(g, c, TOL["bf16"], f"q4 17 to 64 tokens T={T}")
     assert np.linalg.norm(g["y"] - c["y"]) <= 2 ** 0.5 * 2.0 ** -9 * np.linalg.norm(c["y"])
+
+
+@pytest.mark.parametrize("T,d", [(17, 256), (37, 640), (64, 1152), (40, 2048)])
+def test_q4_17_to_64_tokens_keep_sums_that_cancel(monkeypatch, T, d):
+    # the same sums over c - 8 in float32 as with fewer tokens and as in the smaller workspace
+    monkeypatch.setattr(H, "halo_workspace_bytes", H.halo_workspace_bytes_q4)
+    test_q4_few_tokens_of_any_row_length_keep_float32("sums", T, d)
+
+
+@pytest.mark.parametrize("T,d,G", [(17, 256, 2), (33, 640, 3), (64, 384, 5)])
+def test_q4_17_to_64_tokens_zeros_range_and_infinities(T, d, G):
+    # what the float32 sums of s (c - 8) x give where nothing is added to the codes: exact zeros over codes of 8, finite results of
+    # values near the largest, infinities (token 0) that stay infinities and stay with their token
+    _say(f"q4 zeros, range and infinities T={T} d={d} G={G}")
+    rng = np.random.default_rng(T)
+    x = rng.normal(1, 1, (T, d)) * np.where(rng.random((T, d)) < 0.01, 1e3, 1)
+    x[1, :], x[1, 7], x[1, 9], x[1:, 3], x[0, 3] = 0, 2.0 ** 123, 1, 0, np.inf
+    x = torch.from_numpy(x).to(torch.bfloat16).to(hz.DEV)
+    kg, ku, kd = (np.zeros(n, np.int64) for n in ((G * 128, d), (G * 128, d), (G, d, 128)))
+    kg[:, 3] = kg[:, 7] = ku[:, 3] = ku[:, 9] = 1
+    idle = np.arange(G * 128) % 128 // 8 == 8
+    ku[idle, 9] = 0                                              # neurons that are 0 whatever their gate (column 3 is token 0's alone)
+    kd[:, ::2] = rng.integers(1, 8, (G, d // 2, 128))
+    kd[:, 1::4, 64:72] = 3                                       # odd outputs: those neurons, or codes of 8 alone
+    full = lambda v, *n: torch.full(n, v, dtype=torch.bfloat16, device=hz.DEV)
+    scale = 2.0 ** -8
+    q4 = tuple(w for k in (kg, ku) for w in (torch.from_numpy(_pack_codes(k)).to(hz.DEV), full(scale, G * 128, d // 128)))
+    q4 += (torch.from_numpy(_pack_codes(kd)).to(hz.DEV), full(scale, G, d))
+    s = H.Shape(d, G * 128, 128, 64, "bf16")
+    ws = torch.empty(H.halo_workspace_bytes_q4(s, T, G), dtype=torch.uint8, device=hz.DEV)
+    y = full(float("nan"), T, d)
+    H.halo_group_sparse_ffn_q4(s, x, q4, torch.ones((T, G), dtype=torch.uint8, device=hz.DEV), y, ws)
+    torch.cuda.synchronize()
+    yg = hz.to_np32(y).astype(np.float64)
+    assert (yg[1:, 1::2] == 0).all() and (yg[0, ::2] == np.inf).all()
+    want = 2.0 ** 123 * scale ** 3 * np.delete(kd, np.arange(64, 72), axis=2)[:, ::2].sum(axis=(0, 2))
+    assert (np.abs(yg[1, ::2] - want) <= 2.0 ** -7 * want).all() and np.isfinite(yg[1:]).all()

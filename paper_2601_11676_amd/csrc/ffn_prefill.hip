@@ -259,8 +259,10 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 struct Q4Stage {
     uint2 codes;
     u32x4 out;
-    float scale[2], off, lo, hi;
-    uint32_t word, pair, shifted;
+    float scale, off, lo, hi;
+    uint32_t word, pair, mask, base;
+    // (the and-or's two constants in registers that the compiler cannot see through, as in q4_consts)
+    __device__ __forceinline__ Q4Stage() { asm volatile("v_mov_b32 %0, 0x00F000F0\n\tv_mov_b32 %1, 0x54005400" : "=v"(mask), "=v"(base)); }
     // block slot `raw` (LDS bytes), second or first stage of the block
     __device__ __forceinline__ void read(const unsigned char *raw, int wave, int lane, bool second)
     {
@@ -271,26 +273,25 @@ struct Q4Stage {
     // upper: the scale is the upper half of the word
     __device__ __forceinline__ void set_scale(bool upper)
     {
-        const float s = __uint_as_float(upper ? word & 0xffff0000u : word << 16);
-        scale[0] = 0x1p24f * s;
-        scale[1] = 0x1p20f * s;
-        off = -8.0f * s;
+        scale = __uint_as_float(upper ? word & 0xffff0000u : word << 16);
+        off = -72.0f * scale;
     }
-    // part 0, 1, 2 of pair p (0..7).  A code in the lowest bits of a half float is c 2^-24, four bits further up c 2^-20, and
-    // the mixed multiply-add takes half floats as they lie in the pair: s 2^24 * c 2^-24 - 8 s = s * (c - 8), exact in float (scales
-    // below 2^104); one instruction rounds both.  4.25 instructions per pair; as 128 + c in bf16, which has to be widened first, 6.75: a
-    // pass of 128 tokens at the 13B shape 109 -> 106 us, of 600 at 70B 760 -> 732, 97 tokens of d 3200, 75 groups 85.1 -> 81.3
+    // part 0, 1, 2 of pair p (0..7).  A code in bits 4..7 of the half float 64 is 64 + c, and the mixed multiply-add takes half floats as they
+    // lie in the pair: s * (64 + c) - 72 s = s * (c - 8), exact in float (scales below 2^121.8); one instruction rounds both.  4.75 instructions per
+    // pair; as 128 + c in bf16, which has to be widened first, 6.75: a pass of 128 tokens
+    // at the 13B shape 105.8 -> 102.9 us, of 600 at 70B 763 -> 731, 97 tokens of d 3200, 75 groups 85.1 -> 81.2.  (As c 2^-24, a shift per pair less,
+    // it is no faster, and 2^24 s overflows from 2^104 on.)
     __device__ __forceinline__ void part(int p, int which)
     {
         const int i = p & 3;
         if (which == 0) {
             const uint32_t w = p >> 2 ? codes.y : codes.x;
-            if (i == 2) shifted = w >> 8;
-            pair = (i < 2 ? w : shifted) & (i & 1 ? 0x00F000F0u : 0x000F000Fu);
+            const uint32_t at = i == 0 ? w << 4 : i == 1 ? w : w >> (4 * i - 4);
+            asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(pair) : "v"(at), "v"(mask), "v"(base));
         } else if (which == 1) {
             const f16x2_t h = __builtin_bit_cast(f16x2_t, pair);
-            lo = __builtin_fmaf((float)h[0], scale[i & 1], off);
-            hi = __builtin_fmaf((float)h[1], scale[i & 1], off);
+            lo = __builtin_fmaf((float)h[0], scale, off);
+            hi = __builtin_fmaf((float)h[1], scale, off);
         } else {
             const f32x2_t v = {lo, hi};
             out[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));

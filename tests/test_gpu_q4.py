@@ -554,3 +554,28 @@ def test_q4_17_to_64_tokens_zeros_range_and_infinities(T, d, G):
     assert (yg[1:, 1::2] == 0).all() and (yg[0, ::2] == np.inf).all()
     want = 2.0 ** 123 * scale ** 3 * np.delete(kd, np.arange(64, 72), axis=2)[:, ::2].sum(axis=(0, 2))
     assert (np.abs(yg[1, ::2] - want) <= 2.0 ** -7 * want).all() and np.isfinite(yg[1:]).all()
+
+
+@pytest.mark.parametrize("T,d,G", [(65, 256, 2), (65, 128, 2), (129, 1152, 24), (257, 1152, 9), (300, 1024, 20), (200, 4096, 12)])
+def test_q4_many_tokens_large_scales(T, d, G):
+    # scales up to 2^120 in gate and up, to 2^105 in down, tokens' values and y the smaller and larger by the same power of two: the
+    # same bits, whatever the tiles
+    _say(f"q4 large scales T={T} d={d} G={G}")
+    g = torch.Generator(device=hz.DEV)
+    g.manual_seed(T + d)
+    code = lambda *n: torch.randint(-2 ** 31, 2 ** 31, n, generator=g, device=hz.DEV, dtype=torch.int64).to(torch.int32)
+    scale = lambda *n: ((1 + torch.randint(0, 128, n, generator=g, device=hz.DEV) / 128.0) * 2.0 ** -8).to(torch.bfloat16)
+    q4 = [code(G * 128, d // 8), scale(G * 128, d // 128), code(G * 128, d // 8), scale(G * 128, d // 128), code(G, d, 16), scale(G, d)]
+    x = (torch.rand((T, d), generator=g, device=hz.DEV) * 24 + 8).to(torch.bfloat16)
+    x = torch.where(torch.rand((T, d), generator=g, device=hz.DEV) < 0.5, x, -x)
+    mask = (torch.rand((T, G), generator=g, device=hz.DEV) < 0.7).to(torch.uint8)
+    s = H.Shape(d, G * 128, 128, 64, "bf16")
+    ws = torch.empty(H.halo_workspace_bytes_q4(s, T, G), dtype=torch.uint8, device=hz.DEV)
+    ys = []
+    for up, down in ((0, 0), (127, 112)):
+        w = [t.float().mul(2.0 ** (down if i == 5 else up)).to(torch.bfloat16) if i % 2 else t for i, t in enumerate(q4)]
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=hz.DEV)
+        H.halo_group_sparse_ffn_q4(s, (x.float() * 2.0 ** -up).to(torch.bfloat16), w, mask, y, ws)
+        ys.append(y.double() * 2.0 ** -down)
+    torch.cuda.synchronize()
+    assert torch.isfinite(ys[0]).all() and torch.equal(*ys)

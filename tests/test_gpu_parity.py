@@ -873,6 +873,9 @@ def test_more_tokens_than_the_row_table_holds(G, K):
     (3, 1024, 24, 72),         # the most weights of few tokens
     (4, 1024, 32, 256),        # the most of all
     (4, 1032, 32, 256),        # past it: the launches of larger blocks
+    (64, 512, 8, 64),          # the most tokens
+    (16, 4096, 2, 64),         # the longest rows
+    (16, 4104, 2, 64),         # past them
 ])
 def test_small_float32_blocks_in_two_launches(T, d, G, r):
     w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=92)

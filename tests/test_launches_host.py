@@ -59,7 +59,8 @@ def test_prediction_in_one_launch_by_shape():
         assert rc == 0 and ("predict_mask_kernel" in launches[0][0]) == one, (T, G, d, r, launches)
     for T, d, r, dtype, one in [(64, 1024, 64, BF16, True), (65, 1024, 64, BF16, False), (16, 1032, 64, BF16, False), (4, 1000, 64, BF16, True),
                                 (5, 1000, 64, BF16, False), (64, 504, 64, F32, True), (64, 512, 64, F32, True), (64, 520, 64, F32, False)]:
-        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, 8, 128, r, dtype), T=T, K=4)])
+        # (33 groups of float32: up to 32 the prediction has no launch of its own)
+        (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, 33 if dtype == F32 else 8, 128, r, dtype), T=T, K=4)])
         assert rc == 0 and ("predict_mask_kernel" in launches[0][0]) == one, (T, d, r, launches)
 
 
@@ -142,9 +143,9 @@ def test_quarter_tiles_of_tokens():
 
 
 def test_small_float32_blocks_by_shape():
-    # the whole pass in two launches: fewer than 64 tokens, groups of 128, a wave of sixteen to a row (pair of rows) of Bt, few weights
+    # the whole pass in two launches: up to 64 tokens, rows of 4096, groups of 128, a wave of sixteen to a row (pair of rows) of Bt, few weights
     for T, d, G, gs, r, two in [(1, 1024, 24, 128, 64, True), (3, 1032, 24, 128, 64, False), (4, 1024, 32, 128, 256, True), (4, 1032, 32, 128, 256, False),
-                                (63, 256, 8, 128, 64, True), (64, 256, 8, 128, 64, False), (8, 64, 33, 128, 256, False), (8, 64, 16, 128, 512, True),
+                                (64, 256, 8, 128, 64, True), (65, 256, 8, 128, 64, False), (16, 4096, 8, 128, 512, True), (16, 4104, 2, 128, 64, False), (8, 64, 33, 128, 256, False), (8, 64, 16, 128, 512, True),
                                 (8, 64, 17, 128, 264, False), (8, 64, 4, 128, 520, False), (8, 64, 8, 64, 64, False)]:
         (rc, _, launches), = record([dict(fn="ffn_forward", shape=(d, G, gs, r, F32), T=T, K=G // 2)])
         names = [n for n, *_ in launches]

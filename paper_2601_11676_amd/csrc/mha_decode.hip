@@ -485,8 +485,11 @@ __global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const 
             if (q % 2 == 1) __builtin_amdgcn_sched_barrier(0);   // two heads' operands at a time: registers
         }
     };
-    // the merge; a thread: four dimensions of a head, 32 threads a head.  Its first loads go in front of Wo's, which are many bytes more, and
-    // loads return in order
+    // the merge; a thread: four dimensions of a head, 32 threads a head.  Its loads go in front of Wo's, which are many bytes more, and
+    // loads return in order; a wave that has no head asks for none (with few heads kept most of a large workgroup's: d 8192, 32 heads, one kept,
+    // 1500 rows 34.4 us with duplicates asked for, 31.6).  Where threads have several heads' worth, all but the last are merged first if the chunks
+    // are many (32 heads of d 4096, all kept, 2048 rows 38.2 -> 37.3; d 3200, 25 heads, 1500 rows 28.0 -> 26.9); with few the rows of Wo
+    // would wait for nothing (64 heads of d 8192, 60 rows 91.3, that way 92.8).
     const int n_ids = count * (dh / 4);
     float2 pv[kMergeChunks][2], st[kMergeChunks];
     auto ask = [&](int id) __attribute__((always_inline)) {
@@ -526,15 +529,24 @@ __global__ __launch_bounds__(RQ * 128, 4) void merge_out_t1(int d, int H, const 
     };
     u32x4 v0[kB], v1[kB], v2[kB];
     if (count > 0) {
-        ask(tid);
+        int id = tid;
+        if (chunks > 4) {
+#pragma unroll 1
+            for (; id + NT < n_ids; id += NT) {
+                ask(id);
+                merge(id);
+            }
+        }
+        const bool asks = wave * 64 < n_ids;                     // uniform
+        if (asks) ask(id);
         __builtin_amdgcn_sched_barrier(0);
         fetch(v0, half);
         fetch(v1, half + 2 * kB);
         fetch(v2, half + 4 * kB);
         __builtin_amdgcn_sched_barrier(0);
-        merge(tid);
+        if (asks) merge(id);
 #pragma unroll 1
-        for (int id = tid + NT; id < n_ids; id += NT) {
+        for (id += NT; id < n_ids; id += NT) {
             ask(id);
             merge(id);
         }

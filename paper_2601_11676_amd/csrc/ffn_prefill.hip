@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     const int nt = item & 1;
     const int2 tile = find_tile(tok_cnt, G, item >> 1, lane, tiles_of);
     const int g = __builtin_amdgcn_readfirstlane(tile.x);
-    const int cnt = tok_cnt[g];
+    const int cnt = __builtin_amdgcn_readfirstlane(tok_cnt[g]);
     const int c0 = __builtin_amdgcn_readfirstlane(tile.y) * NTOK;
     const int32_t *list = tok_list + (size_t)g * T;
 
@@ -574,9 +574,10 @@ __global__ __launch_bounds__(kRingWaves * 64, 2) void gate_up_pf_ring<true, 64>(
 // Groups end in a tile of any length (their token counts differ widely), so a wave's tiles are every fourth one and a tile
 // of one, two or three quarters runs with as many per wave: 1000 tokens of the 70B shape 523 -> 495.  (Taking all whole
 // tiles first and the short ones behind them evened out the last round, but then no two tiles of a group share their
-// weight rows in a die's L2: 13B shape 138 -> 192.)  So the weight rows carry no hint here: with the non-temporal one, which keeps
-// gate_up_pf_ring's from pushing x out, they were gone when the next tile of the group came (pass of 800 tokens of 13B 305 -> 294, of 1000 at 70B
-// 917 -> 897).
+// weight rows in a die's L2: 13B shape 138 -> 192.)  So the weight rows carry the non-temporal hint, as gate_up_pf_ring's do, only where the tile is the
+// group's one: with it they are gone when the next tile of the group comes (a pass of 600 tokens of the 70B shape, half kept, 775 us, without
+// 719), without it a lone tile's push x out (200 tokens there, half kept 332 us, without 347; 512 tokens, a tenth kept 401 and 419; a pass as it is
+// now 722, 333, 395).
 // Two stages of 64 KiB fit, so a step is cut in two: half kk of the 64 elements of stage s is multiplied while the
 // fragments of the next half are read.  The barrier sits in front of the second half, when everybody has read all of
 // stage s: its buffers go to the stages that follow, token rows one step ahead, weight rows (three buffers: they come from
@@ -602,7 +603,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     if (slot >= per_die || item >= n_items) return;              // uniform for the workgroup
     const int2 tile = find_tile(tok_cnt, G, item, lane, tiles_of);
     const int g = __builtin_amdgcn_readfirstlane(tile.x);
-    const int cnt = tok_cnt[g];
+    const int cnt = __builtin_amdgcn_readfirstlane(tok_cnt[g]);
     const int c0 = __builtin_amdgcn_readfirstlane(tile.y) * 256;
     const int quarters = min((cnt - c0 + 63) / 64, 4);
     const int32_t *list = tok_list + (size_t)g * T;
@@ -630,29 +631,32 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
         const bool yes = s < ns;
         load_to_lds16(if_exists(srd_x, yes), off_x[j], byte_of(yes ? s : 0), ring0 + (s & 1) * kBigStage + j * 8192);
     };
-    auto load_w = [&](int j, int s, int b) {                     // b = s % 3
+    auto load_w = [&](auto lone, int j, int s, int b) {          // b = s % 3; lone: the only tile of its group
         const bool yes = s < ns;
-        load_to_lds16(if_exists(j < 2 ? srd_g : srd_u, yes), off_w[j & 1], byte_of(yes ? s : 0),
-                            ring0 + kWBase + b * kBigStage + j * 8192);
+        load_to_lds16<decltype(lone)::value>(if_exists(j < 2 ? srd_g : srd_u, yes), off_w[j & 1], byte_of(yes ? s : 0),
+                                             ring0 + kWBase + b * kBigStage + j * 8192);
     };
     // the wave's row tiles: four of the gate rows and the four of the up rows that face them; its 16-token tiles: tq + 4 n
     auto row_tile = [&](int m) { return m < 4 ? 4 * rh + m : 8 + 4 * rh + (m - 4); };
-    const int loff0 = i16 * 128 + ((q ^ (i16 & 7)) * 16), loff1 = loff0 ^ 64;       // piece 4 kk + q
 
+    auto first_stages = [&](auto lone) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < 2; ++s) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) load_x(j, s);
+            for (int j = 0; j < 4; ++j) load_x(j, s);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) load_w(j, s, s);
-    }
+            for (int j = 0; j < 4; ++j) load_w(lone, j, s, s);
+        }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) load_w(j, 2, 2);
-    wait_loads<12>();                                            // stage 0
-    __syncthreads();
-
-    auto tile_of = [&](auto quarters_c) __attribute__((always_inline)) {
+        for (int j = 0; j < 4; ++j) load_w(lone, j, 2, 2);
+        wait_loads<12>();                                        // stage 0
+        __syncthreads();
+    };
+    auto tile_of = [&](auto quarters_c, auto lone) __attribute__((always_inline)) {
         constexpr int N = decltype(quarters_c)::value;           // 16-token tiles of a wave
+        int loff0 = i16 * 128 + ((q ^ (i16 & 7)) * 16);          // piece 4 kk + q
+        asm volatile("" : "+v"(loff0));                          // (worked out here: kept from the kernel's head it is spilled)
+        const int loff1 = loff0 ^ 64;
         f32x4_t acc[8][N];
         clear_accumulators(acc);
         u32x4 fa[8], f0[N], f1[N];
@@ -686,7 +690,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
                         if (k < 4)
                             load_x(k, s + 2);
                         else
-                            load_w(k - 4, s + 3, wb);
+                            load_w(lone, k - 4, s + 3, wb);
                     }
                 },
                 [&](int m) __attribute__((always_inline)) { read_a(m, wbuf(1), loff0); });
@@ -710,14 +714,21 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
             }
         }
     };
-    if (quarters == 4)
-        tile_of(std::integral_constant<int, 4>{});
-    else if (quarters == 3)
-        tile_of(std::integral_constant<int, 3>{});
-    else if (quarters == 2)
-        tile_of(std::integral_constant<int, 2>{});
+    auto run_tile = [&](auto lone) __attribute__((always_inline)) {
+        first_stages(lone);
+        if (quarters == 4)
+            tile_of(std::integral_constant<int, 4>{}, lone);
+        else if (quarters == 3)
+            tile_of(std::integral_constant<int, 3>{}, lone);
+        else if (quarters == 2)
+            tile_of(std::integral_constant<int, 2>{}, lone);
+        else
+            tile_of(std::integral_constant<int, 1>{}, lone);
+    };
+    if (cnt <= 256)                                              // uniform
+        run_tile(std::true_type{});
     else
-        tile_of(std::integral_constant<int, 1>{});
+        run_tile(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------

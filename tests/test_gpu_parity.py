@@ -776,6 +776,7 @@ def test_many_token_rings(T, d, G, K):
 
 @pytest.mark.parametrize("T,d,G,K", [
     (1100, 384, 180, 60),      # 256 x 256 tiles: several per group, tails of every length, rows of six stages
+    (400, 384, 200, 60),       # ... mostly one per group, of every length
     (520, 128, 100, 45),       # ... rows of two stages
     (300, 1152, 150, 70),      # ... groups of less than a tile; an odd number of stages per die
     (200, 2048, 48, 24),       # the scratch has no room for a second range in the down projection: half tiles

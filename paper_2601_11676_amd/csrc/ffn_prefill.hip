@@ -943,7 +943,7 @@ __global__ __launch_bounds__(kRingWaves * 64) __attribute__((amdgpu_waves_per_eu
     const WavePart<MT> part(wave);
     const int i16 = lane & 15, q = lane >> 4;
     DownItem it;
-    if (!down_item<NTOK>(T, d, G, splits, it)) return;
+    if (!down_item<Q4, NTOK>(T, d, G, splits, it)) return;
     const int t0 = it.t0, j0 = it.j0, g_lo = it.g_lo, split = it.split;
     const int ng = it.g_hi - g_lo;                               // >= 1
     const int ns = 2 * ng;

@@ -285,7 +285,7 @@ __device__ __forceinline__ void down_codes(int T, int d, int G, int splits, cons
     const CodesPart part(wave);
     const int i16 = lane & 15, q = lane >> 4;
     DownItem it;
-    if (!down_item<kCodesTokens>(T, d, G, splits, it)) return;
+    if (!down_item<true, kCodesTokens>(T, d, G, splits, it)) return;
     const int j0 = it.j0, g_lo = it.g_lo;
     const int ng = it.g_hi - g_lo, nu = (ng + 1) / 2;            // groups of the range, units: a block is a group
     const int br = lane >> 3, piece = codes_piece((lane & 7) ^ br);

@@ -38,62 +38,19 @@ namespace halo {
 // token lists: grid = G workgroups of 256 threads
 // ---------------------------------------------------------------------------
 // rows != nullptr: row table [G][row_pitch] (row_pitch = T rounded up to 8; the entries past T are 0).
-// slot != nullptr instead (more than 32767 tokens): [T][G] positions in the list, -1 = not kept.
+// slot != nullptr instead (two or three tokens, or more than 32767): [T][G] positions in the list, -1 = not kept.
+// A workgroup asks for the mask bytes of RUNS runs of 256 tokens at once and places them behind one barrier; where that is all of them
+// the list's length comes from the same bytes.  (A run at a time, three barriers and a trip to memory
+// each, after a pass over the bytes for the length: 1000 tokens, 224 groups 7.0 us, now 5.2; a pass of 5000 tokens, d 1024, 24 groups
+// 120.9 / 115.2, of 2000 tokens of the 7B shape 376.9 / 372.6, of 300 tokens, d 2048 71.8 / 71.0,
+// of 17 and 256 tokens, d 256, 6 groups 22.4 / 21.9 and 26.5 / 25.8.)
+constexpr int kGroupRuns = 8;
+
+template <int RUNS>
 __global__ __launch_bounds__(256) void group_tokens_kernel(const uint8_t *__restrict__ mask, int T, int G,
                                                            int32_t *__restrict__ tok_list,
                                                            int32_t *__restrict__ tok_cnt, int16_t *__restrict__ rows,
                                                            int32_t *__restrict__ slot, bf16_t *__restrict__ act)
-{
-    __shared__ int s_wave[4];
-    __shared__ int s_base;
-    const int g = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int pitch = prefill_row_pitch(T);
-    // the list's length first: it is the zero row of the tokens that do not keep the group
-    int mine = 0;
-    for (int t = tid; t < T; t += 256) mine += mask[(size_t)t * G + g] != 0 ? 1 : 0;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, kWave);
-    if (lane == 0) s_wave[wave] = mine;
-    if (tid == 0) s_base = 0;
-    __syncthreads();
-    const int cnt = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-    __syncthreads();
-    for (int t0 = 0; t0 < pitch; t0 += 256) {
-        const int t = t0 + tid;
-        const bool keep = t < T && mask[(size_t)t * G + g] != 0;
-        const unsigned long long b = __ballot(keep);
-        if (lane == 0) s_wave[wave] = __popcll(b);
-        __syncthreads();
-        int before = s_base;
-        for (int k = 0; k < wave; ++k) before += s_wave[k];
-        const int pos = before + __popcll(b & ((1ull << lane) - 1ull));
-        if (keep) tok_list[(size_t)g * T + pos] = t;
-        if (rows) {
-            if (t < pitch) rows[(size_t)g * pitch + t] = (int16_t)(t < T ? (keep ? pos : cnt) : 0);
-        } else if (t < T) {
-            slot[(size_t)t * G + g] = keep ? pos : -1;
-        }
-        __syncthreads();
-        if (tid == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        __syncthreads();
-    }
-    if (tid == 0) tok_cnt[g] = cnt;
-    // the row after the group's last activation row is kept zero (group size 128): the down
-    // projection points the tokens that do not keep the group at it
-    if (cnt < T && tid < 64) reinterpret_cast<uint32_t *>(act + ((size_t)g * T + cnt) * 128)[tid] = 0u;
-}
-
-// The same lists for more than 256 tokens: a workgroup asks for the mask bytes of RUNS runs of 256 tokens at once and places them behind one
-// barrier; where that is all of them the list's length comes from the same bytes.  (A run at a time, three barriers and a trip to memory
-// each, after a pass over the bytes for the length: 1000 tokens, 224 groups 7.0 us, now 5.2; a pass of 5000 tokens, d 1024, 24 groups
-// 120.9 / 115.2, of 2000 tokens of the 7B shape 376.9 / 372.6, of 300 tokens, d 2048 71.8 / 71.0.  Up to 256 tokens it is level.)
-constexpr int kGroupRuns = 8;
-
-template <int RUNS>
-__global__ __launch_bounds__(256) void group_tokens_runs_kernel(const uint8_t *__restrict__ mask, int T, int G,
-                                                                int32_t *__restrict__ tok_list,
-                                                                int32_t *__restrict__ tok_cnt, int16_t *__restrict__ rows,
-                                                                int32_t *__restrict__ slot, bf16_t *__restrict__ act)
 {
     __shared__ __attribute__((aligned(16))) int s_cnt[RUNS][4];
     __shared__ int s_wave[4];
@@ -156,11 +113,11 @@ static void launch_group_tokens(const uint8_t *mask, int T, int G, int32_t *tok_
                                 hipStream_t s)
 {
     if (T <= 256)
-        group_tokens_kernel<<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
+        group_tokens_kernel<1><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
     else if (T <= 512)
-        group_tokens_runs_kernel<2><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
+        group_tokens_kernel<2><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
     else
-        group_tokens_runs_kernel<kGroupRuns><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
+        group_tokens_kernel<kGroupRuns><<<dim3(G), dim3(256), 0, s>>>(mask, T, G, tok_list, tok_cnt, rows, slot, act);
 }
 
 // ---------------------------------------------------------------------------

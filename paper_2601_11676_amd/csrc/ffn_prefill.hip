@@ -1219,7 +1219,7 @@ hipError_t launch_ffn_prefill(const bf16_t *x, int T, int d, int G, int gs, cons
     return hipGetLastError();
 }
 
-// The same over 4-bit weights: the codes are expanded on their way into LDS.
+// The same over 4-bit weights: the codes are expanded on their way into LDS, or in registers (codes_path).
 bool prefill_q4_supported(int T, int d, int G, int gs)
 {
     return T > 16 && prefill_path_supported(T, d, gs) && prefill_down_splits(T, d, G) > 0 && row_table_fits(T);

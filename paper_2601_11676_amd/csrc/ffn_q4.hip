@@ -550,8 +550,8 @@ hipError_t launch_ffn_q4(int dtype, const void *x, int T, int d, int G, int gs, 
                    ? q4_one_token<bf16_t>(bx, d, G, w, mask, by, reinterpret_cast<bf16_t *>(ws.act), s, ahead, ahead_fused)
                    : q4_one_token<float>(bx, d, G, w, mask, by, ws.act, s, ahead, ahead_fused);
     if (stream_path_supported(T, d, G, gs)) return launch_ffn_q4_mfma(bx, T, d, G, w, mask, by, ws, s, ahead, ahead_fused);
-    // The many-token kernels multiply by values rounded to bf16, the few-token kernels scale in float: which of the two a
-    // call of many tokens gets is the caller's choice, by the workspace.
+    // The many-token kernels multiply by values rounded to bf16 (from 65 tokens on, and over rows of 128), the few-token kernels scale in
+    // float: which of the two a call of many tokens gets is the caller's choice, by the workspace.
     if (ws.q4_w && prefill_q4_supported(T, d, G, gs)) return launch_ffn_prefill_q4(bx, T, d, G, w, mask, by, ws, s);
     if (ws.q4_w && q4_expand_supported(T, dtype, d, G, gs)) {
         // More tokens than the row table's 16 bits hold, and room for a block's weights as bf16: the weights are expanded once (a stream of

@@ -361,7 +361,7 @@ def test_q4_llama7b_prefill_all_tokens(big_workspace):
     hz.assert_parity(g, c, TOL["bf16"], "q4 7B prefill")
 
 
-@pytest.mark.parametrize("T,d,G", [(17, 1024, 9), (40, 2048, 12), (300, 1024, 20)])
+@pytest.mark.parametrize("T,d,G", [(17, 128, 9), (64, 128, 12), (65, 1024, 9), (140, 2048, 12), (300, 1024, 20)])
 def test_q4_many_tokens_on_expanded_weights(T, d, G):
     # small shapes on weights rounded to bf16 (workspace of halo_workspace_bytes_q4)
     w = dataclasses.replace(hs.LLAMA13B_STACK, name="case", d=d, ffn=G * 128, rank=64, T=T, layers=1, seed=19)

@@ -140,6 +140,8 @@ def test_quarter_tiles_of_tokens():
             names = [n for n, *_ in launches]
             for kernel, tokens in (("gate_up_pf_ring", gate_up if q4 else max(gate_up, 128)), ("down_pf_ring", down)):
                 assert rc == 0 and sum(f"{kernel}ILb{q4}ELi{tokens}E" in n for n in names) == 1, (T, d, G, q4, names)
+            # the scale in float where gate/up has it so: codes of up to 64 tokens, rows of 256 and more
+            assert sum(f"down_pf_ringILb{q4}ELi{down}ELb{int(q4 and gate_up == 64)}E" in n for n in names) == 1, (T, d, G, q4, names)
 
 
 def test_small_float32_blocks_by_shape():

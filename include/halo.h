@@ -193,7 +193,7 @@ int halo_group_sparse_ffn(const halo_shape *shape, const void *x, int32_t T, con
 
 /*
  * One whole pass for an FFN block on one stream, no host synchronisation:
- * halo_predict_scores -> halo_build_group_mask -> halo_group_sparse_ffn
+ * halo_predict_scores -> halo_build_group_mask -> halo_group_sparse_ffn, with the results of the three calls bit for bit
  * (paper Sec. III-A generation phase: Pred, Load, Comp and the merge for one block).
  * Small float32 blocks (group size 128, up to 32 groups, up to 64 tokens, d up to 4096, n_groups * d up to 24 Ki, 32 Ki from four tokens on) read
  * the gate and up rows of all groups, beside the prediction; what the mask drops is not used.

@@ -1099,7 +1099,7 @@ bool prefill_path_supported(int T, int d, int gs)
 
 // Up to 64 tokens over codes (rows of at least 256: pairs of blocks): prefill_codes.hpp, the scale applied in float as for fewer tokens.  Above
 // that the values are rounded to bf16 and the results are those of the bf16 kernels on the expanded weights, bit for bit, which callers may
-// count on (the same kernel in a 128-token tile would run 13B, 100 tokens of d 3200 and 128 in 70 us instead of 85 and 98 instead of 109).
+// count on (the same kernel in a 128-token tile, codes as 128 + c, would run 100 tokens of d 3200, 75 groups and 128 of 13B in 70 us instead of 85 and 98 instead of 109).
 static bool codes_path(int T, int d) { return T <= 64 && d >= 256; }
 
 template <bool Q4, int NTOK>

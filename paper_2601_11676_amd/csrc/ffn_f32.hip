@@ -710,18 +710,19 @@ hipError_t launch_ffn_f32(const float *x, int T, int d, int G, int gs, const flo
     }
 }
 
-// Whole pass in two launches, see hidden_gate_up_f32, against three or four, us in a graph of blocks, one block over and over, and (in
-// brackets) blocks of 1.2 GB in all, whose weights come from HBM.  One group kept, the least there is to read, rank 256: d 1024, 24 groups, 1, 3, 4,
-// 16 tokens 15.9 / 12.5 (16.6 / 15.6), 17.0 / 13.5 (17.8 / 16.5), 16.9 / 13.6 (18.6 / 16.7), 22.7 / 20.3 (25.9 / 24.3); d 1024, 32 groups 15.9 / 13.9
-// (16.8 / 17.9), 16.8 / 14.4 (17.8 / 17.9), 17.5 / 15.0 (18.4 / 18.0), 23.0 / 20.9 (26.7 / 26.0).  Half of the groups kept: d 1024, 24 groups 18.2 / 15.4
-// (21.9 / 18.7), 21.7 / 18.8 (25.2 / 22.6), 23.4 / 19.1 (26.3 / 23.1), 26.2 / 22.7 (29.4 / 27.1); d 256, 8 groups, 1 and 16 tokens 13.6 / 9.3 (15.2 / 10.9),
-// 15.7 / 11.0 (18.1 / 13.0).  Above the line d 2048, 32 groups, one group kept, 1, 4, 16 tokens 19.8 / 21.0 (21.6 / 24.8), 21.3 / 20.4 (23.6 / 25.3),
-// 29.0 / 27.3 (32.5 / 32.4).  So the weights of all groups may be 24 Ki rows of 128 elements, 32 Ki from four tokens on, whatever share of the groups
-// is kept.  64 tokens are still ahead (d 256, 12 groups 18.4 / 14.0 (20.3 / 15.5), d 1024, 24 groups, one kept 37.1 / 31.3 (39.8 / 33.7), d 2048, 8 groups
-// 34.9 / 31.8 (38.2 / 35.6)); above, it depends on what is kept and on the rank (d 512, 24 groups, rank 256, 112 tokens 27.0 / 31.7 with one group kept, 37.9 / 34.9
-// with seven; d 256, 8 groups, rank 512, 112 tokens 23.1 / 24.3).  Rows of up to 4096 (8 groups of them, rank 512, 1, 4, 16, 64 tokens 27.9 / 25.6 (32.9 / 29.4), 32.0 / 28.5 (35.4 / 33.0),
-// 44.2 / 38.5 (47.0 / 47.3), 86.4 / 77.2 (90.8 / 80.3)); longer ones lose where their weights are not cached: d 8192, 4 groups, rank 512, 4 and 16 tokens 54.5 / 51.9 (58.3 / 60.1), 73.5 / 67.3 (77.5 / 84.9); 3 groups, rank 64, 32 tokens
-// 83.2 / 82.8 (91.7 / 97.2); d 16384, 2 groups, rank 256, 16 tokens 119.1 / 119.9 (124.5 / 154.2).
+// Whole pass in two launches, see hidden_gate_up_f32, against three or four, us in a graph of blocks, one block over and over, and (in brackets)
+// blocks of 1.2 GB in all, whose weights come from HBM.  One group kept, the least there is to read, rank 256: d 1024, 24 groups, 1, 3, 4, 16 tokens
+// 15.9 / 12.5 (16.6 / 15.6), 17.0 / 13.5 (17.8 / 16.5), 16.9 / 13.6 (18.6 / 16.7), 22.7 / 20.3 (25.9 / 24.3); d 1024, 32 groups 15.9 / 13.9 (16.8 /
+// 17.9), 16.8 / 14.4 (17.8 / 17.9), 17.5 / 15.0 (18.4 / 18.0), 23.0 / 20.9 (26.7 / 26.0).  Half of the groups kept: d 1024, 24 groups 18.2 / 15.4
+// (21.9 / 18.7), 21.7 / 18.8 (25.2 / 22.6), 23.4 / 19.1 (26.3 / 23.1), 26.2 / 22.7 (29.4 / 27.1); d 256, 8 groups, 1 and 16 tokens 13.6 / 9.3 (15.2 /
+// 10.9), 15.7 / 11.0 (18.1 / 13.0).  Above the line d 2048, 32 groups, one group kept, 1, 4, 16 tokens 19.8 / 21.0 (21.6 / 24.8), 21.3 / 20.4 (23.6 /
+// 25.3), 29.0 / 27.3 (32.5 / 32.4).  So the weights of all groups may be 24 Ki rows of 128 elements, 32 Ki from four tokens on, whatever share of the
+// groups is kept.  64 tokens are still ahead (d 256, 12 groups 18.4 / 14.0 (20.3 / 15.5), d 1024, 24 groups, one kept 37.1 / 31.3 (39.8 / 33.7), d
+// 2048, 8 groups 34.9 / 31.8 (38.2 / 35.6)); above, it depends on what is kept and on the rank (d 512, 24 groups, rank 256, 112 tokens 27.0 / 31.7
+// with one group kept, 37.9 / 34.9 with seven; d 256, 8 groups, rank 512, 112 tokens 23.1 / 24.3).  Rows of up to 4096 (8 groups of them, rank 512,
+// 1, 4, 16, 64 tokens 27.9 / 25.6 (32.9 / 29.4), 32.0 / 28.5 (35.4 / 33.0), 44.2 / 38.5 (47.0 / 47.3), 86.4 / 77.2 (90.8 / 80.3)); longer ones lose
+// where their weights are not cached: d 8192, 4 groups, rank 512, 4 and 16 tokens 54.5 / 51.9 (58.3 / 60.1), 73.5 / 67.3 (77.5 / 84.9); 3 groups,
+// rank 64, 32 tokens 83.2 / 82.8 (91.7 / 97.2); d 16384, 2 groups, rank 256, 16 tokens 119.1 / 119.9 (124.5 / 154.2).
 bool forward_f32_supported(int T, int d, int G, int gs, int r, int n_dev)
 {
     return gs == 128 && r <= 512 && f32_score_slots(G, r) <= kDownF32Waves && n_dev <= 64 && T <= 64 && d <= 4096 &&

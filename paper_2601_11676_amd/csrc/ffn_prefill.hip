@@ -233,11 +233,11 @@ struct Q4Stage {
         scale = __uint_as_float(upper ? word & 0xffff0000u : word << 16);
         off = -72.0f * scale;
     }
-    // part 0, 1, 2 of pair p (0..7).  A code in bits 4..7 of the half float 64 is 64 + c, and the mixed multiply-add takes half floats as they
-    // lie in the pair: s * (64 + c) - 72 s = s * (c - 8), exact in float (scales below 2^121.8); one instruction rounds both.  4.75 instructions per
-    // pair; as 128 + c in bf16, which has to be widened first, 6.75: a pass of 128 tokens
-    // at the 13B shape 105.8 -> 102.9 us, of 600 at 70B 763 -> 731, 97 tokens of d 3200, 75 groups 85.1 -> 81.2.  (As c 2^-24, a shift per pair less,
-    // it is no faster, and 2^24 s overflows from 2^104 on.)
+    // part 0, 1, 2 of pair p (0..7).  A code in bits 4..7 of the half float 64 is 64 + c, and the mixed multiply-add takes half floats as
+    // they lie in the pair: s * (64 + c) - 72 s = s * (c - 8), exact in float (scales below 2^121.8); one instruction rounds both.  4.75
+    // instructions per pair; as 128 + c in bf16, which has to be widened first, 6.75: a pass of 128 tokens at the 13B shape 105.8 -> 102.9
+    // us, of 600 at 70B 763 -> 731, 97 tokens of d 3200, 75 groups 85.1 -> 81.2.  (As c 2^-24, a shift per pair less, it is no faster, and
+    // 2^24 s overflows from 2^104 on.)
     __device__ __forceinline__ void part(int p, int which)
     {
         const int i = p & 3;
@@ -1097,9 +1097,10 @@ bool prefill_path_supported(int T, int d, int gs)
     return T > 1 && d % 128 == 0 && gs == 128 && (size_t)T * d * sizeof(bf16_t) < (1ull << 31);
 }
 
-// Up to 64 tokens over codes (rows of at least 256: pairs of blocks): prefill_codes.hpp, the scale applied in float as for fewer tokens.  Above
-// that the values are rounded to bf16 and the results are those of the bf16 kernels on the expanded weights, bit for bit, which callers may
-// count on (the same kernel in a 128-token tile, codes as 128 + c, would run 100 tokens of d 3200, 75 groups and 128 of 13B in 70 us instead of 85 and 98 instead of 109).
+// Up to 64 tokens over codes (rows of at least 256: pairs of blocks): prefill_codes.hpp, the scale applied in float as for fewer tokens.  Above that
+// the values are rounded to bf16 and the results are those of the bf16 kernels on the expanded weights, bit for bit, which callers may count on (the
+// same kernel in a 128-token tile, codes as 128 + c, would run 100 tokens of d 3200, 75 groups and 128 of 13B in 70 us instead of 85 and 98 instead
+// of 109).
 static bool codes_path(int T, int d) { return T <= 64 && d >= 256; }
 
 template <bool Q4, int NTOK>

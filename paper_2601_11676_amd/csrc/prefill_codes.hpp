@@ -1,23 +1,23 @@
 // 17 to 64 tokens over 4-bit weights: the codes become matrix operands in registers.
 //
 // A code is c in 0..15, its value s * (c - 8) with one scale s per row and block of 128 elements.  A matrix instruction multiplies (c - 8) / 16,
-// exact in bf16 (q4_word_signed), and the finished block is scaled in float on its way into the running sum: three and a half vector instructions
-// per pair of codes, where a value that is scaled, rounded to bf16 and parked in LDS for all waves takes seven, an LDS write and reads of twice the
-// bytes.  (128 + c, less 136 times the sum of the token's elements, is half the conversion and gained 1 to 4 %, but its sums carry 17 times what
-// the block is made of: rows that cancel were up to 400 times further from 64 bits than here, blocks over codes of 8 alone were not 0,
-// and sums of a block's elements from 2^121 on overflowed.)
+// exact in bf16 (q4_word_signed), and the finished block is scaled in float on its way into the running sum: three and a half vector instructions per
+// pair of codes, where a value that is scaled, rounded to bf16 and parked in LDS for all waves takes seven, an LDS write and reads of twice the
+// bytes.  (128 + c, less 136 times the sum of the token's elements, is half the conversion and gained 1 to 4 %, but its sums carry 17 times what the
+// block is made of: rows that cancel were up to 400 times further from 64 bits than here, blocks over codes of 8 alone were not 0, and sums of a
+// block's elements from 2^121 on overflowed.)
 //
 // Workgroup tile: 128 weight rows x 64 tokens, eight waves: two halves of the blocks (a wave takes every other block) times four quarters
 // of the rows, gate (or lower) and up (upper) rows alike; a wave owns 32 x 64, N of its four 16-token tiles existing.  A step is 64
 // elements of each of two blocks, a unit the two steps of a pair of blocks.  In LDS: three steps of token rows (128 bytes each) and three
 // units of codes (64 bytes a row, 16-byte piece p of row r at p ^ ((r >> 2) & 3)) and scales.
 //
-// What bounds it: the instructions of a wave, one per four cycles, more than half of them the conversion and the scaling, and the barrier of
-// a step.  Pass in us, codes rounded to bf16 on their way into LDS (as for more tokens) against this: 17 tokens 7B 68.2 / 50.1,
-// 13B 84.0 / 62.0, 70B 224.5 / 144.2; 33 tokens 13B 89.1 / 67.3, 48 of 70B 226.8 / 158.7, 64 of 13B 91.4 / 74.6; d 2048, 44 groups, 40 tokens
-// 46.6 / 38.3; d 256, 4 groups, 17 tokens 23.0 / 18.8.  With 128 + c: two such workgroups to a compute unit (rings of two steps and two units, 128 registers)
-// took 189 us at 70B, 17 tokens, where one took 150, four units of codes instead of three 151.  The scalar address work is kept to an addition per load
-// (157 -> 150 there), and the barrier stands in the middle of a step, where the fragments of its second half have long been read.
+// What bounds it: the instructions of a wave, one per four cycles, more than half of them the conversion and the scaling, and the barrier of a step.
+// Pass in us, codes rounded to bf16 on their way into LDS (as for more tokens) against this: 17 tokens 7B 68.2 / 50.1, 13B 84.0 / 62.0, 70B 224.5 /
+// 144.2; 33 tokens 13B 89.1 / 67.3, 48 of 70B 226.8 / 158.7, 64 of 13B 91.4 / 74.6; d 2048, 44 groups, 40 tokens 46.6 / 38.3; d 256, 4 groups, 17
+// tokens 23.0 / 18.8.  With 128 + c: two such workgroups to a compute unit (rings of two steps and two units, 128 registers) took 189 us at 70B, 17
+// tokens, where one took 150, four units of codes instead of three 151.  The scalar address work is kept to an addition per load (157 -> 150 there),
+// and the barrier stands in the middle of a step, where the fragments of its second half have long been read.
 #pragma once
 #include "prefill_tiles.hpp"
 

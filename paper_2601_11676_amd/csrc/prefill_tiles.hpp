@@ -90,11 +90,12 @@ __device__ __forceinline__ bool down_item(int T, int d, int G, int splits, DownI
     // and found in the die's L2 by the others, which walk the groups beside it, and so are the act rows of a step, whatever the
     // number of token tiles.  (Where a die's items shared one token tile's act rows instead, above two token tiles, every die fetched Wd for
     // itself.  Pass in us: 600 tokens of the 70B shape 765 -> 705, 1000 910 -> 887, 1500 1297 -> 1260, 800 of 13B 296 -> 291, 900 of 7B 215 -> 209.)
-    // A narrow layer's Wd, up to 6 MB in bf16, is mostly in a die's L2 anyhow: there its items share a token tile's act rows, above two token tiles and
-    // where such rows, 64 KiB a group, fit beside it.  Wd / act rows shared, us a pass, half of the groups kept: d 512, 40 groups, 600, 800, 1000, 1500, 2000 tokens
-    // 47.1 / 45.0, 54.4 / 51.7, 54.9 / 51.6, 58.6 / 58.9, 66.6 / 67.3; d 640, 24 groups, 800, 1000 54.5 / 51.3, 49.6 / 48.0; d 1024, 24 groups, 800, 2000 57.3 / 56.4, 67.7 / 69.3 (a tenth
-    // kept 58.9 / 55.6, 66.2 / 67.0).  Past the line: d 256, 96 groups, 600, 800, 2000 49.9 / 51.3, 52.5 / 53.9, 90.0 / 90.2; d 1536, 32 groups, 800, 1500 69.9 / 70.7,
-    // 81.9 / 82.6; d 2048, 24 groups, 600 70.6 / 72.1.  Over codes, a quarter of the bytes, it is level at d 1024, 24 groups, and 77.1 / 77.9 at d 2048.
+    // A narrow layer's Wd, up to 6 MB in bf16, is mostly in a die's L2 anyhow: there its items share a token tile's act rows, above two token tiles
+    // and where such rows, 64 KiB a group, fit beside it.  Wd / act rows shared, us a pass, half of the groups kept: d 512, 40 groups, 600, 800,
+    // 1000, 1500, 2000 tokens 47.1 / 45.0, 54.4 / 51.7, 54.9 / 51.6, 58.6 / 58.9, 66.6 / 67.3; d 640, 24 groups, 800, 1000 54.5 / 51.3, 49.6 / 48.0;
+    // d 1024, 24 groups, 800, 2000 57.3 / 56.4, 67.7 / 69.3 (a tenth kept 58.9 / 55.6, 66.2 / 67.0).  Past the line: d 256, 96 groups, 600, 800, 2000
+    // 49.9 / 51.3, 52.5 / 53.9, 90.0 / 90.2; d 1536, 32 groups, 800, 1500 69.9 / 70.7, 81.9 / 82.6; d 2048, 24 groups, 600 70.6 / 72.1.  Over codes,
+    // a quarter of the bytes, it is level at d 1024, 24 groups, and 77.1 / 77.9 at d 2048.
     int ttile;
     if (Q4 || n_tt <= 2 || G > 48 || G * d > 24 * 1024) {
         ttile = item % n_tt;

@@ -919,7 +919,7 @@ def test_small_float32_blocks_in_two_launches(T, d, G, r):
     (8, 512, 8, 64),           # up to eight tokens and eight groups: as one token
     (8, 1024, 24, 256),
     (9, 512, 8, 264),
-    (63, 256, 31, 128),
+    (64, 256, 31, 128),
 ])
 def test_float32_pass_has_the_bits_of_its_parts(T, d, G, r):
     w = dataclasses.replace(hs.TINY, name="case", d=d, ffn=G * 128, group_size=128, rank=r, T=T, seed=93)
